@@ -174,19 +174,19 @@ int vfa_kblock_summary_append(const void* K, void* Krepr, int B, int Hkv, int n_
 /* Bytes of workspace vfa_decode_fwd needs (partial sums of n_splits key ranges per query head). */
 size_t vfa_decode_workspace_bytes(int B, int Hq, int d, int n_splits);
 
-/* Decode step (Alg. 1 with one query token per head that sees every cached key; the split over
- * key ranges uses Step 3: once the max is frozen, partial sums need no rescale).
+/* Decode step: one query token per head against every cached key.
  *   Q [B, Hq, d], O [B, Hq, d] bf16; LSE [B, Hq] fp32 or NULL
  *   K, V [B, Hkv, n_cap, d] bf16, rows [0, n_keys) valid (rows beyond are never read)
  *   Krepr  summaries of those n_keys rows, laid out for n_cap (see vfa_kblock_summary_append);
- *          read when use_minit == 1, may be NULL when use_minit == 0
- * The running max is m = max(m_init, exact row max over the first n_sink and the last n_local key
- * blocks), m_init = max_j scale * q . Krepr_j (or -inf); the cache is cut into n_splits ranges of
- * whole blocks; each range accumulates sum exp(s - m) and sum exp(s - m) v; the ranges are added in
- * index order (bit-identical results from run to run), divided, and LSE = m + ln l.  The result is
- * exact attention over the n_keys rows.  n_splits >= 1 (ranges may be empty; up to four (KV head, range) pairs
- * share a compute unit, and B * Hkv * n_splits of 1.5 to 4 times the number of compute units runs within a few
- * percent of the best); Hq / Hkv <= 32;
+ *          must be given when use_minit == 1, may be NULL when use_minit == 0
+ * The cache is cut into n_splits ranges of whole blocks; each range accumulates sum exp(s - m) and
+ * sum exp(s - m) v with its own running row max m; the ranges are added in a fixed order, each weighted by
+ * exp(m - largest m) (bit-identical results from run to run), divided, and LSE = largest m + ln l.  The max of
+ * every range is exact whatever n_sink, n_local and use_minit say: an estimate from the summaries, or a max fixed
+ * after the sink and local blocks, saves nothing in a step that is bound by reading the cache.  The result is
+ * exact attention over the n_keys rows.  n_splits >= 1 (ranges may be empty; B * Hkv * n_splits of 1.5 to 4 times the
+ * number of compute units runs within a few percent of the best; n_splits = 1 is a single launch and leaves the
+ * workspace alone); Hq / Hkv <= 32;
  * block_n = 64; d in {64, 128}.  workspace: vfa_decode_workspace_bytes(...) bytes, 16-byte aligned,
  * contents irrelevant on entry.  VFA_ERR_INVALID_ARG for n_keys < 1 or > n_cap, for
  * use_minit == 0 with n_sink + n_local == 0, and for the pointer / size errors listed above. */
@@ -201,7 +201,7 @@ int vfa_decode_fwd(const void* Q, const void* K, const void* V, const void* Krep
  * in one fixed array of VFA_DECODE_NOALLOC_MAX_BYTES bytes of device memory that is part of the library's
  * code object (each device the library is used on holds one copy until the process ends).  The call
  * allocates nothing, frees nothing, clears nothing (every slot that is read is written earlier in the same
- * call) and enqueues the same three kernels on `stream`.
+ * call) and enqueues the same kernels on `stream`.
  * Limit: B * Hq * n_splits * (2 + d) * 4 bytes <= VFA_DECODE_NOALLOC_MAX_BYTES (4 MiB: 8065 (head, range)
  * rows at d = 128, e.g. B * Hq = 504 with 16 ranges), else VFA_ERR_TOO_LARGE and nothing is launched.
  * The first call on a device looks the array's address up (hipGetSymbolAddress; VFA_ERR_HIP if that fails):
@@ -219,8 +219,9 @@ int vfa_decode_noalloc_fwd(const void* Q, const void* K, const void* V, const vo
  * seq_lens are DEVICE arrays of B ints (4-byte aligned), read by the kernels (the host never looks at
  * them, so a serving loop can update them on the GPU): sequence b has seq_lens[b] valid rows in its
  * part of the cache, values are clamped to [1, n_cap] (to [0, n_cap] in the append call, where
- * old >= new means nothing to do).  Everything else as in vfa_kblock_summary_append / vfa_decode_fwd;
- * each sequence's key range is cut into n_splits ranges of its own length. */
+ * old >= new means nothing to do).  Everything else as in vfa_kblock_summary_append / vfa_decode_fwd,
+ * except that n_splits is a mean: the B * n_splits ranges are dealt to the sequences by length, so that all
+ * are about equally long (with n_splits = 1 each sequence is one range). */
 int vfa_kblock_summary_append_varlen(const void* K, void* Krepr, int B, int Hkv, int n_cap,
                                      const int* old_lens, const int* new_lens, int d, int block_n,
                                      void* stream);

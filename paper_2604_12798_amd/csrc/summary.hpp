@@ -22,8 +22,10 @@ __device__ inline uint32_t key_max(uint32_t a, uint32_t b) {
 // N = row stride of one head's key array (its capacity), n_valid = keys present, Tc = block stride of
 // one head's summary array, j0 = first block to (re)compute and n_blocks their number: a growing cache
 // recomputes only the blocks that received keys.
-// With per-sequence lengths (old_len / new_len device arrays indexed by batch entry, Hkv heads per entry) the
-// grid covers every block of the capacity and a wave whose block received no key returns at once.
+// With per-sequence lengths (old_len / new_len device arrays indexed by batch entry, Hkv heads per entry) the blocks that
+// received keys follow from them, and the waves of a head's workgroups walk them in strides: the host, which does not know
+// how many there are, launches enough workgroups to fill the GPU once.  (One wave for every block of the capacity took
+// 4.9 us for one new key in each of 128 caches of 8192 rows, nearly all of it in workgroups with nothing to do.)
 template <int D>
 __global__ __launch_bounds__(256) void kblock_summary_kernel(const uint16_t* __restrict__ K, uint16_t* __restrict__ R,
                                                              int N, int n_valid, int Tc, int block_n, int j0, int n_blocks,
@@ -31,41 +33,42 @@ __global__ __launch_bounds__(256) void kblock_summary_kernel(const uint16_t* __r
                                                              const int* __restrict__ new_len = nullptr, int Hkv = 1) {
     constexpr int CH = D / 8;        // 16-byte chunks per row
     constexpr int RG = 64 / CH;      // rows a wave reads at once
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int jb = blockIdx.x * 4 + wave, bh = blockIdx.y;
-    if (jb >= n_blocks) return;
-    const int j = j0 + jb;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, bh = blockIdx.y;
+    const int ch = lane % CH, rg = lane / CH;
     if (new_len) {
         const int b = bh / Hkv;
-        const int n_new = min(max(new_len[b], 0), N), n_old = min(max(old_len[b], 0), n_new);
-        if (j < n_old / block_n || j * block_n >= n_new) return;  // (uniform over the wave)
-        n_valid = n_new;
+        n_valid = min(max(new_len[b], 0), N);
+        const int n_old = min(max(old_len[b], 0), n_valid);
+        j0 = n_old / block_n;
+        n_blocks = (n_valid + block_n - 1) / block_n - j0;
     }
-    const int ch = lane % CH, rg = lane / CH;
-    const int c0 = j * block_n, c1 = min(n_valid, c0 + block_n);
-    const uint16_t* base = K + (size_t)bh * N * D + ch * 8;
-    const uint32_t zero_key = sabs_key(0u);  // +0: the smallest magnitude, already the positive one
-    u32x4 acc = {zero_key, zero_key, zero_key, zero_key};
-    for (int r0 = c0 + rg; r0 < c1; r0 += 8 * RG) {
-        u32x4 x[8];
+    for (int jb = blockIdx.x * 4 + wave; jb < n_blocks; jb += gridDim.x * 4) {
+        const int j = j0 + jb;
+        const int c0 = j * block_n, c1 = min(n_valid, c0 + block_n);
+        const uint16_t* base = K + (size_t)bh * N * D + ch * 8;
+        const uint32_t zero_key = sabs_key(0u);  // +0: the smallest magnitude, already the positive one
+        u32x4 acc = {zero_key, zero_key, zero_key, zero_key};
+        for (int r0 = c0 + rg; r0 < c1; r0 += 8 * RG) {
+            u32x4 x[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int r = r0 + u * RG;
-            // (non-temporal: a streaming read; 10 % faster at 64 MiB of keys, no change to the attention kernel behind it)
-            x[u] = r < c1 ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (size_t)r * D)) : u32x4{0, 0, 0, 0};
+            for (int u = 0; u < 8; ++u) {
+                const int r = r0 + u * RG;
+                // (non-temporal: a streaming read; 10 % faster at 64 MiB of keys, no change to the attention kernel behind it)
+                x[u] = r < c1 ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (size_t)r * D)) : u32x4{0, 0, 0, 0};
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] = key_max(acc[e], sabs_key(x[u][e]));
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
+        for (int m = CH; m < 64; m <<= 1)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] = key_max(acc[e], sabs_key(x[u][e]));
-    }
-#pragma unroll
-    for (int m = CH; m < 64; m <<= 1)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] = key_max(acc[e], (uint32_t)__shfl_xor((int)acc[e], m));
-    if (rg == 0) {
-        const u32x4 out = {sabs_unkey(acc[0]), sabs_unkey(acc[1]), sabs_unkey(acc[2]), sabs_unkey(acc[3])};
-        *reinterpret_cast<u32x4*>(R + ((size_t)bh * Tc + j) * D + ch * 8) = out;
+            for (int e = 0; e < 4; ++e) acc[e] = key_max(acc[e], (uint32_t)__shfl_xor((int)acc[e], m));
+        if (rg == 0) {
+            const u32x4 out = {sabs_unkey(acc[0]), sabs_unkey(acc[1]), sabs_unkey(acc[2]), sabs_unkey(acc[3])};
+            *reinterpret_cast<u32x4*>(R + ((size_t)bh * Tc + j) * D + ch * 8) = out;
+        }
     }
 }
 

@@ -381,7 +381,9 @@ int vfa_kblock_summary_append_varlen(const void* K, void* Krepr, int B, int Hkv,
     if ((reinterpret_cast<uintptr_t>(old_lens) | reinterpret_cast<uintptr_t>(new_lens)) & 3u) return VFA_ERR_INVALID_ARG;
     if ((long long)B * Hkv > 65535) return VFA_ERR_UNSUPPORTED;
     const int tc_cap = ceil_div(n_cap, block_n);
-    const dim3 grid((unsigned)ceil_div(tc_cap, 4), (unsigned)(B * Hkv));
+    // (1024 workgroups: four of 256 threads on each compute unit, 128 KiB of loads in flight there)
+    const int per_head = min(ceil_div(tc_cap, 4), max(1, 1024 / (B * Hkv)));
+    const dim3 grid((unsigned)per_head, (unsigned)(B * Hkv));
     hipStream_t s = (hipStream_t)stream;
     (void)hipGetLastError();
     if (d == 128)
@@ -412,25 +414,32 @@ int decode_common(const void* Q, const void* K, const void* V, const void* Krepr
     if (workspace_bytes < vfa_decode_workspace_bytes(B, Hq, d, n_splits)) return VFA_ERR_INVALID_ARG;
     if ((long long)B * Hkv > 65535 || (long long)B * Hq > 0x7fffffffLL) return VFA_ERR_UNSUPPORTED;
     DecodeParams p{};
-    p.Q = (const uint16_t*)Q; p.K = (const uint16_t*)K; p.V = (const uint16_t*)V; p.Krepr = (const uint16_t*)Krepr;
+    p.Q = (const uint16_t*)Q; p.K = (const uint16_t*)K; p.V = (const uint16_t*)V;
     p.O = (uint16_t*)O; p.LSE = LSE;
-    p.B = B; p.Hq = Hq; p.Hkv = Hkv; p.n_cap = n_cap; p.n_keys = n_keys; p.seq_lens = seq_lens; p.tc_cap = ceil_div(n_cap, block_n);
-    p.n_splits = n_splits; p.n_sink = n_sink; p.n_local = n_local; p.use_minit = use_minit;
+    p.B = B; p.Hq = Hq; p.Hkv = Hkv; p.n_cap = n_cap; p.n_keys = n_keys; p.seq_lens = seq_lens; p.n_splits = n_splits;
     const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)d);
     p.c = scale * kLog2e;
     const size_t rows = (size_t)B * Hq * n_splits;
     p.opart = (float*)workspace; p.pm = p.opart + rows * d; p.lpart = p.pm + rows;  // the 16-byte stores go first
     hipStream_t s = (hipStream_t)stream;
-    const dim3 grid((unsigned)n_splits, (unsigned)(B * Hkv));
+    const dim3 grid((unsigned)n_splits, (unsigned)B, (unsigned)Hkv);
+    // Waves per range: two tiles of 16 KiB in flight per wave at d = 128, of 8 KiB at d = 64, and what the reads need is about
+    // 64 KiB in flight per compute unit.  At 512 ranges (two per compute unit) one wave each is enough at d = 128 (512 MiB:
+    // 88.8 us against 92.9 with two) and four are best at d = 64 (125 MiB: 28.1 us against 29.4 with two and 33 with one);
+    // a range with fewer tiles than waves leaves waves idle
+    const long long wgs = (long long)B * Hkv * n_splits;
+    const int tiles = ceil_div(ceil_div(n_keys, BN), n_splits);
+    const int n_cu = cu_count() > 0 ? cu_count() : 256;
     (void)hipGetLastError();
     if (d == 128) {
-        decode_max_kernel<128><<<grid, 64, 0, s>>>(p);
-        decode_split_kernel<128><<<grid, 64, 0, s>>>(p);
-        decode_merge_kernel<128><<<(unsigned)(B * Hq), 128, 0, s>>>(p);
+        if (tiles >= 2 && wgs <= n_cu) decode_split_kernel<128, 2><<<grid, 128, 0, s>>>(p);
+        else decode_split_kernel<128, 1><<<grid, 64, 0, s>>>(p);
+        if (n_splits > 1) decode_merge_kernel<128><<<(unsigned)(B * Hq), 256, 0, s>>>(p);
     } else {
-        decode_max_kernel<64><<<grid, 64, 0, s>>>(p);
-        decode_split_kernel<64><<<grid, 64, 0, s>>>(p);
-        decode_merge_kernel<64><<<(unsigned)(B * Hq), 64, 0, s>>>(p);
+        if (tiles >= 4 && wgs <= 2LL * n_cu) decode_split_kernel<64, 4><<<grid, 256, 0, s>>>(p);
+        else if (tiles >= 2 && wgs <= 4LL * n_cu) decode_split_kernel<64, 2><<<grid, 128, 0, s>>>(p);
+        else decode_split_kernel<64, 1><<<grid, 64, 0, s>>>(p);
+        if (n_splits > 1) decode_merge_kernel<64><<<(unsigned)(B * Hq), 256, 0, s>>>(p);
     }
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
 }

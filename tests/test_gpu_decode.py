@@ -209,3 +209,33 @@ def test_decode_with_per_sequence_lengths(vfa, oracle, name, shape, lens, n_spli
         err = np.abs(O[b].float().cpu().numpy().astype(np.float64) - ref["O"][0])
         lerr = np.abs(L[b].cpu().numpy().astype(np.float64) - ref["LSE"][0]).max()
         assert err.max() <= O_MAX_ABS and err.mean() <= O_MEAN_ABS and lerr <= LSE_ABS, (b, n, err.max(), lerr)
+
+
+@pytest.mark.parametrize("d,Hkv,n_splits", [(128, 1, 1), (128, 2, 3), (64, 1, 2), (64, 2, 40)])
+def test_varlen_ranges_of_more_entries_than_a_wave_has_lanes(vfa, oracle, d, Hkv, n_splits):
+    """The ranges are dealt out 64 entries at a time: 70 entries, lengths from 1 to the capacity, one of them far longer than
+    the rest (so the first estimates of the range length do not fit), one out of range (clamped)."""
+    import torch
+    B, g, n_cap = 70, 2, 640
+    t = _cache(B=B, Hq=g * Hkv, Hkv=Hkv, n_cap=n_cap, d=d, F=4 if d == 64 else 8)
+    lens = np.random.default_rng(3).integers(1, 130, size=B).astype(np.int32)
+    lens[[0, 63, 64, 69]] = [n_cap, 64, 65, 1]
+    given = lens.copy()
+    given[0] = n_cap + 1000
+    Qb = np.ascontiguousarray(np.stack([t["Q"][b, :, lens[b] - 1] for b in range(B)]))
+    O, L = vfa.decode_varlen_fwd(to_gpu(Qb), to_gpu(t["K"]), to_gpu(t["V"]), torch.from_numpy(given).cuda(), use_minit=False,
+                                 n_splits=n_splits)
+    torch.cuda.synchronize()
+    O, L = O.float().cpu().numpy().astype(np.float64), L.cpu().numpy()
+    Kh, Vh = wl.bf16_bits_to_f32(t["K"]), wl.bf16_bits_to_f32(t["V"])
+    for b in range(B):
+        ref = oracle.decode(wl.bf16_bits_to_f32(Qb[b:b + 1]), Kh[b:b + 1], Vh[b:b + 1], int(lens[b]), 64)
+        # bf16 weights and output: half an ulp each of a value of at most max|V|
+        assert np.abs(O[b] - ref["O"][0]).max() <= 2.0 ** -7 * np.abs(Vh[b]).max() and np.abs(L[b] - ref["LSE"][0]).max() <= LSE_ABS, b
+
+
+@pytest.mark.parametrize("d,n_keys,n_splits", [(128, 64, 1), (128, 200, 1), (128, 129, 2), (64, 257, 1), (64, 1000, 2), (64, 130, 3)])
+def test_decode_waves_per_range(vfa, oracle, d, n_keys, n_splits):
+    """One, two and four waves to a range, ranges of fewer tiles than waves, and the single range that skips the merge."""
+    t = _cache(B=1, Hq=6, Hkv=2, n_cap=1024, d=d, F=4 if d == 64 else 8)
+    _check(vfa, oracle, t, n_keys, n_splits=n_splits)
