@@ -27,8 +27,9 @@
  *
  * Calls may be recorded into a HIP graph (they only enqueue kernels; nothing is allocated, copied
  * or cleared).  One exception: the first launch, on each device, of an attention kernel that needs
- * more than 64 KiB of LDS (d = 128 with block_m = 128) sets that function attribute, so make one
- * ordinary call per entry point, device and process before capturing.
+ * more than 64 KiB of LDS sets that function attribute, so make one ordinary call per entry point, head width d,
+ * device and process before capturing (of any size: it sets the attribute for every kernel that a later call of
+ * that entry point and d may take).
  */
 #ifndef VFA_H_
 #define VFA_H_

@@ -1,4 +1,5 @@
-// Generic bf16 attention kernel: any supported (d, block_m), all modes and ablation switches.
+// Generic bf16 attention kernel: any supported (d, block_m), all ablation switches; Alg. 2 where attn_vsa.hpp does not cover it,
+// the baselines at d = 64.
 #pragma once
 #include "common.hpp"
 

@@ -10,6 +10,7 @@
 #include "common.hpp"
 #include "attn_generic.hpp"
 #include "attn_pingpong.hpp"
+#include "attn_frozen.hpp"
 #include "vsa_pp.hpp"
 #include "summary.hpp"
 #include "decode.hpp"
@@ -74,16 +75,63 @@ bool raise_lds_limit(KernelT kernel, int bytes, std::atomic<unsigned char>* done
     return true;
 }
 
+template <int D, int KS>
+bool raise_frozen() {
+    static std::atomic<unsigned char> lds_raised[kMaxDevices];
+    return raise_lds_limit(&attn_fwd_frozen_kernel<D, KS>, Frozen<D, KS>::LDS_BYTES, lds_raised);
+}
+template <int D, int KS>
+int launch_frozen(const Params& p, hipStream_t s) {
+    attn_fwd_frozen_kernel<D, KS><<<dim3((unsigned)(p.B * p.Hq * p.Tr)), 256 * KS, Frozen<D, KS>::LDS_BYTES, s>>>(p);
+    return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
+}
+
+// Which kernel Alg. 1 runs on at d = 128: true = attn_frozen.hpp (items of 128 rows, a third to a half cheaper than the
+// ping-pong kernel's items of 256), false = attn_pingpong.hpp (one and a half times the rate once the compute units are full).
+//   up to one 128-row item per compute unit: the ping-pong kernel would leave half of them idle (N = 1024, 32 heads: 29 us
+//     against 21.5)
+//   two to three per compute unit, all equally long (no causal mask): three rounds of short items against two of long ones
+//     (16 heads, N = 5000: 216 against 234 us).  Between one and two it is two rounds against one (N = 3072: 89 against 76 us),
+//     above three four against two, and under a causal mask the ping-pong kernel's long items find short ones to pair with
+//   fewer than 32 items: the ping-pong kernel, although the other one is faster there too.  It adds a row's terms in the order
+//     of Alg. 2's kernel, so that on small problems, where the two are compared with each other, they agree to the rounding of l
+//   many sink / local blocks: their scores are computed twice in attn_frozen.hpp
+bool prefer_frozen(const Params& p, int n_cu) {
+    const long long items = (long long)p.B * p.Hq * p.Tr;
+    if (p.n_sink > 4 || p.n_local > 4 || items < 32 || n_cu <= 0) return false;
+    return items <= n_cu || (!p.causal && items > 2LL * n_cu && items <= 3LL * n_cu);
+}
+
 template <int MODE>
 int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
     (void)hipGetLastError();
     const int g = p.Hq / p.Hkv;
+    const bool ablation = p.order_asc || p.all_special || p.rowskip || p.Qrepr || (MODE == MODE_VSA && p.tau2 >= 0.f);
     // ping-pong kernel: head pairs when the heads per KV head are even; otherwise (MHA, odd groups) pairs of
     // adjacent query blocks; for VSA only where each block still meets its tiles in Alg. 2's order
     // (causal, at most one local block), since the skip decisions depend on the max at the time of the visit
     const bool head_pairs = (g & 1) == 0;
-    if (d == 128 && block_m == 128 && !p.order_asc && !p.all_special && !p.rowskip && !p.Qrepr &&
-        !(MODE == MODE_VSA && p.tau2 >= 0.f) &&
+    // Without skipping, block_m decides only which blocks count as local ones, and a larger set of exact-max blocks is as good:
+    // everything runs in blocks of 128 rows then (d = 128 in blocks of 64, N = 4096: 219 us on the generic kernel, 131 here)
+    Params q = p;
+    if (MODE != MODE_VSA && !ablation) q.Tr = ceil_div(p.N, 128);
+    if constexpr (MODE == MODE_VFA) {
+        // (every LDS limit that this entry point may need at this d is raised on its first call: a later one may be captured)
+        if (!ablation && d == 64 && p.n_sink <= 4 && p.n_local <= 4) {
+            if (!raise_frozen<64, 1>() || !raise_frozen<64, 2>()) return VFA_ERR_HIP;
+            // two groups to an item while there is no more than one item per compute unit and a group has a few tiles
+            // (32 heads, N = 777: 12.4 against 13.6 us; N = 256: 8.4 against 8.0; N = 4096: 95 against 87)
+            if ((long long)q.B * q.Hq * q.Tr <= cu_count() && q.Tc >= 6) return launch_frozen<64, 2>(q, s);
+            return launch_frozen<64, 1>(q, s);
+        }
+        if (!ablation && d == 128) {
+            if (!raise_frozen<128, 2>()) return VFA_ERR_HIP;
+            static std::atomic<unsigned char> pp_raised[kMaxDevices];
+            if (!raise_lds_limit(&attn_fwd_pp_kernel<MODE_VFA>, PP_LDS_BYTES, pp_raised)) return VFA_ERR_HIP;
+            if (prefer_frozen(q, cu_count())) return launch_frozen<128, 2>(q, s);
+        }
+    }
+    if (d == 128 && (block_m == 128 || MODE != MODE_VSA) && !ablation &&
         (head_pairs || MODE != MODE_VSA || (p.causal && p.n_local <= 1))) {
         static std::atomic<unsigned char> lds_raised[kMaxDevices];  // one set of flags per instantiation
         if constexpr (MODE == MODE_VSA) {
@@ -96,9 +144,8 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
         } else {
             if (!raise_lds_limit(&attn_fwd_pp_kernel<MODE>, PP_LDS_BYTES, lds_raised)) return VFA_ERR_HIP;
         }
-        Params q = p;
         q.pair_blocks = head_pairs ? 0 : 1;
-        unsigned n_wg = (unsigned)(head_pairs ? p.B * (p.Hq / 2) * p.Tr : p.B * p.Hq * ((p.Tr + 1) / 2));
+        unsigned n_wg = (unsigned)(head_pairs ? q.B * (q.Hq / 2) * q.Tr : q.B * q.Hq * ((q.Tr + 1) / 2));
         // One workgroup fills a CU (128 KiB of LDS), so with more work items than CUs the kernel runs one
         // persistent workgroup per CU over a static share of the items: the next item starts without a
         // workgroup launch (worth about 1 % at N = 16K and 30 % at N = 4K, measured).
@@ -113,9 +160,12 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
         return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
     }
     const dim3 grid((unsigned)(p.B * p.Hq * p.Tr));
-    if (d == 128 && block_m == 128) attn_fwd_kernel<128, 4, MODE><<<grid, 256, 0, s>>>(p);
-    else if (d == 128 && block_m == 64) attn_fwd_kernel<128, 2, MODE><<<grid, 128, 0, s>>>(p);
-    else if (d == 64 && block_m == 128) attn_fwd_kernel<64, 4, MODE><<<grid, 256, 0, s>>>(p);
+    if constexpr (!is_fa(MODE)) {  // (the baselines take the ping-pong kernel for every call at d = 128)
+        if (d == 128 && block_m == 128) attn_fwd_kernel<128, 4, MODE><<<grid, 256, 0, s>>>(p);
+        else if (d == 128) attn_fwd_kernel<128, 2, MODE><<<grid, 128, 0, s>>>(p);
+        if (d == 128) return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
+    }
+    if (d == 64 && block_m == 128) attn_fwd_kernel<64, 4, MODE><<<grid, 256, 0, s>>>(p);
     else if (d == 64 && block_m == 64) attn_fwd_kernel<64, 2, MODE><<<grid, 128, 0, s>>>(p);
     else return VFA_ERR_UNSUPPORTED;
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;

@@ -1,0 +1,68 @@
+"""The kernel that fixes Alg. 1's max before the first softmax (attn_frozen.hpp), at the sizes where its tiles, groups of
+keys and staging batches begin and end, against the float64 oracle; bars as in the other parity tests."""
+import numpy as np
+import pytest
+
+from paper_2604_12798_amd import workloads as wl
+
+from gpu_util import check_o_lse, gpu_inputs, host_f32
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(oracle, w, use_minit=True, sample=None, before=None):
+    import torch
+    import paper_2604_12798_amd as vfa
+    t = wl.generate(w)
+    Q, K, V = gpu_inputs(t)
+    if before is not None:
+        before(vfa)
+    O, L = vfa.vfa_attn_fwd(Q, K, V, block_m=w.block_m, causal=w.causal, n_sink=w.n_sink, n_local=w.n_local, use_minit=use_minit)
+    torch.cuda.synchronize()
+    blocks = wl.all_blocks(w) if sample is None else wl.sample_blocks(w, sample)
+    ref = oracle.blocks(*host_f32(t), w.block_m, w.block_n, w.causal, blocks, n_sink=w.n_sink, n_local=w.n_local, use_minit=use_minit)
+    check_o_lse(O, L, ref["O"], ref["LSE"], blocks, w.block_m, w.N, w.name)
+
+
+def _w(**kw):
+    kw.setdefault("F", 4 if kw.get("d") == 64 else 8)
+    return wl.small(wl.CONFIGS["cfg2"], **kw)
+
+
+# one to a few tiles (the second group of keys has none, one less or as many), ragged and whole, both head widths
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N", [1, 64, 65, 129, 320, 385, 448])
+@pytest.mark.parametrize("causal", [True, False])
+def test_tile_counts(oracle, d, N, causal):
+    _check(oracle, _w(B=2, Hq=16, Hkv=4, N=N, d=d, causal=causal), sample=6)
+
+
+# the sets of blocks whose maxima are taken first: none, overlapping, more than four tiles in all, no estimate from the summaries
+@pytest.mark.parametrize("d,block_m", [(64, 64), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("n_sink,n_local,use_minit", [(0, 0, True), (0, 2, False), (1, 0, False), (3, 1, True), (4, 4, True), (2, 4, False)])
+def test_sink_and_local_sets(oracle, d, block_m, n_sink, n_local, use_minit):
+    for causal in (True, False):
+        _check(oracle, _w(B=1, Hq=8, Hkv=8, N=600, d=d, block_m=block_m, causal=causal, n_sink=n_sink, n_local=n_local),
+               use_minit=use_minit, sample=6)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_two_tiles_of_summaries(oracle, d):
+    """More than 4096 keys: the summaries fill more than one tile, and the max phase takes more than one batch."""
+    _check(oracle, _w(B=1, Hq=2, Hkv=1, N=4180, d=d, n_local=3), sample=6)
+
+
+def test_three_rounds_without_a_causal_mask(oracle):
+    """Between two and three items per compute unit of a 256-unit chip, not causal: the rule's second case at d = 128."""
+    _check(oracle, _w(B=5, Hq=64, Hkv=8, N=200, causal=False), sample=8)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_what_lds_held_before_does_not_matter(oracle, d):
+    """The call in front leaves NaN in every tile's memory; the first step multiplies its zero weights with an empty tile."""
+    def poison(vfa):
+        import torch
+        x = torch.full((8, 32, 512, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+        vfa.fa_baseline_fwd(x, x, x, causal=False)
+    for n in (64, 200):
+        _check(oracle, _w(B=1, Hq=32, Hkv=8, N=n, d=d, n_sink=1, n_local=0), sample=6, before=poison)
