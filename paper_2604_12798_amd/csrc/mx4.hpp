@@ -28,85 +28,108 @@ struct Tile4 {
     __device__ static int k_off(int r, int c) { return r * 64 + ((c ^ ((r >> 2) & 3)) << 4); }
 };
 
-// E2M1 magnitudes by code (sign in bit 3)
-__device__ __forceinline__ float e2m1_value(uint32_t code) {
-    const uint32_t mag = code & 7u;
-    const float v = mag < 2u ? 0.5f * (float)mag : __builtin_ldexpf(1.0f + 0.5f * (float)(mag & 1u), (int)(mag >> 1) - 1);
-    return (code & 8u) ? -v : v;
-}
-
 // X bf16 -> MXFP4: thread = 8 consecutive elements, 4 threads = one block of 32.  y = x * pre_scale (fp32);
 // scale byte = exponent field of max|y| - 2, at least 0; element = y / 2^(byte - 127) rounded to the nearest
-// of 0, 0.5, 1, 1.5, 2, 3, 4, 6, ties to the even mantissa (the comparisons below), saturated at 6.
+// of 0, 0.5, 1, 1.5, 2, 3, 4, 6, ties to the even mantissa, saturated at 6.  The rounding is integer arithmetic on the bits of
+// |y| 2^(127 - byte): from 1 up the code is the top of the float rounded to one mantissa bit (nearest even: half an ulp less
+// one, plus the bit that stays last), below 1 it is 2 |y| rounded to a whole number (nearest even), and at 1 the two agree.
+// (Seven comparisons per element took 36 us for 94 MiB, bound by the vector unit.)
 __global__ __launch_bounds__(256) void mx4_quantize_kernel(const uint16_t* __restrict__ X, uint8_t* __restrict__ Y,
                                                            uint8_t* __restrict__ S, long long n8, float pre_scale) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    const bool live = i < n8;  // (n8 is a multiple of 4, so the four threads of a block are live together)
-    u32x4 x = {0, 0, 0, 0};
-    if (live) x = *reinterpret_cast<const u32x4*>(X + i * 8);
-    float v[8];
-    float amax = 0.f;
+    // (a workgroup's loads as in fp8_quantize_kernel.  n8 is a multiple of 4, so the four threads of a block are live together)
+    const long long i0 = (long long)blockIdx.x * (256 * QUANT_CHUNKS) + threadIdx.x;
+    u32x4 x[QUANT_CHUNKS];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        v[2 * e] = __uint_as_float(x[e] << 16) * pre_scale;
-        v[2 * e + 1] = __uint_as_float(x[e] & 0xffff0000u) * pre_scale;
-        amax = fmaxf(amax, fmaxf(fabsf(v[2 * e]), fabsf(v[2 * e + 1])));
-    }
-    amax = fmaxf(amax, __shfl_xor(amax, 1));
-    amax = fmaxf(amax, __shfl_xor(amax, 2));
-    const int ef = (int)((__float_as_uint(amax) >> 23) & 0xffu);
-    const int sb = max(ef - 2, 0);
-    const float mult = __uint_as_float((uint32_t)(254 - sb) << 23);  // 2^(127 - sb)
-    uint32_t w = 0;
+    for (int u = 0; u < QUANT_CHUNKS; ++u)
+        x[u] = i0 + 256 * u < n8 ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(X + (i0 + 256 * u) * 8)) : u32x4{0, 0, 0, 0};
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float y = fabsf(v[e]) * mult;
-        uint32_t c = (uint32_t)(y > 0.25f) + (uint32_t)(y >= 0.75f) + (uint32_t)(y > 1.25f) + (uint32_t)(y >= 1.75f) +
-                     (uint32_t)(y > 2.5f) + (uint32_t)(y >= 3.5f) + (uint32_t)(y > 5.0f);
-        c |= (__float_as_uint(v[e]) >> 28) & 8u;
-        w |= c << (4 * e);
-    }
-    if (live) {
-        *reinterpret_cast<uint32_t*>(Y + i * 4) = w;
-        if ((threadIdx.x & 3) == 0) S[i >> 2] = (uint8_t)sb;
+    for (int u = 0; u < QUANT_CHUNKS; ++u) {
+        const long long i = i0 + 256 * u;
+        float v[8];
+        float amax = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[2 * e] = __uint_as_float(x[u][e] << 16) * pre_scale;
+            v[2 * e + 1] = __uint_as_float(x[u][e] & 0xffff0000u) * pre_scale;
+            amax = fmaxf(amax, fmaxf(fabsf(v[2 * e]), fabsf(v[2 * e + 1])));
+        }
+        amax = fmaxf(amax, __shfl_xor(amax, 1));
+        amax = fmaxf(amax, __shfl_xor(amax, 2));
+        const int ef = (int)((__float_as_uint(amax) >> 23) & 0xffu);
+        const int sb = max(ef - 2, 0);
+        const float mult = __uint_as_float((uint32_t)(254 - sb) << 23);  // 2^(127 - sb)
+        uint32_t w = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float y = __builtin_amdgcn_fmed3f(fabsf(v[e]) * mult, 0.f, 6.f);  // (a NaN becomes 0)
+            const uint32_t b = __float_as_uint(y);
+            const uint32_t hi = ((b + 0x1fffffu + ((b >> 22) & 1u)) >> 22) - 252u;  // 1.0 = 0x3f800000 -> 254 -> code 2
+            const uint32_t lo = (uint32_t)__builtin_rintf(y + y);
+            uint32_t c = y < 1.f ? lo : hi;
+            c |= (__float_as_uint(v[e]) >> 28) & 8u;
+            w |= c << (4 * e);
+        }
+        if (i < n8) {
+            *reinterpret_cast<uint32_t*>(Y + i * 4) = w;
+            if ((threadIdx.x & 3) == 0) S[i >> 2] = (uint8_t)sb;
+        }
     }
 }
 
 // sabsmax of a block of MXFP4 keys, per feature over the dequantised values (tie -> the positive one), stored
 // as MX blocks of E5M2: scale byte = exponent field of the block maximum - 15; codes [B*Hkv, Tc, 128],
-// scales [B*Hkv, Tc, 4].  256 threads: thread (row, blk) dequantises the 32 elements of MX block blk of key row
-// into LDS (rows past the end of a ragged block repeat its last row), then one thread per feature folds the 64
-// rows; the pick is commutative and associative up to the sign of a zero, which is set to + at the end.
+// scales [B*Hkv, Tc, 4].  Magnitudes are compared as whole numbers: an element of magnitude code m (1 .. 7) under scale byte s
+// has rank 2 s + {0, 2, 3, 4, 5, 6, 7}[m - 1] + 2 (two ranks to a binade, so equal values have equal ranks whatever their scales),
+// a zero has rank 0, and the key (rank << 1 | positive) picks the larger magnitude and of equal ones the positive.
+// 256 threads: thread (row group, c) takes dword c (eight features) of four rows (rows past the end of a ragged block repeat its
+// last row); lanes, then the four waves, combine.
 __global__ __launch_bounds__(256) void mx4_kblock_summary_kernel(const uint8_t* __restrict__ K4, const uint8_t* __restrict__ KS,
                                                                  uint8_t* __restrict__ R, uint8_t* __restrict__ RS, int N,
                                                                  int Tc) {
-    __shared__ float val[BN][128 + 1];
+    __shared__ uint32_t part[4][128];
     const int j = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;
     const int rows = min(BN, N - j * BN);
-    {
-        const int row = tid >> 2, blk = tid & 3;
-        const size_t r = (size_t)bh * N + (size_t)j * BN + min(row, rows - 1);
-        const u32x4 c = *reinterpret_cast<const u32x4*>(K4 + r * 64 + blk * 16);
-        const int e = (int)KS[r * 4 + blk] - 127;
+    const int c = tid & 15, rg = tid >> 4;
+    uint32_t best[8];
 #pragma unroll
-        for (int q = 0; q < 32; ++q) val[row][32 * blk + q] = __builtin_ldexpf(e2m1_value((c[q >> 3] >> (4 * (q & 7))) & 0xfu), e);
+    for (int q = 0; q < 8; ++q) best[q] = 1u;  // +0
+    uint32_t w[4], sc[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const size_t r = (size_t)bh * N + (size_t)j * BN + min(4 * rg + u, rows - 1);
+        w[u] = *reinterpret_cast<const uint32_t*>(K4 + r * 64 + 4 * c);
+        sc[u] = KS[r * 4 + (c >> 2)];
     }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const uint32_t code = (w[u] >> (4 * q)) & 0xfu, m = code & 7u;
+            const uint32_t rank = m == 0u ? 0u : 2u * sc[u] + 2u + (m == 1u ? 0u : m);
+            best[q] = max(best[q], (rank << 1) | (code < 8u ? 1u : 0u));
+        }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        best[q] = max(best[q], (uint32_t)__shfl_xor((int)best[q], 16));
+        best[q] = max(best[q], (uint32_t)__shfl_xor((int)best[q], 32));
+    }
+    if ((tid & 63) < 16)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) part[tid >> 6][8 * c + q] = best[q];
     __syncthreads();
     if (tid < 128) {
         const int t = tid;
-        float best = val[0][t];
-        for (int r = 1; r < BN; ++r) {
-            const float v = val[r][t];
-            const float av = fabsf(v), ab = fabsf(best);
-            best = (av > ab || (av == ab && v > best)) ? v : best;
-        }
-        best = best == 0.f ? 0.f : best;  // a column of zeros of either sign: +0
-        float amax = fabsf(best);
+        const uint32_t key = max(max(part[0][t], part[1][t]), max(part[2][t], part[3][t]));
+        const int rank = (int)(key >> 1) - 2;  // 2 E + man: the magnitude is (1 + man / 2) 2^(E - 1 - 127)
+        float v = key < 2u ? 0.f : __builtin_ldexpf((rank & 1) ? 1.5f : 1.f, (rank >> 1) - 128);
+        v = (key & 1u) ? v : -v;
+        v = v == 0.f ? 0.f : v;  // (a column of zeros of either sign: +0)
+        float amax = fabsf(v);
 #pragma unroll
         for (int o = 16; o >= 1; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o));  // the 32 features of one MX block
         const int ef = (int)((__float_as_uint(amax) >> 23) & 0xffu);
         const int sb = max(ef - 15, 0);
-        const float y = __builtin_ldexpf(best, 127 - sb);  // at most 1.5 * 2^15: inside E5M2's finite range
+        const float y = __builtin_ldexpf(v, 127 - sb);  // at most 1.5 * 2^15: inside E5M2's finite range
         R[((size_t)bh * Tc + j) * 128 + t] = (uint8_t)(__builtin_amdgcn_cvt_pk_bf8_f32(y, 0.f, 0, false) & 0xff);
         if ((t & 31) == 0) RS[((size_t)bh * Tc + j) * 4 + (t >> 5)] = (uint8_t)sb;
     }
@@ -193,9 +216,12 @@ __global__ __launch_bounds__(256, 3) void attn_mx4_kernel(const Mx4Params p) {
     // Alg. 1 keeps exp(S - m) in E5M2: the summaries of MXFP4 keys collect the upward rounding errors of 64 keys per
     // feature, so the seeded max can sit ten binades above the scores, more than E4M3 has to spare
     constexpr bool P_BF8 = MODE == MODE_VFA;
-    // two K stages of 4 KiB (together: the 8 KiB summary tile of the m-initialisation), two V^T stages of 8 KiB
-    __shared__ __attribute__((aligned(16))) uint8_t smem[2 * Tile4::KBYTES + 2 * Tile8::VBYTES];
+    // two K stages of 4 KiB, two V^T stages of 8 KiB; Alg. 1: three tiles of 8 KiB more for the max phase (with the second V^T
+    // stage four slots, each large enough for a tile of summaries)
+    constexpr int RING = 2 * Tile4::KBYTES + 2 * Tile8::VBYTES;
+    __shared__ __attribute__((aligned(16))) uint8_t smem[RING + (MODE == MODE_VFA ? 3 * Tile8::KBYTES : 0)];
     __shared__ uint32_t kscale[2][BN];
+    __shared__ uint32_t mscale[MODE == MODE_VFA ? 4 : 1][BN];
     uint8_t* const Ksm = smem;
     uint8_t* const Vsm = smem + 2 * Tile4::KBYTES;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -240,72 +266,98 @@ __global__ __launch_bounds__(256, 3) void attn_mx4_kernel(const Mx4Params p) {
             qs[kh] = spread_byte(sw, 2 * kh + hh) + (NOEXP ? 0x02020202 : 0);  // (scale bytes of real data are far from 253)
         }
     }
-    auto load_k = [&](int j, int buf) __attribute__((always_inline)) {
+    const int nv = j_hi + 1;
+    auto load_kv = [&](int j, int buf) __attribute__((always_inline)) {
         load_tile4(Kg, j * BN, N, Ksm + buf * Tile4::KBYTES, wave, lane);
+        load_tile8<true, 4>(Vg + (size_t)j * Tile8::VBYTES, 0, 0, Vsm + buf * Tile8::VBYTES, wave, lane);
         if (wave == 0) load_scales64(Ksg, j * BN, N, kscale[buf], lane);
     };
     float m2 = -INFINITY;
-    if (MODE == MODE_VFA && p.use_minit) {
+    if (MODE == MODE_VFA) {
+        // as in attn_fp8_kernel
         const uint8_t* Rg = p.Krepr + ((size_t)(b * p.Hkv + hkv) * p.Tc) * D;
         const uint8_t* RSg = p.KreprS + ((size_t)(b * p.Hkv + hkv) * p.Tc) * 4;
+        const MaxTiles mt = max_tiles(p.use_minit, p.n_sink, p.n_local, a_lo, a_hi, nv);
+        auto stage = [&](int u) __attribute__((always_inline)) { return u < 3 ? smem + RING + u * Tile8::KBYTES : Vsm + Tile8::VBYTES; };
         float mx = -INFINITY;
-        for (int ts = 0; ts * BN <= j_hi; ++ts) {
-            __syncthreads();
-            load_tile8<false, 4>(Rg, ts * BN, p.Tc, Ksm, wave, lane);
-            if (wave == 0) load_scales64(RSg, ts * BN, p.Tc, kscale[0], lane);
-            wait_vm0_and_sync();
-            f32x16 st[2];
+        for (int t0 = 0; t0 < mt.total; t0 += 4) {
+            if (t0) __syncthreads();
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int row = 32 * t + ql;
-                const uint32_t sc = kscale[0][row];
-#pragma unroll
-                for (int kh = 0; kh < 2; ++kh) {
-                    // 8-bit operand: bytes 0..15 of half hh are k = 16 hh + j, bytes 16..31 are k = 32 + 16 hh + j
-                    const int c0 = 4 * kh + hh;
-                    const i32x8 f = lds_frag8(Ksm + Tile8::k_off(row, c0), Ksm + Tile8::k_off(row, c0 + 2));
-                    st[t] = mfma_bf8_f4(f, qf[kh], kh ? st[t] : f32x16{0}, spread_byte(sc, 2 * kh + hh), qs[kh]);
+            for (int u = 0; u < 4; ++u) {
+                const int t = t0 + u;
+                if (t < mt.n_sum) {
+                    load_tile8<false, 4>(Rg, t * BN, nv, stage(u), wave, lane);
+                    if (wave == 0) load_scales64(RSg, t * BN, nv, mscale[u], lane);
+                } else if (t < mt.total) {
+                    load_tile4(Kg, mt.block(t) * BN, N, stage(u), wave, lane);
+                    if (wave == 0) load_scales64(Ksg, mt.block(t) * BN, N, mscale[u], lane);
                 }
             }
-            mx = fmaxf(mx, tile_rowmax<true>(st, ts * BN, j_hi, hh));
+            if (t0 == 0) {
+                load_kv(0, 0);
+                // the staged tiles have landed, not yet those of the main loop (three loads, four in the wave that moves the scales)
+                if (wave == 0) __builtin_amdgcn_s_waitcnt(0x0F74);
+                else __builtin_amdgcn_s_waitcnt(0x0F73);
+            } else {
+                __builtin_amdgcn_s_waitcnt(0x0F70);
+            }
+            __syncthreads();
+#pragma unroll 1
+            for (int t = t0; t < min(t0 + 4, mt.total); ++t) {
+                const uint8_t* const tile = stage(t - t0);
+                const uint32_t* const sc = mscale[t - t0];
+                f32x16 st[2];
+                if (t < mt.n_sum) {
+#pragma unroll
+                    for (int h2 = 0; h2 < 2; ++h2) {
+                        const int row = 32 * h2 + ql;
+#pragma unroll
+                        for (int kh = 0; kh < 2; ++kh) {
+                            // 8-bit operand: bytes 0..15 of half hh are k = 16 hh + j, bytes 16..31 are k = 32 + 16 hh + j
+                            const int c0 = 4 * kh + hh;
+                            const i32x8 f = lds_frag8(tile + Tile8::k_off(row, c0), tile + Tile8::k_off(row, c0 + 2));
+                            st[h2] = mfma_bf8_f4(f, qf[kh], kh ? st[h2] : f32x16{0}, spread_byte(sc[row], 2 * kh + hh), qs[kh]);
+                        }
+                    }
+                } else {
+                    qk_tile4(tile, sc, qf, qs, st, ql, hh);
+                }
+                const int j = mt.block(t);
+                if (t < mt.n_sum || (j * BN + BN <= N && !(p.causal && j * BN + BN - 1 > row0))) mx = fmaxf(mx, tile_rowmax<false>(st, 0, 0, hh));
+                else mx = fmaxf(mx, tile_rowmax<true>(st, j * BN, limit, hh));
+            }
         }
         m2 = xhalf_max(mx) * p.c;
-        __syncthreads();
+    } else {
+        load_kv(0, 0);
     }
-    Params vp{};
-    vp.n_sink = p.n_sink; vp.n_local = p.n_local;
-    const Visit vis = make_visit<MODE>(vp, a_lo, a_hi, j_hi);
+    wait_vm0_and_sync();
     f32x16 ot[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db) ot[db] = f32x16{0};
     float lsum = 0.f;
-    {
-        const int j0 = vis.tile(0);
-        load_k(j0, 0);
-        load_tile8<true, 4>(Vg + (size_t)j0 * Tile8::VBYTES, 0, 0, Vsm, wave, lane);
-        wait_vm0_and_sync();
-    }
     f32x16 start;  // FOLD: -(m + H) of this lane's query in all 16 registers, set once the max is frozen
     f32x16 lt = {0};   // NOEXP: 32 copies of this lane's row sum of the rounded weights (times 2^15)
     float code0 = 0.f;  // NOEXP: code offset - 4 (m + H)
-    auto visit = [&](int k, auto special_c, auto masked_c) __attribute__((always_inline)) {
-        constexpr bool SPECIAL = decltype(special_c)::value, MASKED = decltype(masked_c)::value;
-        const int j = vis.tile(k), buf = k & 1;
-        if (k + 1 < vis.total) {
-            const int jn = vis.tile(k + 1);
-            load_k(jn, buf ^ 1);
-            load_tile8<true, 4>(Vg + (size_t)jn * Tile8::VBYTES, 0, 0, Vsm + (buf ^ 1) * Tile8::VBYTES, wave, lane);
-        }
+    if (FOLD) {
+        const float v = -(m2 + p.headroom);
+        if (NOEXP) code0 = kCodeOffset + kCodesPerBinade * v;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) start[r] = v;
+    }
+    auto visit = [&](int j, auto masked_c) __attribute__((always_inline)) {
+        constexpr bool SPECIAL = is_fa(MODE), MASKED = decltype(masked_c)::value;
+        const int buf = j & 1;
+        if (j + 1 < nv) load_kv(j + 1, buf ^ 1);
         f32x16 st[2];
         uint32_t pk[8];
         __builtin_amdgcn_s_setprio(1);
-        if (FOLD && !SPECIAL && !NOEXP) qk_tile4(Ksm + buf * Tile4::KBYTES, kscale[buf], qf, qs, st, ql, hh, &start);
+        if (FOLD && !NOEXP) qk_tile4(Ksm + buf * Tile4::KBYTES, kscale[buf], qf, qs, st, ql, hh, &start);
         else qk_tile4(Ksm + buf * Tile4::KBYTES, kscale[buf], qf, qs, st, ql, hh);
         __builtin_amdgcn_s_setprio(0);
         const bool needs_mask = (p.causal && j * BN + BN - 1 > row0) || (j + 1) * BN > N;
-        if (NOEXP && !SPECIAL) codes_tile8<MASKED>(st, pk, j * BN, needs_mask ? limit : 0x3fffffff, hh, code0);
-        else if (NOEXP) special_tile8_noexp<MASKED>(st, pk, ot, lt, m2, p.headroom, j * BN, needs_mask ? limit : 0x3fffffff, hh);
-        else if (FOLD && !SPECIAL) softmax_tile8_folded<MASKED, P_BF8>(st, pk, lsum, j * BN, needs_mask ? limit : 0x3fffffff, hh);
+        if (NOEXP) codes_tile8<MASKED>(st, pk, j * BN, needs_mask ? limit : 0x3fffffff, hh, code0);
+        else if (FOLD) softmax_tile8_folded<MASKED, P_BF8>(st, pk, lsum, j * BN, needs_mask ? limit : 0x3fffffff, hh);
         else softmax_tile8<SPECIAL, MASKED, P_BF8>(st, pk, ot, m2, lsum, p.c, p.headroom, j * BN, needs_mask ? limit : 0x3fffffff, hh);
         __builtin_amdgcn_s_setprio(1);
         pv_tile8<P_BF8>(Vsm + buf * Tile8::VBYTES, pk, ot, lane, hh);
@@ -319,43 +371,18 @@ __global__ __launch_bounds__(256, 3) void attn_mx4_kernel(const Mx4Params p) {
     };
     using std::false_type;
     using std::true_type;
-    constexpr bool TAIL_SPECIAL = is_fa(MODE);
-    const int n_lead = TAIL_SPECIAL ? 0 : min(vis.n_special, vis.total);
-    int k_fast_end;
-    {
-        int j_masked = p.causal ? a_lo : p.Tc;
-        if (N % BN) j_masked = min(j_masked, p.Tc - 1);
-        int cnt = max(0, j_masked - vis.n1);
-        if (vis.n2 > 0) cnt -= max(0, min(j_masked, vis.s2 + vis.n2) - vis.s2);
-        k_fast_end = max(n_lead, min(vis.total, n_lead + cnt));
-    }
-    int k = 0;
-    for (; k < n_lead; ++k) visit(k, true_type{}, true_type{});
-    if (FOLD) {
-        const float v = -(m2 + p.headroom);
-        if (NOEXP) code0 = kCodeOffset + kCodesPerBinade * v;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) start[r] = v;
-    }
-    for (; k < k_fast_end; ++k) visit(k, std::integral_constant<bool, TAIL_SPECIAL>{}, false_type{});
-    for (; k < vis.total; ++k) visit(k, std::integral_constant<bool, TAIL_SPECIAL>{}, true_type{});
+    int j_masked = p.causal ? a_lo : p.Tc;  // first tile that needs masking
+    if (N % BN) j_masked = min(j_masked, p.Tc - 1);
+    int j = 0;
+    for (; j < min(j_masked, nv); ++j) visit(j, false_type{});
+    for (; j < nv; ++j) visit(j, true_type{});
     // (NOEXP: every register of lt holds the whole row sum, with the same 2^15 as the numerator)
     const float l = NOEXP ? lt[0] * 0x1p-15f : xhalf_sum(lsum);
     const float inv = l > 0.f ? p.descale_v * (P_BF8 ? 0x1p-15f : 0x1p-8f) / l : 0.f;
-    if (qrow < N) {
-        uint16_t* Og = p.O + ((size_t)(b * p.Hq + h) * N + qrow) * D;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const u32x2 w = {pack_bf16(ot[db][4 * q4] * inv, ot[db][4 * q4 + 1] * inv),
-                                 pack_bf16(ot[db][4 * q4 + 2] * inv, ot[db][4 * q4 + 3] * inv)};
-                *reinterpret_cast<u32x2*>(Og + 32 * db + 8 * q4 + 4 * hh) = w;
-            }
-        if (p.LSE && hh == 0)
-            p.LSE[(size_t)(b * p.Hq + h) * N + qrow] =
-                l > 0.f ? (m2 + p.headroom + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
-    }
+    const size_t row = (size_t)(b * p.Hq + h) * N + qrow;
+    store_row8(p.O + row * D, qrow < N, ot, inv, hh);
+    if (qrow < N && p.LSE && hh == 0)
+        p.LSE[row] = l > 0.f ? (m2 + p.headroom + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
 }
 
 }  // namespace

@@ -506,7 +506,7 @@ int vfa_fp8_quantize(const void* X, void* X8, long long n, float inv_scale, void
     if (n < 0 || (n & 7) || !(inv_scale > 0.f) || !isfinite(inv_scale)) return VFA_ERR_INVALID_ARG;
     if (n == 0) return VFA_OK;
     if (!X || !X8 || !aligned16(X) || (reinterpret_cast<uintptr_t>(X8) & 7u)) return VFA_ERR_INVALID_ARG;
-    const long long n8 = n / 8, blocks = (n8 + 255) / 256;
+    const long long n8 = n / 8, blocks = (n8 + 256 * QUANT_CHUNKS - 1) / (256 * QUANT_CHUNKS);
     if (blocks > 0x7fffffffLL) return VFA_ERR_UNSUPPORTED;
     (void)hipGetLastError();
     fp8_quantize_kernel<<<(unsigned)blocks, 256, 0, (hipStream_t)stream>>>((const uint16_t*)X, (uint8_t*)X8, n8, inv_scale);
@@ -621,7 +621,7 @@ int vfa_mxfp4_quantize(const void* X, void* X4, void* XS, long long n, float pre
     if (n < 0 || (n & 31) || !(pre_scale > 0.f) || !isfinite(pre_scale)) return VFA_ERR_INVALID_ARG;
     if (n == 0) return VFA_OK;
     if (!X || !X4 || !XS || !aligned16(X) || (reinterpret_cast<uintptr_t>(X4) & 3u)) return VFA_ERR_INVALID_ARG;
-    const long long n8 = n / 8, blocks = (n8 + 255) / 256;
+    const long long n8 = n / 8, blocks = (n8 + 256 * QUANT_CHUNKS - 1) / (256 * QUANT_CHUNKS);
     if (blocks > 0x7fffffffLL) return VFA_ERR_UNSUPPORTED;
     (void)hipGetLastError();
     mx4_quantize_kernel<<<(unsigned)blocks, 256, 0, (hipStream_t)stream>>>((const uint16_t*)X, (uint8_t*)X4, (uint8_t*)XS, n8,
