@@ -1,5 +1,9 @@
 """Thin Python binding of libvfa.so (the C ABI declared in include/vfa.h).
 
+`lib()` is the library through ctypes, for callers who want the C ABI itself; the functions below go through the CPython
+module `_native` (csrc/binding.cpp), because ctypes takes 4 to 5 us to convert the twenty arguments of a call, which is
+more than the kernel launches behind it.
+
 Argument marshalling only: every step of the attention path runs in the HIP kernels behind
 the C entry points.  torch is used for device memory and streams.  There is no fallback: if
 the library is missing, or a call returns an error code, an exception is raised.
@@ -96,17 +100,32 @@ def strerror(code: int) -> str:
 
 
 def workspace_bytes(B: int, Hkv: int, N: int, d: int, block_n: int) -> int:
-    return int(lib().vfa_workspace_bytes(B, Hkv, N, d, block_n))
+    return _n().vfa_workspace_bytes(B, Hkv, N, d, block_n)
+
+
+_native = None
+
+
+def _n():
+    """The same entry points through the CPython module `_native` (csrc/binding.cpp), which the wrappers below call."""
+    global _native
+    if _native is None:
+        lib()  # torch and libvfa.so first, with their checks
+        import importlib
+        _native = importlib.import_module(__name__ + "._native")
+    return _native
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    # (the handle behind torch.cuda.current_stream(), without making a Stream object for it)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check_qkv(Q, K, V):
@@ -138,9 +157,9 @@ def kblock_summary(K, block_n: int = 64, out=None, stream=None, repr_mode: int =
     Tc = -(-N // block_n)
     R = torch.empty((B, Hkv, Tc, d), dtype=torch.bfloat16, device=K.device) if out is None else out
     if repr_mode == 0:
-        rc = lib().vfa_kblock_summary(_ptr(K), _ptr(R), B, Hkv, N, d, block_n, _stream(stream))
+        rc = _n().vfa_kblock_summary(_ptr(K), _ptr(R), B, Hkv, N, d, block_n, _stream(stream))
     else:
-        rc = lib().vfa_kblock_summary_mode(_ptr(K), _ptr(R), B, Hkv, N, d, block_n, int(repr_mode), _stream(stream))
+        rc = _n().vfa_kblock_summary_mode(_ptr(K), _ptr(R), B, Hkv, N, d, block_n, int(repr_mode), _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_kblock_summary")
     return R
@@ -150,7 +169,7 @@ def fa_baseline_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, softmax_sc
                     want_lse=True, stream=None):
     B, Hq, Hkv, N, d = _check_qkv(Q, K, V)
     O, L = _outputs(Q, out, lse, want_lse)
-    rc = lib().fa_baseline_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
+    rc = _n().fa_baseline_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
                                int(bool(causal)), float(softmax_scale), _stream(stream))
     if rc != 0:
         raise VfaError(rc, "fa_baseline_fwd")
@@ -161,7 +180,7 @@ def fa_lazy_rescale_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, softma
                         lse=None, want_lse=True, stream=None):
     B, Hq, Hkv, N, d = _check_qkv(Q, K, V)
     O, L = _outputs(Q, out, lse, want_lse)
-    rc = lib().fa_lazy_rescale_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
+    rc = _n().fa_lazy_rescale_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
                                    int(bool(causal)), float(softmax_scale), float(rescale_tau), _stream(stream))
     if rc != 0:
         raise VfaError(rc, "fa_lazy_rescale_fwd")
@@ -172,7 +191,7 @@ def fa_lazy_rescale_softexp_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True
                                 out=None, lse=None, want_lse=True, stream=None):
     B, Hq, Hkv, N, d = _check_qkv(Q, K, V)
     O, L = _outputs(Q, out, lse, want_lse)
-    rc = lib().fa_lazy_rescale_softexp_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m,
+    rc = _n().fa_lazy_rescale_softexp_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m,
                                            block_n, int(bool(causal)), float(softmax_scale), float(rescale_tau),
                                            _stream(stream))
     if rc != 0:
@@ -183,9 +202,8 @@ def fa_lazy_rescale_softexp_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True
 def _workspace(Q, K, block_n, workspace):
     import torch
     B, Hkv, N, d = K.shape
-    need = workspace_bytes(B, Hkv, N, d, block_n)
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=Q.device)
+        workspace = torch.empty(max(workspace_bytes(B, Hkv, N, d, block_n), 256), dtype=torch.uint8, device=Q.device)
     return workspace, workspace.numel() * workspace.element_size()
 
 
@@ -194,7 +212,7 @@ def vfa_attn_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, n_sink=1, n_l
     B, Hq, Hkv, N, d = _check_qkv(Q, K, V)
     O, L = _outputs(Q, out, lse, want_lse)
     ws, ws_bytes = _workspace(Q, K, block_n, workspace)
-    rc = lib().vfa_attn_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
+    rc = _n().vfa_attn_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
                             int(bool(causal)), int(n_sink), int(n_local), int(use_minit), float(softmax_scale),
                             _ptr(ws), ws_bytes, _stream(stream))
     if rc != 0:
@@ -212,7 +230,7 @@ def vsa_attn_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, n_sink=1, n_l
     M = skip_mask
     if M is None and want_mask:
         M = torch.empty((B, Hq, -(-N // block_m), -(-N // block_n)), dtype=torch.uint8, device=Q.device)
-    rc = lib().vsa_attn_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
+    rc = _n().vsa_attn_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
                             int(bool(causal)), int(n_sink), int(n_local), int(use_minit), float(softmax_scale),
                             float(skip_threshold_nats), _ptr(M), _ptr(ws), ws_bytes, _stream(stream))
     if rc != 0:
@@ -235,7 +253,7 @@ def vfa_variant_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, n_sink=1, 
     M = skip_mask
     if M is None and skip_threshold_nats != 0.0:
         M = torch.empty((B, Hq, -(-N // block_m), -(-N // block_n)), dtype=torch.uint8, device=Q.device)
-    rc = lib().vfa_variant_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
+    rc = _n().vfa_variant_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
                                int(bool(causal)), int(n_sink), int(n_local), int(use_minit), int(repr_mode),
                                int(q_repr_mode), int(bool(reorder)), int(bool(freeze)), int(bool(rowskip)), float(lazy_rescale_tau),
                                float(softmax_scale), float(skip_threshold_nats),
@@ -248,7 +266,7 @@ def vfa_variant_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, n_sink=1, 
 def kblock_summary_append(K, Krepr, n_old: int, n_new: int, block_n: int = 64, stream=None):
     """Refresh, in place, the summaries of the blocks of cache K [B, Hkv, n_cap, d] that hold rows [n_old, n_new)."""
     B, Hkv, n_cap, d = K.shape
-    rc = lib().vfa_kblock_summary_append(_ptr(K), _ptr(Krepr), B, Hkv, n_cap, int(n_old), int(n_new), d, block_n,
+    rc = _n().vfa_kblock_summary_append(_ptr(K), _ptr(Krepr), B, Hkv, n_cap, int(n_old), int(n_new), d, block_n,
                                          _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_kblock_summary_append")
@@ -258,7 +276,7 @@ def kblock_summary_append(K, Krepr, n_old: int, n_new: int, block_n: int = 64, s
 def kblock_summary_append_varlen(K, Krepr, old_lens, new_lens, block_n: int = 64, stream=None):
     """As kblock_summary_append with per-sequence lengths (int32 device tensors of B entries)."""
     B, Hkv, n_cap, d = K.shape
-    rc = lib().vfa_kblock_summary_append_varlen(_ptr(K), _ptr(Krepr), B, Hkv, n_cap, _ptr(old_lens), _ptr(new_lens), d,
+    rc = _n().vfa_kblock_summary_append_varlen(_ptr(K), _ptr(Krepr), B, Hkv, n_cap, _ptr(old_lens), _ptr(new_lens), d,
                                                 block_n, _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_kblock_summary_append_varlen")
@@ -274,9 +292,10 @@ def decode_varlen_fwd(q, K, V, seq_lens, *, krepr=None, block_n=64, n_sink=1, n_
     assert seq_lens.is_cuda and seq_lens.dtype == torch.int32 and seq_lens.numel() == B
     O = torch.empty_like(q) if out is None else out
     L = lse if (lse is not None or not want_lse) else torch.empty((B, Hq), dtype=torch.float32, device=q.device)
-    need = decode_workspace_bytes(B, Hq, d, n_splits)
-    ws = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device) if workspace is None else workspace
-    rc = lib().vfa_decode_varlen_fwd(_ptr(q), _ptr(K), _ptr(V), _ptr(krepr), _ptr(O), _ptr(L), B, Hq, Hkv, n_cap,
+    ws = workspace
+    if ws is None:
+        ws = torch.empty(max(decode_workspace_bytes(B, Hq, d, n_splits), 256), dtype=torch.uint8, device=q.device)
+    rc = _n().vfa_decode_varlen_fwd(_ptr(q), _ptr(K), _ptr(V), _ptr(krepr), _ptr(O), _ptr(L), B, Hq, Hkv, n_cap,
                                      _ptr(seq_lens), d, block_n, int(n_sink), int(n_local), int(bool(use_minit)),
                                      int(n_splits), float(softmax_scale), _ptr(ws), ws.numel() * ws.element_size(),
                                      _stream(stream))
@@ -286,7 +305,7 @@ def decode_varlen_fwd(q, K, V, seq_lens, *, krepr=None, block_n=64, n_sink=1, n_
 
 
 def decode_workspace_bytes(B: int, Hq: int, d: int, n_splits: int) -> int:
-    return int(lib().vfa_decode_workspace_bytes(B, Hq, d, n_splits))
+    return int(_n().vfa_decode_workspace_bytes(B, Hq, d, n_splits))
 
 
 def decode_fwd(q, K, V, n_keys: int, *, krepr=None, block_n=64, n_sink=1, n_local=1, use_minit=True, n_splits=8,
@@ -300,9 +319,10 @@ def decode_fwd(q, K, V, n_keys: int, *, krepr=None, block_n=64, n_sink=1, n_loca
             raise ValueError("q, K, V must be contiguous bf16 tensors on the GPU")
     O = torch.empty_like(q) if out is None else out
     L = lse if (lse is not None or not want_lse) else torch.empty((B, Hq), dtype=torch.float32, device=q.device)
-    need = decode_workspace_bytes(B, Hq, d, n_splits)
-    ws = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device) if workspace is None else workspace
-    rc = lib().vfa_decode_fwd(_ptr(q), _ptr(K), _ptr(V), _ptr(krepr), _ptr(O), _ptr(L), B, Hq, Hkv, n_cap, int(n_keys), d,
+    ws = workspace
+    if ws is None:
+        ws = torch.empty(max(decode_workspace_bytes(B, Hq, d, n_splits), 256), dtype=torch.uint8, device=q.device)
+    rc = _n().vfa_decode_fwd(_ptr(q), _ptr(K), _ptr(V), _ptr(krepr), _ptr(O), _ptr(L), B, Hq, Hkv, n_cap, int(n_keys), d,
                               block_n, int(n_sink), int(n_local), int(bool(use_minit)), int(n_splits), float(softmax_scale),
                               _ptr(ws), ws.numel() * ws.element_size(), _stream(stream))
     if rc != 0:
@@ -319,7 +339,7 @@ def decode_noalloc_fwd(q, K, V, n_keys: int, out, lse=None, *, krepr=None, block
     the output tensors (lse may be None) and the partial sums live in the library's fixed device array."""
     B, Hq, d = q.shape
     Hkv, n_cap = K.shape[1], K.shape[2]
-    rc = lib().vfa_decode_noalloc_fwd(_ptr(q), _ptr(K), _ptr(V), _ptr(krepr), _ptr(out), _ptr(lse), B, Hq, Hkv, n_cap,
+    rc = _n().vfa_decode_noalloc_fwd(_ptr(q), _ptr(K), _ptr(V), _ptr(krepr), _ptr(out), _ptr(lse), B, Hq, Hkv, n_cap,
                                       int(n_keys), d, block_n, int(n_sink), int(n_local), int(bool(use_minit)),
                                       int(n_splits), float(softmax_scale), _stream(stream))
     if rc != 0:
@@ -332,7 +352,7 @@ def fp8_quantize(X, inv_scale: float, stream=None):
     import torch
     assert X.is_cuda and X.dtype == torch.bfloat16 and X.is_contiguous()
     Y = torch.empty(X.shape, dtype=torch.uint8, device=X.device)
-    rc = lib().vfa_fp8_quantize(_ptr(X), _ptr(Y), X.numel(), float(inv_scale), _stream(stream))
+    rc = _n().vfa_fp8_quantize(_ptr(X), _ptr(Y), X.numel(), float(inv_scale), _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_fp8_quantize")
     return Y
@@ -343,7 +363,7 @@ def fp8_pack_v(V, inv_scale: float, stream=None):
     import torch
     B, Hkv, N, d = V.shape
     Vt = torch.empty((B, Hkv, -(-N // 64), 128, 64), dtype=torch.uint8, device=V.device)
-    rc = lib().vfa_fp8_pack_v(_ptr(V), _ptr(Vt), B, Hkv, N, d, float(inv_scale), _stream(stream))
+    rc = _n().vfa_fp8_pack_v(_ptr(V), _ptr(Vt), B, Hkv, N, d, float(inv_scale), _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_fp8_pack_v")
     return Vt
@@ -364,9 +384,9 @@ def fp8_attn_fwd(Q8, K8, Vt8, *, descale_q, descale_k, descale_v, frozen=True, b
             float(softmax_scale), float(descale_q), float(descale_k), float(descale_v), _ptr(ws),
             ws.numel() * ws.element_size(), _stream(stream))
     if noexp:
-        rc = lib().vfa_fp8_attn_noexp_fwd(_ptr(Q8), _ptr(K8), _ptr(Vt8), _ptr(O), _ptr(L), *tail)
+        rc = _n().vfa_fp8_attn_noexp_fwd(_ptr(Q8), _ptr(K8), _ptr(Vt8), _ptr(O), _ptr(L), *tail)
     else:
-        rc = lib().vfa_fp8_attn_fwd(int(bool(frozen)), _ptr(Q8), _ptr(K8), _ptr(Vt8), _ptr(O), _ptr(L), *tail)
+        rc = _n().vfa_fp8_attn_fwd(int(bool(frozen)), _ptr(Q8), _ptr(K8), _ptr(Vt8), _ptr(O), _ptr(L), *tail)
     if rc != 0:
         raise VfaError(rc, "vfa_fp8_attn_noexp_fwd" if noexp else "vfa_fp8_attn_fwd")
     return O, L
@@ -379,14 +399,14 @@ def mxfp4_quantize(X, pre_scale: float = 1.0, stream=None):
     d = X.shape[-1]
     X4 = torch.empty(X.shape[:-1] + (d // 2,), dtype=torch.uint8, device=X.device)
     XS = torch.empty(X.shape[:-1] + (d // 32,), dtype=torch.uint8, device=X.device)
-    rc = lib().vfa_mxfp4_quantize(_ptr(X), _ptr(X4), _ptr(XS), X.numel(), float(pre_scale), _stream(stream))
+    rc = _n().vfa_mxfp4_quantize(_ptr(X), _ptr(X4), _ptr(XS), X.numel(), float(pre_scale), _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_mxfp4_quantize")
     return X4, XS
 
 
 def mxfp4_workspace_bytes(B, Hkv, N) -> int:
-    return int(lib().vfa_mxfp4_workspace_bytes(B, Hkv, N))
+    return int(_n().vfa_mxfp4_workspace_bytes(B, Hkv, N))
 
 
 def mxfp4_attn_fwd(Q4, QS, K4, KS, Vt8, *, descale_v, frozen=True, block_m=128, block_n=64, causal=True, n_sink=1,
@@ -399,12 +419,13 @@ def mxfp4_attn_fwd(Q4, QS, K4, KS, Vt8, *, descale_v, frozen=True, block_m=128, 
     d, Hkv = 2 * dh, K4.shape[1]
     O = torch.empty((B, Hq, N, d), dtype=torch.bfloat16, device=Q4.device) if out is None else out
     L = lse if (lse is not None or not want_lse) else torch.empty((B, Hq, N), dtype=torch.float32, device=Q4.device)
-    need = mxfp4_workspace_bytes(B, Hkv, N)
-    ws = torch.empty(max(need, 256), dtype=torch.uint8, device=Q4.device) if workspace is None else workspace
+    ws = workspace
+    if ws is None:
+        ws = torch.empty(max(mxfp4_workspace_bytes(B, Hkv, N), 256), dtype=torch.uint8, device=Q4.device)
     tail = (B, Hq, Hkv, N, d, block_m, block_n, int(bool(causal)), int(n_sink), int(n_local), int(use_minit),
             float(softmax_scale), float(descale_v), _ptr(ws), ws.numel() * ws.element_size(), _stream(stream))
     ops = (_ptr(Q4), _ptr(QS), _ptr(K4), _ptr(KS), _ptr(Vt8), _ptr(O), _ptr(L))
-    rc = lib().vfa_mxfp4_attn_noexp_fwd(*ops, *tail) if noexp else lib().vfa_mxfp4_attn_fwd(int(bool(frozen)), *ops, *tail)
+    rc = _n().vfa_mxfp4_attn_noexp_fwd(*ops, *tail) if noexp else _n().vfa_mxfp4_attn_fwd(int(bool(frozen)), *ops, *tail)
     if rc != 0:
         raise VfaError(rc, "vfa_mxfp4_attn_noexp_fwd" if noexp else "vfa_mxfp4_attn_fwd")
     return O, L, ws

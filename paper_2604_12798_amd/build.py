@@ -8,6 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvfa.so")
+BINDING = os.path.join(HERE, "_native.so")
 SOURCES = ["vfa_fwd.hip", "vsa_pp.hip"]
 # attn_vsa_pp_kernel sits at the register limit; with the scheduler's default register-pressure tracking the allocator
 # spills an accumulator inside its steady loops, with this tracker it does not (checked on the generated code)
@@ -50,7 +51,18 @@ def build_lib(verbose: bool = False, extra: list[str] | None = None) -> str:
                  verbose)
             objs.append(obj)
         _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs, verbose)
+    build_binding(verbose)
     return LIB
+
+
+def build_binding(verbose: bool = False) -> str:
+    """The Python module in front of libvfa.so: host code only, found beside it at run time."""
+    import sysconfig
+    cxx = os.environ.get("CXX", "g++")
+    _run([cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-I" + os.path.join(ROOT, "include"),
+          "-I" + sysconfig.get_paths()["include"], "-o", BINDING, os.path.join(CSRC, "binding.cpp"),
+          "-L" + HERE, "-l:libvfa.so", "-Wl,-rpath,$ORIGIN"], verbose)
+    return BINDING
 
 
 def build_probe(verbose: bool = False) -> str:
