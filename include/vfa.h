@@ -116,10 +116,11 @@ int vfa_attn_fwd(const void* Q, const void* K, const void* V, void* O, float* LS
  * m~ - max(m, m~) < -skip_threshold_nats for ALL rows of the query block
  * (skip_threshold_nats = -ln(lambda) > 0).  A skipped tile changes no state.  Rows whose
  * tiles were all skipped give O = 0, LSE = -inf.
- * What a skipped tile costs: its K tile, Q.K^T and the row max.  With d = 128 and block_m = 128
- * (the ping-pong kernel) its V tile is never requested, no exponential is computed and no P.V
- * runs: the decision is read one barrier after the vote, before any of them starts.  The other
- * shapes (generic kernel) save the exponentials and the P.V but have fetched V by then. */
+ * What a skipped tile costs: its K tile, Q.K^T and the row max.  With d = 128, block_m = 128 and
+ * a long sequence (over 10240 tokens, non-causal over 5120: the ping-pong kernel) its V tile is
+ * never requested, no exponential is computed and no P.V runs: the decision is read one barrier
+ * after the vote, before any of them starts.  The other calls (generic kernel) save the
+ * exponentials and the P.V but have fetched V by then. */
 int vsa_attn_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE, int B, int Hq,
                  int Hkv, int N, int d, int block_m, int block_n, int causal, int n_sink,
                  int n_local, int use_minit, float softmax_scale, float skip_threshold_nats,

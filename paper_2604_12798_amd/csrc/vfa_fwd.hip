@@ -102,6 +102,16 @@ bool prefer_frozen(const Params& p, int n_cu) {
     return items <= n_cu || (!p.causal && items > 2LL * n_cu && items <= 3LL * n_cu);
 }
 
+// Alg. 2 at d = 128, block_m = 128: the generic kernel up to this many tokens (causal; half as many non-causal), the ping-pong
+// kernel above.  In the generic kernel a workgroup drops a tile alone (the ping-pong kernel's interval is short only where
+// both of its groups drop theirs), and the ends of a work item cost no more than its middle; the ping-pong kernel's steps
+// overlap better and don't fetch V for a dropped tile.  Generic / ping-pong us, 32/8 heads, 20 to 40 % of the tiles dropped:
+// N = 777 29 / 64, 2048 68 / 101, 4096 161 / 202, 8000 511 / 560, 10000 784 / 847, 16384 1863 / 1884, 64K (8 heads) 7147 /
+// 6290; with nothing dropped 8000 583 / 614, 10000 881 / 919, 12200 1262 / 1268, 16384 2262 / 2169; 8/1 heads 10000 268 / 290,
+// 16384 515 / 493; with 98 % dropped 10200 535 / 532; four batches of N = 8000 1901 / 2386.
+// Non-causal: N = 4096 264 / 286, 5000 395 / 454, 6100 547 / 550, nothing dropped 655 / 643.
+constexpr int VSA_GENERIC_MAX_N = 10240;
+
 template <int MODE>
 int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
     (void)hipGetLastError();
@@ -131,19 +141,21 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
             if (prefer_frozen(q, cu_count())) return launch_frozen<128, 2>(q, s);
         }
     }
-    if (d == 128 && (block_m == 128 || MODE != MODE_VSA) && !ablation &&
-        (head_pairs || MODE != MODE_VSA || (p.causal && p.n_local <= 1))) {
-        static std::atomic<unsigned char> lds_raised[kMaxDevices];  // one set of flags per instantiation
-        if constexpr (MODE == MODE_VSA) {
+    static std::atomic<unsigned char> lds_raised[kMaxDevices];  // one set of flags per instantiation
+    if constexpr (MODE == MODE_VSA) {
+        if (!ablation && d == 128 && block_m == 128) {  // (on the first call of any length)
             const int dev = current_device();
             if (dev < 0) return VFA_ERR_HIP;
             if (!lds_raised[dev].load(std::memory_order_acquire)) {
                 if (vfa_detail_vsa_pp_raise_lds() != 0) return VFA_ERR_HIP;
                 lds_raised[dev].store(1, std::memory_order_release);
             }
-        } else {
-            if (!raise_lds_limit(&attn_fwd_pp_kernel<MODE>, PP_LDS_BYTES, lds_raised)) return VFA_ERR_HIP;
         }
+    }
+    if (d == 128 && (block_m == 128 || MODE != MODE_VSA) && !ablation &&
+        (MODE != MODE_VSA || (p.N > (p.causal ? VSA_GENERIC_MAX_N : VSA_GENERIC_MAX_N / 2) && (head_pairs || (p.causal && p.n_local <= 1))))) {
+        if constexpr (MODE != MODE_VSA)
+            if (!raise_lds_limit(&attn_fwd_pp_kernel<MODE>, PP_LDS_BYTES, lds_raised)) return VFA_ERR_HIP;
         q.pair_blocks = head_pairs ? 0 : 1;
         unsigned n_wg = (unsigned)(head_pairs ? q.B * (q.Hq / 2) * q.Tr : q.B * q.Hq * ((q.Tr + 1) / 2));
         // One workgroup fills a CU (128 KiB of LDS), so with more work items than CUs the kernel runs one
@@ -160,6 +172,16 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
         return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
     }
     const dim3 grid((unsigned)(p.B * p.Hq * p.Tr));
+    if constexpr (MODE == MODE_VSA) {
+        if (!ablation) {
+            if (d == 128 && block_m == 128) attn_fwd_kernel<128, 4, MODE, true><<<grid, 256, 0, s>>>(p);
+            else if (d == 128 && block_m == 64) attn_fwd_kernel<128, 2, MODE, true><<<grid, 128, 0, s>>>(p);
+            else if (d == 64 && block_m == 128) attn_fwd_kernel<64, 4, MODE, true><<<grid, 256, 0, s>>>(p);
+            else if (d == 64 && block_m == 64) attn_fwd_kernel<64, 2, MODE, true><<<grid, 128, 0, s>>>(p);
+            else return VFA_ERR_UNSUPPORTED;
+            return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
+        }
+    }
     if constexpr (!is_fa(MODE)) {  // (the baselines take the ping-pong kernel for every call at d = 128)
         if (d == 128 && block_m == 128) attn_fwd_kernel<128, 4, MODE><<<grid, 256, 0, s>>>(p);
         else if (d == 128) attn_fwd_kernel<128, 2, MODE><<<grid, 128, 0, s>>>(p);
