@@ -93,13 +93,36 @@ int launch_frozen(const Params& p, hipStream_t s) {
 //   two to three per compute unit, all equally long (no causal mask): three rounds of short items against two of long ones
 //     (16 heads, N = 5000: 216 against 234 us).  Between one and two it is two rounds against one (N = 3072: 89 against 76 us),
 //     above three four against two, and under a causal mask the ping-pong kernel's long items find short ones to pair with
-//   fewer than 32 items: the ping-pong kernel, although the other one is faster there too.  It adds a row's terms in the order
+//   fewer than 32 items of a call with block_m = 128: the ping-pong kernel, although the other one is faster there too.  It adds a row's terms in the order
 //     of Alg. 2's kernel, so that on small problems, where the two are compared with each other, they agree to the rounding of l
 //   many sink / local blocks: their scores are computed twice in attn_frozen.hpp
-bool prefer_frozen(const Params& p, int n_cu) {
+bool prefer_frozen(const Params& p, int n_cu, int block_m) {
     const long long items = (long long)p.B * p.Hq * p.Tr;
-    if (p.n_sink > 4 || p.n_local > 4 || items < 32 || n_cu <= 0) return false;
+    if (p.n_sink > 4 || p.n_local > 4 || (items < 32 && block_m == 128) || n_cu <= 0) return false;
     return items <= n_cu || (!p.causal && items > 2LL * n_cu && items <= 3LL * n_cu);
+}
+
+// Calls with block_m = 64 and without skipping, d = 128 (`p` in blocks of 128 rows): true = items of 64 rows on the generic
+// kernel, two to a compute unit, false = blocks of 128 rows.  The short items run at 50 to 80 % of the rate but waste fewer rows
+// and take less to start, which is more only for a few tiles each, and where they need no more rounds (generic / other us):
+//   Alg. 1 against the frozen kernel with one item per compute unit: up to three tiles, no causal mask, one round (64 heads,
+//     N = 192 14.1 / 14.8)
+//   Alg. 1 otherwise: five to ten tiles (96 heads, N = 320 20.2 / 22.5, N = 640 46.8 / 47.5; 192 heads, N = 320, no causal mask
+//     36 / 43).  One round more: N = 500 37.2 / 28.9, N = 384 without a causal mask 30 / 24.  Causal items get shorter towards
+//     the end, and an eighth more of them is still one round: N = 384 21.3 / 23.4
+//   the baselines, which have no max to find in front: up to twelve tiles, under a causal mask a
+//     quarter more items to a round (32 heads, N = 512 18.4 / 23.6, 768 26.7 / 29.1, 1280 43 / 41; 128 heads, N = 320 18.8 / 22.3,
+//     N = 640 40.6 / 46.9; one round more: 96 heads, N = 450 29.7 / 25.9)
+bool prefer_rows64(const Params& p, int n_cu, bool head_pairs, bool frozen, bool baseline) {
+    if (n_cu <= 0) return false;
+    const long long heads = (long long)p.B * p.Hq, items = heads * ceil_div(p.N, 64), slots = 2LL * n_cu;
+    if (frozen && heads * p.Tr <= n_cu) return !p.causal && p.Tc <= 3 && items <= slots;
+    if (p.Tc < (baseline ? 1 : 5) || p.Tc > (baseline ? 12 : 10)) return false;
+    long long rounds = (items + slots - 1) / slots;
+    if (p.causal && baseline) rounds = (4 * items + 5 * slots - 1) / (5 * slots);
+    else if (p.causal && 8 * items <= 9 * slots) rounds = 1;
+    const long long pairs = head_pairs ? heads / 2 * p.Tr : heads * ((p.Tr + 1) / 2);
+    return rounds <= (pairs + n_cu - 1) / n_cu;
 }
 
 // Alg. 2 at d = 128, block_m = 128: the generic kernel up to this many tokens (causal; half as many non-causal), the ping-pong
@@ -122,9 +145,10 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
     // (causal, at most one local block), since the skip decisions depend on the max at the time of the visit
     const bool head_pairs = (g & 1) == 0;
     // Without skipping, block_m decides only which blocks count as local ones, and a larger set of exact-max blocks is as good:
-    // everything runs in blocks of 128 rows then (d = 128 in blocks of 64, N = 4096: 219 us on the generic kernel, 131 here)
+    // nearly everything runs in blocks of 128 rows then (d = 128 in blocks of 64, N = 4096: 219 us on the generic kernel, 131 here)
     Params q = p;
     if (MODE != MODE_VSA && !ablation) q.Tr = ceil_div(p.N, 128);
+    bool rows64 = false;
     if constexpr (MODE == MODE_VFA) {
         // (every LDS limit that this entry point may need at this d is raised on its first call: a later one may be captured)
         if (!ablation && d == 64 && p.n_sink <= 4 && p.n_local <= 4) {
@@ -138,10 +162,16 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
             if (!raise_frozen<128, 2>()) return VFA_ERR_HIP;
             static std::atomic<unsigned char> pp_raised[kMaxDevices];
             if (!raise_lds_limit(&attn_fwd_pp_kernel<MODE_VFA>, PP_LDS_BYTES, pp_raised)) return VFA_ERR_HIP;
-            if (prefer_frozen(q, cu_count())) return launch_frozen<128, 2>(q, s);
+            const bool frozen = prefer_frozen(q, cu_count(), block_m);
+            rows64 = block_m == 64 && prefer_rows64(q, cu_count(), head_pairs, frozen, false);
+            if (frozen && !rows64) return launch_frozen<128, 2>(q, s);
         }
     }
     static std::atomic<unsigned char> lds_raised[kMaxDevices];  // one set of flags per instantiation
+    if constexpr (is_fa(MODE)) {
+        if (d == 128 && !raise_lds_limit(&attn_fwd_pp_kernel<MODE>, PP_LDS_BYTES, lds_raised)) return VFA_ERR_HIP;
+        rows64 = d == 128 && block_m == 64 && prefer_rows64(q, cu_count(), head_pairs, false, true);
+    }
     if constexpr (MODE == MODE_VSA) {
         if (!ablation && d == 128 && block_m == 128) {  // (on the first call of any length)
             const int dev = current_device();
@@ -152,10 +182,8 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
             }
         }
     }
-    if (d == 128 && (block_m == 128 || MODE != MODE_VSA) && !ablation &&
+    if (d == 128 && (block_m == 128 || MODE != MODE_VSA) && !ablation && !rows64 &&
         (MODE != MODE_VSA || (p.N > (p.causal ? VSA_GENERIC_MAX_N : VSA_GENERIC_MAX_N / 2) && (head_pairs || (p.causal && p.n_local <= 1))))) {
-        if constexpr (MODE != MODE_VSA)
-            if (!raise_lds_limit(&attn_fwd_pp_kernel<MODE>, PP_LDS_BYTES, lds_raised)) return VFA_ERR_HIP;
         q.pair_blocks = head_pairs ? 0 : 1;
         unsigned n_wg = (unsigned)(head_pairs ? q.B * (q.Hq / 2) * q.Tr : q.B * q.Hq * ((q.Tr + 1) / 2));
         // One workgroup fills a CU (128 KiB of LDS), so with more work items than CUs the kernel runs one
@@ -182,10 +210,15 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
             return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
         }
     }
-    if constexpr (!is_fa(MODE)) {  // (the baselines take the ping-pong kernel for every call at d = 128)
-        if (d == 128 && block_m == 128) attn_fwd_kernel<128, 4, MODE><<<grid, 256, 0, s>>>(p);
-        else if (d == 128) attn_fwd_kernel<128, 2, MODE><<<grid, 128, 0, s>>>(p);
-        if (d == 128) return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
+    if (d == 128 && block_m == 64) {
+        attn_fwd_kernel<128, 2, MODE><<<grid, 128, 0, s>>>(p);
+        return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
+    }
+    if constexpr (!is_fa(MODE)) {  // (the baselines take the ping-pong kernel for every such call)
+        if (d == 128 && block_m == 128) {
+            attn_fwd_kernel<128, 4, MODE><<<grid, 256, 0, s>>>(p);
+            return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
+        }
     }
     if (d == 64 && block_m == 128) attn_fwd_kernel<64, 4, MODE><<<grid, 256, 0, s>>>(p);
     else if (d == 64 && block_m == 64) attn_fwd_kernel<64, 2, MODE><<<grid, 128, 0, s>>>(p);
