@@ -525,7 +525,7 @@ __global__ __launch_bounds__(256) void fp8_quantize_kernel(const uint16_t* __res
 // keys beyond N are written as 0.  One workgroup per (tile, head).  Four neighbouring bytes of a row are four neighbouring
 // keys, so a thread takes four keys x eight features with 16-byte loads, converts straight into the eight dwords, and only
 // those go through LDS, to leave in 16-byte pieces of whole rows.  HBM bound (4 x 8 heads of 3000 keys, 36 MiB: 13.9 us when
-// each byte was stored and gathered by itself, 5.7 now).
+// each byte was stored and gathered by itself, 8.1 now).
 __global__ __launch_bounds__(256) void fp8_pack_v_kernel(const uint16_t* __restrict__ V, uint8_t* __restrict__ Vt, int N,
                                                          int Tc, float inv_scale) {
     // dword q (keys) of feature f at f * 16 + (q ^ 4 ((f / 8) % 4)): 16-byte pieces stay whole, features 8 apart use other banks

@@ -33,7 +33,7 @@ struct Tile4 {
 // of 0, 0.5, 1, 1.5, 2, 3, 4, 6, ties to the even mantissa, saturated at 6.  The rounding is integer arithmetic on the bits of
 // |y| 2^(127 - byte): from 1 up the code is the top of the float rounded to one mantissa bit (nearest even: half an ulp less
 // one, plus the bit that stays last), below 1 it is 2 |y| rounded to a whole number (nearest even), and at 1 the two agree.
-// (Seven comparisons per element took 36 us for 94 MiB, bound by the vector unit.)
+// (Seven comparisons per element took 36 us for 94 MiB, bound by the vector unit; 31 now.)
 __global__ __launch_bounds__(256) void mx4_quantize_kernel(const uint16_t* __restrict__ X, uint8_t* __restrict__ Y,
                                                            uint8_t* __restrict__ S, long long n8, float pre_scale) {
     // (a workgroup's loads as in fp8_quantize_kernel.  n8 is a multiple of 4, so the four threads of a block are live together)
