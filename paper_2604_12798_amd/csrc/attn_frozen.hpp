@@ -33,7 +33,8 @@ struct Frozen {
     static constexpr int LDS_BYTES = KS * RING + EXTRA * Tile<D>::BYTES + (KS == 2 ? 1024 : 0);  // (and the exchange of the max)
 };
 
-template <int D, int KS>
+// ROWS64: the call is causal and in blocks of 64 rows, and a block of 128 stands for two of them.
+template <int D, int KS, bool ROWS64>
 __global__ __launch_bounds__(256 * KS, 2) void attn_fwd_frozen_kernel(const Params p) {
     using T = Tile<D>;
     using F = Frozen<D, KS>;
@@ -89,6 +90,10 @@ __global__ __launch_bounds__(256 * KS, 2) void attn_fwd_frozen_kernel(const Para
     const int qrow = row0 + 32 * w4 + ql;
     const int qrow_c = min(qrow, N - 1);
     const int limit = p.causal ? qrow_c : N - 1;
+    // Last key block that may reach this wave's rows: with ROWS64 the diagonal one of its own 64.  The summary
+    // of the next one may lie far above every score that the rows see (all their exponentials would be 0), and a weight of 0 times
+    // a NaN among its values is not 0.
+    const int own_hi = ROWS64 ? min(j_hi, a_lo + (w4 >> 1)) : j_hi;
     bf16x8 qf[KK];
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk)
@@ -214,7 +219,8 @@ __global__ __launch_bounds__(256 * KS, 2) void attn_fwd_frozen_kernel(const Para
             if (t >= n_max) break;
             qk_tile_pipe<D>(frozen_smem + stage(u), qf, sa, ql, hh);
             const int j = t - n_sum < n1 ? t - n_sum : lo2 + (t - n_sum - n1);
-            if (t < n_sum || (j * BN + BN <= N && !(p.causal && j * BN + BN - 1 > row0))) mx = fmaxf(mx, tile_rowmax<false>(sa, 0, 0, hh));
+            if (t < n_sum ? (!ROWS64 || own_hi == j_hi) : (j * BN + BN <= N && !(p.causal && j * BN + BN - 1 > row0))) mx = fmaxf(mx, tile_rowmax<false>(sa, 0, 0, hh));
+            else if (ROWS64) mx = fmaxf(mx, tile_rowmax<true>(sa, (t < n_sum ? t : j) * BN, t < n_sum ? own_hi : limit, hh));
             else mx = fmaxf(mx, tile_rowmax<true>(sa, j * BN, limit, hh));
         }
     }
@@ -338,7 +344,7 @@ __global__ __launch_bounds__(256 * KS, 2) void attn_fwd_frozen_kernel(const Para
         for (int e = 0; e < 16; ++e) pa[e] = pb[e];
     }
     step(k, sa, sb, pb, pa, true_type{}, true_type{});
-    pv_tile_pipe<D>(Vs + (k % S) * T::BYTES, pb, ot, lane, hh);
+    if (!ROWS64 || KS * k + grp <= own_hi) pv_tile_pipe<D>(Vs + (k % S) * T::BYTES, pb, ot, lane, hh);  // (the next 64's block is the last tile)
 
     if (KS == 1) {
         store_output<D, 0, DB>(p, ot, m2, lsum, b, h, qrow, hh);

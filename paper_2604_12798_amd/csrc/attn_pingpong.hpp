@@ -17,7 +17,14 @@ namespace {
 constexpr int PP_STAGES = 4;
 constexpr int PP_LDS_BYTES = 2 * PP_STAGES * Tile<128>::BYTES;
 
-template <int MODE>
+// ROWS64: the call is causal and in blocks of 64 rows, and a block of 128 stands for two of them.  A wave then also meets tiles
+// that none of its rows may know of.  Their summaries do not count for its max (one may lie far above every score that the
+// rows see), and in place of their values it multiplies a tile of zeros, kept in LDS behind the rings: the weights are 0, but
+// 0 times a NaN is not.
+template <bool ROWS64>
+constexpr int pp_lds_bytes() { return PP_LDS_BYTES + (ROWS64 ? Tile<128>::BYTES : 0); }
+
+template <int MODE, bool ROWS64>
 __global__ __launch_bounds__(512, 2) void attn_fwd_pp_kernel(const Params p) {
     constexpr int D = 128;
     using T = Tile<D>;
@@ -48,6 +55,8 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_pp_kernel(const Params p) {
     // workgroup, item = workgroup id.  persist = P > 0: P workgroups (one per CU) each take every P-th item of
     // the list, in boustrophedon order so that the early (long) and late (short) items even out.
     const int n_items = G * gp * Ti;
+    if (ROWS64)
+        for (int o = tid * 16; o < T::BYTES; o += 512 * 16) *reinterpret_cast<u32x4*>(pp_smem + PP_LDS_BYTES + o) = u32x4{0, 0, 0, 0};
     for (int round = 0;; ++round) {
     int b, hkv, hp, i;
     {
@@ -86,8 +95,8 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_pp_kernel(const Params p) {
     const int a_lo = row0 / BN, a_hi = last_row / BN;
     const int j_hi = p.causal ? a_hi : p.Tc - 1;
     const int row0_g = row0 + (pb ? grp * BM : 0);               // first row of this group
-    // last key block this group's rows can see (a group past the end of the sequence mirrors row N - 1)
-    const int j_hi_g = p.causal ? (min(N, row0_g + BM) - 1) / BN : p.Tc - 1;
+    // last key block this group's rows can see, with ROWS64 this wave's (a group past the end of the sequence mirrors row N - 1)
+    const int j_hi_g = p.causal ? (min(N, row0_g + (ROWS64 ? 64 * (w4 >> 1) + 64 : BM)) - 1) / BN : p.Tc - 1;
 
     const uint16_t* Qg = p.Q + ((size_t)(b * p.Hq + h) * N) * D;
     const uint16_t* Kg = p.K + ((size_t)(b * p.Hkv + hkv) * N) * D;
@@ -113,6 +122,7 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_pp_kernel(const Params p) {
     f32x16 st[2];
     uint32_t pk[16];
     bool pv_pending = false;  // pk holds a tile whose P.V has not been accumulated yet
+    int v_at = 0;             // ROWS64, Alg. 1: where its values are, from the start of the V ring (the baselines work it out again)
 
     // ---- LDS-direct tile loads.  Per-lane byte offsets inside a tile are fixed for the whole kernel
     // (rows 4*(8u + wave) + lane/16, swizzled chunk), so a full tile costs one scalar base per matrix
@@ -199,11 +209,16 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_pp_kernel(const Params p) {
     };
     bf16x8 fa[4], fb[4];  // fragment double buffer of the matrix phase
 
+    // where the values of visit k are, from the start of the V ring (VISIBLE: to all waves)
+    auto values_at = [&](int k, auto visible_c) __attribute__((always_inline)) {
+        const bool zeros = ROWS64 && !decltype(visible_c)::value && vis.tile(k) > j_hi_g;
+        return (zeros ? PP_STAGES : k & 3) * T::BYTES;
+    };
     // Matrix phase of visit k in the steady state: P.V of visit k-1 (its chunk-0 fragments are already
     // in fa, fetched at the end of the vector phase), then Q.K^T of visit k.  Fragments for the next
     // four MFMAs are read from LDS while the current four issue.  Nothing else is on this path.
-    auto matrix_phase_full = [&](int k) __attribute__((always_inline)) {
-        const uint8_t* vt = Vs + ((k - 1) & 3) * T::BYTES;
+    auto matrix_phase_full = [&](int k, auto steady_c) __attribute__((always_inline)) {
+        const uint8_t* vt = Vs + (ROWS64 && !is_fa(MODE) ? v_at : values_at(k - 1, steady_c));
         const uint8_t* kt = Ks + (k & 3) * T::BYTES;
         if (!is_fa(MODE)) __builtin_amdgcn_s_setprio(1);
         else __builtin_amdgcn_s_setprio(0);  // (also keeps the phase a scheduling region of its own)
@@ -276,7 +291,8 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_pp_kernel(const Params p) {
             else
                 softmax_tile<SPECIAL, true, DB, !FIRST, is_lazy(MODE), softexp_every(MODE)>(
                     st, pk, ot, m2, lsum, p.c, j * BN, tile_masked(j) ? limit : 0x3fffffff, hh, p.tau2);
-            ld_v(fa, Vs + (k & 3) * T::BYTES, 0);  // first fragments of the coming P.V, in flight over the barrier
+            if (ROWS64 && !is_fa(MODE)) v_at = values_at(k, fast_c);
+            ld_v(fa, Vs + (ROWS64 && !is_fa(MODE) ? v_at : values_at(k, fast_c)), 0);  // first fragments of the coming P.V, in flight over the barrier
         }
         if (is_fa(MODE)) __builtin_amdgcn_s_setprio(0);
     };
@@ -331,7 +347,7 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_pp_kernel(const Params p) {
     }
     auto drain = [&]() __attribute__((always_inline)) {  // the P.V of the last visit
         if (pv_pending) {
-            const uint8_t* vt = Vs + ((nv - 1) & 3) * T::BYTES;
+            const uint8_t* vt = Vs + (ROWS64 && !is_fa(MODE) ? v_at : values_at(nv - 1, std::false_type{}));
             pv4(fa, 0);
 #pragma unroll
             for (int c = 1; c < 4; ++c) {
@@ -343,7 +359,7 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_pp_kernel(const Params p) {
     // k may equal nv for group 1 (the matrix phase that follows its last vector phase): the Q.K^T half
     // then runs on whatever the ring slot holds and its scores are never used; only the P.V counts.
     auto matrix_any = [&](int k) __attribute__((always_inline)) {
-        if (pv_pending) matrix_phase_full(k);
+        if (pv_pending) matrix_phase_full(k, std::false_type{});
         else matrix_phase_qk(k);
     };
     // One interval = the stretch between two workgroup barriers.  Group 0 runs matrix phase kv and then
@@ -357,14 +373,14 @@ __global__ __launch_bounds__(512, 2) void attn_fwd_pp_kernel(const Params p) {
         auto interval = [&](int kv, auto special_c, auto fast_c, auto first_c, auto steady_c) __attribute__((always_inline)) {
             constexpr bool STEADY = decltype(steady_c)::value;
             if (GRP == 0) {
-                if (STEADY) matrix_phase_full(kv);
+                if (STEADY) matrix_phase_full(kv, steady_c);
                 else matrix_any(kv);
             }
             __builtin_amdgcn_sched_barrier(0);  // keep the two phases apart in the instruction stream
             vector_phase(kv, special_c, fast_c, first_c);
             __builtin_amdgcn_sched_barrier(0);
             if (GRP == 1) {
-                if (STEADY) matrix_phase_full(kv + 1);
+                if (STEADY) matrix_phase_full(kv + 1, steady_c);
                 else matrix_any(kv + 1);
             }
             __builtin_amdgcn_s_barrier();

@@ -77,13 +77,22 @@ bool raise_lds_limit(KernelT kernel, int bytes, std::atomic<unsigned char>* done
 
 template <int D, int KS>
 bool raise_frozen() {
-    static std::atomic<unsigned char> lds_raised[kMaxDevices];
-    return raise_lds_limit(&attn_fwd_frozen_kernel<D, KS>, Frozen<D, KS>::LDS_BYTES, lds_raised);
+    static std::atomic<unsigned char> lds_raised[2][kMaxDevices];
+    return raise_lds_limit(&attn_fwd_frozen_kernel<D, KS, false>, Frozen<D, KS>::LDS_BYTES, lds_raised[0]) &&
+           raise_lds_limit(&attn_fwd_frozen_kernel<D, KS, true>, Frozen<D, KS>::LDS_BYTES, lds_raised[1]);
 }
 template <int D, int KS>
-int launch_frozen(const Params& p, hipStream_t s) {
-    attn_fwd_frozen_kernel<D, KS><<<dim3((unsigned)(p.B * p.Hq * p.Tr)), 256 * KS, Frozen<D, KS>::LDS_BYTES, s>>>(p);
+int launch_frozen(const Params& p, int block_m, hipStream_t s) {
+    const dim3 grid((unsigned)(p.B * p.Hq * p.Tr));
+    if (block_m == 64 && p.causal) attn_fwd_frozen_kernel<D, KS, true><<<grid, 256 * KS, Frozen<D, KS>::LDS_BYTES, s>>>(p);
+    else attn_fwd_frozen_kernel<D, KS, false><<<grid, 256 * KS, Frozen<D, KS>::LDS_BYTES, s>>>(p);
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
+}
+template <int MODE>
+bool raise_pp() {
+    static std::atomic<unsigned char> lds_raised[2][kMaxDevices];
+    return raise_lds_limit(&attn_fwd_pp_kernel<MODE, false>, pp_lds_bytes<false>(), lds_raised[0]) &&
+           raise_lds_limit(&attn_fwd_pp_kernel<MODE, true>, pp_lds_bytes<true>(), lds_raised[1]);
 }
 
 // Which kernel Alg. 1 runs on at d = 128: true = attn_frozen.hpp (items of 128 rows, a third to a half cheaper than the
@@ -155,25 +164,23 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
             if (!raise_frozen<64, 1>() || !raise_frozen<64, 2>()) return VFA_ERR_HIP;
             // two groups to an item while there is no more than one item per compute unit and a group has a few tiles
             // (32 heads, N = 777: 12.4 against 13.6 us; N = 256: 8.4 against 8.0; N = 4096: 95 against 87)
-            if ((long long)q.B * q.Hq * q.Tr <= cu_count() && q.Tc >= 6) return launch_frozen<64, 2>(q, s);
-            return launch_frozen<64, 1>(q, s);
+            if ((long long)q.B * q.Hq * q.Tr <= cu_count() && q.Tc >= 6) return launch_frozen<64, 2>(q, block_m, s);
+            return launch_frozen<64, 1>(q, block_m, s);
         }
         if (!ablation && d == 128) {
-            if (!raise_frozen<128, 2>()) return VFA_ERR_HIP;
-            static std::atomic<unsigned char> pp_raised[kMaxDevices];
-            if (!raise_lds_limit(&attn_fwd_pp_kernel<MODE_VFA>, PP_LDS_BYTES, pp_raised)) return VFA_ERR_HIP;
+            if (!raise_frozen<128, 2>() || !raise_pp<MODE_VFA>()) return VFA_ERR_HIP;
             const bool frozen = prefer_frozen(q, cu_count(), block_m);
             rows64 = block_m == 64 && prefer_rows64(q, cu_count(), head_pairs, frozen, false);
-            if (frozen && !rows64) return launch_frozen<128, 2>(q, s);
+            if (frozen && !rows64) return launch_frozen<128, 2>(q, block_m, s);
         }
     }
-    static std::atomic<unsigned char> lds_raised[kMaxDevices];  // one set of flags per instantiation
     if constexpr (is_fa(MODE)) {
-        if (d == 128 && !raise_lds_limit(&attn_fwd_pp_kernel<MODE>, PP_LDS_BYTES, lds_raised)) return VFA_ERR_HIP;
+        if (d == 128 && !raise_pp<MODE>()) return VFA_ERR_HIP;
         rows64 = d == 128 && block_m == 64 && prefer_rows64(q, cu_count(), head_pairs, false, true);
     }
     if constexpr (MODE == MODE_VSA) {
         if (!ablation && d == 128 && block_m == 128) {  // (on the first call of any length)
+            static std::atomic<unsigned char> lds_raised[kMaxDevices];
             const int dev = current_device();
             if (dev < 0) return VFA_ERR_HIP;
             if (!lds_raised[dev].load(std::memory_order_acquire)) {
@@ -194,10 +201,13 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
             q.persist = n_cu;
             n_wg = (unsigned)n_cu;
         }
-        const dim3 grid_pp(n_wg);
-        if constexpr (MODE == MODE_VSA) return vfa_detail_vsa_pp_launch(&q, sizeof(q), n_wg, s) == 0 ? VFA_OK : VFA_ERR_HIP;
-        attn_fwd_pp_kernel<MODE><<<grid_pp, 512, PP_LDS_BYTES, s>>>(q);
-        return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
+        if constexpr (MODE == MODE_VSA) {
+            return vfa_detail_vsa_pp_launch(&q, sizeof(q), n_wg, s) == 0 ? VFA_OK : VFA_ERR_HIP;
+        } else {
+            if (block_m == 64 && p.causal) attn_fwd_pp_kernel<MODE, true><<<dim3(n_wg), 512, pp_lds_bytes<true>(), s>>>(q);
+            else attn_fwd_pp_kernel<MODE, false><<<dim3(n_wg), 512, pp_lds_bytes<false>(), s>>>(q);
+            return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
+        }
     }
     const dim3 grid((unsigned)(p.B * p.Hq * p.Tr));
     if constexpr (MODE == MODE_VSA) {

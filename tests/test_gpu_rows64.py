@@ -46,3 +46,40 @@ def test_rows64(oracle, B, Hq, Hkv, N, causal):
     # every row of the two, which compute the same attention
     assert (outs[0][0].float() - outs[1][0].float()).abs().max().item() <= 4e-2
     assert (outs[0][1] - outs[1][1]).abs().max().item() <= 2e-3
+
+
+# (what the call runs on at d = 128: the kernel of attn_frozen.hpp, the ping-pong kernel in head pairs, in block pairs, the
+# generic kernel), one row of the list for each; the same calls at d = 64
+LATER = [(1, 8, 2, 777, {}), (1, 4, 2, 1100, dict(n_sink=5)), (1, 3, 1, 1100, dict(n_sink=5)), (1, 3, 3, 1000, dict(n_sink=5, n_local=2)),
+         (3, 32, 8, 320, {}), (5, 32, 32, 200, {}), (1, 8, 2, 128, dict(n_sink=0)), (1, 8, 2, 640, dict(n_sink=0, n_local=0))]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,N,kw", LATER)
+def test_a_block_of_64_rows_does_not_see_the_next_one(d, B, Hq, Hkv, N, kw):
+    """Causal: whatever the keys and values behind a block of 64 rows hold (keys whose estimate would drown every real score, NaN
+    in the values, as in the padding of a cache), its rows come out bit for bit the same."""
+    import torch
+    import paper_2604_12798_amd as vfa
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    R = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    Q, K, V = R(B, Hq, N, d).abs().bfloat16(), R(B, Hkv, N, d).bfloat16(), R(B, Hkv, N, d).bfloat16()
+    calls = {"vfa": lambda k, v: vfa.vfa_attn_fwd(Q, k, v, block_m=64, **kw),
+             "fa": lambda k, v: vfa.fa_baseline_fwd(Q, k, v, block_m=64),
+             "lazy": lambda k, v: vfa.fa_lazy_rescale_fwd(Q, k, v, block_m=64),
+             "softexp": lambda k, v: vfa.fa_lazy_rescale_softexp_fwd(Q, k, v, block_m=64)}
+    if kw:
+        calls = {"vfa": calls["vfa"]}
+    Tc = -(-N // 64)
+    for what, call in calls.items():
+        O, L = call(K, V)
+        assert torch.isfinite(O.float()).all() and torch.isfinite(L).all()
+        for a in sorted({1, 2, Tc // 2 | 1, Tc - 1}):
+            if not 0 < a < Tc:
+                continue
+            print(what, d, B, Hq, Hkv, N, kw, "from block", a, flush=True)
+            K2, V2 = K.clone(), V.clone()
+            K2[:, :, 64 * a:] = 1e3
+            V2[:, :, 64 * a:] = float("nan")
+            O2, L2 = call(K2, V2)
+            assert torch.equal(O2[:, :, :64 * a], O[:, :, :64 * a]) and torch.equal(L2[:, :, :64 * a], L[:, :, :64 * a]), (what, a)
