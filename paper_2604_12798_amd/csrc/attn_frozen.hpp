@@ -229,7 +229,7 @@ __global__ __launch_bounds__(256 * KS, 2) void attn_fwd_frozen_kernel(const Para
     if (KS == 2 && hh == 0) xm[grp * BM + 32 * w4 + ql] = mx;
     wait_vm0_and_sync();
     if (KS == 2) mx = fmaxf(mx, xm[(grp ^ 1) * BM + 32 * w4 + ql]);
-    const float m2 = mx * p.c;
+    const float m2 = finite_max(mx * p.c);
     // step 0 finds "V of tile -1" all zeros (an empty buffer; what the slot held, times zero weights, could be NaN)
     request(0, 0, off[0], off[1], off[LI - 2], off[LI - 1], grp * F::RING + (2 * S - 1) * T::BYTES);
     qk_tile_pipe<D>(Ks, qf, sa, ql, hh);

@@ -103,6 +103,10 @@ __device__ inline float xhalf_sum(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// The fixed max of a row: -inf (every score that went into it is) counts as 0, so that exp2(-inf - max) is 0 and not NaN, as in
+// the exact-max update of softmax_tile.
+__device__ inline float finite_max(float m2) { return m2 == -INFINITY ? 0.f : m2; }
+
 __device__ inline uint32_t pack_bf16(float a, float b) {
     f32x2 v = {a, b};
     bf16x2 r = __builtin_convertvector(v, bf16x2);  // v_cvt_pk_bf16_f32, round to nearest even

@@ -429,7 +429,7 @@ __global__ __launch_bounds__(256, FOLD ? 3 : 2) void attn_fp8_kernel(const Fp8Pa
                 else mx = fmaxf(mx, tile_rowmax<true>(st, j * BN, limit, hh));
             }
         }
-        m2 = xhalf_max(mx) * p.c;
+        m2 = finite_max(xhalf_max(mx) * p.c);
     } else {
         load_kv(0, 0);
     }

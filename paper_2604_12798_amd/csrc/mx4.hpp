@@ -327,7 +327,7 @@ __global__ __launch_bounds__(256, 3) void attn_mx4_kernel(const Mx4Params p) {
                 else mx = fmaxf(mx, tile_rowmax<true>(st, j * BN, limit, hh));
             }
         }
-        m2 = xhalf_max(mx) * p.c;
+        m2 = finite_max(xhalf_max(mx) * p.c);
     } else {
         load_kv(0, 0);
     }
