@@ -222,8 +222,9 @@ int vfa_decode_noalloc_fwd(const void* Q, const void* K, const void* V, const vo
  * them, so a serving loop can update them on the GPU): sequence b has seq_lens[b] valid rows in its
  * part of the cache, values are clamped to [1, n_cap] (to [0, n_cap] in the append call, where
  * old >= new means nothing to do).  Everything else as in vfa_kblock_summary_append / vfa_decode_fwd,
- * except that n_splits is a mean: the B * n_splits ranges are dealt to the sequences by length, so that all
- * are about equally long (with n_splits = 1 each sequence is one range). */
+ * except that for B up to 64 (and, where that is faster, up to 256) n_splits is a mean: the B * n_splits ranges
+ * are dealt to the sequences by length, so that all are about equally long.  Otherwise, and with n_splits = 1,
+ * each sequence's keys are cut into n_splits ranges. */
 int vfa_kblock_summary_append_varlen(const void* K, void* Krepr, int B, int Hkv, int n_cap,
                                      const int* old_lens, const int* new_lens, int d, int block_n,
                                      void* stream);

@@ -36,69 +36,87 @@ struct DecodeParams {
     float c;
 };
 
-// Key tiles of batch entry b.
+// What the entries of a batch have: one length; lengths of their own and n_splits ranges each; lengths of their own and ranges
+// dealt out by length.
+enum Lens { LENS_ONE = 0, LENS_FIXED = 1, LENS_DEALT = 2 };
+
+// Keys of batch entry b.
 __device__ __forceinline__ int decode_keys(const DecodeParams& p, int b) {
     return p.seq_lens ? min(max(p.seq_lens[b], 1), p.n_cap) : p.n_keys;
 }
+
+// Sum over the wave: rotations within the rows of 16, then the rows.
 __device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x121, 0xf, 0xf, false);  // row_ror:1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x122, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x124, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, false);
+    const auto a = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+    x = (int)(a[0] + a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+    return __builtin_amdgcn_readfirstlane((int)(b[0] + b[1]));
+}
+// Sum over the lanes up to this one.
+__device__ __forceinline__ int wave_prefix(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 and 31: the rows before
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
     return x;
 }
 
-// Which tiles a range covers when every entry of the batch has a length of its own.  The B * n_splits ranges are dealt to
-// the entries by length, so that all are about equally long (a fixed number per entry leaves the ranges of short entries
-// idle: the kernel took 52 us at 16 entries of 200 to 8192 keys, it takes 30): `per` tiles a range, the smallest value found from the even share
-// upwards, in steps of an eighth, for which the entries' ranges fit into B * n_splits.  Every wave works this out by itself.
+// Which tiles a range covers when every entry of the batch has a length of its own (LENS_DEALT).  The B * n_splits ranges are dealt
+// to the entries by length, so that all are about equally long (a fixed number per entry leaves the ranges of short entries
+// idle: the kernel took 52 us at 16 entries of 200 to 8192 keys, it takes 30): `per` tiles a range, the smallest value found
+// from the even share upwards, in steps of an eighth, for which the entries' ranges fit into B * n_splits.  Every wave works
+// this out by itself, from up to DEAL_MAX_B / 64 entries in each lane.  It is not done where that costs more than it gives:
+//   more entries, or above 64 of them more than eight ranges for each compute unit: there is a search in each of many waves, and
+//     the number of ranges evens out what dealing would (search over the whole batch against n_splits ranges each, d = 128: 256
+//     entries of up to 512 keys, 8 KV heads, two ranges 77 / 39 us; 1024 entries 523 / 116; 4096 entries 6060 / 480)
+//   above 64 entries with ranges of a tile or two (256 entries of up to 128 keys, one KV head, two ranges, d = 64 11.5 / 8)
+//   one range per entry: there is nothing to deal
+// In between it is worth it: 128 entries of up to 8192 keys, one KV head, four ranges 28 us dealt, 57 not.
+constexpr int DEAL_MAX_B = 256;
 struct Ranges {
-    int per;           // tiles per range
     int b, first, nb;  // an entry, the ranges of the entries before it, its own number of ranges
 };
-__device__ __forceinline__ int varlen_per(const DecodeParams& p, int lane) {
-    int tiles = 0, longest = 1;
-    for (int b0 = 0; b0 < p.B; b0 += 64) {
-        const int t = b0 + lane < p.B ? (decode_keys(p, b0 + lane) + BN - 1) / BN : 0;
-        tiles += t;  // (at most 65535 entries of 2^25 tiles: the sum may pass 2^31 only where the cache would not fit the GPU)
-        longest = max(longest, t);
-    }
-    tiles = wave_sum(tiles);
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) longest = max(longest, __shfl_xor(longest, m));
-    const int slots = p.B * p.n_splits;
-    int per = max(1, (tiles + slots - 1) / slots);
-    while (per < longest) {
-        int n = 0;
-        for (int b0 = 0; b0 < p.B; b0 += 64)
-            n += b0 + lane < p.B ? ((decode_keys(p, b0 + lane) + BN - 1) / BN + per - 1) / per : 0;
-        if (wave_sum(n) <= slots) break;
-        per += max(1, per >> 3);
-    }
-    return per;  // (per >= longest: one range per entry, B <= B * n_splits of them)
-}
 // the entry that range w of the list belongs to (b = -1: past the last range), or, with w < 0, the ranges of entry b
 __device__ __forceinline__ Ranges varlen_find(const DecodeParams& p, int lane, int w, int b) {
-    Ranges out;
-    out.per = varlen_per(p, lane);
-    out.b = -1; out.first = 0; out.nb = 0;
-    int before = 0;
-    for (int b0 = 0; b0 < p.B; b0 += 64) {
-        const int n = b0 + lane < p.B ? ((decode_keys(p, b0 + lane) + BN - 1) / BN + out.per - 1) / out.per : 0;
-        int upto = n;  // inclusive prefix sum over the lanes
+    constexpr int E = DEAL_MAX_B / 64;
+    int tiles[E], n[E], sum = 0;
 #pragma unroll
-        for (int m = 1; m < 64; m <<= 1) {
-            const int v = __shfl_up(upto, m);
-            upto += lane >= m ? v : 0;
+    for (int e = 0; e < E; ++e) {
+        tiles[e] = 64 * e + lane < p.B ? (decode_keys(p, 64 * e + lane) + BN - 1) / BN : 0;
+        sum += tiles[e];  // (256 entries of 2^25 tiles at most: a sum past 2^31 would not fit the GPU)
+    }
+    const int slots = p.B * p.n_splits;
+    int per = max(1, (wave_sum(sum) + slots - 1) / slots);
+    for (;; per += max(1, per >> 3)) {  // (ends where per passes the longest entry, with one range for each, or before)
+        int ranges = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            n[e] = 64 * e < p.B ? (tiles[e] + per - 1) / per : 0;
+            ranges += n[e];
         }
-        const bool hit = n > 0 && (w >= 0 ? (w >= before + upto - n && w < before + upto) : b0 + lane == b);
-        const uint64_t found = __builtin_amdgcn_ballot_w64(hit);
-        if (found) {
-            const int l = __builtin_ctzll(found);
-            out.b = b0 + l;
-            out.nb = __shfl(n, l);
-            out.first = before + __shfl(upto, l) - out.nb;
-            break;
+        if (wave_sum(ranges) <= slots) break;
+    }
+    Ranges out = {-1, 0, 0};
+    int before = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        if (64 * e < p.B && out.b < 0) {
+            const int upto = before + wave_prefix(n[e]);
+            const uint64_t found = __builtin_amdgcn_ballot_w64(n[e] > 0 && (w >= 0 ? w >= upto - n[e] && w < upto : 64 * e + lane == b));
+            if (found) {
+                const int l = __builtin_ctzll(found);
+                out.b = 64 * e + l;
+                out.nb = __builtin_amdgcn_readlane(n[e], l);
+                out.first = __builtin_amdgcn_readlane(upto, l) - out.nb;
+            }
+            before = __builtin_amdgcn_readlane(upto, 63);
         }
-        before += __shfl(upto, 63);
     }
     return out;
 }
@@ -160,7 +178,7 @@ __device__ __forceinline__ void regs_to_tile(uint8_t* dst, int lane, const u32x4
 // ragged one, take the same body with the missing requests compiled out.
 // (64-wide heads: half the bytes per tile and half the registers, so twice the waves per SIMD keep the same number of bytes
 // in flight.)
-template <int D, int W>
+template <int D, int W, int LENS>
 __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void decode_split_kernel(const DecodeParams p) {
     using T = Tile<D>;
     constexpr int KK = D / 16, DB = D / 32;
@@ -172,26 +190,19 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void decode_split_kernel(c
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t* const Ks = smem + wave * 2 * T::BYTES;
     uint8_t* const Vs = Ks + T::BYTES;
-    const int g = p.Hq / p.Hkv, hkv = blockIdx.z;
-    const int w = blockIdx.y * p.n_splits + blockIdx.x;  // range of the batch's list
-    int b, r0, r1;  // batch entry, tiles [r0, r1)
-    if (p.seq_lens) {
+    // (lengths that differ and are not dealt out: all heads of an entry start together, so that no long one starts late)
+    const int g = p.Hq / p.Hkv, hkv = LENS == LENS_FIXED ? blockIdx.y : blockIdx.z;
+    int b = LENS == LENS_FIXED ? blockIdx.z : blockIdx.y, r = blockIdx.x, nb = p.n_splits;  // batch entry, its range, the number of its ranges
+    const int w = b * p.n_splits + r;  // range of the batch's list
+    if (LENS == LENS_DEALT) {
         const Ranges rg = varlen_find(p, lane, w, 0);
-        b = __builtin_amdgcn_readfirstlane(rg.b);
-        if (b < 0) return;  // (the same in all waves of the workgroup)
-        const int first = __builtin_amdgcn_readfirstlane(rg.first), nb = __builtin_amdgcn_readfirstlane(rg.nb);
-        const int Tc = (decode_keys(p, b) + BN - 1) / BN, per = (Tc + nb - 1) / nb, r = w - first;
-        r0 = r * per;
-        r1 = min(Tc, r0 + per);
-    } else {
-        b = blockIdx.y;
-        const int r = blockIdx.x;
-        const int Tc = (p.n_keys + BN - 1) / BN, per = (Tc + p.n_splits - 1) / p.n_splits;
-        r0 = r * per;
-        r1 = min(Tc, r0 + per);
+        if (rg.b < 0) return;  // (the same in all waves of the workgroup)
+        b = rg.b; r = w - rg.first; nb = rg.nb;
     }
     const size_t slot = (size_t)w * p.Hq + hkv * g;
-    const int n_keys = __builtin_amdgcn_readfirstlane(decode_keys(p, b));
+    const int n_keys = LENS == LENS_ONE ? p.n_keys : __builtin_amdgcn_readfirstlane(decode_keys(p, b));
+    const int Tc = (n_keys + BN - 1) / BN, per = (Tc + nb - 1) / nb;
+    const int r0 = r * per, r1 = min(Tc, r0 + per);  // its tiles
     const int share = (max(r1 - r0, 0) + W - 1) / W;
     const int t_lo = r0 + wave * share, t_hi = min(r1, t_lo + share);
     const int t_whole = min(t_hi, n_keys / BN);  // tiles below this index are whole
@@ -306,14 +317,14 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void decode_split_kernel(c
 // rounds in flight, each group of threads with a running max of its own; the groups meet in LDS.  The order of the sums is
 // fixed.  (One thread per output element walking the ranges one by one took 8.6 us for 32 heads of 32
 // ranges and 6.3 us for 128 heads of 16, a chain of load latencies; this takes 2.8 and 4.8.)
-template <int D>
+template <int D, bool DEALT>
 __global__ __launch_bounds__(256) void decode_merge_kernel(const DecodeParams p) {
     constexpr int C4 = D / 4, NG = 256 / C4, U = 4;
     __shared__ float xo[NG][D], xm[NG], xl[NG];
     const int row = blockIdx.x, b = row / p.Hq, h = row - b * p.Hq;
     const int c4 = threadIdx.x % C4, gr = threadIdx.x / C4;
     int first = b * p.n_splits, nb = p.n_splits;
-    if (p.seq_lens) {
+    if (DEALT) {
         const Ranges rg = varlen_find(p, threadIdx.x & 63, -1, b);
         first = rg.first;
         nb = rg.nb;

@@ -537,24 +537,36 @@ int decode_common(const void* Q, const void* K, const void* V, const void* Krepr
     const size_t rows = (size_t)B * Hq * n_splits;
     p.opart = (float*)workspace; p.pm = p.opart + rows * d; p.lpart = p.pm + rows;  // the 16-byte stores go first
     hipStream_t s = (hipStream_t)stream;
-    const dim3 grid((unsigned)n_splits, (unsigned)B, (unsigned)Hkv);
     // Waves per range: two tiles of 16 KiB in flight per wave at d = 128, of 8 KiB at d = 64, and what the reads need is about
     // 64 KiB in flight per compute unit.  At 512 ranges (two per compute unit) one wave each is enough at d = 128 (512 MiB:
     // 88.8 us against 92.9 with two) and four are best at d = 64 (125 MiB: 28.1 us against 29.4 with two and 33 with one);
-    // a range with fewer tiles than waves leaves waves idle
+    // a range with fewer tiles than waves leaves waves idle.  Lengths that differ and are not dealt out: the longest entries finish
+    // last, with few others left beside them, so d = 64 keeps two waves (4096 entries of up to 8192 keys, one KV head, one range
+    // 304 us with one wave, 270 with two; d = 128 does not gain)
     const long long wgs = (long long)B * Hkv * n_splits;
     const int tiles = ceil_div(ceil_div(n_keys, BN), n_splits);
     const int n_cu = cu_count() > 0 ? cu_count() : 256;
     (void)hipGetLastError();
+    // (the lines are explained at varlen_find)
+    const bool dealt = seq_lens && n_splits > 1 && (B <= 64 || (B <= DEAL_MAX_B && wgs <= 8LL * n_cu && ceil_div(n_keys, BN) > 2 * n_splits));
+    auto launch = [&](auto d_c, auto w_c) {
+        constexpr int D = decltype(d_c)::value, W = decltype(w_c)::value;
+        const dim3 grid((unsigned)n_splits, (unsigned)B, (unsigned)Hkv);
+        if (!seq_lens) decode_split_kernel<D, W, LENS_ONE><<<grid, 64 * W, 0, s>>>(p);
+        else if (dealt) decode_split_kernel<D, W, LENS_DEALT><<<grid, 64 * W, 0, s>>>(p);
+        else decode_split_kernel<D, W, LENS_FIXED><<<dim3((unsigned)n_splits, (unsigned)Hkv, (unsigned)B), 64 * W, 0, s>>>(p);
+        if (n_splits == 1) return;
+        if (dealt) decode_merge_kernel<D, true><<<(unsigned)(B * Hq), 256, 0, s>>>(p);
+        else decode_merge_kernel<D, false><<<(unsigned)(B * Hq), 256, 0, s>>>(p);
+    };
+    using std::integral_constant;
     if (d == 128) {
-        if (tiles >= 2 && wgs <= n_cu) decode_split_kernel<128, 2><<<grid, 128, 0, s>>>(p);
-        else decode_split_kernel<128, 1><<<grid, 64, 0, s>>>(p);
-        if (n_splits > 1) decode_merge_kernel<128><<<(unsigned)(B * Hq), 256, 0, s>>>(p);
+        if (tiles >= 2 && wgs <= n_cu) launch(integral_constant<int, 128>{}, integral_constant<int, 2>{});
+        else launch(integral_constant<int, 128>{}, integral_constant<int, 1>{});
     } else {
-        if (tiles >= 4 && wgs <= 2LL * n_cu) decode_split_kernel<64, 4><<<grid, 256, 0, s>>>(p);
-        else if (tiles >= 2 && wgs <= 4LL * n_cu) decode_split_kernel<64, 2><<<grid, 128, 0, s>>>(p);
-        else decode_split_kernel<64, 1><<<grid, 64, 0, s>>>(p);
-        if (n_splits > 1) decode_merge_kernel<64><<<(unsigned)(B * Hq), 256, 0, s>>>(p);
+        if (tiles >= 4 && wgs <= 2LL * n_cu) launch(integral_constant<int, 64>{}, integral_constant<int, 4>{});
+        else if ((tiles >= 2 && wgs <= 4LL * n_cu) || (seq_lens && !dealt && tiles >= 8)) launch(integral_constant<int, 64>{}, integral_constant<int, 2>{});
+        else launch(integral_constant<int, 64>{}, integral_constant<int, 1>{});
     }
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
 }

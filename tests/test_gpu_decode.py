@@ -213,13 +213,26 @@ def test_decode_with_per_sequence_lengths(vfa, oracle, name, shape, lens, n_spli
 
 @pytest.mark.parametrize("d,Hkv,n_splits", [(128, 1, 1), (128, 2, 3), (64, 1, 2), (64, 2, 40)])
 def test_varlen_ranges_of_more_entries_than_a_wave_has_lanes(vfa, oracle, d, Hkv, n_splits):
-    """The ranges are dealt out 64 entries at a time: 70 entries, lengths from 1 to the capacity, one of them far longer than
-    the rest (so the first estimates of the range length do not fit), one out of range (clamped)."""
+    """70 entries (64 to a step of the search where the ranges are dealt out, n_splits ranges each where they are not), lengths
+    from 1 to the capacity, one of them far longer than the rest (so the first estimates of the range length do not fit), one
+    out of range (clamped)."""
+    _check_varlen_batch(vfa, oracle, 70, d, Hkv, n_splits)
+
+
+# on both sides of each line between dealt and fixed ranges: 64 and 65 entries, 256 and 257, ranges of two tiles and more, more
+# than eight ranges for each of 256 compute units
+@pytest.mark.parametrize("B,d,Hkv,n_splits", [(64, 64, 1, 5), (65, 64, 1, 5), (65, 64, 1, 4), (256, 64, 1, 3), (256, 128, 1, 2),
+                                              (257, 64, 1, 3), (180, 64, 4, 3), (170, 64, 4, 3), (300, 64, 1, 1)])
+def test_varlen_dealt_and_fixed_ranges(vfa, oracle, B, d, Hkv, n_splits):
+    _check_varlen_batch(vfa, oracle, B, d, Hkv, n_splits)
+
+
+def _check_varlen_batch(vfa, oracle, B, d, Hkv, n_splits):
     import torch
-    B, g, n_cap = 70, 2, 640
+    g, n_cap = 2, 640
     t = _cache(B=B, Hq=g * Hkv, Hkv=Hkv, n_cap=n_cap, d=d, F=4 if d == 64 else 8)
     lens = np.random.default_rng(3).integers(1, 130, size=B).astype(np.int32)
-    lens[[0, 63, 64, 69]] = [n_cap, 64, 65, 1]
+    lens[[0, 63, min(64, B - 2), B - 1]] = [n_cap, 64, 65, 1]
     given = lens.copy()
     given[0] = n_cap + 1000
     Qb = np.ascontiguousarray(np.stack([t["Q"][b, :, lens[b] - 1] for b in range(B)]))
