@@ -74,10 +74,10 @@ __device__ __forceinline__ int wave_prefix(int x) {
 // this out by itself, from up to DEAL_MAX_B / 64 entries in each lane.  It is not done where that costs more than it gives:
 //   more entries, or above 64 of them more than eight ranges for each compute unit: there is a search in each of many waves, and
 //     the number of ranges evens out what dealing would (search over the whole batch against n_splits ranges each, d = 128: 256
-//     entries of up to 512 keys, 8 KV heads, two ranges 77 / 39 us; 1024 entries 523 / 116; 4096 entries 6060 / 480)
-//   above 64 entries with ranges of a tile or two (256 entries of up to 128 keys, one KV head, two ranges, d = 64 11.5 / 8)
+//     entries of up to 512 keys, 8 KV heads, two ranges 77 / 46 us; 1024 entries 523 / 154; 4096 entries 6060 / 608)
+//   above 64 entries with ranges of a tile or two (256 entries of up to 128 keys, one KV head, two ranges, d = 64 11.5 / 7.2)
 //   one range per entry: there is nothing to deal
-// In between it is worth it: 128 entries of up to 8192 keys, one KV head, four ranges 28 us dealt, 57 not.
+// In between it is worth it: 128 entries of up to 8192 keys, one KV head, four ranges 25 us dealt, 57 not.
 constexpr int DEAL_MAX_B = 256;
 struct Ranges {
     int b, first, nb;  // an entry, the ranges of the entries before it, its own number of ranges
