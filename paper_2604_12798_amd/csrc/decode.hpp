@@ -45,28 +45,6 @@ __device__ __forceinline__ int decode_keys(const DecodeParams& p, int b) {
     return p.seq_lens ? min(max(p.seq_lens[b], 1), p.n_cap) : p.n_keys;
 }
 
-// Sum over the wave: rotations within the rows of 16, then the rows.
-__device__ __forceinline__ int wave_sum(int x) {
-    x += __builtin_amdgcn_update_dpp(0, x, 0x121, 0xf, 0xf, false);  // row_ror:1, 2, 4, 8
-    x += __builtin_amdgcn_update_dpp(0, x, 0x122, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x124, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, false);
-    const auto a = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
-    x = (int)(a[0] + a[1]);
-    const auto b = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
-    return __builtin_amdgcn_readfirstlane((int)(b[0] + b[1]));
-}
-// Sum over the lanes up to this one.
-__device__ __forceinline__ int wave_prefix(int x) {
-    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
-    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 and 31: the rows before
-    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
-    return x;
-}
-
 // Which tiles a range covers when every entry of the batch has a length of its own (LENS_DEALT).  The B * n_splits ranges are dealt
 // to the entries by length, so that all are about equally long (a fixed number per entry leaves the ranges of short entries
 // idle: the kernel took 52 us at 16 entries of 200 to 8192 keys, it takes 30): `per` tiles a range, the smallest value found

@@ -20,55 +20,127 @@ __device__ inline uint32_t key_max(uint32_t a, uint32_t b) {
 }
 
 // N = row stride of one head's key array (its capacity), n_valid = keys present, Tc = block stride of
-// one head's summary array, j0 = first block to (re)compute and n_blocks their number: a growing cache
-// recomputes only the blocks that received keys.
-// With per-sequence lengths (old_len / new_len device arrays indexed by batch entry, Hkv heads per entry) the blocks that
-// received keys follow from them, and the waves of a head's workgroups walk them in strides: the host, which does not know
-// how many there are, launches enough workgroups to fill the GPU once.  (One wave for every block of the capacity took
-// 4.9 us for one new key in each of 128 caches of 8192 rows, nearly all of it in workgroups with nothing to do.)
+// one head's summary array.
 template <int D>
-__global__ __launch_bounds__(256) void kblock_summary_kernel(const uint16_t* __restrict__ K, uint16_t* __restrict__ R,
-                                                             int N, int n_valid, int Tc, int block_n, int j0, int n_blocks,
-                                                             const int* __restrict__ old_len = nullptr,
-                                                             const int* __restrict__ new_len = nullptr, int Hkv = 1) {
+__device__ __forceinline__ void summary_of_block(const uint16_t* __restrict__ K, uint16_t* __restrict__ R, int bh, int j, int N,
+                                                 int n_valid, int Tc, int block_n, int lane) {
     constexpr int CH = D / 8;        // 16-byte chunks per row
     constexpr int RG = 64 / CH;      // rows a wave reads at once
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, bh = blockIdx.y;
     const int ch = lane % CH, rg = lane / CH;
-    if (new_len) {
-        const int b = bh / Hkv;
-        n_valid = min(max(new_len[b], 0), N);
-        const int n_old = min(max(old_len[b], 0), n_valid);
-        j0 = n_old / block_n;
-        n_blocks = (n_valid + block_n - 1) / block_n - j0;
+    const int c0 = j * block_n, c1 = min(n_valid, c0 + block_n);
+    const uint16_t* base = K + (size_t)bh * N * D + ch * 8;
+    const uint32_t zero_key = sabs_key(0u);  // +0: the smallest magnitude, already the positive one
+    u32x4 acc = {zero_key, zero_key, zero_key, zero_key};
+    for (int r0 = c0 + rg; r0 < c1; r0 += 8 * RG) {
+        u32x4 x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int r = r0 + u * RG;
+            // (non-temporal: a streaming read; 10 % faster at 64 MiB of keys, no change to the attention kernel behind it)
+            x[u] = r < c1 ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (size_t)r * D)) : u32x4{0, 0, 0, 0};
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = key_max(acc[e], sabs_key(x[u][e]));
     }
-    for (int jb = blockIdx.x * 4 + wave; jb < n_blocks; jb += gridDim.x * 4) {
-        const int j = j0 + jb;
-        const int c0 = j * block_n, c1 = min(n_valid, c0 + block_n);
-        const uint16_t* base = K + (size_t)bh * N * D + ch * 8;
-        const uint32_t zero_key = sabs_key(0u);  // +0: the smallest magnitude, already the positive one
-        u32x4 acc = {zero_key, zero_key, zero_key, zero_key};
-        for (int r0 = c0 + rg; r0 < c1; r0 += 8 * RG) {
-            u32x4 x[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int r = r0 + u * RG;
-                // (non-temporal: a streaming read; 10 % faster at 64 MiB of keys, no change to the attention kernel behind it)
-                x[u] = r < c1 ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (size_t)r * D)) : u32x4{0, 0, 0, 0};
-            }
+    for (int m = CH; m < 64; m <<= 1)
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[e] = key_max(acc[e], sabs_key(x[u][e]));
+        for (int e = 0; e < 4; ++e) acc[e] = key_max(acc[e], (uint32_t)__shfl_xor((int)acc[e], m));
+    if (rg == 0) {
+        const u32x4 out = {sabs_unkey(acc[0]), sabs_unkey(acc[1]), sabs_unkey(acc[2]), sabs_unkey(acc[3])};
+        *reinterpret_cast<u32x4*>(R + ((size_t)bh * Tc + j) * D + ch * 8) = out;
+    }
+}
+
+// j0 = first block to (re)compute and n_blocks their number: a growing cache recomputes only the blocks that received keys.
+template <int D>
+__global__ __launch_bounds__(256) void kblock_summary_kernel(const uint16_t* __restrict__ K, uint16_t* __restrict__ R,
+                                                             int N, int n_valid, int Tc, int block_n, int j0, int n_blocks) {
+    const int lane = threadIdx.x & 63, jb = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (jb < n_blocks) summary_of_block<D>(K, R, blockIdx.y, j0 + jb, N, n_valid, Tc, block_n, lane);
+}
+
+// With per-sequence lengths (device arrays indexed by batch entry, Hkv heads each) the host does not know which blocks received
+// keys.  The kernel counts them, and its waves walk the list of them in order of memory, a block at a time: reads bound it when
+// there is much to do, a launch and the count when there is little.
+// E = 1, 4: up to 64 E entries, E in each lane of every wave.  E = 0: more; the entries are dealt out to the threads of a workgroup,
+// and two levels of sums in LDS lead to the thread that has an item's entry (16 waves to a workgroup, as each counts the batch).
+// Before: one wave for every block of the capacity, most of them with nothing to do, then a fixed number of waves for every head,
+// most of them idle where the heads have different numbers of blocks.  In us (first / second / now), d = 128, 8 KV heads:
+//   a new key in each of 128 caches of 8192 rows 44 / 3.7 / 4.7; 32768 new rows in one of 128 and a key in the others 96 / 285 / 14;
+//   in every fourth 368 / 710 / 392; in all 1424 / 1521 / 1501 (waves that stay lose the order of memory, a wave for each block keeps it)
+constexpr int APPEND_WAVES = 8192;  // eight to a SIMD
+template <int D, int E>
+__global__ __launch_bounds__(E ? 256 : 1024) void kblock_summary_varlen_kernel(const uint16_t* __restrict__ K, uint16_t* __restrict__ R,
+                                                                               int B, int Hkv, int N, int Tc, int block_n,
+                                                                               const int* __restrict__ old_len,
+                                                                               const int* __restrict__ new_len) {
+    constexpr int NW = E ? 4 : 16, T = 64 * NW, C = E ? E : 1;
+    __shared__ int upto[E ? 1 : T], wave_upto[16];  // blocks of one head: of the entries of the threads, of the waves up to one
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int j0[C], n_valid[C], n[C], up[C];  // of entries in each lane: first block, keys, number of blocks, the same up to the entry
+    auto look_at = [&](int b, int e) __attribute__((always_inline)) {
+        n[e] = j0[e] = n_valid[e] = 0;
+        if (b < B) {
+            n_valid[e] = min(max(new_len[b], 0), N);
+            j0[e] = min(max(old_len[b], 0), n_valid[e]) / block_n;
+            n[e] = (n_valid[e] + block_n - 1) / block_n - j0[e];
         }
+    };
+    int total = 0;
+    if (E) {
 #pragma unroll
-        for (int m = CH; m < 64; m <<= 1)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] = key_max(acc[e], (uint32_t)__shfl_xor((int)acc[e], m));
-        if (rg == 0) {
-            const u32x4 out = {sabs_unkey(acc[0]), sabs_unkey(acc[1]), sabs_unkey(acc[2]), sabs_unkey(acc[3])};
-            *reinterpret_cast<u32x4*>(R + ((size_t)bh * Tc + j) * D + ch * 8) = out;
+        for (int e = 0; e < E; ++e) {
+            look_at(64 * e + lane, e);
+            up[e] = total + wave_prefix(n[e]);
+            total = __builtin_amdgcn_readlane(up[e], 63);
         }
+    } else {
+        int own = 0;
+        for (int b = threadIdx.x; b < B; b += T) {
+            look_at(b, 0);
+            own += n[0];
+        }
+        const int sum = wave_prefix(own);
+        if (lane == 63) wave_upto[wave] = sum;
+        __syncthreads();
+        const int waves_upto = wave_prefix(lane < NW ? wave_upto[lane] : 0);
+        __syncthreads();
+        const int before = wave ? __builtin_amdgcn_readlane(waves_upto, wave - 1) : 0;
+        upto[E ? 0 : threadIdx.x] = before + sum;
+        if (lane == 63) wave_upto[wave] = before + sum;
+        __syncthreads();
+        total = __builtin_amdgcn_readlane(waves_upto, NW - 1);
+    }
+    total *= Hkv;
+    for (int item = blockIdx.x * NW + wave; item < total; item += gridDim.x * NW) {
+        int bh = 0, j = 0, nv = 0;
+        // the item's entry: b0 + l * stride, l the first lane whose sum lies behind the item
+        auto found = [&](int e, int b0, int stride) __attribute__((always_inline)) {
+            const int l = __builtin_ctzll(__builtin_amdgcn_ballot_w64(item < up[e] * Hkv) | (1ull << 63));
+            const int nb = __builtin_amdgcn_readlane(n[e], l), rem = item - (__builtin_amdgcn_readlane(up[e], l) - nb) * Hkv, h = rem / nb;
+            bh = (b0 + l * stride) * Hkv + h;
+            j = __builtin_amdgcn_readlane(j0[e], l) + (rem - h * nb);
+            nv = __builtin_amdgcn_readlane(n_valid[e], l);
+        };
+        if (E) {
+            bool done = false;
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (!done && item < __builtin_amdgcn_readlane(up[e], 63) * Hkv) {
+                    found(e, 64 * e, 1);
+                    done = true;
+                }
+        } else {
+            const int w = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < NW && wave_upto[lane & (NW - 1)] * Hkv <= item));
+            const int t = 64 * w + __builtin_popcountll(__builtin_amdgcn_ballot_w64(upto[E ? 0 : (64 * w + lane) & (T - 1)] * Hkv <= item));
+            look_at(t + lane * T, 0);  // (the thread's entries, one to a lane: no more than 64 of a batch of at most 65535)
+            up[0] = (t ? upto[E ? 0 : t - 1] : 0) + wave_prefix(n[0]);
+            found(0, t, T);
+        }
+        summary_of_block<D>(K, R, bh, j, N, nv, Tc, block_n, lane);
     }
 }
 

@@ -496,15 +496,21 @@ int vfa_kblock_summary_append_varlen(const void* K, void* Krepr, int B, int Hkv,
     if ((reinterpret_cast<uintptr_t>(old_lens) | reinterpret_cast<uintptr_t>(new_lens)) & 3u) return VFA_ERR_INVALID_ARG;
     if ((long long)B * Hkv > 65535) return VFA_ERR_UNSUPPORTED;
     const int tc_cap = ceil_div(n_cap, block_n);
-    // (1024 workgroups: four of 256 threads on each compute unit, 128 KiB of loads in flight there)
-    const int per_head = min(ceil_div(tc_cap, 4), max(1, 1024 / (B * Hkv)));
-    const dim3 grid((unsigned)per_head, (unsigned)(B * Hkv));
     hipStream_t s = (hipStream_t)stream;
     (void)hipGetLastError();
-    if (d == 128)
-        kblock_summary_kernel<128><<<grid, 256, 0, s>>>((const uint16_t*)K, (uint16_t*)Krepr, n_cap, 0, tc_cap, block_n, 0, tc_cap, old_lens, new_lens, Hkv);
-    else
-        kblock_summary_kernel<64><<<grid, 256, 0, s>>>((const uint16_t*)K, (uint16_t*)Krepr, n_cap, 0, tc_cap, block_n, 0, tc_cap, old_lens, new_lens, Hkv);
+    auto launch = [&](auto d_c, auto e_c) {
+        constexpr int E = decltype(e_c)::value, NW = E ? 4 : 16;
+        const long long wgs = min(((long long)B * Hkv * tc_cap + NW - 1) / NW, (long long)(APPEND_WAVES / NW));
+        kblock_summary_varlen_kernel<decltype(d_c)::value, E><<<(unsigned)wgs, 64 * NW, 0, s>>>(
+            (const uint16_t*)K, (uint16_t*)Krepr, B, Hkv, n_cap, tc_cap, block_n, old_lens, new_lens);
+    };
+    auto launch_d = [&](auto d_c) {
+        if (B <= 64) launch(d_c, std::integral_constant<int, 1>{});
+        else if (B <= 256) launch(d_c, std::integral_constant<int, 4>{});
+        else launch(d_c, std::integral_constant<int, 0>{});
+    };
+    if (d == 128) launch_d(std::integral_constant<int, 128>{});
+    else launch_d(std::integral_constant<int, 64>{});
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
 }
 

@@ -252,3 +252,28 @@ def test_decode_waves_per_range(vfa, oracle, d, n_keys, n_splits):
     """One, two and four waves to a range, ranges of fewer tiles than waves, and the single range that skips the merge."""
     t = _cache(B=1, Hq=6, Hkv=2, n_cap=1024, d=d, F=4 if d == 64 else 8)
     _check(vfa, oracle, t, n_keys, n_splits=n_splits)
+
+
+@pytest.mark.parametrize("B,Hkv,n_cap,d", [(32, 8, 41 * 64, 128), (140, 8, 650, 128), (140, 8, 700, 64), (513, 1, 41 * 64, 64),
+                                              (64, 2, 41 * 64, 64), (65, 2, 41 * 64, 64), (257, 2, 700, 64), (2100, 1, 650, 64)])
+def test_append_with_more_blocks_than_waves(vfa, B, Hkv, n_cap, d):
+    """The per-sequence append launches a bounded number of waves, which walk the list of blocks that received keys; how an item
+    of the list is found depends on the batch (64 entries and fewer, 256 and fewer, up to 1024, more)."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    K = torch.randn((B, Hkv, n_cap, d), generator=gen, device="cuda").bfloat16()
+    rng = np.random.default_rng(2)
+    new = rng.integers(0, n_cap + 1, size=B).astype(np.int32)
+    old = (new * rng.random(B)).astype(np.int32)
+    new[:4], old[:4] = [n_cap, n_cap, n_cap, n_cap - 1], [0, 1, 65, 100]
+    new[4], old[4] = n_cap + 500, 70                     # clamped to the capacity
+    R = torch.full((B, Hkv, -(-n_cap // 64), d), 7.0, dtype=torch.bfloat16, device="cuda")
+    vfa.kblock_summary_append_varlen(K, R, torch.from_numpy(old).cuda(), torch.from_numpy(new).cuda())
+    n = torch.from_numpy(new).cuda().clamp(max=n_cap)[:, None, None, None]
+    valid = torch.arange(n_cap, device="cuda")[None, None, :, None] < n
+    want = vfa.kblock_summary(torch.where(valid, K, torch.zeros_like(K)), 64)   # (rows of +0 change no block that has keys)
+    j = torch.arange(R.shape[2], device="cuda")[None, None, :, None]
+    o = torch.from_numpy(old).cuda()[:, None, None, None]
+    touched = (j >= o // 64) & (j * 64 < n) & (o < n)
+    torch.cuda.synchronize()
+    assert torch.equal(R, torch.where(touched, want, torch.full_like(R, 7.0)))
