@@ -494,16 +494,23 @@ __global__ __launch_bounds__(256, FOLD ? 3 : 2) void attn_fp8_kernel(const Fp8Pa
         p.LSE[row] = l > 0.f ? (m2 + p.headroom + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
 }
 
+// The run `i` of eight elements (zeros past the end).  STREAM: a non-temporal load.
+template <bool STREAM>
+__device__ __forceinline__ u32x4 quant_load(const uint16_t* __restrict__ X, long long i, long long n8) {
+    if (i >= n8) return u32x4{0, 0, 0, 0};
+    const u32x4* const a = reinterpret_cast<const u32x4*>(X + i * 8);
+    return STREAM ? __builtin_nontemporal_load(a) : *a;
+}
 // bf16 -> E4M3 codes of x * inv_scale (saturated at +-448), same layout.  A workgroup takes QUANT_CHUNKS * 256 runs of eight
-// elements (16 KiB in), all loads in flight at once.
-constexpr int QUANT_CHUNKS = 4;
+// elements, all loads in flight at once (see vfa_fp8_quantize for how many).
+template <int QUANT_CHUNKS, bool STREAM>
 __global__ __launch_bounds__(256) void fp8_quantize_kernel(const uint16_t* __restrict__ X, uint8_t* __restrict__ Y,
                                                            long long n8, float inv_scale) {
     const long long i0 = (long long)blockIdx.x * (256 * QUANT_CHUNKS) + threadIdx.x;
     u32x4 x[QUANT_CHUNKS];
 #pragma unroll
     for (int u = 0; u < QUANT_CHUNKS; ++u)
-        x[u] = i0 + 256 * u < n8 ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(X + (i0 + 256 * u) * 8)) : u32x4{0, 0, 0, 0};
+        x[u] = quant_load<STREAM>(X, i0 + 256 * u, n8);
 #pragma unroll
     for (int u = 0; u < QUANT_CHUNKS; ++u) {
         float v[8];

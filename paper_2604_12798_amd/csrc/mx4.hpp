@@ -34,6 +34,7 @@ struct Tile4 {
 // |y| 2^(127 - byte): from 1 up the code is the top of the float rounded to one mantissa bit (nearest even: half an ulp less
 // one, plus the bit that stays last), below 1 it is 2 |y| rounded to a whole number (nearest even), and at 1 the two agree.
 // (Seven comparisons per element took 36 us for 94 MiB, bound by the vector unit; 31 now.)
+template <int QUANT_CHUNKS, bool STREAM>
 __global__ __launch_bounds__(256) void mx4_quantize_kernel(const uint16_t* __restrict__ X, uint8_t* __restrict__ Y,
                                                            uint8_t* __restrict__ S, long long n8, float pre_scale) {
     // (a workgroup's loads as in fp8_quantize_kernel.  n8 is a multiple of 4, so the four threads of a block are live together)
@@ -41,7 +42,7 @@ __global__ __launch_bounds__(256) void mx4_quantize_kernel(const uint16_t* __res
     u32x4 x[QUANT_CHUNKS];
 #pragma unroll
     for (int u = 0; u < QUANT_CHUNKS; ++u)
-        x[u] = i0 + 256 * u < n8 ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(X + (i0 + 256 * u) * 8)) : u32x4{0, 0, 0, 0};
+        x[u] = quant_load<STREAM>(X, i0 + 256 * u, n8);
 #pragma unroll
     for (int u = 0; u < QUANT_CHUNKS; ++u) {
         const long long i = i0 + 256 * u;

@@ -39,6 +39,19 @@ def test_quantisers_at_the_edges_of_a_workgroup(oracle, n):
     assert int(scales[0, 0]) == 126 and (codes.cpu().numpy().view(np.uint8) & 0x77)[0, 1:].max() == 0 and int(codes[0, 0]) >> 4 == 7
 
 
+@pytest.mark.parametrize("n", [1 << 22, (1 << 22) + 32, (1 << 26) - 32, 1 << 26, (1 << 26) + 32])
+def test_quantisers_of_large_arrays(n):
+    """Runs per thread and the kind of load change with the size: the same bytes as from small pieces."""
+    import torch
+    import paper_2604_12798_amd as vfa
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    X = (torch.randn(n, generator=gen, device="cuda") * 3).bfloat16()
+    pieces = torch.split(X, 1 << 20)
+    assert torch.equal(vfa.fp8_quantize(X, 0.7), torch.cat([vfa.fp8_quantize(p, 0.7) for p in pieces]))
+    got, want = vfa.mxfp4_quantize(X, 1.3), [vfa.mxfp4_quantize(p, 1.3) for p in pieces]
+    assert torch.equal(got[0], torch.cat([w[0] for w in want])) and torch.equal(got[1], torch.cat([w[1] for w in want]))
+
+
 @pytest.mark.parametrize("N,causal,n_sink,n_local,use_minit", [
     (1, True, 1, 1, True), (129, True, 4, 3, True), (700, False, 5, 6, False), (640, True, 2, 1, False), (4230, True, 1, 2, True)])
 @pytest.mark.parametrize("path", ["fp8", "fp8_fold", "mxfp4", "mxfp4_fold"])
