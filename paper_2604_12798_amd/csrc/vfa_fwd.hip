@@ -97,18 +97,18 @@ bool raise_pp() {
 
 // Which kernel Alg. 1 runs on at d = 128: true = attn_frozen.hpp (items of 128 rows, a third to a half cheaper than the
 // ping-pong kernel's items of 256), false = attn_pingpong.hpp (one and a half times the rate once the compute units are full).
-//   up to one 128-row item per compute unit: the ping-pong kernel would leave half of them idle (N = 1024, 32 heads: 29 us
-//     against 21.5)
-//   two to three per compute unit, all equally long (no causal mask): three rounds of short items against two of long ones
-//     (16 heads, N = 5000: 216 against 234 us).  Between one and two it is two rounds against one (N = 3072: 89 against 76 us),
-//     above three four against two, and under a causal mask the ping-pong kernel's long items find short ones to pair with
-//   fewer than 32 items of a call with block_m = 128: the ping-pong kernel, although the other one is faster there too.  It adds a row's terms in the order
-//     of Alg. 2's kernel, so that on small problems, where the two are compared with each other, they agree to the rounding of l
+//   up to one 128-row item per compute unit: the ping-pong kernel would leave half of them idle (us, ping-pong / frozen: 2 heads,
+//     N = 512 22.3 / 17.3; 8 heads, N = 256 18.4 / 14.6; 32 heads, N = 1024 31.7 / 24.6)
+//   two to 2.9 per compute unit, all equally long (no causal mask) and of more than twelve tiles: three rounds of short items
+//     against two of long ones (16 heads, N = 5000 241 / 227).  Where the third round is nearly full or the items are short it is
+//     the other way round (256 heads, N = 300 38.2 / 42.5; 32 heads, N = 3000 155 / 160; 160 heads, N = 512 47 / 49.5).  Between
+//     one and two it is two rounds against one (N = 3072: 89 against 76 us), above three four against two, and under a causal mask
+//     the ping-pong kernel's long items find short ones to pair with
 //   many sink / local blocks: their scores are computed twice in attn_frozen.hpp
-bool prefer_frozen(const Params& p, int n_cu, int block_m) {
+bool prefer_frozen(const Params& p, int n_cu) {
     const long long items = (long long)p.B * p.Hq * p.Tr;
-    if (p.n_sink > 4 || p.n_local > 4 || (items < 32 && block_m == 128) || n_cu <= 0) return false;
-    return items <= n_cu || (!p.causal && items > 2LL * n_cu && items <= 3LL * n_cu);
+    if (p.n_sink > 4 || p.n_local > 4 || n_cu <= 0) return false;
+    return items <= n_cu || (!p.causal && p.Tc > 12 && items > 2LL * n_cu && 10 * items <= 29LL * n_cu);
 }
 
 // Calls with block_m = 64 and without skipping, d = 128 (`p` in blocks of 128 rows): true = items of 64 rows on the generic
@@ -169,7 +169,7 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
         }
         if (!ablation && d == 128) {
             if (!raise_frozen<128, 2>() || !raise_pp<MODE_VFA>()) return VFA_ERR_HIP;
-            const bool frozen = prefer_frozen(q, cu_count(), block_m);
+            const bool frozen = prefer_frozen(q, cu_count());
             rows64 = block_m == 64 && prefer_rows64(q, cu_count(), head_pairs, frozen, false);
             if (frozen && !rows64) return launch_frozen<128, 2>(q, block_m, s);
         }
