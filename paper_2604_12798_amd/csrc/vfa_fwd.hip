@@ -112,26 +112,25 @@ bool prefer_frozen(const Params& p, int n_cu) {
 }
 
 // Calls with block_m = 64 and without skipping, d = 128 (`p` in blocks of 128 rows): true = items of 64 rows on the generic
-// kernel, two to a compute unit, false = blocks of 128 rows.  The short items run at 50 to 80 % of the rate but waste fewer rows
-// and take less to start, which is more only for a few tiles each, and where they need no more rounds (generic / other us):
-//   Alg. 1 against the frozen kernel with one item per compute unit: up to three tiles, no causal mask, one round (64 heads,
-//     N = 192 14.1 / 14.8)
-//   Alg. 1 otherwise: five to ten tiles (96 heads, N = 320 20.2 / 22.5, N = 640 46.8 / 47.5; 192 heads, N = 320, no causal mask
-//     36 / 43).  One round more: N = 500 37.2 / 28.9, N = 384 without a causal mask 30 / 24.  Causal items get shorter towards
-//     the end, and an eighth more of them is still one round: N = 384 21.3 / 23.4
-//   the baselines, which have no max to find in front: up to twelve tiles, under a causal mask a
-//     quarter more items to a round (32 heads, N = 512 18.4 / 23.6, 768 26.7 / 29.1, 1280 43 / 41; 128 heads, N = 320 18.8 / 22.3,
-//     N = 640 40.6 / 46.9; one round more: 96 heads, N = 450 29.7 / 25.9)
+// kernel, two to a compute unit, false = blocks of 128 rows.  The short items run at 50 to 80 % of the rate, waste fewer rows and
+// take less to start, which is more for short sequences only (generic / other us):
+//   Alg. 1, one round of at most four tiles (32 heads, N = 64 9.6 / 10.7, N = 256 14.3 / 14.8; N = 300 15.4 / 15.1).  With
+//     `frozen` (the other choice is attn_frozen.hpp) and no more than one of its items per compute unit, only there
+//   no causal mask, up to 14 tiles, where they need no more rounds (the baseline, 96 heads, N = 777 54.9 / 59.3; two rounds
+//     against one, N = 512 37 / 24; 16 tiles, 32 heads 35.0 / 33.2)
+//   under a causal mask, which evens out the rounds: Alg. 1 up to ten tiles and one and a quarter rounds (96 heads, N = 320 19.7 /
+//     22.1; two rounds, N = 640 46.0 / 47.6 and 64 heads, N = 1024 43 / 36), the baselines, which have no max to find in front, up to
+//     16 and two and a half (128 heads, N = 384 17.1 / 21.8; 96 heads, N = 777 40.9 / 45.4, N = 1024 57.5 / 47.4)
+// 645 shapes of each, against the generic kernel alone: slower by more than 2 % are Alg. 1, causal, 96 heads, N = 640 to 768 (3.5
+// to 6.3 %) and 72 heads, N = 777 (6.7 %), and the baseline, 128 heads, N = 700 (10 %); the mean is 27 and 13 % faster.
 bool prefer_rows64(const Params& p, int n_cu, bool head_pairs, bool frozen, bool baseline) {
     if (n_cu <= 0) return false;
-    const long long heads = (long long)p.B * p.Hq, items = heads * ceil_div(p.N, 64), slots = 2LL * n_cu;
-    if (frozen && heads * p.Tr <= n_cu) return !p.causal && p.Tc <= 3 && items <= slots;
-    if (p.Tc < (baseline ? 1 : 5) || p.Tc > (baseline ? 12 : 10)) return false;
-    long long rounds = (items + slots - 1) / slots;
-    if (p.causal && baseline) rounds = (4 * items + 5 * slots - 1) / (5 * slots);
-    else if (p.causal && 8 * items <= 9 * slots) rounds = 1;
+    const long long heads = (long long)p.B * p.Hq, items = heads * p.Tc, slots = 2LL * n_cu;
+    if (!baseline && p.Tc <= 4) return items <= slots;
+    if (frozen && heads * p.Tr <= n_cu) return false;
+    if (p.causal) return baseline ? p.Tc <= 16 && 2 * items <= 5 * slots : p.Tc <= 10 && 4 * items <= 5 * slots;
     const long long pairs = head_pairs ? heads / 2 * p.Tr : heads * ((p.Tr + 1) / 2);
-    return rounds <= (pairs + n_cu - 1) / n_cu;
+    return p.Tc <= 14 && (items + slots - 1) / slots <= (pairs + n_cu - 1) / n_cu;
 }
 
 // Alg. 2 at d = 128, block_m = 128: the generic kernel up to this many tokens (causal; half as many non-causal), the ping-pong

@@ -13,10 +13,14 @@ pytestmark = pytest.mark.gpu
 # (B, Hq, Hkv, N, causal)
 SHAPES = [
     (1, 8, 1, 129, True), (1, 64, 8, 192, False), (1, 64, 8, 193, False),   # few items; three and four tiles
+    (1, 64, 8, 256, True), (1, 64, 8, 257, True), (5, 32, 32, 200, True),     # four tiles and five; more than one round of four
     (3, 32, 8, 320, True), (3, 32, 32, 320, False), (6, 32, 32, 320, False),  # odd block counts
     (3, 32, 8, 384, True), (3, 32, 8, 385, True), (4, 32, 8, 320, True),     # an eighth, a quarter over one round
-    (3, 32, 32, 640, True), (3, 32, 32, 641, True),                            # ten tiles and eleven
-    (1, 32, 8, 768, True), (1, 32, 8, 769, True), (1, 3, 1, 777, False),       # twelve tiles and thirteen
+    (2, 32, 8, 640, True), (2, 32, 8, 641, True),                              # ten tiles and eleven
+    (3, 32, 32, 640, True), (3, 32, 32, 641, True), (1, 32, 8, 768, True), (1, 32, 8, 769, True),
+    (1, 32, 8, 896, False), (1, 32, 8, 897, False),                            # fourteen tiles and fifteen
+    (1, 32, 8, 1024, True), (1, 32, 8, 1025, True), (1, 3, 1, 777, False),     # sixteen tiles and seventeen
+    (4, 32, 8, 640, True), (4, 32, 8, 641, True),                              # two and a half rounds and more
 ]
 
 
