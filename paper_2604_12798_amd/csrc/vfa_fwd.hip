@@ -111,6 +111,24 @@ bool prefer_frozen(const Params& p, int n_cu) {
     return items <= n_cu || (!p.causal && p.Tc > 12 && items > 2LL * n_cu && 10 * items <= 29LL * n_cu);
 }
 
+// The same at d = 64 (`p` in blocks of 128 rows, `block_m` the call's): true = attn_frozen.hpp, false = the generic kernel, which has
+// no max to find in front, fits two items of 128 rows or four of 64 on a compute unit and runs at 80 to 90 % of the rate
+// (us, generic / frozen):
+//   up to one 128-row item per compute unit: more than four tiles (32 heads, N = 128 7.7 / 8.9, N = 448 12.7 / 12.0, N = 777 17.5 /
+//     14.7); in blocks of 64 also fewer, where the generic kernel's items are more than one per compute unit (72 heads, N = 300 13.3 / 11.1)
+//   up to two: more than eight (160 heads, N = 256 12.2 / 14.0)
+//   more: in blocks of 128 more than 24 tiles (256 heads, N = 300 16.9 / 20.6; 128 heads, N = 777 28 / 32; 64 heads, N = 4096 182 / 167),
+//     in blocks of 64 always, under a causal mask from nine tiles on (160 heads, N = 448 17.6 / 22.0; 256 heads, N = 448 no mask 33.5 / 29.3)
+// 676 shapes of each block_m, against the generic kernel alone: 13 and 4 are more than 2 % slower, the largest 32 heads, N = 3000
+// (6 %), in blocks of 64 128 heads, N = 700 (8 %); the mean is 8 and 15 % faster.
+bool prefer_frozen64(const Params& p, int block_m, int n_cu) {
+    if (p.n_sink > 4 || p.n_local > 4) return false;
+    const long long heads = (long long)p.B * p.Hq, items = heads * p.Tr;
+    if (items <= n_cu) return p.Tc > 4 || (block_m == 64 && heads * p.Tc > n_cu);
+    if (items <= 2LL * n_cu) return p.Tc > 8;
+    return block_m == 64 ? !p.causal || p.Tc > 8 : p.Tc > 24;
+}
+
 // Calls with block_m = 64 and without skipping, d = 128 (`p` in blocks of 128 rows): true = items of 64 rows on the generic
 // kernel, two to a compute unit, false = blocks of 128 rows.  The short items run at 50 to 80 % of the rate, waste fewer rows and
 // take less to start, which is more for short sequences only (generic / other us):
@@ -159,12 +177,14 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
     bool rows64 = false;
     if constexpr (MODE == MODE_VFA) {
         // (every LDS limit that this entry point may need at this d is raised on its first call: a later one may be captured)
-        if (!ablation && d == 64 && p.n_sink <= 4 && p.n_local <= 4) {
+        if (!ablation && d == 64) {
             if (!raise_frozen<64, 1>() || !raise_frozen<64, 2>()) return VFA_ERR_HIP;
-            // two groups to an item while there is no more than one item per compute unit and a group has a few tiles
-            // (32 heads, N = 777: 12.4 against 13.6 us; N = 256: 8.4 against 8.0; N = 4096: 95 against 87)
-            if ((long long)q.B * q.Hq * q.Tr <= cu_count() && q.Tc >= 6) return launch_frozen<64, 2>(q, block_m, s);
-            return launch_frozen<64, 1>(q, block_m, s);
+            if (prefer_frozen64(q, block_m, cu_count())) {
+                // two groups to an item while there is no more than one item per compute unit and a group has a few tiles
+                // (32 heads, N = 777: 12.4 against 13.6 us; N = 256: 8.4 against 8.0; N = 4096: 95 against 87)
+                if ((long long)q.B * q.Hq * q.Tr <= cu_count() && q.Tc >= 6) return launch_frozen<64, 2>(q, block_m, s);
+                return launch_frozen<64, 1>(q, block_m, s);
+            }
         }
         if (!ablation && d == 128) {
             if (!raise_frozen<128, 2>() || !raise_pp<MODE_VFA>()) return VFA_ERR_HIP;

@@ -37,6 +37,17 @@ def test_tile_counts(oracle, d, N, causal):
     _check(oracle, _w(B=2, Hq=16, Hkv=4, N=N, d=d, causal=causal), sample=6)
 
 
+# d = 64: on both sides of the lines to the generic kernel on a chip of 256 units: four tiles, and as many blocks of 64 rows as units,
+# with one block of 128 rows per unit; eight tiles with two; eight and 24 with more
+@pytest.mark.parametrize("B,Hq,N,causal", [(1, 8, 256, True), (1, 8, 257, True), (2, 32, 256, True), (3, 24, 256, False), (1, 8, 576, False),
+                                           (1, 8, 577, True), (1, 8, 641, False), (2, 32, 512, True), (2, 32, 513, True), (2, 32, 600, False),
+                                           (5, 32, 448, False), (5, 32, 512, True), (5, 32, 513, True), (3, 16, 1536, False),
+                                           (3, 16, 1537, False), (3, 16, 1537, True)])
+@pytest.mark.parametrize("block_m", [64, 128])
+def test_tile_counts_d64(oracle, B, Hq, N, causal, block_m):
+    _check(oracle, _w(B=B, Hq=Hq, Hkv=4, N=N, d=64, causal=causal, block_m=block_m), sample=6)
+
+
 # the sets of blocks whose maxima are taken first: none, overlapping, more than four tiles in all, no estimate from the summaries
 @pytest.mark.parametrize("d,block_m", [(64, 64), (64, 128), (128, 64), (128, 128)])
 @pytest.mark.parametrize("n_sink,n_local,use_minit", [(0, 0, True), (0, 2, False), (1, 0, False), (3, 1, True), (4, 4, True), (2, 4, False)])
@@ -64,5 +75,5 @@ def test_what_lds_held_before_does_not_matter(oracle, d):
         import torch
         x = torch.full((8, 32, 512, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
         vfa.fa_baseline_fwd(x, x, x, causal=False)
-    for n in (64, 200):
+    for n in (64, 200, 520, 600):
         _check(oracle, _w(B=1, Hq=32, Hkv=8, N=n, d=d, n_sink=1, n_local=0), sample=6, before=poison)

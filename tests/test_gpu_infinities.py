@@ -12,11 +12,22 @@ def _empty(O, L, what):
     assert (O == 0).all() and torch.isneginf(L).all(), what
 
 
+# every row's blocks are sink or local ones, where all kernels take the exact max; at 600 rows the others too, on attn_frozen.hpp
 @pytest.mark.parametrize("d,block_m", [(64, 64), (64, 128), (128, 64), (128, 128)])
 @pytest.mark.parametrize("B,Hq,Hkv,N,kw", [(1, 4, 2, 128, {}), (2, 32, 8, 100, {}), (1, 32, 2, 300, dict(n_local=4)),
                                           (1, 32, 2, 300, dict(n_local=4, use_minit=False)), (1, 4, 2, 300, dict(n_sink=5)),
-                                          (4, 64, 8, 64, dict(causal=False)), (1, 32, 2, 400, {})])
+                                          (4, 64, 8, 64, dict(causal=False)), (1, 32, 2, 400, dict(n_sink=4, n_local=4)),
+                                          (1, 4, 2, 600, {}), (1, 4, 2, 600, dict(use_minit=False))])
 def test_bf16(d, block_m, B, Hq, Hkv, N, kw):
+    _infinite_feature(d, block_m, B, Hq, Hkv, N, kw)
+
+
+@pytest.mark.parametrize("block_m", [64, 128])
+def test_bf16_d64_one_group_of_keys(block_m):
+    _infinite_feature(64, block_m, 1, 64, 8, 600, {})
+
+
+def _infinite_feature(d, block_m, B, Hq, Hkv, N, kw):
     """KV head 0: an infinite feature in every key.  The other heads are what they are without it."""
     import torch
     import paper_2604_12798_amd as vfa
