@@ -26,10 +26,9 @@
  * The functions never throw, abort or print.  Same inputs give bit-identical outputs.
  *
  * Calls may be recorded into a HIP graph (they only enqueue kernels; nothing is allocated, copied
- * or cleared).  One exception: the first launch, on each device, of an attention kernel that needs
- * more than 64 KiB of LDS sets that function attribute, so make one ordinary call per entry point, head width d,
- * device and process before capturing (of any size: it sets the attribute for every kernel that a later call of
- * that entry point and d may take).
+ * or cleared).  One exception: the first bf16 attention call on each device, of any entry point and size, sets a
+ * function attribute of every kernel that needs more than 64 KiB of LDS, so make one such call per device and
+ * process before capturing.
  */
 #ifndef VFA_H_
 #define VFA_H_

@@ -63,23 +63,32 @@ int cu_count() {
     return n > 0 ? n : 0;
 }
 
-// opt a kernel in to more than 64 KiB of LDS, once per kernel and device (idempotent, so a race only repeats it)
+// Opt the kernels that need more than 64 KiB of LDS in to it: all of them on the first attention call on a device, whatever call
+// that is, so that no later one, which may be a captured one, has to (idempotent, so a race only repeats it).
 template <typename KernelT>
-bool raise_lds_limit(KernelT kernel, int bytes, std::atomic<unsigned char>* done) {
+bool raise_lds_limit(KernelT kernel, int bytes) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
+}
+template <int D, int KS>
+bool raise_frozen() {
+    return raise_lds_limit(&attn_fwd_frozen_kernel<D, KS, false>, Frozen<D, KS>::LDS_BYTES) &&
+           raise_lds_limit(&attn_fwd_frozen_kernel<D, KS, true>, Frozen<D, KS>::LDS_BYTES);
+}
+template <int MODE>
+bool raise_pp() {
+    return raise_lds_limit(&attn_fwd_pp_kernel<MODE, false>, pp_lds_bytes<false>()) &&
+           raise_lds_limit(&attn_fwd_pp_kernel<MODE, true>, pp_lds_bytes<true>());
+}
+bool raise_lds_limits() {
+    static std::atomic<unsigned char> done[kMaxDevices];
     const int dev = current_device();
     if (dev < 0) return false;
     if (done[dev].load(std::memory_order_acquire)) return true;
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess)
+    if (!raise_frozen<64, 1>() || !raise_frozen<64, 2>() || !raise_frozen<128, 2>() || !raise_pp<MODE_VFA>() || !raise_pp<MODE_FA>() ||
+        !raise_pp<MODE_FA_LAZY>() || !raise_pp<MODE_FA_SOFTEXP>() || vfa_detail_vsa_pp_raise_lds() != 0)
         return false;
     done[dev].store(1, std::memory_order_release);
     return true;
-}
-
-template <int D, int KS>
-bool raise_frozen() {
-    static std::atomic<unsigned char> lds_raised[2][kMaxDevices];
-    return raise_lds_limit(&attn_fwd_frozen_kernel<D, KS, false>, Frozen<D, KS>::LDS_BYTES, lds_raised[0]) &&
-           raise_lds_limit(&attn_fwd_frozen_kernel<D, KS, true>, Frozen<D, KS>::LDS_BYTES, lds_raised[1]);
 }
 template <int D, int KS>
 int launch_frozen(const Params& p, int block_m, hipStream_t s) {
@@ -87,12 +96,6 @@ int launch_frozen(const Params& p, int block_m, hipStream_t s) {
     if (block_m == 64 && p.causal) attn_fwd_frozen_kernel<D, KS, true><<<grid, 256 * KS, Frozen<D, KS>::LDS_BYTES, s>>>(p);
     else attn_fwd_frozen_kernel<D, KS, false><<<grid, 256 * KS, Frozen<D, KS>::LDS_BYTES, s>>>(p);
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
-}
-template <int MODE>
-bool raise_pp() {
-    static std::atomic<unsigned char> lds_raised[2][kMaxDevices];
-    return raise_lds_limit(&attn_fwd_pp_kernel<MODE, false>, pp_lds_bytes<false>(), lds_raised[0]) &&
-           raise_lds_limit(&attn_fwd_pp_kernel<MODE, true>, pp_lds_bytes<true>(), lds_raised[1]);
 }
 
 // Which kernel Alg. 1 runs on at d = 128: true = attn_frozen.hpp (items of 128 rows, a third to a half cheaper than the
@@ -164,6 +167,7 @@ constexpr int VSA_GENERIC_MAX_N = 10240;
 template <int MODE>
 int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
     (void)hipGetLastError();
+    if (!raise_lds_limits()) return VFA_ERR_HIP;
     const int g = p.Hq / p.Hkv;
     const bool ablation = p.order_asc || p.all_special || p.rowskip || p.Qrepr || (MODE == MODE_VSA && p.tau2 >= 0.f);
     // ping-pong kernel: head pairs when the heads per KV head are even; otherwise (MHA, odd groups) pairs of
@@ -176,37 +180,20 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
     if (MODE != MODE_VSA && !ablation) q.Tr = ceil_div(p.N, 128);
     bool rows64 = false;
     if constexpr (MODE == MODE_VFA) {
-        // (every LDS limit that this entry point may need at this d is raised on its first call: a later one may be captured)
-        if (!ablation && d == 64) {
-            if (!raise_frozen<64, 1>() || !raise_frozen<64, 2>()) return VFA_ERR_HIP;
-            if (prefer_frozen64(q, block_m, cu_count())) {
-                // two groups to an item while there is no more than one item per compute unit and a group has a few tiles
-                // (32 heads, N = 777: 12.4 against 13.6 us; N = 256: 8.4 against 8.0; N = 4096: 95 against 87)
-                if ((long long)q.B * q.Hq * q.Tr <= cu_count() && q.Tc >= 6) return launch_frozen<64, 2>(q, block_m, s);
-                return launch_frozen<64, 1>(q, block_m, s);
-            }
+        if (!ablation && d == 64 && prefer_frozen64(q, block_m, cu_count())) {
+            // two groups to an item while there is no more than one item per compute unit and a group has a few tiles
+            // (32 heads, N = 777: 12.4 against 13.6 us; N = 256: 8.4 against 8.0; N = 4096: 95 against 87)
+            if ((long long)q.B * q.Hq * q.Tr <= cu_count() && q.Tc >= 6) return launch_frozen<64, 2>(q, block_m, s);
+            return launch_frozen<64, 1>(q, block_m, s);
         }
         if (!ablation && d == 128) {
-            if (!raise_frozen<128, 2>() || !raise_pp<MODE_VFA>()) return VFA_ERR_HIP;
             const bool frozen = prefer_frozen(q, cu_count());
             rows64 = block_m == 64 && prefer_rows64(q, cu_count(), head_pairs, frozen, false);
             if (frozen && !rows64) return launch_frozen<128, 2>(q, block_m, s);
         }
     }
     if constexpr (is_fa(MODE)) {
-        if (d == 128 && !raise_pp<MODE>()) return VFA_ERR_HIP;
         rows64 = d == 128 && block_m == 64 && prefer_rows64(q, cu_count(), head_pairs, false, true);
-    }
-    if constexpr (MODE == MODE_VSA) {
-        if (!ablation && d == 128 && block_m == 128) {  // (on the first call of any length)
-            static std::atomic<unsigned char> lds_raised[kMaxDevices];
-            const int dev = current_device();
-            if (dev < 0) return VFA_ERR_HIP;
-            if (!lds_raised[dev].load(std::memory_order_acquire)) {
-                if (vfa_detail_vsa_pp_raise_lds() != 0) return VFA_ERR_HIP;
-                lds_raised[dev].store(1, std::memory_order_release);
-            }
-        }
     }
     if (d == 128 && (block_m == 128 || MODE != MODE_VSA) && !ablation && !rows64 &&
         (MODE != MODE_VSA || (p.N > (p.causal ? VSA_GENERIC_MAX_N : VSA_GENERIC_MAX_N / 2) && (head_pairs || (p.causal && p.n_local <= 1))))) {

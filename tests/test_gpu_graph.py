@@ -60,3 +60,59 @@ def test_prefill_and_decode_replay_from_a_graph():
                            ("decode O", Od, eod), ("decode LSE", Ld, eld)):
             assert torch.equal(a, b), (rnd, name)
         assert int((M == 1).sum().item()) > 0 and not torch.isnan(O.float()).any()
+
+
+# the warm-up call and the captured one differ in size, blocks, switches, head width and entry point; each pair in a process of its
+# own, where no other test has made the library's one-time attribute calls
+PAIRS = {
+    "d64_many_sinks_first": ("vfa_attn_fwd", 64, dict(N=200, n_sink=5), "vfa_attn_fwd", 64, dict(N=1000)),
+    "d128_many_sinks_first": ("vfa_attn_fwd", 128, dict(N=200, n_sink=5, block_m=64), "vfa_attn_fwd", 128, dict(N=777)),
+    "vsa_block_m_64_first": ("vsa_attn_fwd", 128, dict(N=200, block_m=64, skip_threshold_nats=4.0),
+                             "vsa_attn_fwd", 128, dict(N=10304, skip_threshold_nats=4.0)),
+    "variant_ascending_first": ("vfa_variant_fwd", 128, dict(N=200, reorder=False), "vfa_variant_fwd", 128, dict(N=2048)),
+    "variant_skipping_last": ("vfa_variant_fwd", 128, dict(N=200), "vfa_variant_fwd", 128, dict(N=10304, skip_threshold_nats=4.0)),
+    "baseline_at_d64_first": ("fa_baseline_fwd", 64, dict(N=64, block_m=64), "vfa_attn_fwd", 128, dict(N=4000, n_sink=6, block_m=64)),
+}
+CHILD = """
+import sys, json, torch
+import paper_2604_12798_amd as vfa
+name1, d1, first, name2, d2, second = json.loads(sys.argv[1])
+def call(name, d, N, **kw):
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    Q, K, V = (torch.randn((1, h, N, d), generator=gen, device="cuda").bfloat16() for h in (4, 2, 2))
+    bm = kw.get("block_m", 128)
+    ws = torch.empty(vfa.workspace_bytes(1, 2, N, d, 64), dtype=torch.uint8, device="cuda")
+    o, l = torch.empty_like(Q), torch.empty((1, 4, N), device="cuda")
+    extra = {} if name == "fa_baseline_fwd" else dict(workspace=ws)
+    if "skip_threshold_nats" in kw: extra.update(skip_mask=torch.empty((1, 4, -(-N // bm), -(-N // 64)), dtype=torch.uint8, device="cuda"))
+    return (lambda: getattr(vfa, name)(Q, K, V, out=o, lse=l, **extra, **kw)), o, l
+call(name1, d1, **first)[0]()
+torch.cuda.synchronize()
+fn, o, l = call(name2, d2, **second)
+torch.cuda.synchronize()
+g = torch.cuda.CUDAGraph()
+with torch.cuda.graph(g):
+    fn()
+seen = []
+for rnd in range(3):
+    o.fill_(float("nan")); l.fill_(float("nan"))
+    torch.cuda.synchronize()
+    g.replay()
+    torch.cuda.synchronize()
+    seen.append((o.clone(), l.clone()))
+fn()
+torch.cuda.synchronize()
+assert all(torch.equal(a, o) and torch.equal(b, l) for a, b in seen) and torch.isfinite(l).all()
+print("captured", name2, flush=True)
+"""
+
+
+@pytest.mark.parametrize("name", PAIRS)
+def test_warm_up_call_of_another_kind(name):
+    import json
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", CHILD, json.dumps(PAIRS[name])], cwd=root, timeout=100, capture_output=True, text=True)
+    assert r.returncode == 0 and "captured" in r.stdout, r.stdout + r.stderr
