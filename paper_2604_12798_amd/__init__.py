@@ -1,8 +1,7 @@
 """Thin Python binding of libvfa.so (the C ABI declared in include/vfa.h).
 
 `lib()` is the library through ctypes, for callers who want the C ABI itself; the functions below go through the CPython
-module `_native` (csrc/binding.cpp), because ctypes takes 4 to 5 us to convert the twenty arguments of a call, which is
-more than the kernel launches behind it.
+module `_native` (csrc/binding.cpp), because ctypes takes 2.6 us and more to convert the twenty arguments of a call.
 
 Argument marshalling only: every step of the attention path runs in the HIP kernels behind
 the C entry points.  torch is used for device memory and streams.  There is no fallback: if

@@ -1,36 +1,26 @@
 // CPython module `_native`: the C ABI of libvfa.so (vfa.h) as Python functions with the same names and the same arguments in the
-// same order, returning the status code.  Pointers are integers or None.  A call through ctypes spends 4 to 5 us on converting
-// twenty arguments one object at a time, more than the two kernel launches behind it; this takes 0.6 us.  The conversions follow
-// from the declared argument types, so a signature that changes in vfa.h changes here by itself.
+// same order, returning the status code.  Pointers are integers or None.  It checks no tensors (the package's __init__.py does).
+// Converting the twenty arguments of a call that is refused at once takes 2.6 us through ctypes, one object at a time, and 0.2 us
+// here (measured on the host; a step of two calls got 6.4 us shorter).  The conversions follow from the declared argument types, so
+// a signature that changes in vfa.h changes here by itself.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
-#include <climits>
 #include <cstddef>
+#include <cstdint>
 #include <tuple>
+#include <type_traits>
 #include <utility>
 
 #include "vfa.h"
 
 namespace {
 
-bool convert(PyObject* o, int& v) {
-    const long x = PyLong_AsLong(o);
-    if (x == -1 && PyErr_Occurred()) return false;
-    if (x < INT_MIN || x > INT_MAX) {
-        PyErr_SetString(PyExc_OverflowError, "argument does not fit a C int");
-        return false;
-    }
-    v = (int)x;
-    return true;
-}
-bool convert(PyObject* o, long long& v) {
-    v = PyLong_AsLongLong(o);
-    return !(v == -1 && PyErr_Occurred());
-}
-bool convert(PyObject* o, size_t& v) {
-    v = PyLong_AsSize_t(o);
-    return !(v == (size_t)-1 && PyErr_Occurred());
+// Whole numbers (and what has __index__): the low bits of the C type, as ctypes takes them; the entry point judges the range.
+template <typename T, std::enable_if_t<std::is_integral_v<T>, int> = 0>
+bool convert(PyObject* o, T& v) {
+    v = (T)PyLong_AsUnsignedLongLongMask(o);
+    return !(v == (T)-1 && PyErr_Occurred());
 }
 bool convert(PyObject* o, float& v) {
     v = (float)PyFloat_AsDouble(o);
@@ -38,8 +28,14 @@ bool convert(PyObject* o, float& v) {
 }
 template <typename T>
 bool convert(PyObject* o, T*& v) {
-    v = o == Py_None ? nullptr : static_cast<T*>(PyLong_AsVoidPtr(o));
-    return !(v == nullptr && PyErr_Occurred());
+    v = nullptr;
+    if (o == Py_None) return true;
+    if (!PyLong_Check(o)) {
+        PyErr_SetString(PyExc_TypeError, "a pointer is an integer or None");
+        return false;
+    }
+    v = reinterpret_cast<T*>((uintptr_t)PyLong_AsUnsignedLongLongMask(o));
+    return true;
 }
 
 template <typename R, typename... A, size_t... I>
@@ -55,7 +51,7 @@ PyObject* call(R (*f)(A...), PyObject* const* args, Py_ssize_t n, std::index_seq
     Py_BEGIN_ALLOW_THREADS  // (as ctypes does: other threads run while the launches are enqueued)
     r = f(std::get<I>(v)...);
     Py_END_ALLOW_THREADS
-    return PyLong_FromLongLong((long long)r);
+    return std::is_unsigned_v<R> ? PyLong_FromUnsignedLongLong((unsigned long long)r) : PyLong_FromLongLong((long long)r);
 }
 template <auto F>
 struct Wrap;
