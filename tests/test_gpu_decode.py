@@ -64,7 +64,7 @@ def test_decode_matches_oracle(vfa, oracle, name, shape, n_keys, kw):
 
 def _random_decode_cases(n, seed):
     """Seeded decode shapes: heads per KV head from 1 to 32, d, cache capacity and fill, 1 to 24 key ranges (also more
-    ranges than tiles), 0-2 sink and 0-3 local blocks, with and without the summary estimate."""
+    ranges than tiles); 0-2 sink and 0-3 local blocks, with and without the summary estimate, which must not matter."""
     rng = np.random.default_rng(seed)
     out = []
     for i in range(n):
@@ -252,6 +252,23 @@ def test_decode_waves_per_range(vfa, oracle, d, n_keys, n_splits):
     """One, two and four waves to a range, ranges of fewer tiles than waves, and the single range that skips the merge."""
     t = _cache(B=1, Hq=6, Hkv=2, n_cap=1024, d=d, F=4 if d == 64 else 8)
     _check(vfa, oracle, t, n_keys, n_splits=n_splits)
+
+
+def test_decode_does_not_depend_on_the_summaries(vfa):
+    """Every range takes its exact max: what the summary tensor holds and how many sink / local blocks there are changes no bit."""
+    import torch
+    t = _cache(B=2, Hq=8, Hkv=2, n_cap=1024, d=128)
+    K, V = to_gpu(t["K"]), to_gpu(t["V"])
+    q = to_gpu(np.ascontiguousarray(t["Q"][:, :, 900]))
+    lens = torch.tensor([901, 77], dtype=torch.int32, device="cuda")
+    R = vfa.kblock_summary(K, 64)
+    for ns in (1, 5):
+        for fn, n in ((vfa.decode_fwd, 901), (vfa.decode_varlen_fwd, lens)):
+            O, L = fn(q, K, V, n, krepr=R, n_splits=ns)
+            for kw in (dict(krepr=torch.full_like(R, float("nan"))), dict(krepr=R, n_sink=3, n_local=0), dict(use_minit=False)):
+                O2, L2 = fn(q, K, V, n, n_splits=ns, **kw)
+                torch.cuda.synchronize()
+                assert torch.equal(O, O2) and torch.equal(L, L2)
 
 
 @pytest.mark.parametrize("B,Hkv,n_cap,d", [(32, 8, 41 * 64, 128), (140, 8, 650, 128), (140, 8, 700, 64), (513, 1, 41 * 64, 64),

@@ -154,10 +154,10 @@ def test_vsa_mask_bit_exact_and_output(vfa, oracle, name, w, thr):
     assert sparsity > 0.02
 
 
-# The VSA ping-pong kernel runs a step in a general or in a fast form, chosen per step from the visit list's shape
-# (sink / local visits at the head, masked or ragged tiles at the tail, five visits of look-ahead).  Non-causal lengths
-# put the same visit count on every query block, so a sweep over lengths walks the switch points one by one: no fast
-# step at all, a single pair, a ragged last tile that shortens the fast range, sinks / locals that move its start.
+# Short sequences (the generic kernel, whose loop falls into sink / local visits, a run of unmasked ones and the rest): non-causal
+# lengths put the same visit count on every query block, so a sweep over lengths moves the ends of the three parts one by one,
+# ragged last tiles and sinks / locals shift them.  (The ping-pong kernel's step forms, which long sequences take:
+# test_gpu_vsa_routes.py.)
 STEP_FORM_CASES = [
     ("pairs_tc9", W(B=1, Hq=4, Hkv=2, N=576, beta=6.0, kappa=3.0, causal=False), 5.0),
     ("pairs_tc11", W(B=1, Hq=4, Hkv=2, N=704, beta=6.0, kappa=3.0, causal=False), 5.0),

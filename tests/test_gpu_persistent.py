@@ -61,8 +61,40 @@ def test_persistent_workgroups(oracle, name, base, over):
         dl = (La - L_fa).abs().max().item()
         print(name, what, "vs fa over all rows: max |dO| %.4f max |dLSE| %.2e" % (do, dl), flush=True)
         assert do <= 4e-2 and dl <= 2e-3, (name, what, do, dl)
-    # VSA with a threshold nothing reaches: the same attention again, every visited tile kept
+    # VSA with a threshold nothing reaches: the same attention again, every visited tile kept (on the generic kernel up to 10240 tokens)
     O_s, L_s, M = vfa.vsa_attn_fwd(Q, K, V, skip_threshold_nats=1e4, **vkw)
     torch.cuda.synchronize()
     assert int((M == 1).sum().item()) == 0
     assert (O_s.float() - O_v.float()).abs().max().item() <= 4e-2 and (L_s - L_v).abs().max().item() <= 2e-3
+
+
+# Alg. 2's kernel as persistent workgroups: over 10240 tokens, both pairings with one list per XCD and with one for the whole chip
+VSA_CASES = [
+    ("xcd_lists_head_pairs", "cfg3", dict(B=1, Hq=16, Hkv=8, N=10304)),
+    ("chip_list_head_pairs", "cfg3", dict(B=2, Hq=6, Hkv=3, N=10250)),
+    ("xcd_lists_block_pairs", "cfg2", dict(B=1, Hq=8, Hkv=8, N=10304)),
+    ("chip_list_block_pairs", "cfg2", dict(B=1, Hq=7, Hkv=7, N=10500)),
+]
+
+
+@pytest.mark.parametrize("name,base,over", VSA_CASES, ids=[c[0] for c in VSA_CASES])
+def test_persistent_workgroups_vsa(name, base, over):
+    import torch
+    import paper_2604_12798_amd as vfa
+    w = wl.small(wl.CONFIGS[base], **over)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    items = w.B * (w.Hq // 2) * w.Tr if (w.Hq // w.Hkv) % 2 == 0 else w.B * w.Hq * ((w.Tr + 1) // 2)
+    assert w.N > 10240 and w.block_m == 128 and w.causal and items > n_cu, "not the persistent form of Alg. 2's ping-pong kernel"
+    print(f"{name}: {items} items on {n_cu} CUs", flush=True)
+    Q, K, V = gpu_inputs(wl.generate(w))
+    kw = dict(block_m=w.block_m, block_n=w.block_n, causal=w.causal, n_sink=w.n_sink, n_local=w.n_local)
+    O_v, L_v = vfa.vfa_attn_fwd(Q, K, V, **kw)
+    O = torch.full_like(Q, float("nan"))
+    L = torch.full((w.B, w.Hq, w.N), float("nan"), dtype=torch.float32, device=Q.device)
+    M = torch.full((w.B, w.Hq, w.Tr, w.Tc), 9, dtype=torch.uint8, device=Q.device)
+    vfa.vsa_attn_fwd(Q, K, V, skip_threshold_nats=1e4, out=O, lse=L, skip_mask=M, **kw)
+    torch.cuda.synchronize()
+    j, i = torch.arange(w.Tc, device=M.device), torch.arange(w.Tr, device=M.device)
+    seen = j[None, :] * w.block_n < torch.clamp((i[:, None] + 1) * w.block_m, max=w.N)
+    assert torch.equal(M, torch.where(seen, 0, 2).to(torch.uint8).expand_as(M))
+    assert (O.float() - O_v.float()).abs().max().item() <= 4e-2 and (L - L_v).abs().max().item() <= 2e-3

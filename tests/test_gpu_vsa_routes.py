@@ -34,16 +34,40 @@ CASES = [
 ]
 
 
+# The ping-pong kernel runs a step in a general or in a fast form, chosen per step from the visit list's shape (sink / local visits
+# at the head, masked or ragged tiles at the tail, five visits of look-ahead; two steps to a turn of the loop).  Non-causal lengths
+# put the same visit count on every query block, so a sweep over consecutive counts with every head of the list walks the start and
+# the end of the fast range and its parity; causal ones have every count from one up among their first query blocks.
+STEP_FORMS = [("noncausal_tc%d%s_s%dl%d" % (tc, "r" if rag else "", s, l),
+               W(Hq=2, Hkv=1, N=64 * tc - rag, causal=False, n_sink=s, n_local=l), thr)
+              for tc, rag, s, l, thr in ((81, 0, 1, 1, 5.0), (82, 0, 1, 1, 5.0), (83, 0, 1, 1, 9.0), (84, 0, 0, 1, 5.0), (85, 0, 2, 1, 5.0),
+                                         (86, 0, 1, 2, 5.0), (87, 0, 2, 2, 5.0), (82, 17, 1, 1, 5.0), (83, 40, 1, 1, 9.0),
+                                         (84, 63, 0, 2, 5.0), (85, 1, 2, 0, 5.0), (88, 0, 1, 0, 5.0), (89, 5, 0, 0, 9.0), (90, 0, 2, 1, 9.0))]
+STEP_FORMS += [("causal_%s_%d_s%dl%d" % ("blocks" if Hq == Hkv else "heads", N, s, l), W(Hq=Hq, Hkv=Hkv, N=N, n_sink=s, n_local=l), thr)
+               for Hq, Hkv, N, s, l, thr in ((2, 2, 10304, 1, 1, 4.0), (2, 2, 10305, 0, 1, 4.0), (1, 1, 10400, 2, 1, 6.0), (1, 1, 10367, 1, 0, 4.0),
+                                             (2, 1, 10304, 1, 1, 4.0), (2, 1, 10345, 2, 2, 4.0), (2, 1, 10432, 0, 1, 6.0), (2, 1, 10305, 2, 0, 4.0))]
+
+
+@pytest.mark.parametrize("name,w,thr", STEP_FORMS, ids=[c[0] for c in STEP_FORMS])
+def test_vsa_step_forms(oracle, name, w, thr):
+    assert w.N > (10240 if w.causal else 5120) and w.block_m == 128, "a sequence that the generic kernel takes"
+    rows = [0, 1, w.Tr // 2, w.Tr - 2, w.Tr - 1] if not w.causal else [*range(0, 16), w.Tr - 2, w.Tr - 1]
+    _check(oracle, name, w, thr, rows)
+
+
 @pytest.mark.parametrize("name,w,thr", CASES, ids=[c[0] for c in CASES])
 def test_vsa_routes(oracle, name, w, thr):
+    last = w.Tr - 1
+    _check(oracle, name, w, thr, sorted(set([*range(0, 12), last // 2, last - 2, last - 1, last])))
+
+
+def _check(oracle, name, w, thr, rows):
     import torch
     import paper_2604_12798_amd as vfa
     t = wl.generate(w)
     Q, K, V = gpu_inputs(t)
     Qh, Kh, Vh = host_f32(t)
-    last = w.Tr - 1
-    rows = sorted(set([*range(0, 12), last // 2, last - 2, last - 1, last]))
-    blocks = [(0, h, i) for h in range(min(w.Hq, 2)) for i in rows if 0 <= i <= last]
+    blocks = [(0, h, i) for h in range(min(w.Hq, 2)) for i in rows if 0 <= i < w.Tr]
     print(name, flush=True)
     O = torch.full_like(Q, float("nan"))
     L = torch.full((w.B, w.Hq, w.N), float("nan"), dtype=torch.float32, device=Q.device)
