@@ -96,12 +96,17 @@ int fa_lazy_rescale_softexp_fwd(const void* Q, const void* K, const void* V, voi
 /* VFA forward (Alg. 1).  For each query block: the running max starts at
  * m_init = max_j scale * Q_i . Krepr_j over the visible key blocks (use_minit = 1: the summaries
  * are computed into `workspace` first; use_minit = 2: `workspace` already holds them, e.g. from
- * vfa_kblock_summary on an earlier call; use_minit = 0: the max starts at -inf).  Key blocks
- * are visited as: the first n_sink blocks, then the local blocks (those overlapping the query
- * block's own token range plus the n_local-1 blocks before them; none if n_local == 0), then
- * all remaining visible blocks in ascending order, each block once.  Sink and
- * local blocks take the exact online-softmax update; all others reuse the frozen max (no row
- * max, no rescale).  O = acc / l, LSE = m + ln l.  Mathematically equal to exact attention.
+ * vfa_kblock_summary on an earlier call; use_minit = 0: the max starts at -inf).  The scores of the
+ * sink blocks (the first n_sink) and of the local blocks (those overlapping the query block's own
+ * token range plus the n_local-1 blocks before them; none if n_local == 0) then enter the max
+ * exactly; all other visible blocks reuse it (no row max, no rescale).  Each block is added once.
+ * O = acc / l, LSE = m + ln l.  Mathematically equal to exact attention.
+ * Which of two forms runs depends on the sizes: sink and local blocks first, each with the online-softmax
+ * update, the rest behind them; or all their row maxima first and then every block with that max, in
+ * order.  The results differ by rounding only (and a row whose sink and local scores are all -inf
+ * gives NaN in the first form if it sees other blocks).  block_m = 64 may run as blocks of 128
+ * rows, whose local blocks include those of both halves; with a causal mask no key block behind a
+ * row's own 64 reaches it (neither its summary nor its values).
  * use_minit == 0 with n_sink + n_local == 0 is rejected (the max would stay -inf).
  * `workspace` must hold vfa_workspace_bytes(...) bytes when use_minit != 0; use_minit = 1
  * overwrites it. */
@@ -178,8 +183,8 @@ size_t vfa_decode_workspace_bytes(int B, int Hq, int d, int n_splits);
 /* Decode step: one query token per head against every cached key.
  *   Q [B, Hq, d], O [B, Hq, d] bf16; LSE [B, Hq] fp32 or NULL
  *   K, V [B, Hkv, n_cap, d] bf16, rows [0, n_keys) valid (rows beyond are never read)
- *   Krepr  summaries of those n_keys rows, laid out for n_cap (see vfa_kblock_summary_append);
- *          must be given when use_minit == 1, may be NULL when use_minit == 0
+ *   Krepr  checked as before (given and 16-byte aligned when use_minit == 1, may be NULL when use_minit == 0) but not
+ *          read: the step does not need the summaries, and a caller need not keep them up to date for it
  * The cache is cut into n_splits ranges of whole blocks; each range accumulates sum exp(s - m) and
  * sum exp(s - m) v with its own running row max m; the ranges are added in a fixed order, each weighted by
  * exp(m - largest m) (bit-identical results from run to run), divided, and LSE = largest m + ln l.  The max of
@@ -277,8 +282,8 @@ int vfa_fp8_attn_fwd(int frozen, const void* Q8, const void* K8, const void* Vt8
  * weights (measured: mean-abs error as the rounded-exponential path, max-abs within 2^-3 max|V|).  LSE is computed
  * from that row sum: within 0.12 nats of the exact value.  This is the performance discussion's argument taken to
  * its end for 8-bit P: with the max known before the tile, no per-score vector arithmetic but a clamp and a
- * conversion is left.  Everything else as vfa_fp8_attn_fwd with frozen = 1 (sink / local blocks keep the
- * exact-max update, one exponential per row and block there). */
+ * conversion is left.  Everything else as vfa_fp8_attn_fwd with frozen = 1.  (Both, and the 4-bit forms, take the
+ * row maxima of the sink and local blocks in front of the first tile, so every block is a frozen one.) */
 int vfa_fp8_attn_noexp_fwd(const void* Q8, const void* K8, const void* Vt8, void* O, float* LSE, int B,
                            int Hq, int Hkv, int N, int d, int block_m, int block_n, int causal,
                            int n_sink, int n_local, int use_minit, float softmax_scale, float descale_q,

@@ -37,3 +37,33 @@ def test_vsa_fast_loops_have_no_scratch_access(tmp_path):
     fast = sorted(loops.values())[:2]
     assert all(length < 1300 for length, _ in fast), fast
     assert all(scratch == 0 for _, scratch in fast), f"scratch accesses in the VSA fast loops: {fast}"
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_inner_loops_have_no_scratch_access(tmp_path):
+    """The other kernels: several (the ping-pong baselines, the 8-bit and 4-bit forms with folded scales) have spilled registers, all
+    of them outside the loops over tiles.  Left out: the generic kernel with ablation switches at d = 128, block_m = 128."""
+    out = tmp_path / "vfa_fwd.s"
+    flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    subprocess.run([HIPCC] + flags + ["-S", "--cuda-device-only", "-o", str(out), os.path.join(build.CSRC, "vfa_fwd.hip")],
+                   check=True, capture_output=True)
+    seen = []
+    for m in re.finditer(r"^(_Z\S*):[^\n]*\n(.*?)\.Lfunc_end", out.read_text(), re.S | re.M):
+        kernel = re.search(r"(attn_\w+?_kernel|decode_split_kernel)I(\w+?)EEv", m.group(1))
+        if not kernel or re.fullmatch(r"Li128ELi4ELi[12]ELb0", kernel.group(2)):
+            continue
+        body = m.group(2).split("\n")
+        labels = {x.group(1): n for n, l in enumerate(body) if (x := re.match(r"^(\.LBB\d+_\d+):", l))}
+        loops = {}  # first line -> last line
+        for n, l in enumerate(body):
+            x = re.search(r"s_c?branch\w* (\.LBB\d+_\d+)", l)
+            if x and labels.get(x.group(1), n) < n:
+                loops[labels[x.group(1)]] = n
+        inner = [body[a:b] for a, b in loops.items() if not any(a < c and d <= b for c, d in loops.items())]
+        tiles = [seg for seg in inner if any("v_mfma" in x for x in seg)]
+        assert tiles, m.group(1)
+        for seg in tiles:
+            assert not any("scratch_" in x for x in seg), m.group(1)
+        seen.append(kernel.group(1))
+    assert {"attn_fwd_pp_kernel", "attn_fwd_frozen_kernel", "attn_fwd_kernel", "attn_fp8_kernel", "attn_mx4_kernel",
+            "decode_split_kernel"} <= set(seen), seen
