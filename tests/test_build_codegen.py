@@ -50,7 +50,7 @@ def test_inner_loops_have_no_scratch_access(tmp_path):
     seen = []
     for m in re.finditer(r"^(_Z\S*):[^\n]*\n(.*?)\.Lfunc_end", out.read_text(), re.S | re.M):
         kernel = re.search(r"(attn_\w+?_kernel|decode_split_kernel)I(\w+?)EEv", m.group(1))
-        if not kernel or re.fullmatch(r"Li128ELi4ELi[12]ELb0", kernel.group(2)):
+        if not kernel or re.fullmatch(r"Li128ELi4ELi[12]ELb0E", kernel.group(2)):
             continue
         body = m.group(2).split("\n")
         labels = {x.group(1): n for n, l in enumerate(body) if (x := re.match(r"^(\.LBB\d+_\d+):", l))}
