@@ -161,7 +161,8 @@ bool prefer_rows64(const Params& p, int n_cu, bool head_pairs, bool frozen, bool
 // N = 777 29 / 64, 2048 68 / 101, 4096 161 / 202, 8000 511 / 560, 10000 784 / 847, 16384 1863 / 1884, 64K (8 heads) 7147 /
 // 6290; with nothing dropped 8000 583 / 614, 10000 881 / 919, 12200 1262 / 1268, 16384 2262 / 2169; 8/1 heads 10000 268 / 290,
 // 16384 515 / 493; with 98 % dropped 10200 535 / 532; four batches of N = 8000 1901 / 2386.
-// Non-causal: N = 4096 264 / 286, 5000 395 / 454, 6100 547 / 550, nothing dropped 655 / 643.
+// Non-causal: N = 4096 264 / 286, 5000 395 / 454, 6100 547 / 550, nothing dropped 655 / 643.  Slower here by more than 2 %: 98 %
+// dropped, non-causal N = 5100 (4.5 %), and 12 heads, N = 10200 (2.5 %).
 constexpr int VSA_GENERIC_MAX_N = 10240;
 
 template <int MODE>

@@ -1,5 +1,5 @@
 // attn_vsa_pp_kernel (Alg. 2 on the ping-pong structure) in a translation unit of its own, because it is compiled with
-// one code-generation option more than the rest of the library (build.py: VSA_EXTRA_FLAGS).  The kernel lives at 233
+// one code-generation option more than the rest of the library (build.py: EXTRA_FLAGS).  The kernel lives at 233
 // of 256 vector registers; with the default register-pressure tracking of the scheduler the allocator spills an
 // accumulator inside the steady loops of this formulation, with the option it does not.  The option changes
 // scheduling decisions only; the results are the same either way.
