@@ -110,11 +110,11 @@ __global__ __launch_bounds__(256 * KS, 2) void attn_fwd_frozen_kernel(const Para
 #pragma unroll
     for (int u = 0; u < LI; ++u) {
         const int r0 = RPI * LI * w4 + lane / T::CH, r = r0 + RPI * u;  // (row of the first piece; of this one)
-        offK[u] = (uint32_t)(r0 * T::ROWB + ((cp ^ (r & (T::CH - 1))) << 4));
-        off[u] = role_v ? (uint32_t)(r0 * T::ROWB + ((cp ^ ((r & (T::CH / 4 - 1)) << 2)) << 4)) : offK[u];
+        offK[u] = (uint32_t)(r0 * T::ROWB + ((cp ^ T::k_mix(r)) << 4));
+        off[u] = role_v ? (uint32_t)(r0 * T::ROWB + ((cp ^ T::v_mix(r)) << 4)) : offK[u];
     }
     const uint32_t offV = (uint32_t)((RPI * LI * w4 + lane / T::CH) * T::ROWB +
-                                     ((cp ^ (((RPI * LI * w4 + lane / T::CH) & (T::CH / 4 - 1)) << 2)) << 4));  // (KS = 1: the same for all pieces)
+                                     ((cp ^ T::v_mix(RPI * LI * w4 + lane / T::CH)) << 4));  // (KS = 1: the same for all pieces)
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
         (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)(frozen_smem + w4 * LI * 1024));
     // `rows` rows (0 to BN, a negative number counts as 0) at address a to LDS byte `at`

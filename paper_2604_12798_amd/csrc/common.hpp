@@ -72,24 +72,29 @@ struct Params {
 // ---------------------------------------------------------------------------------------------
 // LDS tile layout.  A tile is 64 rows of D bf16 (ROWB = 2*D bytes, CH = ROWB/16 16-byte chunks).
 // K tiles are read with ds_read_b128, 32 consecutive rows at one chunk column per half wave:
-// chunk' = chunk ^ (row & (CH-1)) spreads 16 consecutive rows over all 64 banks.
+// chunk' = chunk ^ (row & 15) spreads 16 consecutive rows over all 64 banks.
 // V tiles are read with ds_read_b64_tr_b16, 4 consecutive rows x 64 contiguous bytes per half
 // wave: the 64-byte window index is XORed with (row & 3) so the 4 rows use distinct banks.
+// At D = 64 two rows fill the banks once, so row / 2 takes the place of row in both (with row itself every
+// read met half of the banks twice).
 template <int D>
 struct Tile {
     static constexpr int ROWB = 2 * D;
     static constexpr int CH = ROWB / 16;
     static constexpr int BYTES = BN * ROWB;
-    __device__ static int k_off(int row, int chunk) { return row * ROWB + ((chunk ^ (row & (CH - 1))) << 4); }
-    __device__ static int v_off(int row, int chunk) { return row * ROWB + ((chunk ^ ((row & (CH / 4 - 1)) << 2)) << 4); }
+    static constexpr int SH = D == 64 ? 1 : 0;  // log2 of the rows that share one pass over the banks
+    __device__ static int k_mix(int row) { return (row >> SH) & (CH - 1); }
+    __device__ static int v_mix(int row) { return ((row >> SH) & (CH / 4 - 1)) << 2; }
+    __device__ static int k_off(int row, int chunk) { return row * ROWB + ((chunk ^ k_mix(row)) << 4); }
+    __device__ static int v_off(int row, int chunk) { return row * ROWB + ((chunk ^ v_mix(row)) << 4); }
     // Per-lane bases from which every fragment address of a tile follows by XOR with a constant
     // (the swizzles are XORs, so the varying index bits commute with them):
     //   K fragment (t, kk) of lane (ql, hh):  (k_base(ql, hh) ^ (kk << 5)) + t * 32 * ROWB
     //   V fragment (c, u, db) of a lane:      (v_base(lane, hh) ^ (db << 6)) + (16 c + 8 u) * ROWB
-    __device__ static int k_base(int ql, int hh) { return ql * ROWB + ((hh ^ (ql & (CH - 1))) << 4); }
+    __device__ static int k_base(int ql, int hh) { return ql * ROWB + ((hh ^ k_mix(ql)) << 4); }
     __device__ static int v_base(int lane, int hh) {
         const int s = lane & 15, dsel = (lane >> 4) & 1, row = 4 * hh + (s >> 2);
-        return row * ROWB + (((2 * dsel + ((s & 3) >> 1)) ^ ((row & (CH / 4 - 1)) << 2)) << 4) + ((s & 1) << 3);
+        return row * ROWB + (((2 * dsel + ((s & 3) >> 1)) ^ v_mix(row)) << 4) + ((s & 1) << 3);
     }
 };
 
@@ -194,7 +199,7 @@ __device__ __forceinline__ void load_tile(const uint16_t* base, int first_row, i
         const int q = u * NWAVES + wave;
         const int r = RPI * q + lane / T::CH;
         const int cp = lane % T::CH;
-        const int ch = is_v ? (cp ^ ((r & (T::CH / 4 - 1)) << 2)) : (cp ^ (r & (T::CH - 1)));
+        const int ch = cp ^ (is_v ? T::v_mix(r) : T::k_mix(r));
         const int gr = full ? first_row + r : min(first_row + r, row_limit - 1);
         // Written as inline asm on purpose: the compiler's wait-count pass treats every LDS read as
         // dependent on every outstanding LDS-direct load and would drain them all (vmcnt(0)) before the

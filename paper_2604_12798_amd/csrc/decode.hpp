@@ -113,7 +113,7 @@ __device__ __forceinline__ void tile_lane_offsets(bool is_v, int lane, uint32_t*
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int rr = RPI * u + lane / T::CH;
-        const int ch = is_v ? (cp ^ ((rr & (T::CH / 4 - 1)) << 2)) : (cp ^ (rr & (T::CH - 1)));
+        const int ch = cp ^ (is_v ? T::v_mix(rr) : T::k_mix(rr));
         offs[u] = (uint32_t)((lane / T::CH) * T::ROWB + ch * 16);
     }
 }
@@ -131,7 +131,7 @@ __device__ __forceinline__ void tile_to_regs(const uint16_t* base, int first_row
 #pragma unroll
         for (int u = 0; u < NI; ++u) {
             const int rr = RPI * u + lane / T::CH;
-            const int ch = is_v ? (cp ^ ((rr & (T::CH / 4 - 1)) << 2)) : (cp ^ (rr & (T::CH - 1)));
+            const int ch = cp ^ (is_v ? T::v_mix(rr) : T::k_mix(rr));
             const int gr = min(first_row + rr, row_limit - 1);
             r[u] = __builtin_nontemporal_load(
                 reinterpret_cast<const u32x4*>(reinterpret_cast<const uint8_t*>(base) + (size_t)gr * T::ROWB + ch * 16));
