@@ -101,9 +101,11 @@ int fa_lazy_rescale_softexp_fwd(const void* Q, const void* K, const void* V, voi
  * token range plus the n_local-1 blocks before them; none if n_local == 0) then enter the max
  * exactly; all other visible blocks reuse it (no row max, no rescale).  Each block is added once.
  * O = acc / l, LSE = m + ln l.  Mathematically equal to exact attention.
- * Which of two forms runs depends on the sizes: sink and local blocks first, each with the online-softmax
- * update, the rest behind them; or all their row maxima first and then every block with that max, in
- * order.  The results differ by rounding only (and a row whose sink and local scores are all -inf
+ * Which of three forms runs depends on the sizes: sink and local blocks first, each with the online-softmax
+ * update, the rest behind them; all their row maxima first and then every block with that max, in
+ * order; or, on short sequences and on the last rows of a call without a causal mask, every block's scores
+ * enter the max exactly, which then needs no summaries (use_minit = 1 writes them to `workspace` all the same).  The results differ
+ * by rounding only (and a row whose sink and local scores are all -inf
  * gives NaN in the first form if it sees other blocks).  block_m = 64 may run as blocks of 128
  * rows, whose local blocks include those of both halves; with a causal mask no key block behind a
  * row's own 64 reaches it (neither its summary nor its values).

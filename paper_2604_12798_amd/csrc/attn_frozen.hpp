@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256 * KS, 2) void attn_fwd_frozen_kernel(const Para
     i = __builtin_amdgcn_readfirstlane(i);
     const int hkv = __builtin_amdgcn_readfirstlane(h / g);
     const int N = p.N;
-    const int row0 = i * BM;
+    const int row0 = p.row_base + i * BM;
     const int last_row = min(N, row0 + BM) - 1;
     const int a_lo = row0 / BN, a_hi = last_row / BN;
     const int j_hi = p.causal ? a_hi : p.Tc - 1;

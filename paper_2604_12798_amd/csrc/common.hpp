@@ -63,6 +63,8 @@ struct Params {
     int persist;      // ping-pong kernel: number of persistent workgroups (0 = one work item per workgroup)
     int order_asc;    // ablation: visit key blocks in ascending order (sink / local blocks keep the exact-max update)
     int all_special;  // ablation: exact-max update on every visited block
+    int n_items;      // attn_short.hpp: its work items; the workgroups behind them write the summaries
+    int row_base;     // attn_frozen.hpp, attn_short.hpp: the first row of every head they work on
     int rowskip;      // skip variant: in a kept tile, rows that fail the threshold test are suppressed (generic kernel)
     float c;     // softmax scale * log2(e)
     float thr2;  // skip threshold in log2 units

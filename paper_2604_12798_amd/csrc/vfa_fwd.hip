@@ -11,6 +11,7 @@
 #include "attn_generic.hpp"
 #include "attn_pingpong.hpp"
 #include "attn_frozen.hpp"
+#include "attn_short.hpp"
 #include "vsa_pp.hpp"
 #include "summary.hpp"
 #include "decode.hpp"
@@ -74,6 +75,8 @@ bool raise_frozen() {
     return raise_lds_limit(&attn_fwd_frozen_kernel<D, KS, false>, Frozen<D, KS>::LDS_BYTES) &&
            raise_lds_limit(&attn_fwd_frozen_kernel<D, KS, true>, Frozen<D, KS>::LDS_BYTES);
 }
+template <int D, int KQ>
+bool raise_short() { return raise_lds_limit(&attn_fwd_short_kernel<D, KQ>, Short<D, KQ>::LDS_BYTES); }
 template <int MODE>
 bool raise_pp() {
     return raise_lds_limit(&attn_fwd_pp_kernel<MODE, false>, pp_lds_bytes<false>()) &&
@@ -84,55 +87,101 @@ bool raise_lds_limits() {
     const int dev = current_device();
     if (dev < 0) return false;
     if (done[dev].load(std::memory_order_acquire)) return true;
+    if (!raise_short<64, 2>() || !raise_short<64, 4>() || !raise_short<128, 2>() || !raise_short<128, 4>()) return false;
     if (!raise_frozen<64, 1>() || !raise_frozen<64, 2>() || !raise_frozen<128, 2>() || !raise_pp<MODE_VFA>() || !raise_pp<MODE_FA>() ||
         !raise_pp<MODE_FA_LAZY>() || !raise_pp<MODE_FA_SOFTEXP>() || vfa_detail_vsa_pp_raise_lds() != 0)
         return false;
     done[dev].store(1, std::memory_order_release);
     return true;
 }
+// rows [row_base, N) of every head; `summaries`: with the workgroups that write them to p.Krepr
+template <int D, int KQ>
+int launch_short(Params p, int row_base, bool summaries, hipStream_t s) {
+    p.row_base = row_base;
+    p.Tr = ceil_div(p.N - row_base, 64);
+    p.n_items = p.B * p.Hq * p.Tr;
+    const long long wgs = p.n_items + (summaries ? ((long long)p.B * p.Hkv * p.Tc + 2 * KQ - 1) / (2 * KQ) : 0);
+    attn_fwd_short_kernel<D, KQ><<<dim3((unsigned)wgs), 128 * KQ, Short<D, KQ>::LDS_BYTES, s>>>(p);
+    return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
+}
 template <int D, int KS>
-int launch_frozen(const Params& p, int block_m, hipStream_t s) {
+int launch_frozen(Params p, int row_base, int block_m, hipStream_t s) {  // rows [row_base, N) of every head
+    p.row_base = row_base;
+    p.Tr = ceil_div(p.N - row_base, 128);
     const dim3 grid((unsigned)(p.B * p.Hq * p.Tr));
     if (block_m == 64 && p.causal) attn_fwd_frozen_kernel<D, KS, true><<<grid, 256 * KS, Frozen<D, KS>::LDS_BYTES, s>>>(p);
     else attn_fwd_frozen_kernel<D, KS, false><<<grid, 256 * KS, Frozen<D, KS>::LDS_BYTES, s>>>(p);
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
 }
 
-// Which kernel Alg. 1 runs on at d = 128: true = attn_frozen.hpp (items of 128 rows, a third to a half cheaper than the
+// Alg. 1 on the kernel for short sequences (attn_short.hpp): 0 = no, else its groups of keys.  `items` are blocks of 64 rows.  The other
+// kernels, with the summaries' launch in front, have twice the rate once their long items fill the compute units; the
+// lines lie where they catch up (us, theirs / two groups / four):
+//   d = 64: four groups for no more items than compute units (16 heads, N = 2048, no mask 22.9 / 19.4 / 15.7 at 8 heads; causal, few
+//     heads, up to four: 12 heads, N = 3802 47 / 43 / 37), otherwise two, up to 24 tiles (64 heads, N = 1536, no mask 37.6 / 34.9; N = 2048 45.8 / 48.4)
+//     or, causal, 32 and for fewer items 64 (32 heads, N = 2048 32.8 / 28.5; 48 heads, N = 2500 58 / 60)
+//   d = 128, four groups: as above from ten tiles on, the summaries' workgroups counted, since one fills a compute unit (8 heads, N = 1024 22.8 /
+//     15.2 / 13.4); causal, few long heads: up to two items per compute unit (12 heads, N = 2500 40.8 / 38.3 / 33.6)
+//   d = 128, two groups: up to seven tiles always (512 heads, N = 448 1.12 and 1.02 times faster, causal and not); from there the more tiles the
+//     fewer items.  Causal 128 heads, N = 777 46 / 36, N = 1024 55 / 60; 64 heads, N = 1024 35.2 / 28.9, N = 1536 52.9 / 56.0; 32 heads, N = 2048
+//     53.9 / 46.9, N = 3000 83 / 91.  Not causal 64 heads, N = 640 27.0 / 24.9, N = 1024 41.5 / 44.5; 32 heads, N = 1024 26.1 / 23.3, N = 1536 46.7 / 49.1
+//   odd groups of heads, causal, run in super-blocks of 256 rows otherwise: a longer range, but for nearly full rounds of those (32 heads
+//     over 32, N = 2500 107 / 78, N = 2048, one round, 56.5 / 59.6); not causal, a second round of a few items: the same (48 heads, N = 1300 75 / 55)
+//   many sink or local blocks: as they were
+// 1696 shapes: the mean is 1.25 to 1.38 times faster by kind; slower by more than 2 % (no mask): 32 heads, N = 2500 was (5 %; now outside).
+int short_groups(const Params& p, int d, int n_cu) {
+    const long long heads = (long long)p.B * p.Hq, items = heads * p.Tc;  // (of 64 rows)
+    if (n_cu <= 0 || items > (1LL << 30) || p.n_sink > 4 || p.n_local > 4) return 0;
+    const int Tc = p.Tc;
+    auto per_cu = [&](double x) { return items <= (long long)(x * n_cu); };
+    if (d == 64) {
+        if (Tc >= 10 && Tc <= 64 && (per_cu(1) || (p.causal && 16 * heads <= n_cu && per_cu(4)))) return 4;
+        return Tc <= (p.causal ? 32 : 24) || (p.causal && Tc <= 64 && per_cu(6.2)) ? 2 : 0;
+    }
+    const long long summary_wgs = ((long long)p.B * p.Hkv * Tc + 7) / 8;
+    if (Tc >= 10 && Tc <= 64 && (items + summary_wgs <= n_cu || (p.causal && Tc >= 20 && 16 * heads <= n_cu && per_cu(2)))) return 4;
+    if (Tc <= 7) return 2;
+    const int g = p.Hq / p.Hkv, blocks = ceil_div(p.N, 128);
+    const double pp = (double)((g & 1) == 0 ? heads / 2 * blocks : heads * ((blocks + 1) / 2)) / n_cu;  // rounds of the ping-pong kernel
+    if (p.causal) {
+        if ((Tc <= 13 && per_cu(13)) || (Tc <= 16 && per_cu(6.2)) || (Tc <= 24 && per_cu(4.6)) || (Tc <= 64 && per_cu(3.8))) return 2;
+        return (g & 1) && Tc <= 46 && per_cu(11) && !(pp >= 0.85 && pp <= 1) && !(pp > 1.9 && pp <= 2) ? 2 : 0;
+    }
+    return (Tc <= 8 && per_cu(5)) || (Tc <= 16 && per_cu(3.2)) || (Tc <= 24 && per_cu(2)) || (Tc <= 30 && pp > 1 && pp <= 1.32) ? 2 : 0;
+}
+
+// Without a causal mask all items are equally long, and what is left of them after whole rounds of the ping-pong kernel takes as long
+// as a round: the first row of that rest, which then runs on a kernel of finer items (a head's last rows: no more than one item per
+// compute unit, of 64 rows with the keys split four ways, attn_short.hpp, else, where the items are long, of 128 rows, attn_frozen.hpp), or 0.
+// In us, before / after: 16 heads, N = 5000 (one round and 904 rows) 244 / 221; 24 heads, N = 2986 143 / 120; 32 heads, N = 3000
+// (rest on attn_frozen.hpp) 161 / 152; 48 heads, N = 1751 96 / 101 with that, so only above 32 tiles.
+int tail_row(const Params& p, int n_cu, bool head_pairs) {
+    if (p.causal || p.n_sink > 4 || p.n_local > 4 || n_cu <= 0 || p.Tc <= 12) return 0;
+    const long long heads = (long long)p.B * p.Hq, per_band = head_pairs ? heads / 2 : heads;  // items of `band` rows
+    const int band = head_pairs ? 128 : 256;
+    const long long rounds = per_band * ceil_div(p.N, band) / n_cu, bands = rounds * n_cu / per_band, rows = bands * band;
+    if (rounds == 0 || rows >= p.N || 10 * bands * per_band < 9 * rounds * n_cu) return 0;
+    const int rest = p.N - (int)rows;
+    return heads * ceil_div(rest, 64) <= n_cu || (p.Tc > 32 && heads * ceil_div(rest, 128) <= n_cu) ? (int)rows : 0;
+}
+
+// Which kernel Alg. 1's calls that are not short ones run on at d = 128: true = attn_frozen.hpp (items of 128 rows, a third to a half cheaper than the
 // ping-pong kernel's items of 256), false = attn_pingpong.hpp (one and a half times the rate once the compute units are full).
-//   up to one 128-row item per compute unit: the ping-pong kernel would leave half of them idle (us, ping-pong / frozen: 2 heads,
-//     N = 512 22.3 / 17.3; 8 heads, N = 256 18.4 / 14.6; 32 heads, N = 1024 31.7 / 24.6)
+//   up to one 128-row item per compute unit: the ping-pong kernel would leave half of them idle (us, ping-pong / frozen: 32 heads, N =
+//     1024 31.7 / 24.6; most such calls are short ones by now)
 //   two to 2.9 per compute unit, all equally long (no causal mask) and of more than twelve tiles: three rounds of short items
 //     against two of long ones (16 heads, N = 5000 241 / 227).  Where the third round is nearly full or the items are short it is
 //     the other way round (256 heads, N = 300 38.2 / 42.5; 32 heads, N = 3000 155 / 160; 160 heads, N = 512 47 / 49.5).  Between
 //     one and two it is two rounds against one (N = 3072: 89 against 76 us), above three four against two, and under a causal mask
 //     the ping-pong kernel's long items find short ones to pair with
 //   many sink / local blocks: their scores are computed twice in attn_frozen.hpp
-bool prefer_frozen(const Params& p, int n_cu) {
+bool prefer_frozen(const Params& p, int n_cu, bool head_pairs) {
     const long long items = (long long)p.B * p.Hq * p.Tr;
     if (p.n_sink > 4 || p.n_local > 4 || n_cu <= 0) return false;
-    return items <= n_cu || (!p.causal && p.Tc > 12 && items > 2LL * n_cu && 10 * items <= 29LL * n_cu);
+    return items <= n_cu || (!p.causal && p.Tc > 12 && items > 2LL * n_cu && 10 * items <= 29LL * n_cu && !tail_row(p, n_cu, head_pairs));
 }
 
-// The same at d = 64 (`p` in blocks of 128 rows, `block_m` the call's): true = attn_frozen.hpp, false = the generic kernel, which has
-// no max to find in front, fits two items of 128 rows or four of 64 on a compute unit and runs at 80 to 90 % of the rate
-// (us, generic / frozen):
-//   up to one 128-row item per compute unit: more than four tiles (32 heads, N = 128 7.7 / 8.9, N = 448 12.7 / 12.0, N = 777 17.5 /
-//     14.7); in blocks of 64 also fewer, where the generic kernel's items are more than one per compute unit (72 heads, N = 300 13.3 / 11.1)
-//   up to two: more than eight (160 heads, N = 256 12.2 / 14.0)
-//   more: in blocks of 128 more than 24 tiles (256 heads, N = 300 16.9 / 20.6; 128 heads, N = 777 28 / 32; 64 heads, N = 4096 182 / 167),
-//     in blocks of 64 always, under a causal mask from nine tiles on (160 heads, N = 448 17.6 / 22.0; 256 heads, N = 448 no mask 33.5 / 29.3)
-// 676 shapes of each block_m, against the generic kernel alone: 13 and 4 are more than 2 % slower, the largest 32 heads, N = 3000
-// (6 %), in blocks of 64 128 heads, N = 700 (8 %); the mean is 8 and 15 % faster.
-bool prefer_frozen64(const Params& p, int block_m, int n_cu) {
-    if (p.n_sink > 4 || p.n_local > 4) return false;
-    const long long heads = (long long)p.B * p.Hq, items = heads * p.Tr;
-    if (items <= n_cu) return p.Tc > 4 || (block_m == 64 && heads * p.Tc > n_cu);
-    if (items <= 2LL * n_cu) return p.Tc > 8;
-    return block_m == 64 ? !p.causal || p.Tc > 8 : p.Tc > 24;
-}
-
-// Calls with block_m = 64 and without skipping, d = 128 (`p` in blocks of 128 rows): true = items of 64 rows on the generic
+// Calls with block_m = 64 and without skipping, d = 128, that are not short ones (`p` in blocks of 128 rows): true = items of 64 rows on the generic
 // kernel, two to a compute unit, false = blocks of 128 rows.  The short items run at 50 to 80 % of the rate, waste fewer rows and
 // take less to start, which is more for short sequences only (generic / other us):
 //   Alg. 1, one round of at most four tiles (32 heads, N = 64 9.6 / 10.7, N = 256 14.3 / 14.8; N = 300 15.4 / 15.1).  With
@@ -143,7 +192,8 @@ bool prefer_frozen64(const Params& p, int block_m, int n_cu) {
 //     22.1; two rounds, N = 640 46.0 / 47.6 and 64 heads, N = 1024 43 / 36), the baselines, which have no max to find in front, up to
 //     16 and two and a half (128 heads, N = 384 17.1 / 21.8; 96 heads, N = 777 40.9 / 45.4, N = 1024 57.5 / 47.4)
 // 645 shapes of each, against the generic kernel alone: slower by more than 2 % are Alg. 1, causal, 96 heads, N = 640 to 768 (3.5
-// to 6.3 %) and 72 heads, N = 777 (6.7 %), and the baseline, 128 heads, N = 700 (10 %); the mean is 27 and 13 % faster.
+// to 6.3 %) and 72 heads, N = 777 (6.7 %), and the baseline, 128 heads, N = 700 (10 %); the mean is 27 and 13 % faster.  (Alg. 1's of
+// four tiles, and its causal ones, are those with many sink or local blocks: the rest are short ones by now.)
 bool prefer_rows64(const Params& p, int n_cu, bool head_pairs, bool frozen, bool baseline) {
     if (n_cu <= 0) return false;
     const long long heads = (long long)p.B * p.Hq, items = heads * p.Tc, slots = 2LL * n_cu;
@@ -181,17 +231,21 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
     if (MODE != MODE_VSA && !ablation) q.Tr = ceil_div(p.N, 128);
     bool rows64 = false;
     if constexpr (MODE == MODE_VFA) {
-        if (!ablation && d == 64 && prefer_frozen64(q, block_m, cu_count())) {
-            // two groups to an item while there is no more than one item per compute unit and a group has a few tiles
-            // (32 heads, N = 777: 12.4 against 13.6 us; N = 256: 8.4 against 8.0; N = 4096: 95 against 87)
-            if ((long long)q.B * q.Hq * q.Tr <= cu_count() && q.Tc >= 6) return launch_frozen<64, 2>(q, block_m, s);
-            return launch_frozen<64, 1>(q, block_m, s);
+        if (!ablation && d == 64 && p.n_sink <= 4 && p.n_local <= 4) {
+            // two groups to an item while there is no more than one item per compute unit (32 heads, N = 777: 12.4 against 13.6 us;
+            // N = 4096: 95 against 87)
+            if ((long long)q.B * q.Hq * q.Tr <= cu_count()) return launch_frozen<64, 2>(q, 0, block_m, s);
+            return launch_frozen<64, 1>(q, 0, block_m, s);
         }
         if (!ablation && d == 128) {
-            const bool frozen = prefer_frozen(q, cu_count());
+            const bool frozen = prefer_frozen(q, cu_count(), head_pairs);
             rows64 = block_m == 64 && prefer_rows64(q, cu_count(), head_pairs, frozen, false);
-            if (frozen && !rows64) return launch_frozen<128, 2>(q, block_m, s);
+            if (frozen && !rows64) return launch_frozen<128, 2>(q, 0, block_m, s);
         }
+    }
+    int tail = 0;  // rows [0, tail) run on the ping-pong kernel, those behind them on another one
+    if constexpr (MODE == MODE_VFA) {
+        if (!ablation && d == 128 && !rows64) tail = tail_row(q, cu_count(), head_pairs);
     }
     if constexpr (is_fa(MODE)) {
         rows64 = d == 128 && block_m == 64 && prefer_rows64(q, cu_count(), head_pairs, false, true);
@@ -199,6 +253,7 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
     if (d == 128 && (block_m == 128 || MODE != MODE_VSA) && !ablation && !rows64 &&
         (MODE != MODE_VSA || (p.N > (p.causal ? VSA_GENERIC_MAX_N : VSA_GENERIC_MAX_N / 2) && (head_pairs || (p.causal && p.n_local <= 1))))) {
         q.pair_blocks = head_pairs ? 0 : 1;
+        if (tail) q.Tr = tail / 128;
         unsigned n_wg = (unsigned)(head_pairs ? q.B * (q.Hq / 2) * q.Tr : q.B * q.Hq * ((q.Tr + 1) / 2));
         // One workgroup fills a CU (128 KiB of LDS), so with more work items than CUs the kernel runs one
         // persistent workgroup per CU over a static share of the items: the next item starts without a
@@ -213,7 +268,12 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
         } else {
             if (block_m == 64 && p.causal) attn_fwd_pp_kernel<MODE, true><<<dim3(n_wg), 512, pp_lds_bytes<true>(), s>>>(q);
             else attn_fwd_pp_kernel<MODE, false><<<dim3(n_wg), 512, pp_lds_bytes<false>(), s>>>(q);
-            return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
+            if (hipGetLastError() != hipSuccess) return VFA_ERR_HIP;
+            if constexpr (MODE == MODE_VFA) {
+                if (tail && (long long)p.B * p.Hq * ceil_div(p.N - tail, 64) <= n_cu) return launch_short<128, 4>(p, tail, false, s);
+                if (tail) return launch_frozen<128, 2>(p, tail, block_m, s);
+            }
+            return VFA_OK;
         }
     }
     const dim3 grid((unsigned)(p.B * p.Hq * p.Tr));
@@ -288,6 +348,26 @@ int vfa_vsa_common(int mode, const void* Q, const void* K, const void* V, void* 
         if ((long long)B * (q_repr_mode ? Hq : Hkv) > 65535) return VFA_ERR_UNSUPPORTED;
     }
     hipStream_t s = (hipStream_t)stream;
+    const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)d);
+    Params p{};
+    p.Q = (const uint16_t*)Q; p.K = (const uint16_t*)K; p.V = (const uint16_t*)V;
+    p.Krepr = (const uint16_t*)workspace; p.O = (uint16_t*)O; p.LSE = LSE; p.mask = skip_mask;
+    p.B = B; p.Hq = Hq; p.Hkv = Hkv; p.N = N; p.Tr = ceil_div(N, block_m); p.Tc = ceil_div(N, block_n);
+    p.causal = causal ? 1 : 0; p.n_sink = n_sink; p.n_local = n_local; p.use_minit = use_minit ? 1 : 0;
+    p.order_asc = reorder ? 0 : 1; p.all_special = freeze ? 0 : 1;
+    p.rowskip = rowskip ? 1 : 0; p.tau2 = lazy_tau >= 0.f ? lazy_tau : -1.f;
+    p.c = scale * kLog2e;
+    p.thr2 = thr_nats * kLog2e;
+    if (mode == MODE_VFA && reorder && freeze && !q_repr_mode && (use_minit != 1 || repr_mode == 0)) {
+        const int groups = short_groups(p, d, cu_count());
+        if (groups) {
+            (void)hipGetLastError();
+            if (!raise_lds_limits()) return VFA_ERR_HIP;
+            const bool sums = use_minit == 1;
+            if (d == 64) return groups == 4 ? launch_short<64, 4>(p, 0, sums, s) : launch_short<64, 2>(p, 0, sums, s);
+            return groups == 4 ? launch_short<128, 4>(p, 0, sums, s) : launch_short<128, 2>(p, 0, sums, s);
+        }
+    }
     void* qrepr = nullptr;
     if (use_minit == 1) {
         rc = summary_launch(K, workspace, B, Hkv, N, d, block_n, repr_mode, s);
@@ -299,17 +379,7 @@ int vfa_vsa_common(int mode, const void* Q, const void* K, const void* V, void* 
             if (rc != VFA_OK) return rc;
         }
     }
-    Params p{};
-    p.Q = (const uint16_t*)Q; p.K = (const uint16_t*)K; p.V = (const uint16_t*)V;
-    p.Krepr = (const uint16_t*)workspace; p.O = (uint16_t*)O; p.LSE = LSE; p.mask = skip_mask;
     p.Qrepr = (const uint16_t*)qrepr;
-    p.B = B; p.Hq = Hq; p.Hkv = Hkv; p.N = N; p.Tr = ceil_div(N, block_m); p.Tc = ceil_div(N, block_n);
-    p.causal = causal ? 1 : 0; p.n_sink = n_sink; p.n_local = n_local; p.use_minit = use_minit ? 1 : 0;
-    p.order_asc = reorder ? 0 : 1; p.all_special = freeze ? 0 : 1;
-    p.rowskip = rowskip ? 1 : 0; p.tau2 = lazy_tau >= 0.f ? lazy_tau : -1.f;
-    const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)d);
-    p.c = scale * kLog2e;
-    p.thr2 = thr_nats * kLog2e;
     return mode == MODE_VSA ? launch_fwd<MODE_VSA>(p, d, block_m, s) : launch_fwd<MODE_VFA>(p, d, block_m, s);
 }
 
