@@ -64,32 +64,51 @@ __device__ __forceinline__ void lds_dma(uint64_t base, uint32_t off, uint32_t ld
                      : "memory");
 }
 
-// K tile (IS_V = false: rows of 128 bytes from a row-major [*, 128] array, rows clamped to row_limit - 1)
-// or V^T tile (IS_V = true: a contiguous 8 KiB block) -> LDS, 8 one-KiB pieces shared by NWAVES waves.
+// 64 rows of 128 bytes from a row-major [*, 128] array, rows clamped to row_limit - 1 -> LDS, 8 one-KiB pieces shared by 4 waves.
 // base is the same for all lanes of the wave.
-template <bool IS_V, int NWAVES>
-__device__ __forceinline__ void load_tile8(const uint8_t* base, int first_row, int row_limit, uint8_t* dst, int wave,
-                                           int lane) {
-    constexpr int NI = 8 / NWAVES;
+__device__ __forceinline__ void load_tile8(const uint8_t* base, int first_row, int row_limit, uint8_t* dst, int wave, int lane) {
     const uint64_t sb = uniform_ptr(base);
 #pragma unroll
-    for (int u = 0; u < NI; ++u) {
-        const int q = u * NWAVES + wave;
-        int r, c;
-        uint32_t off;
-        if (IS_V) {
-            r = 16 * q + (lane >> 2);
-            c = (lane & 3) ^ ((r >> 2) & 3);
-            off = (uint32_t)(r * 64 + c * 16);
-        } else {
-            r = 8 * q + (lane >> 3);
-            c = (lane & 7) ^ ((r >> 1) & 7);
-            off = (uint32_t)min(first_row + r, row_limit - 1) * 128u + (uint32_t)(c * 16);
-        }
+    for (int u = 0; u < 2; ++u) {
+        const int q = u * 4 + wave;
+        const int r = 8 * q + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
         const uint32_t lds_addr = __builtin_amdgcn_readfirstlane(
             (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)(dst + q * 1024));
-        lds_dma<16>(sb, off, lds_addr);
+        lds_dma<16>(sb, (uint32_t)min(first_row + r, row_limit - 1) * 128u + (uint32_t)(c * 16), lds_addr);
     }
+}
+
+// A tile by buffer loads into LDS: the buffer is the tile (`bytes` of it: what lies past the end of the sequence is out of its range
+// and LDS gets zeros), the lanes' offsets are fixed for the whole kernel, and the instruction offset moves both sides, so a request costs
+// a few scalar instructions (lane by lane it was 30 of the 110 to 130 vector instructions of a tile).  Two adjacent pieces of 1 KiB; one; 64 dwords.
+__device__ __forceinline__ u32x4 tile_buffer(uint64_t base, uint32_t bytes) {
+    return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)base), (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)),
+                 (uint32_t)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u};
+}
+__device__ __forceinline__ void request2(uint64_t base, uint32_t bytes, uint32_t o0, uint32_t o1, uint32_t lds) {
+    uint32_t m0_save;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %4, 0 offen lds\n\t"
+                 "buffer_load_dwordx4 %3, %4, 0 offen offset:1024 lds\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0_save)
+                 : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(o0), "v"(o1), "s"(tile_buffer(base, bytes))
+                 : "memory");
+}
+__device__ __forceinline__ void request1(uint64_t base, uint32_t bytes, uint32_t o0, uint32_t lds) {
+    uint32_t m0_save;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0_save)
+                 : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(o0), "s"(tile_buffer(base, bytes))
+                 : "memory");
+}
+__device__ __forceinline__ void request_dwords(uint64_t base, uint32_t bytes, uint32_t o0, uint32_t lds) {
+    uint32_t m0_save;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dword %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0_save)
+                 : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(o0), "s"(tile_buffer(base, bytes))
+                 : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const uint8_t* p) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t*)p;
 }
 
 __device__ __forceinline__ i32x8 lds_frag8(const uint8_t* a0, const uint8_t* a1) {
@@ -97,26 +116,8 @@ __device__ __forceinline__ i32x8 lds_frag8(const uint8_t* a0, const uint8_t* a1)
     return i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
 }
 
-// S^T tile from an E4M3 K tile: st[t][i] as in qk_tile: products of the codes' values times the power of
-// two in scale_a, plus *start (a value per lane, i.e. per query, already spread over 16 registers) if given
-// (NARROW: two fragments in flight instead of four, for a kernel that is short of registers)
-template <bool NARROW = false>
-__device__ __forceinline__ void qk_tile8(const uint8_t* kt, const i32x8* qf, f32x16* st, int ql, int hh,
-                                         int scale_a = 0x7f7f7f7f, const f32x16* start = nullptr) {
-    if (NARROW) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            i32x8 g[2];
-#pragma unroll
-            for (int kh = 0; kh < 2; ++kh) {
-                const int row = 32 * t + ql, c0 = 4 * kh + 2 * hh;
-                g[kh] = lds_frag8(kt + Tile8::k_off(row, c0), kt + Tile8::k_off(row, c0 + 1));
-            }
-            st[t] = mfma_f8(g[0], qf[0], start ? *start : f32x16{0}, scale_a);
-            st[t] = mfma_f8(g[1], qf[1], st[t], scale_a);
-        }
-        return;
-    }
+// S^T tile from an E4M3 K tile: st[t][i] as in qk_tile: products of the codes' values times the power of two in scale_a
+__device__ __forceinline__ void qk_tile8(const uint8_t* kt, const i32x8* qf, f32x16* st, int ql, int hh, int scale_a) {
     i32x8 f[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {  // e = 2 t + kh
@@ -124,42 +125,7 @@ __device__ __forceinline__ void qk_tile8(const uint8_t* kt, const i32x8* qf, f32
         f[e] = lds_frag8(kt + Tile8::k_off(row, c0), kt + Tile8::k_off(row, c0 + 1));
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        st[e >> 1] = mfma_f8(f[e], qf[e & 1], (e & 1) ? st[e >> 1] : (start ? *start : f32x16{0}), scale_a);
-}
-
-// P_BF8: the P operand holds E5M2 codes (V stays E4M3)
-template <bool P_BF8 = false, bool NARROW = false>
-__device__ __forceinline__ void pv_tile8(const uint8_t* vt, const uint32_t* pk, f32x16* ot, int lane, int hh) {
-    const i32x8 pf = {(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3], (int)pk[4], (int)pk[5], (int)pk[6], (int)pk[7]};
-    if (NARROW) {  // two fragments in flight instead of four
-#pragma unroll
-        for (int d2 = 0; d2 < 2; ++d2) {
-            i32x8 g[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int row = 32 * (2 * d2 + u) + (lane & 31);
-                g[u] = lds_frag8(vt + Tile8::v_off(row, 2 * hh), vt + Tile8::v_off(row, 2 * hh + 1));
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int db = 2 * d2 + u;
-                ot[db] = P_BF8 ? __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(g[u], pf, ot[db], 0, 1, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f)
-                               : mfma_f8(g[u], pf, ot[db]);
-            }
-        }
-        return;
-    }
-    i32x8 f[4];
-#pragma unroll
-    for (int db = 0; db < 4; ++db) {
-        const int row = 32 * db + (lane & 31);
-        f[db] = lds_frag8(vt + Tile8::v_off(row, 2 * hh), vt + Tile8::v_off(row, 2 * hh + 1));
-    }
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-        ot[db] = P_BF8 ? __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f[db], pf, ot[db], 0, 1, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f)
-                       : mfma_f8(f[db], pf, ot[db]);
+    for (int e = 0; e < 4; ++e) st[e >> 1] = mfma_f8(f[e], qf[e & 1], (e & 1) ? st[e >> 1] : f32x16{0}, scale_a);
 }
 
 // four values in [0, 1] -> one dword of 8-bit codes: E4M3 of q * 2^8, or (P_BF8) E5M2 of q * 2^15, which trades one
@@ -249,10 +215,9 @@ __device__ __forceinline__ void softmax_tile8_folded(f32x16* st, uint32_t* pk, f
 // logarithm: an E5M2 code c = 4 E + m stands for 2^(E - 15) (1 + m / 4), the chord approximation of
 // 2^(c / 4 - 15), never more than 6.15 % above it.  So when a score arrives as x = s - m - H in log2 units, the
 // code of exp2(x) 2^15 is, up to that chord error and the rounding to a quarter of a binade, just
-// round(4 x + 120): a multiply-add and a float-to-byte conversion.  The multiply (4 = 2^2) goes into the MFMA's
-// block scale and the add into its accumulator start (the frozen max is known before the tile), so a frozen
-// tile's scores leave the matrix unit AS CODES: what is left per score is a clamp to the largest finite code and
-// v_cvt_pk_u8_f32 (round to nearest even, saturating at 0: measured).  The offset is lowered by
+// round(4 x + 120): a multiply-add and a float-to-byte conversion.  The multiply goes into the MFMA's block scale, so a tile's
+// scores leave the matrix unit in units of codes; what is left per score is the add, half a conversion, half a clamp
+// and a quarter of a byte permute (see codes_tile8).  The offset is lowered by
 // 4 log2(1.0303) = 0.1723 to centre the chord error: weight / exact weight lies in [0.89, 1.12] (the format's
 // own rounding would give +-12.5 %).  E5M2 rather than E4M3 because the window has to hold, below the frozen max,
 // the headroom, the overshoot of the seed and the spread of the row, and E4M3's subnormal codes, which the
@@ -260,23 +225,35 @@ __device__ __forceinline__ void softmax_tile8_folded(f32x16* st, uint32_t* pk, f
 // the same rounded weights through one more MFMA (a block of ones times P), so O = sum(w v) / sum(w) is a properly
 // normalised average under weights that are each within 12 % of the exact ones; LSE inherits that error.
 constexpr float kCodeOffset = 119.8277f;  // 4 * (15 + 15) - 0.1723
-constexpr float kMaxCode = 123.f;          // 0x7B = 57344, the largest finite E5M2 value
 constexpr float kCodesPerBinade = 4.f;
 
+// The scores arrive as 256ths of a code (kCodeUnit).  v_cvt_pknorm_u16_f32 rounds two of them to whole 65536ths, clamped to [0, 1]; the
+// code is the upper byte (the half added to the offset makes that a rounding), and one v_perm_b32 collects four: 72 instructions a
+// tile, where a clamp and v_cvt_pk_u8_f32 for every score took 96 (4 x 32 heads, 3000 tokens, 8-bit 175 / 169 us, 4-bit 155 / 150).
+constexpr float kCodeUnit = 0x1p-8f;
+constexpr uint32_t kMaxCode2 = 0x7bff7bffu;  // 0x7B = 57344, the largest finite E5M2 value, in the upper bytes of both halves
+typedef __attribute__((ext_vector_type(2))) unsigned short u16x2_t;
 template <bool MASKED>
-__device__ __forceinline__ void codes_tile8(f32x16* st, uint32_t* pk, int key0, int limit, int hh, float add = 0.f) {
+__device__ __forceinline__ void codes_tile8(f32x16* st, uint32_t* pk, int key0, int limit, int hh, float add) {
+    const int rel = limit - key0 - 4 * hh;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int r = 0; r < 16; r += 4) {
-            uint32_t w = 0;
+            uint32_t w[2];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float c = __builtin_amdgcn_fmed3f(st[t][r + e] + add, 0.f, kMaxCode);  // (fminf would first quiet a NaN)
-                if (MASKED) c = (32 * t + 8 * ((r + e) >> 2) + ((r + e) & 3) <= limit - key0 - 4 * hh) ? c : 0.f;
-                w = __builtin_amdgcn_cvt_pk_u8_f32(c, e, w);
+            for (int e = 0; e < 2; ++e) {
+                float c[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int i = r + 2 * e + u;
+                    c[u] = st[t][i] + add;
+                    if (MASKED) c[u] = 32 * t + 8 * (i >> 2) + (i & 3) <= rel ? c[u] : 0.f;
+                }
+                const auto q = __builtin_amdgcn_cvt_pknorm_u16(c[0], c[1]);
+                w[e] = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, q), __builtin_bit_cast(u16x2_t, kMaxCode2)));
             }
-            pk[4 * t + (r >> 2)] = w;
+            pk[4 * t + (r >> 2)] = __builtin_amdgcn_perm(w[1], w[0], 0x07050301u);
         }
 }
 
@@ -338,8 +315,13 @@ __device__ __forceinline__ MaxTiles max_tiles(int use_minit, int n_sink, int n_l
     return m;
 }
 
-// One workgroup = 4 waves x 32 query rows = one 128-row query block of one head; two-deep K / V^T ring
-// (32 KiB) and two tiles more for the max phase, three workgroups per CU.  MODE_FA or MODE_VFA.
+// One workgroup = 4 waves x 32 query rows = one 128-row query block of one head; three-deep K / V^T ring (48 KiB, the max phase in its
+// second and third stage), filled two tiles ahead, three workgroups per CU.  MODE_FA or MODE_VFA.
+// What bounds it: on long sequences the matrix unit at the clock the power budget leaves (16384 tokens, 2 x 32 heads: 760 cycles a wave
+// and tile at 1.7 GHz, 512 of them MFMA; the vector unit needs 490 for 32 exponentials, 32 adds and 16 conversions, the latter as slow
+// as an exponential); on short ones the start of an item (a tile's latencies, 3 to 4 us of them the max phase) too.  Attention
+// alone in us, before / after the deeper ring, the buffer loads and fragment addresses that stay in registers (no other vector
+// instruction left in a tile): folded, 32 heads, 8192 tokens 266 / 252, 4 x 3000 178 / 169, 777 14.9 / 13.8, 2 x 16384 1987 / 1879.
 // FOLD (Alg. 1 only, when the factor between code products and log2-domain scores is a power of two): the
 // K operand's block scale applies it inside every Q.K^T MFMA, and on frozen tiles the accumulators start at
 // -(m + H), so the scores come out of the matrix unit ready for exp2.
@@ -349,10 +331,8 @@ __global__ __launch_bounds__(256, FOLD ? 3 : 2) void attn_fp8_kernel(const Fp8Pa
     static_assert(!NOEXP || FOLD, "codes straight from the matrix unit need the scale and the max folded into it");
     const int sa = FOLD ? p.scale_a : 0x7f7f7f7f;
     constexpr int D = 128, BM = 128, DB = 4;
-    constexpr int RING = 2 * (Tile8::KBYTES + Tile8::VBYTES);
-    __shared__ __attribute__((aligned(16))) uint8_t smem[RING + (MODE == MODE_VFA ? 2 * Tile8::KBYTES : 0)];
-    uint8_t* const Ks = smem;
-    uint8_t* const Vs = smem + 2 * Tile8::KBYTES;
+    constexpr int S = 3, STAGE = Tile8::KBYTES + Tile8::VBYTES;  // stages of a K and a V^T tile
+    __shared__ __attribute__((aligned(16))) uint8_t smem[S * STAGE];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ql = lane & 31, hh = lane >> 5;
@@ -393,25 +373,26 @@ __global__ __launch_bounds__(256, FOLD ? 3 : 2) void attn_fp8_kernel(const Fp8Pa
         }
     }
     const int nv = j_hi + 1;
-    auto load_kv = [&](int j, int buf) __attribute__((always_inline)) {
-        load_tile8<false, 4>(Kg, j * BN, N, Ks + buf * Tile8::KBYTES, wave, lane);
-        load_tile8<true, 4>(Vg + (size_t)j * Tile8::VBYTES, 0, 0, Vs + buf * Tile8::VBYTES, wave, lane);
+    const uint32_t off_k = (uint32_t)((16 * wave + (lane >> 3)) * 128 + (((lane & 7) ^ (lane >> 4)) << 4)), off_k1 = off_k ^ 64;
+    const uint32_t off_v = (uint32_t)((32 * wave + (lane >> 2)) * 64 + (((lane & 3) ^ ((lane >> 4) & 3)) << 4));
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem)) + 2048 * wave;
+    auto load_kv = [&](int j, uint32_t stage) __attribute__((always_inline)) {  // (stage: its byte offset; past the last tile nothing is read)
+        request2((uint64_t)(uintptr_t)Kg + (uint32_t)j * 8192ull, (uint32_t)(j < nv ? min(N - j * BN, BN) : 0) * 128u, off_k, off_k1, lds0 + stage);
+        request2((uint64_t)(uintptr_t)Vg + (uint32_t)j * 8192ull, j < nv ? 8192u : 0u, off_v, off_v, lds0 + stage + Tile8::KBYTES);
     };
     float m2 = -INFINITY;
     if (MODE == MODE_VFA) {
-        // four tiles at a time, staged in the second half of the ring and behind it; the main loop's first tiles follow the first four
+        // four tiles at a time, staged in the ring behind its first stage, which takes the main loop's first tiles
         const uint8_t* Rg = p.Krepr + ((size_t)(b * p.Hkv + hkv) * p.Tc) * D;
         const MaxTiles mt = max_tiles(p.use_minit, p.n_sink, p.n_local, a_lo, a_hi, nv);
-        auto stage = [&](int u) __attribute__((always_inline)) {
-            return u < 2 ? smem + RING + u * Tile8::KBYTES : (u == 2 ? Ks + Tile8::KBYTES : Vs + Tile8::VBYTES);
-        };
+        auto stage = [&](int u) __attribute__((always_inline)) { return smem + STAGE + u * Tile8::KBYTES; };
         float mx = -INFINITY;
         for (int t0 = 0; t0 < mt.total; t0 += 4) {
             if (t0) __syncthreads();
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int t = t0 + u;  // (summaries: rows clamped to the visible blocks; a repeated row changes no max)
-                if (t < mt.total) load_tile8<false, 4>(t < mt.n_sum ? Rg : Kg, (t < mt.n_sum ? t : mt.block(t)) * BN, t < mt.n_sum ? nv : N, stage(u), wave, lane);
+                if (t < mt.total) load_tile8(t < mt.n_sum ? Rg : Kg, (t < mt.n_sum ? t : mt.block(t)) * BN, t < mt.n_sum ? nv : N, stage(u), wave, lane);
             }
             if (t0 == 0) {
                 load_kv(0, 0);
@@ -443,47 +424,77 @@ __global__ __launch_bounds__(256, FOLD ? 3 : 2) void attn_fp8_kernel(const Fp8Pa
     f32x16 lt = {0};  // NOEXP: 32 copies of this lane's row sum of the rounded weights (times 2^15)
     if (FOLD) {
         const float v = -(m2 + p.headroom);
-        if (NOEXP) code0 = kCodeOffset + kCodesPerBinade * v;
+        if (NOEXP) code0 = kCodeUnit * (kCodeOffset + 0.5f + kCodesPerBinade * v);
 #pragma unroll
         for (int r = 0; r < 16; ++r) start[r] = v;
     }
+    load_kv(1, STAGE);
+    // fragment addresses in a stage: all others follow by constant offsets, which go into the instructions (the loop is unrolled by
+    // the stages)
+    uint32_t ka[4], va[2];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ka[e] = lds_address(smem) + Tile8::k_off(ql, 4 * (e >> 1) + 2 * hh + (e & 1));
+#pragma unroll
+    for (int e = 0; e < 2; ++e) va[e] = lds_address(smem) + Tile8::KBYTES + Tile8::v_off(ql, 2 * hh + e);
+    typedef const __attribute__((address_space(3))) u32x4* lds_ptr;
+    auto frag = [&](uint32_t a0, uint32_t a1, uint32_t off) __attribute__((always_inline)) {
+        const u32x4 lo = *(lds_ptr)(a0 + off), hi = *(lds_ptr)(a1 + off);
+        return i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+    };
     // One tile; MASKED is compile-time so that each of the two loops below has one softmax body (the baseline's takes the exact
     // max, Alg. 1's is a frozen one).
-    auto visit = [&](int j, auto masked_c) __attribute__((always_inline)) {
+    auto visit = [&](int j, uint32_t stage, uint32_t next2, auto masked_c) __attribute__((always_inline)) {
         constexpr bool SPECIAL = is_fa(MODE), MASKED = decltype(masked_c)::value;
-        const int buf = j & 1;
-        if (j + 1 < nv) load_kv(j + 1, buf ^ 1);
         f32x16 st[2];
         uint32_t pk[8];
         __builtin_amdgcn_s_setprio(1);
-        if (NOEXP) qk_tile8<true>(Ks + buf * Tile8::KBYTES, qf, st, ql, hh, sa);
-        else if (FOLD) qk_tile8(Ks + buf * Tile8::KBYTES, qf, st, ql, hh, sa, &start);
-        else qk_tile8(Ks + buf * Tile8::KBYTES, qf, st, ql, hh, sa);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const i32x8 g0 = frag(ka[0], ka[1], stage + t * 4096), g1 = frag(ka[2], ka[3], stage + t * 4096);
+            st[t] = mfma_f8(g0, qf[0], FOLD && !NOEXP ? start : f32x16{0}, sa);
+            st[t] = mfma_f8(g1, qf[1], st[t], sa);
+        }
         __builtin_amdgcn_s_setprio(0);
+        load_kv(j + 2, next2);
         const bool needs_mask = (p.causal && j * BN + BN - 1 > row0) || (j + 1) * BN > N;
         if (NOEXP) codes_tile8<MASKED>(st, pk, j * BN, needs_mask ? limit : 0x3fffffff, hh, code0);
         else if (FOLD) softmax_tile8_folded<MASKED>(st, pk, lsum, j * BN, needs_mask ? limit : 0x3fffffff, hh);
         else softmax_tile8<SPECIAL, MASKED>(st, pk, ot, m2, lsum, p.c, p.headroom, j * BN, needs_mask ? limit : 0x3fffffff, hh);
+        const i32x8 pf = {(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3], (int)pk[4], (int)pk[5], (int)pk[6], (int)pk[7]};
         __builtin_amdgcn_s_setprio(1);
-        pv_tile8<NOEXP, NOEXP>(Vs + buf * Tile8::VBYTES, pk, ot, lane, hh);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            const i32x8 g = frag(va[0], va[1], stage + db * 2048);
+            ot[db] = NOEXP ? __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(g, pf, ot[db], 0, 1, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f) : mfma_f8(g, pf, ot[db]);
+        }
         if (NOEXP) {
             // row sums of the rounded weights: a block of ones times P (E5M2).  The ones are E2M1 (1.0 = code 2): a
             // 4-bit operand takes four registers instead of eight, and with all elements equal the different order of
             // the k index in 4-bit and 8-bit operands does not matter
             const i32x8 ones = {0x22222222, 0x22222222, 0x22222222, 0x22222222, 0, 0, 0, 0};
-            const i32x8 pf = {(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3], (int)pk[4], (int)pk[5], (int)pk[6], (int)pk[7]};
             lt = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ones, pf, lt, 4, 1, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
         }
         __builtin_amdgcn_s_setprio(0);
-        wait_vm0_and_sync();
+        __builtin_amdgcn_s_waitcnt(0x0F74);  // vmcnt(4): tile j + 1 has landed
+        __syncthreads();
     };
     using std::false_type;
     using std::true_type;
     int j_masked = p.causal ? a_lo : p.Tc;  // first tile that needs masking
     if (N % BN) j_masked = min(j_masked, p.Tc - 1);
     int j = 0;
-    for (; j < min(j_masked, nv); ++j) visit(j, false_type{});
-    for (; j < nv; ++j) visit(j, true_type{});
+    for (; j + S <= min(j_masked, nv); j += S) {
+        visit(j, 0, 2 * STAGE, false_type{});
+        visit(j + 1, STAGE, 0, false_type{});
+        visit(j + 2, 2 * STAGE, STAGE, false_type{});
+    }
+#pragma unroll 1
+    for (uint32_t stage = 0; j < nv; ++j) {
+        const uint32_t next = stage == 2 * STAGE ? 0 : stage + STAGE;
+        visit(j, stage, next == 2 * STAGE ? 0 : next + STAGE, true_type{});
+        stage = next;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // (requests past the last tile write zeros to LDS: not behind this workgroup's end)
     // O = descale_v * 2^-8 * O^T / l (the codes of P carry 2^8); LSE = (m2 + H + log2 l) ln 2  (l sums exp2(s c - m2 - H))
     // (NOEXP: every register of lt holds the whole row sum, with the same 2^15 as the numerator)
     const float l = NOEXP ? lt[0] * 0x1p-15f : xhalf_sum(lsum);

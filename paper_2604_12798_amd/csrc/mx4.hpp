@@ -171,9 +171,9 @@ __device__ __forceinline__ void load_tile4(const uint8_t* base, int first_row, i
 }
 
 // S^T tile from an MXFP4 K tile and its scales: st[t][i] as in qk_tile, in units of the dequantised products
-// (the block scales are applied inside the instruction), plus *start if given
+// (the block scales are applied inside the instruction)
 __device__ __forceinline__ void qk_tile4(const uint8_t* kt, const uint32_t* ksc, const u32x4* qf, const int* qs, f32x16* st,
-                                         int ql, int hh, const f32x16* start = nullptr) {
+                                         int ql, int hh) {
     u32x4 f[4];
     uint32_t sc[2];
 #pragma unroll
@@ -183,8 +183,7 @@ __device__ __forceinline__ void qk_tile4(const uint8_t* kt, const uint32_t* ksc,
         f[e] = *reinterpret_cast<const u32x4*>(kt + Tile4::k_off(32 * (e >> 1) + ql, 2 * (e & 1) + hh));
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-        st[e >> 1] = mfma_f4(f[e], qf[e & 1], (e & 1) ? st[e >> 1] : (start ? *start : f32x16{0}),
-                             spread_byte(sc[e >> 1], 2 * (e & 1) + hh), qs[e & 1]);
+        st[e >> 1] = mfma_f4(f[e], qf[e & 1], (e & 1) ? st[e >> 1] : f32x16{0}, spread_byte(sc[e >> 1], 2 * (e & 1) + hh), qs[e & 1]);
 }
 
 struct Mx4Params {
@@ -208,7 +207,9 @@ struct Mx4Params {
 // i.e. the caller folded that factor into Q before quantising): frozen tiles start their accumulators at
 // -(m + H) and go to exp2 untouched.
 // NOEXP (with FOLD): the weights' E5M2 codes are taken from the scores as in attn_fp8_kernel's form without
-// exponentials; the factor 4 of the code scale is added to the queries' block-scale bytes (two binades).
+// exponentials; the code scale, 4 / 256, is taken off the queries' block-scale bytes (six binades).
+// The loop is that of attn_fp8_kernel.  Attention alone in us, before / after it (and, without exponentials, codes by
+// v_cvt_pknorm_u16_f32): 4 x 32 heads, 3000 tokens, without exponentials 155 / 143, folded 164 / 156; 8192 tokens 231 / 214, 242 / 232.
 template <int MODE, bool FOLD, bool NOEXP = false>
 __global__ __launch_bounds__(256, 3) void attn_mx4_kernel(const Mx4Params p) {
     static_assert(!FOLD || MODE == MODE_VFA, "folding needs a max that is known before the tile");
@@ -217,14 +218,12 @@ __global__ __launch_bounds__(256, 3) void attn_mx4_kernel(const Mx4Params p) {
     // Alg. 1 keeps exp(S - m) in E5M2: the summaries of MXFP4 keys collect the upward rounding errors of 64 keys per
     // feature, so the seeded max can sit ten binades above the scores, more than E4M3 has to spare
     constexpr bool P_BF8 = MODE == MODE_VFA;
-    // two K stages of 4 KiB, two V^T stages of 8 KiB; Alg. 1: three tiles of 8 KiB more for the max phase (with the second V^T
-    // stage four slots, each large enough for a tile of summaries)
-    constexpr int RING = 2 * Tile4::KBYTES + 2 * Tile8::VBYTES;
-    __shared__ __attribute__((aligned(16))) uint8_t smem[RING + (MODE == MODE_VFA ? 3 * Tile8::KBYTES : 0)];
-    __shared__ uint32_t kscale[2][BN];
+    // three stages of a K tile of 4 KiB and a V^T tile of 8 KiB; Alg. 1: one tile of 8 KiB more for the max phase (with the second and
+    // third stage four slots, each large enough for a tile of summaries)
+    constexpr int S = 3, STAGE = Tile4::KBYTES + Tile8::VBYTES;
+    __shared__ __attribute__((aligned(16))) uint8_t smem[S * STAGE + (MODE == MODE_VFA ? Tile8::KBYTES : 0)];
+    __shared__ uint32_t kscale[4][S][BN];  // (a copy for each wave: every wave then waits for the same number of requests)
     __shared__ uint32_t mscale[MODE == MODE_VFA ? 4 : 1][BN];
-    uint8_t* const Ksm = smem;
-    uint8_t* const Vsm = smem + 2 * Tile4::KBYTES;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ql = lane & 31, hh = lane >> 5;
@@ -264,14 +263,21 @@ __global__ __launch_bounds__(256, 3) void attn_mx4_kernel(const Mx4Params p) {
 #pragma unroll
         for (int kh = 0; kh < 2; ++kh) {
             qf[kh] = *reinterpret_cast<const u32x4*>(p.Q + qr * 64 + 32 * kh + 16 * hh);
-            qs[kh] = spread_byte(sw, 2 * kh + hh) + (NOEXP ? 0x02020202 : 0);  // (scale bytes of real data are far from 253)
+            qs[kh] = spread_byte(sw, 2 * kh + hh);
+            // (a scale below 2^-121 counts as that: its elements' share of a score is nothing either way)
+            if (NOEXP) qs[kh] = max(qs[kh] & 0xff, 6) * 0x01010101 - 0x06060606;
         }
     }
     const int nv = j_hi + 1;
-    auto load_kv = [&](int j, int buf) __attribute__((always_inline)) {
-        load_tile4(Kg, j * BN, N, Ksm + buf * Tile4::KBYTES, wave, lane);
-        load_tile8<true, 4>(Vg + (size_t)j * Tile8::VBYTES, 0, 0, Vsm + buf * Tile8::VBYTES, wave, lane);
-        if (wave == 0) load_scales64(Ksg, j * BN, N, kscale[buf], lane);
+    const uint32_t off_k = (uint32_t)((16 * wave + (lane >> 2)) * 64 + (((lane & 3) ^ ((lane >> 4) & 3)) << 4));
+    const uint32_t off_v = (uint32_t)((32 * wave + (lane >> 2)) * 64 + (((lane & 3) ^ ((lane >> 4) & 3)) << 4));
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem)), lds_k = lds0 + 1024 * wave, lds_v = lds0 + Tile4::KBYTES + 2048 * wave;
+    const uint32_t lds_s = __builtin_amdgcn_readfirstlane(lds_address(reinterpret_cast<const uint8_t*>(kscale[wave])));
+    auto load_kv = [&](int j, uint32_t stage, uint32_t st) __attribute__((always_inline)) {  // (stage = its byte offset, st = its number; past the last tile nothing is read)
+        const uint32_t rows = (uint32_t)(j < nv ? min(N - j * BN, BN) : 0);
+        request1((uint64_t)(uintptr_t)Kg + (uint32_t)j * 4096ull, rows * 64u, off_k, lds_k + stage);
+        request2((uint64_t)(uintptr_t)Vg + (uint32_t)j * 8192ull, j < nv ? 8192u : 0u, off_v, off_v, lds_v + stage);
+        request_dwords((uint64_t)(uintptr_t)Ksg + (uint32_t)j * 256ull, rows * 4u, lane * 4u, lds_s + st * 256u);
     };
     float m2 = -INFINITY;
     if (MODE == MODE_VFA) {
@@ -279,7 +285,7 @@ __global__ __launch_bounds__(256, 3) void attn_mx4_kernel(const Mx4Params p) {
         const uint8_t* Rg = p.Krepr + ((size_t)(b * p.Hkv + hkv) * p.Tc) * D;
         const uint8_t* RSg = p.KreprS + ((size_t)(b * p.Hkv + hkv) * p.Tc) * 4;
         const MaxTiles mt = max_tiles(p.use_minit, p.n_sink, p.n_local, a_lo, a_hi, nv);
-        auto stage = [&](int u) __attribute__((always_inline)) { return u < 3 ? smem + RING + u * Tile8::KBYTES : Vsm + Tile8::VBYTES; };
+        auto stage = [&](int u) __attribute__((always_inline)) { return smem + STAGE + u * Tile8::KBYTES; };
         float mx = -INFINITY;
         for (int t0 = 0; t0 < mt.total; t0 += 4) {
             if (t0) __syncthreads();
@@ -287,7 +293,7 @@ __global__ __launch_bounds__(256, 3) void attn_mx4_kernel(const Mx4Params p) {
             for (int u = 0; u < 4; ++u) {
                 const int t = t0 + u;
                 if (t < mt.n_sum) {
-                    load_tile8<false, 4>(Rg, t * BN, nv, stage(u), wave, lane);
+                    load_tile8(Rg, t * BN, nv, stage(u), wave, lane);
                     if (wave == 0) load_scales64(RSg, t * BN, nv, mscale[u], lane);
                 } else if (t < mt.total) {
                     load_tile4(Kg, mt.block(t) * BN, N, stage(u), wave, lane);
@@ -295,10 +301,8 @@ __global__ __launch_bounds__(256, 3) void attn_mx4_kernel(const Mx4Params p) {
                 }
             }
             if (t0 == 0) {
-                load_kv(0, 0);
-                // the staged tiles have landed, not yet those of the main loop (three loads, four in the wave that moves the scales)
-                if (wave == 0) __builtin_amdgcn_s_waitcnt(0x0F74);
-                else __builtin_amdgcn_s_waitcnt(0x0F73);
+                load_kv(0, 0, 0);
+                __builtin_amdgcn_s_waitcnt(0x0F74);  // the staged tiles have landed, not yet those of the main loop
             } else {
                 __builtin_amdgcn_s_waitcnt(0x0F70);
             }
@@ -330,9 +334,10 @@ __global__ __launch_bounds__(256, 3) void attn_mx4_kernel(const Mx4Params p) {
         }
         m2 = finite_max(xhalf_max(mx) * p.c);
     } else {
-        load_kv(0, 0);
+        load_kv(0, 0, 0);
     }
     wait_vm0_and_sync();
+    load_kv(1, STAGE, 1);
     f32x16 ot[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db) ot[db] = f32x16{0};
@@ -342,41 +347,72 @@ __global__ __launch_bounds__(256, 3) void attn_mx4_kernel(const Mx4Params p) {
     float code0 = 0.f;  // NOEXP: code offset - 4 (m + H)
     if (FOLD) {
         const float v = -(m2 + p.headroom);
-        if (NOEXP) code0 = kCodeOffset + kCodesPerBinade * v;
+        if (NOEXP) code0 = kCodeUnit * (kCodeOffset + 0.5f + kCodesPerBinade * v);
 #pragma unroll
         for (int r = 0; r < 16; ++r) start[r] = v;
     }
-    auto visit = [&](int j, auto masked_c) __attribute__((always_inline)) {
+    // fragment addresses in a stage: see attn_fp8_kernel
+    uint32_t ka[2], va[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        ka[e] = lds_address(smem) + Tile4::k_off(ql, 2 * e + hh);
+        va[e] = lds_address(smem) + Tile4::KBYTES + Tile8::v_off(ql, 2 * hh + e);
+    }
+    const uint32_t sa = lds_s + 4 * ql;
+    typedef const __attribute__((address_space(3))) u32x4* lds_ptr;
+    typedef const __attribute__((address_space(3))) uint32_t* lds_dword;
+    auto visit = [&](int j, uint32_t stage, uint32_t st_no, uint32_t next2, uint32_t next2_no, auto masked_c) __attribute__((always_inline)) {
         constexpr bool SPECIAL = is_fa(MODE), MASKED = decltype(masked_c)::value;
-        const int buf = j & 1;
-        if (j + 1 < nv) load_kv(j + 1, buf ^ 1);
         f32x16 st[2];
         uint32_t pk[8];
         __builtin_amdgcn_s_setprio(1);
-        if (FOLD && !NOEXP) qk_tile4(Ksm + buf * Tile4::KBYTES, kscale[buf], qf, qs, st, ql, hh, &start);
-        else qk_tile4(Ksm + buf * Tile4::KBYTES, kscale[buf], qf, qs, st, ql, hh);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const uint32_t sc = *(lds_dword)(sa + st_no * 256 + t * 128);
+            const u32x4 g0 = *(lds_ptr)(ka[0] + stage + t * 2048), g1 = *(lds_ptr)(ka[1] + stage + t * 2048);
+            st[t] = mfma_f4(g0, qf[0], FOLD && !NOEXP ? start : f32x16{0}, spread_byte(sc, hh), qs[0]);
+            st[t] = mfma_f4(g1, qf[1], st[t], spread_byte(sc, 2 + hh), qs[1]);
+        }
         __builtin_amdgcn_s_setprio(0);
+        load_kv(j + 2, next2, next2_no);
         const bool needs_mask = (p.causal && j * BN + BN - 1 > row0) || (j + 1) * BN > N;
         if (NOEXP) codes_tile8<MASKED>(st, pk, j * BN, needs_mask ? limit : 0x3fffffff, hh, code0);
         else if (FOLD) softmax_tile8_folded<MASKED, P_BF8>(st, pk, lsum, j * BN, needs_mask ? limit : 0x3fffffff, hh);
         else softmax_tile8<SPECIAL, MASKED, P_BF8>(st, pk, ot, m2, lsum, p.c, p.headroom, j * BN, needs_mask ? limit : 0x3fffffff, hh);
+        const i32x8 pf = {(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3], (int)pk[4], (int)pk[5], (int)pk[6], (int)pk[7]};
         __builtin_amdgcn_s_setprio(1);
-        pv_tile8<P_BF8>(Vsm + buf * Tile8::VBYTES, pk, ot, lane, hh);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            const u32x4 lo = *(lds_ptr)(va[0] + stage + db * 2048), hi = *(lds_ptr)(va[1] + stage + db * 2048);
+            const i32x8 g = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+            ot[db] = P_BF8 ? __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(g, pf, ot[db], 0, 1, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f) : mfma_f8(g, pf, ot[db]);
+        }
         if (NOEXP) {  // row sums of the rounded weights: a block of E2M1 ones times P (E5M2)
             const i32x8 ones = {0x22222222, 0x22222222, 0x22222222, 0x22222222, 0, 0, 0, 0};
-            const i32x8 pf = {(int)pk[0], (int)pk[1], (int)pk[2], (int)pk[3], (int)pk[4], (int)pk[5], (int)pk[6], (int)pk[7]};
             lt = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ones, pf, lt, 4, 1, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
         }
         __builtin_amdgcn_s_setprio(0);
-        wait_vm0_and_sync();
+        // tile j + 1 has landed
+        __builtin_amdgcn_s_waitcnt(0x0F74);
+        __syncthreads();
     };
     using std::false_type;
     using std::true_type;
     int j_masked = p.causal ? a_lo : p.Tc;  // first tile that needs masking
     if (N % BN) j_masked = min(j_masked, p.Tc - 1);
     int j = 0;
-    for (; j < min(j_masked, nv); ++j) visit(j, false_type{});
-    for (; j < nv; ++j) visit(j, true_type{});
+    for (; j + S <= min(j_masked, nv); j += S) {
+        visit(j, 0, 0, 2 * STAGE, 2, false_type{});
+        visit(j + 1, STAGE, 1, 0, 0, false_type{});
+        visit(j + 2, 2 * STAGE, 2, STAGE, 1, false_type{});
+    }
+#pragma unroll 1
+    for (uint32_t no = 0; j < nv; ++j) {
+        const uint32_t next = no == 2 ? 0 : no + 1, next2 = next == 2 ? 0 : next + 1;
+        visit(j, no * STAGE, no, next2 * STAGE, next2, true_type{});
+        no = next;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // (requests past the last tile write zeros to LDS: not behind this workgroup's end)
     // (NOEXP: every register of lt holds the whole row sum, with the same 2^15 as the numerator)
     const float l = NOEXP ? lt[0] * 0x1p-15f : xhalf_sum(lsum);
     const float inv = l > 0.f ? p.descale_v * (P_BF8 ? 0x1p-15f : 0x1p-8f) / l : 0.f;
