@@ -26,7 +26,7 @@
  * The functions never throw, abort or print.  Same inputs give bit-identical outputs.
  *
  * Calls may be recorded into a HIP graph (they only enqueue kernels; nothing is allocated, copied
- * or cleared).  One exception: the first bf16 attention call on each device, of any entry point and size, sets a
+ * or cleared).  One exception: the first bf16 attention or decode call on each device, of any entry point and size, sets a
  * function attribute of every kernel that needs more than 64 KiB of LDS, so make one such call per device and
  * process before capturing.
  */
@@ -187,7 +187,8 @@ size_t vfa_decode_workspace_bytes(int B, int Hq, int d, int n_splits);
  *   K, V [B, Hkv, n_cap, d] bf16, rows [0, n_keys) valid (rows beyond are never read)
  *   Krepr  checked as before (given and 16-byte aligned when use_minit == 1, may be NULL when use_minit == 0) but not
  *          read: the step does not need the summaries, and a caller need not keep them up to date for it
- * The cache is cut into n_splits ranges of whole blocks; each range accumulates sum exp(s - m) and
+ * The cache is cut into n_splits ranges of whole blocks, or left whole where that is faster (few blocks, or about as many KV
+ * heads in the batch as compute units); each range accumulates sum exp(s - m) and
  * sum exp(s - m) v with its own running row max m; the ranges are added in a fixed order, each weighted by
  * exp(m - largest m) (bit-identical results from run to run), divided, and LSE = largest m + ln l.  The max of
  * every range is exact whatever n_sink, n_local and use_minit say: an estimate from the summaries, or a max fixed

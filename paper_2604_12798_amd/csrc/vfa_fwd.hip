@@ -75,6 +75,13 @@ bool raise_frozen() {
     return raise_lds_limit(&attn_fwd_frozen_kernel<D, KS, false>, Frozen<D, KS>::LDS_BYTES) &&
            raise_lds_limit(&attn_fwd_frozen_kernel<D, KS, true>, Frozen<D, KS>::LDS_BYTES);
 }
+template <int D, int W>
+constexpr int decode_lds_bytes() { return W * 2 * Tile<D>::BYTES; }
+template <int D, int W>
+bool raise_decode() {
+    return raise_lds_limit(&decode_split_kernel<D, W, LENS_ONE>, decode_lds_bytes<D, W>()) &&
+           raise_lds_limit(&decode_split_kernel<D, W, LENS_FIXED>, decode_lds_bytes<D, W>());
+}
 template <int D, int KQ>
 bool raise_short() { return raise_lds_limit(&attn_fwd_short_kernel<D, KQ>, Short<D, KQ>::LDS_BYTES); }
 template <int MODE>
@@ -87,6 +94,7 @@ bool raise_lds_limits() {
     const int dev = current_device();
     if (dev < 0) return false;
     if (done[dev].load(std::memory_order_acquire)) return true;
+    if (!raise_decode<64, 8>() || !raise_decode<128, 4>()) return false;
     if (!raise_short<64, 2>() || !raise_short<64, 4>() || !raise_short<128, 2>() || !raise_short<128, 4>()) return false;
     if (!raise_frozen<64, 1>() || !raise_frozen<64, 2>() || !raise_frozen<128, 2>() || !raise_pp<MODE_VFA>() || !raise_pp<MODE_FA>() ||
         !raise_pp<MODE_FA_LAZY>() || !raise_pp<MODE_FA_SOFTEXP>() || vfa_detail_vsa_pp_raise_lds() != 0)
@@ -626,24 +634,58 @@ int decode_common(const void* Q, const void* K, const void* V, const void* Krepr
     // a range with fewer tiles than waves leaves waves idle.  Lengths that differ and are not dealt out: the longest entries finish
     // last, with few others left beside them, so d = 64 keeps two waves (4096 entries of up to 8192 keys, one KV head, one range
     // 304 us with one wave, 270 with two; d = 128 does not gain)
-    const long long wgs = (long long)B * Hkv * n_splits;
-    const int tiles = ceil_div(ceil_div(n_keys, BN), n_splits);
     const int n_cu = cu_count() > 0 ? cu_count() : 256;
     (void)hipGetLastError();
+    if (!raise_lds_limits()) return VFA_ERR_HIP;
+    // One range for each KV head after all, its keys shared by as many waves as fill a compute unit (or half of one, for more heads
+    // than units), which then writes the result: no partial sums, no second launch (2.4 us and more).  `heads` KV heads of
+    // `all` tiles; us, n_splits ranges / one:
+    //   few tiles: up to five at d = 128 (8 heads, 100 keys 12.5 / 9.6, 320 12.5 / 10.4, 640 12.5 / 13.1; 32 heads, 512 12.4 / 13.1), 16 at d = 64
+    //     (32 heads, 1000 keys 12.1 / 11.3, 1500 12.0 / 13.8); more heads than units, half a unit each, 16 (360 heads, d = 128, 700 keys
+    //     28.6 / 27.5, 1500 49.5 / 50.5)
+    //   as many heads as nearly fill the units, or their halves: always (192 heads, d = 128, 3000 keys 57.3 / 49.4; 256 66.5 / 64.2; 400
+    //     heads, 1500 57.8 / 52.5; but 128 heads, 3000 38.3 / 42.1)
+    //   lengths that differ, which n_splits ranges even out: `all` is the longest there may be (16 x 8 heads of up to 700 keys 14.4 / 16.0;
+    //     32 x 8 16.5 / 16.4, of up to 1500 20.5 / 24.5; d = 64 12.7 / 11.0 and 12.8 / 14.6)
+    const long long heads = (long long)B * Hkv;
+    const int all = ceil_div(n_keys, BN);
+    bool single = false;
+    const bool half = heads > n_cu;  // two workgroups to a compute unit
+    if (n_splits > 1 && heads <= 2LL * n_cu) {
+        const bool filled = half ? 2 * heads >= 3LL * n_cu : 10 * heads >= 7LL * n_cu;
+        if (!seq_lens) single = filled || all <= (half || d == 64 ? 16 : 5);
+        else single = all <= (d == 64 ? (half ? 16 : 12) : (filled && !half ? 11 : 5));
+        if (single) p.n_splits = n_splits = 1;
+    }
+    const long long wgs = heads * n_splits;
+    const int tiles = ceil_div(all, n_splits);
     // (the lines are explained at varlen_find)
-    const bool dealt = seq_lens && n_splits > 1 && (B <= 64 || (B <= DEAL_MAX_B && wgs <= 8LL * n_cu && ceil_div(n_keys, BN) > 2 * n_splits));
+    const bool dealt = seq_lens && n_splits > 1 && (B <= 64 || (B <= DEAL_MAX_B && wgs <= 8LL * n_cu && all > 2 * n_splits));
     auto launch = [&](auto d_c, auto w_c) {
         constexpr int D = decltype(d_c)::value, W = decltype(w_c)::value;
+        constexpr int LDS = decode_lds_bytes<D, W>();
         const dim3 grid((unsigned)n_splits, (unsigned)B, (unsigned)Hkv);
-        if (!seq_lens) decode_split_kernel<D, W, LENS_ONE><<<grid, 64 * W, 0, s>>>(p);
-        else if (dealt) decode_split_kernel<D, W, LENS_DEALT><<<grid, 64 * W, 0, s>>>(p);
-        else decode_split_kernel<D, W, LENS_FIXED><<<dim3((unsigned)n_splits, (unsigned)Hkv, (unsigned)B), 64 * W, 0, s>>>(p);
+        if (!seq_lens) {
+            decode_split_kernel<D, W, LENS_ONE><<<grid, 64 * W, LDS, s>>>(p);
+        } else {
+            bool launched = false;
+            if constexpr (W * D <= 256) {  // (more waves share a KV head's only range)
+                if (dealt) decode_split_kernel<D, W, LENS_DEALT><<<grid, 64 * W, LDS, s>>>(p);
+                launched = dealt;
+            }
+            if (!launched) decode_split_kernel<D, W, LENS_FIXED><<<dim3((unsigned)n_splits, (unsigned)Hkv, (unsigned)B), 64 * W, LDS, s>>>(p);
+        }
         if (n_splits == 1) return;
         if (dealt) decode_merge_kernel<D, true><<<(unsigned)(B * Hq), 256, 0, s>>>(p);
         else decode_merge_kernel<D, false><<<(unsigned)(B * Hq), 256, 0, s>>>(p);
     };
     using std::integral_constant;
-    if (d == 128) {
+    if (single) {
+        if (d == 128 && !half) launch(integral_constant<int, 128>{}, integral_constant<int, 4>{});
+        else if (d == 128) launch(integral_constant<int, 128>{}, integral_constant<int, 2>{});
+        else if (!half) launch(integral_constant<int, 64>{}, integral_constant<int, 8>{});
+        else launch(integral_constant<int, 64>{}, integral_constant<int, 4>{});
+    } else if (d == 128) {
         if (tiles >= 2 && wgs <= n_cu) launch(integral_constant<int, 128>{}, integral_constant<int, 2>{});
         else launch(integral_constant<int, 128>{}, integral_constant<int, 1>{});
     } else {

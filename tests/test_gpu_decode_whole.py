@@ -1,0 +1,48 @@
+"""Decode steps whose cache is not cut into ranges although the caller asks for several: one workgroup for each KV head, its waves
+sharing the keys.  On both sides of the lines (a chip of 256 units), against exact attention in 64 bits; bars as in the other
+parity tests."""
+import numpy as np
+import pytest
+
+from gpu_util import LSE_ABS, O_MAX_ABS, O_MEAN_ABS
+
+pytestmark = pytest.mark.gpu
+
+
+def _exact(q, K, V, lens):
+    import torch
+    O, L = [], []
+    for b, n in enumerate(lens):
+        g = q.shape[1] // K.shape[1]
+        k, v = (x[b, :, :n].double().repeat_interleave(g, 0) for x in (K, V))
+        s = (k * q[b].double()[:, None]).sum(-1) * q.shape[-1] ** -0.5
+        L.append(torch.logsumexp(s, 1))
+        O.append(((s - L[-1][:, None]).exp()[..., None] * v).sum(1))
+    return torch.stack(O), torch.stack(L)
+
+
+# few tiles: fewer, as many and more than the workgroup's waves (four at d = 128, eight at d = 64), the last in the list behind the line
+FEW = [(1, 8, 2, 128, n) for n in (1, 64, 65, 192, 256, 257, 320, 321)] + [(1, 8, 2, 64, n) for n in (1, 65, 511, 513, 769, 1024, 1025)]
+# as many KV heads as nearly fill the units, fewer; more than units (two workgroups to each), nearly all of the halves, more
+MANY = [(24, 8, 8, 128, 700), (16, 8, 8, 128, 700), (24, 24, 8, 64, 1100), (33, 16, 8, 128, 130), (33, 16, 8, 64, 1100), (50, 8, 8, 128, 1100),
+        (64, 8, 8, 64, 1100), (65, 8, 8, 128, 130)]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,n", FEW + MANY)
+@pytest.mark.parametrize("ragged", [False, True])
+def test_whole_cache(B, Hq, Hkv, d, n, ragged):
+    import torch
+    import paper_2604_12798_amd as vfa
+    gen = torch.Generator(device="cuda").manual_seed(B + n)
+    q, K, V = (torch.randn(s, generator=gen, device="cuda").bfloat16() for s in ((B, Hq, d), (B, Hkv, n + 7, d), (B, Hkv, n + 7, d)))
+    q *= 2
+    K[:, :, n:], V[:, :, n:] = float("nan"), float("nan")  # rows beyond the keys are not read
+    lens = [n] + [int(x) for x in np.random.default_rng(n).integers(1, n + 1, B - 1)] if ragged else [n] * B
+    if ragged:
+        K, V = K[:, :, :n].contiguous(), V[:, :, :n].contiguous()  # the longest entry fills the capacity
+        O, L = vfa.decode_varlen_fwd(q, K, V, torch.tensor(lens, dtype=torch.int32, device="cuda"), use_minit=False, n_splits=3)
+    else:
+        O, L = vfa.decode_fwd(q, K, V, n, use_minit=False, n_splits=3)
+    eO, eL = _exact(q, K, V, lens)
+    err = (O.double() - eO).abs()
+    assert err.max() <= O_MAX_ABS and err.mean() <= O_MEAN_ABS and (L.double() - eL).abs().max() <= LSE_ABS
