@@ -15,27 +15,29 @@ namespace {
 // Step k of a wave: Q.K^T of its tile k + 1 and P.V of its tile k - 1 with the softmax of tile k dealt out between the MFMAs.
 // Two score buffers and two sets of packed P; the fast loop is unrolled by two so that they swap without moves.
 // What bounds it: at d = 64 the vector unit (measured in a loop of nothing else: a slice of two scores takes it 35 cycles and an
-// MFMA 10 of its issue, so 740 cycles per wave and tile against 512 of MFMA; the kernel takes 960 with two waves on a SIMD, and
-// with three, at 168 registers, it spills), at d = 128 the matrix unit (1024 cycles per wave and tile; 1500 with two waves on a
+// MFMA 10 of its issue, so 740 cycles per wave and tile against 512 of MFMA; the kernel takes about 900 with three waves on a SIMD, which
+// fit with a ring of four fragments, each loaded again behind the MFMA that used it, and two tiles of K and V: 4 x 16
+// heads, N = 4096 165 us with two waves and rings of four tiles, 160 with two, 157 with three), at d = 128 the matrix unit (1024 cycles per wave and tile; 1500 with two waves on a
 // SIMD).  Outside the steps a workgroup spends 14 - 17 K cycles: 2 K to its first request, 6 K until the first tiles are there,
 // 3.5 K on the max, 3 K on the groups' exchange and the output.
 // Kernel times in us, before and after: 32 heads over 8, causal, d = 128: N = 256 15.7 / 12.0, 777 25.0 / 18.9, 1024 29.0 / 21.5
 // (the ping-pong kernel's items leave more than half of the compute units idle); 16 heads, not causal, N = 5000 234 / 216;
-// d = 64 against the generic kernel: 32 heads over 8, causal, N = 777 16.5 / 12.4, 2048 37 / 30; 4 x 16 heads, N = 4096 179 / 164.
-// Each group has rings of S K tiles and S V tiles, filled by LDS-direct loads S - 1 steps ahead; one barrier per step.
+// d = 64 against the generic kernel: 32 heads over 8, causal, N = 777 16.5 / 12.4, 2048 37 / 30; 4 x 16 heads, N = 4096 179 / 157.
+// Each group has rings of S K tiles and S V tiles, filled by LDS-direct loads up to S - 1 steps ahead; one barrier per step.
 // With two groups the waves of the first request the K tiles of both and those of the second the V tiles (adjacent tiles, one
 // address to work out per step).
 template <int D, int KS>
 struct Frozen {
-    static constexpr int S = D == 64 ? 4 : 2;
+    static constexpr bool TIGHT = D == 64 && KS == 1;          // three workgroups to a compute unit: only the first K tile is requested in front of the max
+    static constexpr int S = D == 64 && !TIGHT ? 4 : 2;
     static constexpr int RING = 2 * S * Tile<D>::BYTES;        // one group's
-    static constexpr int EXTRA = 4 - 2 * KS;                   // staging slots beside the two V slots that a group's prologue leaves free
+    static constexpr int EXTRA = TIGHT ? 1 : 4 - 2 * KS;       // staging slots beside those that a group's prologue leaves free (two of V; TIGHT: one of K, two of V)
     static constexpr int LDS_BYTES = KS * RING + EXTRA * Tile<D>::BYTES + (KS == 2 ? 1024 : 0);  // (and the exchange of the max)
 };
 
 // ROWS64: the call is causal and in blocks of 64 rows, and a block of 128 stands for two of them.
 template <int D, int KS, bool ROWS64>
-__global__ __launch_bounds__(256 * KS, 2) void attn_fwd_frozen_kernel(const Params p) {
+__global__ __launch_bounds__(256 * KS, (Frozen<D, KS>::TIGHT ? 3 : 2)) void attn_fwd_frozen_kernel(const Params p) {
     using T = Tile<D>;
     using F = Frozen<D, KS>;
     constexpr int BM = 128, KK = D / 16, DB = D / 32, S = F::S;
@@ -170,6 +172,7 @@ __global__ __launch_bounds__(256 * KS, 2) void attn_fwd_frozen_kernel(const Para
     const int lo2 = p.n_local > 0 ? max(max(0, a_lo - (p.n_local - 1)), n1) : nv, n2 = max(0, min(a_hi, j_hi) + 1 - lo2);
     const int n_max = n_sum + n1 + (p.n_local > 0 ? n2 : 0);
     auto stage = [&](int u) __attribute__((always_inline)) {  // LDS offset of staging slot u
+        if (F::TIGHT) return (uint32_t)((1 + u) * T::BYTES);
         return (uint32_t)(u < 2 * KS ? (u % KS) * F::RING + (2 * S - 1 - u / KS) * T::BYTES : KS * F::RING + (u - 2 * KS) * T::BYTES);
     };
     f32x16 sa[2], sb[2];
@@ -203,10 +206,10 @@ __global__ __launch_bounds__(256 * KS, 2) void attn_fwd_frozen_kernel(const Para
                 }
             } else {
 #pragma unroll
-                for (int k = 0; k < S; ++k) request(tile_addr(Kg, k), k < nv ? N - k * BN : 0, off[0], off[1], off[LI - 2], off[LI - 1], k * T::BYTES);
+                for (int k = 0; k < (F::TIGHT ? 1 : S); ++k) request(tile_addr(Kg, k), k < nv ? N - k * BN : 0, off[0], off[1], off[LI - 2], off[LI - 1], k * T::BYTES);
 #pragma unroll
                 for (int k = 0; k < S - 2; ++k) request(tile_addr(Vg, k), k < nv ? N - k * BN : 0, offV, offV, offV, offV, (S + k) * T::BYTES);
-                constexpr int out = (2 * S - 2) * LI;
+                constexpr int out = (F::TIGHT ? 1 : 2 * S - 2) * LI;
                 __builtin_amdgcn_s_waitcnt(0x0F70 | (out & 15) | ((out >> 4) << 14));
             }
         } else {
@@ -232,6 +235,10 @@ __global__ __launch_bounds__(256 * KS, 2) void attn_fwd_frozen_kernel(const Para
     const float m2 = finite_max(mx * p.c);
     // step 0 finds "V of tile -1" all zeros (an empty buffer; what the slot held, times zero weights, could be NaN)
     request(0, 0, off[0], off[1], off[LI - 2], off[LI - 1], grp * F::RING + (2 * S - 1) * T::BYTES);
+    if (F::TIGHT) {
+#pragma unroll
+        for (int k = 1; k < S; ++k) request(tile_addr(Kg, k), k < nv ? N - k * BN : 0, off[0], off[1], off[LI - 2], off[LI - 1], k * T::BYTES);
+    }
     qk_tile_pipe<D>(Ks, qf, sa, ql, hh);
     wait_vm0_and_sync();  // (also: step 0 requests into K slot 0)
 
@@ -244,24 +251,6 @@ __global__ __launch_bounds__(256 * KS, 2) void attn_fwd_frozen_kernel(const Para
     for (int e = 0; e < 16; ++e) pa[e] = pb[e] = 0;
 
     const int kbase = T::k_base(ql, hh), vbase = T::v_base(lane, hh);
-    // fragments of group gq of a product: V^T of four (key chunk, d block) pairs, K of two k-steps x two key halves
-    auto ld_v = [&](bf16x8* f, const uint8_t* vt, int gq) __attribute__((always_inline)) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int c = (4 * gq + e) / DB, db = (4 * gq + e) % DB;
-            const uint8_t* a = vt + (vbase ^ (db << 6)) + 16 * c * T::ROWB;
-            const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(a));
-            const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(a + 8 * T::ROWB));
-            const u32x2 a0 = __builtin_bit_cast(u32x2, v0), a1 = __builtin_bit_cast(u32x2, v1);
-            const u32x4 aw = {a0[0], a0[1], a1[0], a1[1]};
-            f[e] = __builtin_bit_cast(bf16x8, aw);
-        }
-    };
-    auto ld_k = [&](bf16x8* f, const uint8_t* kt, int gq) __attribute__((always_inline)) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            f[e] = *reinterpret_cast<const bf16x8*>(kt + (kbase ^ ((2 * gq + (e >> 1)) << 5)) + (e & 1) * 32 * T::ROWB);
-    };
     auto mf_v = [&](const bf16x8* f, const uint32_t* pk, int gq, int e) __attribute__((always_inline)) {
         const int c = (4 * gq + e) / DB, db = (4 * gq + e) % DB;
         const u32x4 pw = {pk[4 * c], pk[4 * c + 1], pk[4 * c + 2], pk[4 * c + 3]};
@@ -298,9 +287,20 @@ __global__ __launch_bounds__(256 * KS, 2) void attn_fwd_frozen_kernel(const Para
         constexpr int LEAD = 2;  // slices in front of the first MFMA, while its fragments are on their way
         if (LAST && S == 2) request_step(k);  // (its own V, which a deeper ring has asked for by now)
         if (MASKED) mask(k, s0);
-        bf16x8 f[2][4];
-        if (LAST) ld_v(f[G0 & 1], vt, 0);
-        else ld_k(f[0], kt, 0);
+        bf16x8 f[4];
+        auto ld1 = [&](int x) __attribute__((always_inline)) {  // fragment x of the step: those of Q.K^T, then those of P.V
+            const int gq = x >> 2, e = x & 3;
+            if (gq < NG) return *reinterpret_cast<const bf16x8*>(kt + (kbase ^ ((2 * gq + (e >> 1)) << 5)) + (e & 1) * 32 * T::ROWB);
+            const int c = (4 * (gq - NG) + e) / DB, db = (4 * (gq - NG) + e) % DB;
+            const uint8_t* a = vt + (vbase ^ (db << 6)) + 16 * c * T::ROWB;
+            const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(a));
+            const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(a + 8 * T::ROWB));
+            const u32x2 a0 = __builtin_bit_cast(u32x2, v0), a1 = __builtin_bit_cast(u32x2, v1);
+            const u32x4 aw = {a0[0], a0[1], a1[0], a1[1]};
+            return __builtin_bit_cast(bf16x8, aw);
+        };
+#pragma unroll
+        for (int x = 4 * G0; x < 4 * G0 + 4; ++x) f[x & 3] = ld1(x);
         __builtin_amdgcn_sched_barrier(0);
         int q = 0;
 #pragma unroll
@@ -308,12 +308,11 @@ __global__ __launch_bounds__(256 * KS, 2) void attn_fwd_frozen_kernel(const Para
 #pragma unroll
         for (int gq = G0; gq < 2 * NG; ++gq) {
             if (!LAST && gq == 1) request_step(k);  // (here and not in front, so that the MFMAs start right behind the barrier)
-            if (gq + 1 < NG) ld_k(f[(gq + 1) & 1], kt, gq + 1);
-            else if (gq + 1 < 2 * NG) ld_v(f[(gq + 1) & 1], vt, gq + 1 - NG);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if (gq < NG) mf_k(f[gq & 1], s1, gq, e);
-                else mf_v(f[gq & 1], p1, gq - NG, e);
+                if (gq < NG) mf_k(f, s1, gq, e);
+                else mf_v(f, p1, gq - NG, e);
+                if (4 * gq + e + 4 < 8 * NG) f[e] = ld1(4 * gq + e + 4);
 #pragma unroll
                 for (; q < 16 && (q - LEAD) * NM < (4 * (gq - G0) + e + 1) * (16 - LEAD); ++q) slice(q, s0, p0);
                 __builtin_amdgcn_sched_barrier(0);

@@ -77,3 +77,13 @@ def test_what_lds_held_before_does_not_matter(oracle, d):
         vfa.fa_baseline_fwd(x, x, x, causal=False)
     for n in (64, 200, 520, 600):
         _check(oracle, _w(B=1, Hq=32, Hkv=8, N=n, d=d, n_sink=1, n_local=0), sample=6, before=poison)
+
+
+# calls that are too long for the kernel of short sequences (attn_short.hpp), which the smaller ones above run on: d = 64 with one group
+# of keys (three workgroups to a unit) and with two, d = 128; staging batches of one to eight tiles, no estimate, blocks of 64
+@pytest.mark.parametrize("B,Hq,N,d,causal,kw", [(2, 32, 2113, 64, True, {}), (2, 32, 2113, 64, True, dict(n_sink=4, n_local=4)), (2, 32, 1600, 64, False, {}),
+                                                (2, 32, 1601, 64, False, dict(n_sink=0, n_local=3)), (1, 8, 4200, 64, True, {}), (1, 8, 4200, 64, False, {}),
+                                                (1, 8, 2500, 128, False, {}), (1, 8, 2501, 128, False, dict(n_sink=3, n_local=0))])
+@pytest.mark.parametrize("block_m,use_minit", [(128, True), (64, True), (128, False)])
+def test_longer_calls(oracle, B, Hq, N, d, causal, kw, block_m, use_minit):
+    _check(oracle, _w(B=B, Hq=Hq, Hkv=4, N=N, d=d, causal=causal, block_m=block_m, **kw), use_minit=use_minit, sample=4)
