@@ -1,6 +1,6 @@
 // Alg. 1 with the max fixed before the first softmax: bf16, one 128-row query block per workgroup, the keys split over KS
-// groups of four waves.  d = 64 but for few tiles to an item (attn_generic.hpp); d = 128 where the ping-pong kernel
-// (attn_pingpong.hpp), which works in items of 256 rows, would leave compute units idle.
+// groups of four waves.  d = 64 but for short sequences (attn_short.hpp); d = 128 where the ping-pong kernel
+// (attn_pingpong.hpp), which works in items of 256 rows, would leave compute units idle, and the rest rows of its calls without a mask.
 #pragma once
 #include "common.hpp"
 
