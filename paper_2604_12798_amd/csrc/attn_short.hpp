@@ -252,7 +252,7 @@ __global__ __launch_bounds__(128 * KQ, 2) void attn_fwd_short_kernel(const Param
     using std::false_type;
     using std::true_type;
     auto next_step = [&]() __attribute__((always_inline)) {
-        __builtin_amdgcn_s_waitcnt(0x0F70 | LI);  // all but K of step s + 3
+        __builtin_amdgcn_s_waitcnt(0x0070 | LI);  // all requests but K of step s + 3, and the reads of the slots that are written next
         __builtin_amdgcn_s_barrier();
     };
     const int n_own = k_last < 32 * kq ? 0 : (k_last - 32 * kq) / KT + 1;  // steps that this wave has keys in: the first ones
