@@ -216,7 +216,7 @@ __device__ __forceinline__ void softmax_tile8_folded(f32x16* st, uint32_t* pk, f
 // 2^(c / 4 - 15), never more than 6.15 % above it.  So when a score arrives as x = s - m - H in log2 units, the
 // code of exp2(x) 2^15 is, up to that chord error and the rounding to a quarter of a binade, just
 // round(4 x + 120): a multiply-add and a float-to-byte conversion.  The multiply goes into the MFMA's block scale, so a tile's
-// scores leave the matrix unit in units of codes; what is left per score is the add, half a conversion, half a clamp
+// scores leave the matrix unit in 256ths of a code; what is left per score is a multiply-add, half a conversion, half a clamp
 // and a quarter of a byte permute (see codes_tile8).  The offset is lowered by
 // 4 log2(1.0303) = 0.1723 to centre the chord error: weight / exact weight lies in [0.89, 1.12] (the format's
 // own rounding would give +-12.5 %).  E5M2 rather than E4M3 because the window has to hold, below the frozen max,
@@ -227,10 +227,13 @@ __device__ __forceinline__ void softmax_tile8_folded(f32x16* st, uint32_t* pk, f
 constexpr float kCodeOffset = 119.8277f;  // 4 * (15 + 15) - 0.1723
 constexpr float kCodesPerBinade = 4.f;
 
-// The scores arrive as 256ths of a code (kCodeUnit).  v_cvt_pknorm_u16_f32 rounds two of them to whole 65536ths, clamped to [0, 1]; the
-// code is the upper byte (the half added to the offset makes that a rounding), and one v_perm_b32 collects four: 72 instructions a
-// tile, where a clamp and v_cvt_pk_u8_f32 for every score took 96 (4 x 32 heads, 3000 tokens, 8-bit 175 / 169 us, 4-bit 155 / 150).
-constexpr float kCodeUnit = 0x1p-8f;
+// The scores arrive as 256ths of a code; a code's worth is 256 / 65535 (kCodeUnit): v_cvt_pknorm_u16_f32 takes two values in [0, 1] to the nearest whole 65535ths, i.e. to the
+// nearest 256ths of a code, z, and the code is z's upper byte.  That is one rounding and not two: with half a code less half of a
+// 256th on top (kCodeHalf) z reaches 256 k exactly where the code before rounding reaches k - 1/2.  One v_perm_b32 collects four codes:
+// 72 instructions a tile, where a clamp and v_cvt_pk_u8_f32 for every score took 96 (4 x 32 heads, 3000 tokens, 8-bit 175 / 169 us, 4-bit
+// 155 / 150; with an add and a unit of 2^-8, which leaves a shift of up to half of a 256th, 8-bit 174 for 177, 4-bit 160 for 159).
+constexpr float kCodeUnit = 256.f / 65535.f;
+constexpr float kCodeHalf = 0.5f - 0x1p-9f;
 constexpr uint32_t kMaxCode2 = 0x7bff7bffu;  // 0x7B = 57344, the largest finite E5M2 value, in the upper bytes of both halves
 typedef __attribute__((ext_vector_type(2))) unsigned short u16x2_t;
 template <bool MASKED>
@@ -247,7 +250,7 @@ __device__ __forceinline__ void codes_tile8(f32x16* st, uint32_t* pk, int key0, 
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     const int i = r + 2 * e + u;
-                    c[u] = st[t][i] + add;
+                    c[u] = __builtin_fmaf(st[t][i], 256.f * kCodeUnit, add);
                     if (MASKED) c[u] = 32 * t + 8 * (i >> 2) + (i & 3) <= rel ? c[u] : 0.f;
                 }
                 const auto q = __builtin_amdgcn_cvt_pknorm_u16(c[0], c[1]);
@@ -424,7 +427,7 @@ __global__ __launch_bounds__(256, FOLD ? 3 : 2) void attn_fp8_kernel(const Fp8Pa
     f32x16 lt = {0};  // NOEXP: 32 copies of this lane's row sum of the rounded weights (times 2^15)
     if (FOLD) {
         const float v = -(m2 + p.headroom);
-        if (NOEXP) code0 = kCodeUnit * (kCodeOffset + 0.5f + kCodesPerBinade * v);
+        if (NOEXP) code0 = kCodeUnit * (kCodeOffset + kCodeHalf + kCodesPerBinade * v);
 #pragma unroll
         for (int r = 0; r < 16; ++r) start[r] = v;
     }

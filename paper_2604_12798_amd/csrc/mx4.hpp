@@ -347,7 +347,7 @@ __global__ __launch_bounds__(256, 3) void attn_mx4_kernel(const Mx4Params p) {
     float code0 = 0.f;  // NOEXP: code offset - 4 (m + H)
     if (FOLD) {
         const float v = -(m2 + p.headroom);
-        if (NOEXP) code0 = kCodeUnit * (kCodeOffset + 0.5f + kCodesPerBinade * v);
+        if (NOEXP) code0 = kCodeUnit * (kCodeOffset + kCodeHalf + kCodesPerBinade * v);
 #pragma unroll
         for (int r = 0; r < 16; ++r) start[r] = v;
     }
