@@ -276,16 +276,16 @@ int vfa_fp8_attn_fwd(int frozen, const void* Q8, const void* K8, const void* Vt8
                      void* stream);
 
 /* Alg. 1 on E4M3 operands WITHOUT exponentials.  Needs what the fast path of vfa_fp8_attn_fwd needs (descale_q *
- * descale_k * softmax_scale * log2(e) a power of two to 2^-18, else VFA_ERR_INVALID_ARG), because the scale and
- * the frozen max must sit inside the matrix instruction.  The code of a small float read as an integer is a
+ * descale_k * softmax_scale * log2(e) a power of two to 2^-18, else VFA_ERR_INVALID_ARG), because the scale
+ * must sit inside the matrix instruction.  The code of a small float read as an integer is a
  * piecewise-linear logarithm of its value, so the E5M2 code of exp(S - m) is obtained from the score by a
- * multiply-add (folded into the instruction) and one float-to-byte conversion: each weight is within
+ * multiply-add and one rounding to a whole code: each weight is within
  * [-11 %, +12 %] of the exact one (the format's own rounding would be +-12.5 %), and the row sum is taken over the
  * SAME rounded weights by one more matrix instruction, so O is a properly normalised average of V under those
  * weights (measured: mean-abs error as the rounded-exponential path, max-abs within 2^-3 max|V|).  LSE is computed
  * from that row sum: within 0.12 nats of the exact value.  This is the performance discussion's argument taken to
- * its end for 8-bit P: with the max known before the tile, no per-score vector arithmetic but a clamp and a
- * conversion is left.  Everything else as vfa_fp8_attn_fwd with frozen = 1.  (Both, and the 4-bit forms, take the
+ * its end for 8-bit P: with the max known before the tile, no per-score vector arithmetic but a multiply-add, a
+ * clamp and a conversion is left.  Everything else as vfa_fp8_attn_fwd with frozen = 1.  (Both, and the 4-bit forms, take the
  * row maxima of the sink and local blocks in front of the first tile, so every block is a frozen one.) */
 int vfa_fp8_attn_noexp_fwd(const void* Q8, const void* K8, const void* Vt8, void* O, float* LSE, int B,
                            int Hq, int Hkv, int N, int d, int block_m, int block_n, int causal,
@@ -328,10 +328,8 @@ int vfa_mxfp4_attn_fwd(int frozen, const void* Q4, const void* QS, const void* K
                        void* stream);
 
 /* vfa_mxfp4_attn_fwd's Alg. 1 without exponentials, as vfa_fp8_attn_noexp_fwd: needs softmax_scale * log2(e) = 1
- * (to 2^-18, else VFA_ERR_INVALID_ARG; the caller multiplied Q by its scale * log2(e) before quantising); the
- * factor 4 / 256 of the code scale rides in the queries' block-scale bytes (bytes below 6 count as 6: blocks whose
- * largest element is below 2^-119).  Weights within
- * [-11 %, +12 %] of the exact ones, normalised by their own sum; LSE within 0.12 nats. */
+ * (to 2^-18, else VFA_ERR_INVALID_ARG; the caller multiplied Q by its scale * log2(e) before quantising).  Weights
+ * within [-11 %, +12 %] of the exact ones, normalised by their own sum; LSE within 0.12 nats. */
 int vfa_mxfp4_attn_noexp_fwd(const void* Q4, const void* QS, const void* K4, const void* KS,
                              const void* Vt8, void* O, float* LSE, int B, int Hq, int Hkv, int N, int d,
                              int block_m, int block_n, int causal, int n_sink, int n_local,

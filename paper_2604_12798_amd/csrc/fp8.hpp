@@ -215,9 +215,7 @@ __device__ __forceinline__ void softmax_tile8_folded(f32x16* st, uint32_t* pk, f
 // logarithm: an E5M2 code c = 4 E + m stands for 2^(E - 15) (1 + m / 4), the chord approximation of
 // 2^(c / 4 - 15), never more than 6.15 % above it.  So when a score arrives as x = s - m - H in log2 units, the
 // code of exp2(x) 2^15 is, up to that chord error and the rounding to a quarter of a binade, just
-// round(4 x + 120): a multiply-add and a float-to-byte conversion.  The multiply goes into the MFMA's block scale, so a tile's
-// scores leave the matrix unit in 256ths of a code; what is left per score is a multiply-add, half a conversion, half a clamp
-// and a quarter of a byte permute (see codes_tile8).  The offset is lowered by
+// round(4 x + 120): a multiply-add, half a conversion, half a clamp and a quarter of a byte permute (see codes_tile8).  The offset is lowered by
 // 4 log2(1.0303) = 0.1723 to centre the chord error: weight / exact weight lies in [0.89, 1.12] (the format's
 // own rounding would give +-12.5 %).  E5M2 rather than E4M3 because the window has to hold, below the frozen max,
 // the headroom, the overshoot of the seed and the spread of the row, and E4M3's subnormal codes, which the
@@ -227,7 +225,7 @@ __device__ __forceinline__ void softmax_tile8_folded(f32x16* st, uint32_t* pk, f
 constexpr float kCodeOffset = 119.8277f;  // 4 * (15 + 15) - 0.1723
 constexpr float kCodesPerBinade = 4.f;
 
-// The scores arrive as 256ths of a code; a code's worth is 256 / 65535 (kCodeUnit): v_cvt_pknorm_u16_f32 takes two values in [0, 1] to the nearest whole 65535ths, i.e. to the
+// A code's worth is 256 / 65535 (kCodeUnit): v_cvt_pknorm_u16_f32 takes two values in [0, 1] to the nearest whole 65535ths, i.e. to the
 // nearest 256ths of a code, z, and the code is z's upper byte.  That is one rounding and not two: with half a code less half of a
 // 256th on top (kCodeHalf) z reaches 256 k exactly where the code before rounding reaches k - 1/2.  One v_perm_b32 collects four codes:
 // 72 instructions a tile, where a clamp and v_cvt_pk_u8_f32 for every score took 96 (4 x 32 heads, 3000 tokens, 8-bit 175 / 169 us, 4-bit
@@ -250,7 +248,7 @@ __device__ __forceinline__ void codes_tile8(f32x16* st, uint32_t* pk, int key0, 
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     const int i = r + 2 * e + u;
-                    c[u] = __builtin_fmaf(st[t][i], 256.f * kCodeUnit, add);
+                    c[u] = __builtin_fmaf(st[t][i], kCodesPerBinade * kCodeUnit, add);
                     if (MASKED) c[u] = 32 * t + 8 * (i >> 2) + (i & 3) <= rel ? c[u] : 0.f;
                 }
                 const auto q = __builtin_amdgcn_cvt_pknorm_u16(c[0], c[1]);

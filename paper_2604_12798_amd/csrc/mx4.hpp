@@ -207,7 +207,7 @@ struct Mx4Params {
 // i.e. the caller folded that factor into Q before quantising): frozen tiles start their accumulators at
 // -(m + H) and go to exp2 untouched.
 // NOEXP (with FOLD): the weights' E5M2 codes are taken from the scores as in attn_fp8_kernel's form without
-// exponentials; the code scale, 4 / 256, is taken off the queries' block-scale bytes (six binades).
+// exponentials.
 // The loop is that of attn_fp8_kernel.  Attention alone in us, before / after it (and, without exponentials, codes by
 // v_cvt_pknorm_u16_f32): 4 x 32 heads, 3000 tokens, without exponentials 155 / 143, folded 164 / 156; 8192 tokens 231 / 214, 242 / 232.
 template <int MODE, bool FOLD, bool NOEXP = false>
@@ -264,8 +264,6 @@ __global__ __launch_bounds__(256, 3) void attn_mx4_kernel(const Mx4Params p) {
         for (int kh = 0; kh < 2; ++kh) {
             qf[kh] = *reinterpret_cast<const u32x4*>(p.Q + qr * 64 + 32 * kh + 16 * hh);
             qs[kh] = spread_byte(sw, 2 * kh + hh);
-            // (a scale below 2^-121 counts as that: its elements' share of a score is nothing either way)
-            if (NOEXP) qs[kh] = max(qs[kh] & 0xff, 6) * 0x01010101 - 0x06060606;
         }
     }
     const int nv = j_hi + 1;

@@ -791,10 +791,8 @@ int fp8_common(int frozen, bool noexp, const void* Q8, const void* K8, const voi
         const float mant = frexpf(p.c, &ex);  // p.c = mant * 2^ex, mant in [0.5, 1)
         if (fabsf(mant - 0.5f) <= 0x1p-18f && ex - 1 >= -100 && ex - 1 <= 100) {
             fold = true;
-            // (the form without exponentials takes its scores times 4 / 256: six less in the exponent byte, and the
-            // factor that turns a raw row max into log2 units becomes 64)
-            p.scale_a = (127 + ex - 1 + (noexp ? -6 : 0)) * 0x01010101;
-            p.c = noexp ? 64.f : 1.f;
+            p.scale_a = (127 + ex - 1) * 0x01010101;
+            p.c = 1.f;
         }
     }
     if (noexp && !fold) return VFA_ERR_INVALID_ARG;  // (before anything is launched)
@@ -900,7 +898,7 @@ int mx4_common(int frozen, bool noexp, const void* Q4, const void* QS, const voi
     // Alg. 1 with the scores already in log2 units (the caller multiplied Q by scale * log2(e) before quantising
     // and passes softmax_scale = ln 2): nothing is left to multiply, and the frozen max becomes the accumulators' start
     const bool fold = frozen && fabsf(p.c - 1.f) <= 0x1p-18f;
-    if (fold) p.c = noexp ? 64.f : 1.f;  // (without exponentials the scores come out times 4 / 256)
+    if (fold) p.c = 1.f;
     const dim3 grid((unsigned)(B * Hq * Tr));
     if (noexp) attn_mx4_kernel<MODE_VFA, true, true><<<grid, 256, 0, s>>>(p);
     else if (fold) attn_mx4_kernel<MODE_VFA, true><<<grid, 256, 0, s>>>(p);

@@ -54,7 +54,9 @@ def test_fp8(seed):
     _check(O, c * (q.astype(np.float64) @ k.T.astype(np.float64)))
 
 
-@pytest.mark.parametrize("qs,ks,features", [(127, 121, 128), (100, 148, 128), (200, 48, 128)])
+# block scale bytes of the queries and the keys: the product of the two scales is what counts, wherever each of them lies
+@pytest.mark.parametrize("qs,ks,features", [(127, 121, 128), (0, 248, 128), (5, 243, 128), (6, 242, 128), (128, 120, 128), (200, 48, 128), (248, 0, 128),
+                                            (254, 0, 3)])
 def test_mxfp4(qs, ks, features):
     import torch
     import paper_2604_12798_amd as vfa
