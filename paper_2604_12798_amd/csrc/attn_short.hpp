@@ -10,7 +10,8 @@ namespace {
 // On a short sequence the fixed max of Alg. 1 costs more than it saves: a launch of its own for the summaries (3 - 5 us), one more
 // tile product for them and for the sink and local blocks, and items long enough to pay for both.  Here every block's scores
 // enter the max exactly (all blocks are what Alg. 1 calls special ones), each wave keeping a max of its own, which it moves
-// only when a row exceeds it by more than kKeepMax (the weights are then at most 2^kKeepMax, and the rescale of O is rare); the
+// only when a row exceeds it by more than kKeepMax, so that the rescale of O is rare; the weights are exp2(s - m - kKeepMax), at
+// most 1, and sums of large values overflow no sooner than elsewhere.  The
 // waves' sums are weighted by exp2(m - largest m) when they meet in LDS.  The summaries, which the caller may want
 // from the workspace, are written by workgroups behind the items, of the same launch.
 //
@@ -133,7 +134,6 @@ __global__ __launch_bounds__(128 * KQ, 2) void attn_fwd_short_kernel(const Param
     const int qrow_c = min(qrow, N - 1);
     const int limit = p.causal ? qrow_c : N - 1;
     const int k_last = p.causal ? min(N - 1, qrow0 + 31) : N - 1;  // last key that any row of the wave sees
-    const int k_full = p.causal ? min(N - 1, qrow0) : N - 1;       // last key that every row of the wave sees
     bf16x8 qf[KK];
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk)
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(128 * KQ, 2) void attn_fwd_short_kernel(const Param
             for (int db = 0; db < DB; ++db) ot[db] *= alpha;
             m2 = m_new;
         }
-        const float msub = m2 == -INFINITY ? 0.f : m2;
+        const float msub = m2 == -INFINITY ? 0.f : m2 + kKeepMax;
         uint32_t pk[8];
         auto slice = [&](int q) __attribute__((always_inline)) {
             const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(st[2 * q], p.c, -msub));
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(128 * KQ, 2) void attn_fwd_short_kernel(const Param
     auto finish = [&](auto kq_c) __attribute__((always_inline)) {
         constexpr int KO = decltype(kq_c)::value;
         if (qrow < N && p.LSE && KO == 0 && hh == 0)
-            p.LSE[(size_t)(b * p.Hq + h) * N + qrow] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
+            p.LSE[(size_t)(b * p.Hq + h) * N + qrow] = l > 0.f ? (m + kKeepMax + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
         uint16_t* const Og = p.O + ((size_t)(b * p.Hq + h) * N + qrow_c) * D;
 #pragma unroll
         for (int v = 0; v < OWN; ++v) {

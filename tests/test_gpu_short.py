@@ -66,3 +66,23 @@ def test_what_lds_held_before_does_not_matter(oracle, d):
     for n in (20, 64, 200, 700):
         vfa.fa_baseline_fwd(x, x, x, causal=False)
         _check(oracle, _w(B=1, Hq=8, Hkv=8, N=n, d=d), 6)
+
+
+@pytest.mark.parametrize("d,B,Hq,N", [(64, 1, 8, 256), (128, 1, 8, 256), (64, 1, 4, 700), (128, 1, 4, 700), (128, 2, 16, 448)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_large_values(d, B, Hq, N, causal):
+    """Scores that rise by 7.5 binades behind a wave's first keys, too little for it to move its max, and values near the largest of 32
+    bits divided by the keys: a weight above 1 would overflow their sums, which exact attention's do not."""
+    import torch
+    import paper_2604_12798_amd as vfa
+    Q, K = torch.zeros((B, Hq, N, d), device="cuda"), torch.zeros((B, Hq, N, d), device="cuda")
+    Q[..., 0], K[:, :, N // 4:, 0] = 8.0, 1.0
+    V = torch.full((B, Hq, N, d), 1e35, device="cuda").bfloat16()
+    scale = 7.5 * 0.6931471805599453 / 8
+    O, L = vfa.vfa_attn_fwd(Q.bfloat16(), K.bfloat16(), V, causal=causal, softmax_scale=scale)
+    S = torch.where(torch.arange(N, device="cuda") < N // 4, 0.0, 8.0 * scale).double().expand(N, N)
+    if causal:
+        S = S.masked_fill(torch.ones(N, N, dtype=torch.bool, device="cuda").triu(1), -float("inf"))
+    # all values are alike, so O is that value, but for the weights' rounding against their sum and its own: 2^-8 each
+    assert ((O.double() / V.double() - 1).abs() <= 2.0 ** -7).all()
+    assert (L.double() - S.logsumexp(1)).abs().max() <= 1e-3
