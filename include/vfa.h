@@ -26,9 +26,9 @@
  * The functions never throw, abort or print.  Same inputs give bit-identical outputs.
  *
  * Calls may be recorded into a HIP graph (they only enqueue kernels; nothing is allocated, copied
- * or cleared).  One exception: the first bf16 attention or decode call on each device, of any entry point and size, sets a
+ * or cleared).  One exception: the first bf16 attention call on each device, of any entry point and size, sets a
  * function attribute of every kernel that needs more than 64 KiB of LDS, so make one such call per device and
- * process before capturing.
+ * process before capturing.  (Decode steps set none and may be captured first.)
  */
 #ifndef VFA_H_
 #define VFA_H_

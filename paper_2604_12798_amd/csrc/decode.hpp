@@ -163,8 +163,7 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void decode_split_kernel(c
     constexpr int NI = BN / (1024 / T::ROWB);
     constexpr int OROW = D + 4;  // row of the exchange of partial sums, in floats: padded against bank conflicts
     static_assert(32 * OROW * 4 + 64 * 4 <= 2 * T::BYTES, "the exchange has to fit the tiles' memory");
-    extern __shared__ __attribute__((aligned(16))) uint8_t decode_smem[];
-    uint8_t* const smem = decode_smem;
+    __shared__ __attribute__((aligned(16))) uint8_t smem[W * 2 * T::BYTES];  // (up to 128 KiB; of fixed size, so no limit has to be raised for it)
     const int lane = threadIdx.x & 63, ql = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t* const Ks = smem + wave * 2 * T::BYTES;

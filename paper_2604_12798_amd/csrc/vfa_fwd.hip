@@ -75,13 +75,6 @@ bool raise_frozen() {
     return raise_lds_limit(&attn_fwd_frozen_kernel<D, KS, false>, Frozen<D, KS>::LDS_BYTES) &&
            raise_lds_limit(&attn_fwd_frozen_kernel<D, KS, true>, Frozen<D, KS>::LDS_BYTES);
 }
-template <int D, int W>
-constexpr int decode_lds_bytes() { return W * 2 * Tile<D>::BYTES; }
-template <int D, int W>
-bool raise_decode() {
-    return raise_lds_limit(&decode_split_kernel<D, W, LENS_ONE>, decode_lds_bytes<D, W>()) &&
-           raise_lds_limit(&decode_split_kernel<D, W, LENS_FIXED>, decode_lds_bytes<D, W>());
-}
 template <int D, int KQ>
 bool raise_short() { return raise_lds_limit(&attn_fwd_short_kernel<D, KQ>, Short<D, KQ>::LDS_BYTES); }
 template <int MODE>
@@ -94,7 +87,6 @@ bool raise_lds_limits() {
     const int dev = current_device();
     if (dev < 0) return false;
     if (done[dev].load(std::memory_order_acquire)) return true;
-    if (!raise_decode<64, 8>() || !raise_decode<128, 4>()) return false;
     if (!raise_short<64, 2>() || !raise_short<64, 4>() || !raise_short<128, 2>() || !raise_short<128, 4>()) return false;
     if (!raise_frozen<64, 1>() || !raise_frozen<64, 2>() || !raise_frozen<128, 2>() || !raise_pp<MODE_VFA>() || !raise_pp<MODE_FA>() ||
         !raise_pp<MODE_FA_LAZY>() || !raise_pp<MODE_FA_SOFTEXP>() || vfa_detail_vsa_pp_raise_lds() != 0)
@@ -636,7 +628,6 @@ int decode_common(const void* Q, const void* K, const void* V, const void* Krepr
     // 304 us with one wave, 270 with two; d = 128 does not gain)
     const int n_cu = cu_count() > 0 ? cu_count() : 256;
     (void)hipGetLastError();
-    if (!raise_lds_limits()) return VFA_ERR_HIP;
     // One range for each KV head after all, its keys shared by as many waves as fill a compute unit (or half of one, for more heads
     // than units), which then writes the result: no partial sums, no second launch (2.4 us and more).  `heads` KV heads of
     // `all` tiles; us, n_splits ranges / one:
@@ -663,17 +654,16 @@ int decode_common(const void* Q, const void* K, const void* V, const void* Krepr
     const bool dealt = seq_lens && n_splits > 1 && (B <= 64 || (B <= DEAL_MAX_B && wgs <= 8LL * n_cu && all > 2 * n_splits));
     auto launch = [&](auto d_c, auto w_c) {
         constexpr int D = decltype(d_c)::value, W = decltype(w_c)::value;
-        constexpr int LDS = decode_lds_bytes<D, W>();
         const dim3 grid((unsigned)n_splits, (unsigned)B, (unsigned)Hkv);
         if (!seq_lens) {
-            decode_split_kernel<D, W, LENS_ONE><<<grid, 64 * W, LDS, s>>>(p);
+            decode_split_kernel<D, W, LENS_ONE><<<grid, 64 * W, 0, s>>>(p);
         } else {
             bool launched = false;
             if constexpr (W * D <= 256) {  // (more waves share a KV head's only range)
-                if (dealt) decode_split_kernel<D, W, LENS_DEALT><<<grid, 64 * W, LDS, s>>>(p);
+                if (dealt) decode_split_kernel<D, W, LENS_DEALT><<<grid, 64 * W, 0, s>>>(p);
                 launched = dealt;
             }
-            if (!launched) decode_split_kernel<D, W, LENS_FIXED><<<dim3((unsigned)n_splits, (unsigned)Hkv, (unsigned)B), 64 * W, LDS, s>>>(p);
+            if (!launched) decode_split_kernel<D, W, LENS_FIXED><<<dim3((unsigned)n_splits, (unsigned)Hkv, (unsigned)B), 64 * W, 0, s>>>(p);
         }
         if (n_splits == 1) return;
         if (dealt) decode_merge_kernel<D, true><<<(unsigned)(B * Hq), 256, 0, s>>>(p);

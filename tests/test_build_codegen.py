@@ -39,16 +39,22 @@ def test_vsa_fast_loops_have_no_scratch_access(tmp_path):
     assert all(scratch == 0 for _, scratch in fast), f"scratch accesses in the VSA fast loops: {fast}"
 
 
-@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
-def test_inner_loops_have_no_scratch_access(tmp_path):
-    """The other kernels: several (the ping-pong baselines, the 8-bit and 4-bit forms with folded scales) have spilled registers, all
-    of them outside the loops over tiles.  Left out: the generic kernel with ablation switches at d = 128, block_m = 128."""
-    out = tmp_path / "vfa_fwd.s"
+@pytest.fixture(scope="module")
+def other_kernels(tmp_path_factory):
+    """The AMD assembly of vfa_fwd.hip."""
+    out = tmp_path_factory.mktemp("codegen") / "vfa_fwd.s"
     flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
     subprocess.run([HIPCC] + flags + ["-S", "--cuda-device-only", "-o", str(out), os.path.join(build.CSRC, "vfa_fwd.hip")],
                    check=True, capture_output=True)
+    return out.read_text()
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_inner_loops_have_no_scratch_access(other_kernels):
+    """The other kernels: several (the ping-pong baselines, the 8-bit and 4-bit forms with folded scales) have spilled registers, all
+    of them outside the loops over tiles.  Left out: the generic kernel with ablation switches at d = 128, block_m = 128."""
     seen = []
-    for m in re.finditer(r"^(_Z\S*):[^\n]*\n(.*?)\.Lfunc_end", out.read_text(), re.S | re.M):
+    for m in re.finditer(r"^(_Z\S*):[^\n]*\n(.*?)\.Lfunc_end", other_kernels, re.S | re.M):
         kernel = re.search(r"(attn_\w+?_kernel|decode_split_kernel)I(\w+?)EEv", m.group(1))
         if not kernel or re.fullmatch(r"Li128ELi4ELi[12]ELb0E", kernel.group(2)):
             continue
@@ -67,3 +73,15 @@ def test_inner_loops_have_no_scratch_access(tmp_path):
         seen.append(kernel.group(1))
     assert {"attn_fwd_pp_kernel", "attn_fwd_frozen_kernel", "attn_fwd_kernel", "attn_fp8_kernel", "attn_mx4_kernel",
             "decode_split_kernel"} <= set(seen), seen
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_decode_needs_no_function_attribute(other_kernels):
+    """A decode step may be the first call of a process and be captured: its kernels' LDS is of fixed size, so nothing has to raise a
+    limit for what a launch adds to it, also where four or eight waves take 128 KiB."""
+    lds = {m.group(1): int(m.group(2)) for m in
+           re.finditer(r"\.amdhsa_kernel (\S*decode_split_kernel\S*)\n\s*\.amdhsa_group_segment_fixed_size (\d+)", other_kernels)}
+    assert len(lds) >= 19, sorted(lds)
+    for name, size in lds.items():
+        d, waves = (int(x) for x in re.search(r"ILi(\d+)ELi(\d)E", name).groups())
+        assert size == waves * 2 * 64 * 2 * d, (name, size)  # a tile of K and one of V for each wave

@@ -116,3 +116,43 @@ def test_warm_up_call_of_another_kind(name):
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, "-c", CHILD, json.dumps(PAIRS[name])], cwd=root, timeout=100, capture_output=True, text=True)
     assert r.returncode == 0 and "captured" in r.stdout, r.stdout + r.stderr
+
+
+DECODE_CHILD = """
+import sys, json, torch
+import paper_2604_12798_amd as vfa
+B, Hq, Hkv, n, d, ns, ragged = json.loads(sys.argv[1])
+gen = torch.Generator(device="cuda").manual_seed(n)
+q, K, V = (torch.randn(s, generator=gen, device="cuda").bfloat16() for s in ((B, Hq, d), (B, Hkv, n, d), (B, Hkv, n, d)))
+lens = torch.full((B,), n, dtype=torch.int32, device="cuda")
+ws = torch.empty(vfa.decode_workspace_bytes(B, Hq, d, ns), dtype=torch.uint8, device="cuda")
+o, l = torch.empty_like(q), torch.empty((B, Hq), device="cuda")
+kw = dict(use_minit=False, n_splits=ns, workspace=ws, out=o, lse=l)
+step = (lambda: vfa.decode_varlen_fwd(q, K, V, lens, **kw)) if ragged else (lambda: vfa.decode_fwd(q, K, V, n, **kw))
+torch.cuda.synchronize()
+g = torch.cuda.CUDAGraph()
+with torch.cuda.graph(g, capture_error_mode="global"):
+    step()
+for rnd in range(3):
+    o.fill_(float("nan")); l.fill_(float("nan"))
+    torch.cuda.synchronize()
+    g.replay()
+    torch.cuda.synchronize()
+    S = (K.double()[:, None] * q.double().view(B, Hkv, Hq // Hkv, 1, d).transpose(1, 2)).sum(-1) * d ** -0.5  # [B, g, Hkv, n]
+    want = torch.logsumexp(S, -1).transpose(1, 2).reshape(B, Hq)
+    assert (l.double() - want).abs().max() <= 1e-3 and torch.isfinite(o.float()).all(), rnd
+print("captured", flush=True)
+"""
+
+
+# whole caches (four, two, eight waves to a workgroup) and ranges; the process makes no other call of the library before
+@pytest.mark.parametrize("shape", [(1, 8, 2, 300, 128, 5, False), (1, 8, 2, 600, 64, 5, False), (33, 8, 8, 130, 128, 2, False), (1, 8, 2, 2048, 128, 16, False),
+                                   (2, 8, 2, 300, 128, 5, True), (2, 8, 2, 2048, 64, 16, True)], ids=str)
+def test_first_call_of_a_process_is_a_captured_decode_step(shape):
+    import json
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", DECODE_CHILD, json.dumps(shape)], cwd=root, timeout=100, capture_output=True, text=True)
+    assert r.returncode == 0 and "captured" in r.stdout, r.stdout + r.stderr
