@@ -114,6 +114,9 @@ int launch_frozen(Params p, int row_base, int block_m, hipStream_t s) {  // rows
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
 }
 
+// Workgroups of 256 threads that one launch can have: of 2^32 work-items or more HIP runs a part, without an error
+constexpr long long kMaxWorkgroups256 = (1LL << 24) - 1;
+
 // Alg. 1 on the kernel for short sequences (attn_short.hpp): 0 = no, else its groups of keys.  `items` are blocks of 64 rows.  The other
 // kernels, with the summaries' launch in front, have twice the rate once their long items fill the compute units; the
 // lines lie where they catch up (us, theirs / two groups / four):
@@ -131,7 +134,8 @@ int launch_frozen(Params p, int row_base, int block_m, hipStream_t s) {  // rows
 // 1696 shapes: the mean is 1.25 to 1.38 times faster by kind; slower by more than 2 % (no mask): 32 heads, N = 2500 was (5 %; now outside).
 int short_groups(const Params& p, int d, int n_cu) {
     const long long heads = (long long)p.B * p.Hq, items = heads * p.Tc;  // (of 64 rows)
-    if (n_cu <= 0 || items > (1LL << 30) || p.n_sink > 4 || p.n_local > 4) return 0;
+    if (n_cu <= 0 || p.n_sink > 4 || p.n_local > 4) return 0;
+    if (items + ((long long)p.B * p.Hkv * p.Tc + 3) / 4 > kMaxWorkgroups256) return 0;  // (with the summaries' workgroups; four groups are for few items)
     const int Tc = p.Tc;
     auto per_cu = [&](double x) { return items <= (long long)(x * n_cu); };
     if (d == 64) {
@@ -234,8 +238,10 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
         if (!ablation && d == 64 && p.n_sink <= 4 && p.n_local <= 4) {
             // two groups to an item while there is no more than one item per compute unit (32 heads, N = 777: 12.4 against 13.6 us;
             // N = 4096: 95 against 87)
-            if ((long long)q.B * q.Hq * q.Tr <= cu_count()) return launch_frozen<64, 2>(q, 0, block_m, s);
-            return launch_frozen<64, 1>(q, 0, block_m, s);
+            const long long items = (long long)q.B * q.Hq * q.Tr;
+            if (items <= cu_count()) return launch_frozen<64, 2>(q, 0, block_m, s);
+            // (more than one launch can have: the generic kernel, whose workgroups have half as many threads at block_m = 64)
+            if (items <= kMaxWorkgroups256) return launch_frozen<64, 1>(q, 0, block_m, s);
         }
         if (!ablation && d == 128) {
             const bool frozen = prefer_frozen(q, cu_count(), head_pairs);

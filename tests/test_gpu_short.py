@@ -86,3 +86,22 @@ def test_large_values(d, B, Hq, N, causal):
     # all values are alike, so O is that value, but for the weights' rounding against their sum and its own: 2^-8 each
     assert ((O.double() / V.double() - 1).abs() <= 2.0 ** -7).all()
     assert (L.double() - S.logsumexp(1)).abs().max() <= 1e-3
+
+
+# more heads of one token than a launch of 256 threads each can have workgroups (2^24); d = 128: pairs of heads, an odd number to a KV
+# head; d = 64: the workgroups of blocks of 64 rows have 128 threads
+@pytest.mark.parametrize("Hq,d,block_m", [(258, 128, 64), (257, 128, 128), (257, 64, 64)])
+def test_very_many_heads_of_one_token(Hq, d, block_m):
+    import torch
+    import paper_2604_12798_amd as vfa
+    B = 65528
+    gen = torch.Generator(device="cuda").manual_seed(Hq)
+    R = lambda h: torch.randn((B, h, 1, d), generator=gen, device="cuda", dtype=torch.bfloat16)
+    Q, K, V = R(Hq), R(1), R(1)
+    O, L = torch.full_like(Q, float("nan")), torch.full((B, Hq, 1), float("nan"), device="cuda")
+    vfa.vfa_attn_fwd(Q, K, V, block_m=block_m, out=O, lse=L)
+    # one key: its value, bit for bit (a weight that rounds to a power of two, divided by itself), and its score
+    assert all((O[b:b + 4096] == V[b:b + 4096]).all() for b in range(0, B, 4096))
+    for b in range(0, B, 4096):
+        s = (Q[b:b + 4096, :, 0].float() @ K[b:b + 4096, 0, 0, :, None].float())[..., 0] * d ** -0.5
+        assert (L[b:b + 4096, :, 0] - s).abs().max() <= 1e-3
