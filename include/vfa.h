@@ -42,7 +42,7 @@ extern "C" {
 #define VFA_OK 0
 #define VFA_ERR_INVALID_ARG (-1) /* null/misaligned pointer, negative size, Hq % Hkv != 0, bad flag combination, workspace too small */
 #define VFA_ERR_UNSUPPORTED (-2) /* d or block sizes outside the compiled set, sizes beyond 32-bit grid limits */
-#define VFA_ERR_HIP (-3)         /* the HIP runtime reported a launch error */
+#define VFA_ERR_HIP (-3)         /* the HIP runtime reported a launch error, or a launch would have 2^32 work-items or more */
 #define VFA_ERR_TOO_LARGE (-4)   /* vfa_decode_noalloc_fwd only: the partial sums do not fit the library's fixed device array */
 
 /* Bytes of `workspace` that vfa_attn_fwd / vsa_attn_fwd need (the Krepr tensor, rounded up

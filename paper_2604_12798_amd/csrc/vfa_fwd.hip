@@ -25,6 +25,9 @@ namespace {
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
+// Workgroups of 256 threads that one launch can have: of 2^32 work-items or more HIP runs a part, without an error
+constexpr long long kMaxWorkgroups256 = (1LL << 24) - 1;
+
 int check_common(const void* Q, const void* K, const void* V, void* O, const float* LSE, int B, int Hq, int Hkv,
                  int N, int d, int block_m, int block_n) {
     if (B < 0 || N < 0 || Hq <= 0 || Hkv <= 0 || d <= 0 || block_m <= 0 || block_n <= 0) return VFA_ERR_INVALID_ARG;
@@ -113,9 +116,6 @@ int launch_frozen(Params p, int row_base, int block_m, hipStream_t s) {  // rows
     else attn_fwd_frozen_kernel<D, KS, false><<<grid, 256 * KS, Frozen<D, KS>::LDS_BYTES, s>>>(p);
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
 }
-
-// Workgroups of 256 threads that one launch can have: of 2^32 work-items or more HIP runs a part, without an error
-constexpr long long kMaxWorkgroups256 = (1LL << 24) - 1;
 
 // Alg. 1 on the kernel for short sequences (attn_short.hpp): 0 = no, else its groups of keys.  `items` are blocks of 64 rows.  The other
 // kernels, with the summaries' launch in front, have twice the rate once their long items fill the compute units; the
@@ -283,6 +283,7 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
         }
     }
     const dim3 grid((unsigned)(p.B * p.Hq * p.Tr));
+    if ((long long)p.B * p.Hq * p.Tr > kMaxWorkgroups256 * 128 / block_m) return VFA_ERR_HIP;  // (two threads to a row of a block)
     if constexpr (MODE == MODE_VSA) {
         if (!ablation) {
             if (d == 128 && block_m == 128) attn_fwd_kernel<128, 4, MODE, true><<<grid, 256, 0, s>>>(p);
@@ -764,7 +765,7 @@ int fp8_common(int frozen, bool noexp, const void* Q8, const void* K8, const voi
     if (!Q8 || !K8 || !Vt8 || !O || !aligned16(Q8) || !aligned16(K8) || !aligned16(Vt8) || !aligned16(O)) return VFA_ERR_INVALID_ARG;
     if (LSE && (reinterpret_cast<uintptr_t>(LSE) & 3u)) return VFA_ERR_INVALID_ARG;
     const int Tc = ceil_div(N, BN), Tr = ceil_div(N, block_m);
-    if ((long long)B * Hq * Tr > 0x7fffffffLL || (long long)B * Hq * N > 0x7fffffffLL || (long long)B * Hkv > 65535)
+    if ((long long)B * Hq * Tr > kMaxWorkgroups256 || (long long)B * Hq * N > 0x7fffffffLL || (long long)B * Hkv > 65535)
         return VFA_ERR_UNSUPPORTED;
     const bool minit = frozen && use_minit;
     if (minit && (!workspace || !aligned16(workspace) || workspace_bytes < (size_t)B * Hkv * Tc * 128)) return VFA_ERR_INVALID_ARG;
@@ -863,7 +864,7 @@ int mx4_common(int frozen, bool noexp, const void* Q4, const void* QS, const voi
     if ((reinterpret_cast<uintptr_t>(QS) & 3u) || (reinterpret_cast<uintptr_t>(KS) & 3u)) return VFA_ERR_INVALID_ARG;
     if (LSE && (reinterpret_cast<uintptr_t>(LSE) & 3u)) return VFA_ERR_INVALID_ARG;
     const int Tc = ceil_div(N, BN), Tr = ceil_div(N, block_m);
-    if ((long long)B * Hq * Tr > 0x7fffffffLL || (long long)B * Hq * N > 0x7fffffffLL || (long long)B * Hkv > 65535)
+    if ((long long)B * Hq * Tr > kMaxWorkgroups256 || (long long)B * Hq * N > 0x7fffffffLL || (long long)B * Hkv > 65535)
         return VFA_ERR_UNSUPPORTED;
     const bool minit = frozen && use_minit;
     if (minit && (!workspace || !aligned16(workspace) || workspace_bytes < vfa_mxfp4_workspace_bytes(B, Hkv, N)))

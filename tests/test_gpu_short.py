@@ -105,3 +105,22 @@ def test_very_many_heads_of_one_token(Hq, d, block_m):
     for b in range(0, B, 4096):
         s = (Q[b:b + 4096, :, 0].float() @ K[b:b + 4096, 0, 0, :, None].float())[..., 0] * d ** -0.5
         assert (L[b:b + 4096, :, 0] - s).abs().max() <= 1e-3
+
+
+def test_more_workgroups_than_a_launch_can_have_is_an_error():
+    """Where no kernel covers that many heads the call fails and writes nothing (HIP would run a part of the launch, without an error)."""
+    import torch
+    import paper_2604_12798_amd as vfa
+    B, Hq, d = 65528, 257, 64
+    Q, K = torch.zeros((B, Hq, 1, d), device="cuda", dtype=torch.bfloat16), torch.zeros((B, 1, 1, d), device="cuda", dtype=torch.bfloat16)
+    O, L = torch.full_like(Q, 7.0), torch.full((B, Hq, 1), 7.0, device="cuda")
+    for call in (vfa.vfa_attn_fwd, vfa.fa_baseline_fwd):
+        with pytest.raises(vfa.VfaError):
+            call(Q, K, K, block_m=128, out=O, lse=L)
+    q8, k8 = (torch.zeros((B, h, 1, 128), device="cuda", dtype=torch.uint8) for h in (Hq, 1))
+    v8 = torch.zeros((B, 1, 1, 128, 64), device="cuda", dtype=torch.uint8)
+    O8 = torch.full(q8.shape, 7.0, device="cuda", dtype=torch.bfloat16)
+    with pytest.raises(vfa.VfaError):
+        vfa.fp8_attn_fwd(q8, k8, v8, descale_q=1.0, descale_k=1.0, descale_v=1.0, out=O8, lse=L)
+    torch.cuda.synchronize()
+    assert (O == 7).all() and (L == 7).all() and (O8 == 7).all()
