@@ -104,7 +104,8 @@ int fa_lazy_rescale_softexp_fwd(const void* Q, const void* K, const void* V, voi
  * Which of three forms runs depends on the sizes: sink and local blocks first, each with the online-softmax
  * update, the rest behind them; all their row maxima first and then every block with that max, in
  * order; or, on short sequences and on the last rows of a call without a causal mask, every block's scores
- * enter the max exactly, which then needs no summaries (use_minit = 1 writes them to `workspace` all the same).  The results differ
+ * enter the max exactly, which then needs no summaries (use_minit = 1 writes them to `workspace` all the same; those of
+ * use_minit = 2 are not read).  The results differ
  * by rounding only (and a row whose sink and local scores are all -inf
  * gives NaN in the first form if it sees other blocks).  block_m = 64 may run as blocks of 128
  * rows, whose local blocks include those of both halves; with a causal mask no key block behind a
@@ -156,12 +157,13 @@ int vsa_attn_fwd(const void* Q, const void* K, const void* V, void* O, float* LS
  *              suppressed (scores -inf, its state untouched); needs skipping and freeze = 0
  *   lazy_rescale_tau  >= 0 = Blasst_FA4: on kept tiles a row keeps its old max while the new one
  *              exceeds it by at most tau * ln 2; negative = off; needs skipping and freeze = 0
- * reorder = freeze = 1, repr_mode = q_repr_mode = 0, rowskip = 0, tau < 0 is exactly vfa_attn_fwd /
- * vsa_attn_fwd.
+ * reorder = freeze = 1, repr_mode = q_repr_mode = 0, rowskip = 0, tau < 0 is vfa_attn_fwd / vsa_attn_fwd, but
+ * that without skipping the max is the fixed one on all rows (vfa_attn_fwd takes every block's scores into it on
+ * short sequences and on the last rows of some calls), so that use_minit, n_sink and n_local act as in the other settings.
  * Vanilla BLASST is (use_minit 0, reorder 0, freeze 0, threshold > 0); Blasst_SWA is the same with
  * reorder 1.
  * Every setting without skipping is exact attention; they differ in how far the frozen max sits
- * from the true one, which is what the ablation measures.  These run on the generic kernel. */
+ * from the true one, which is what the ablation measures.  Those that are not the method's run on the generic kernel. */
 int vfa_variant_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE, int B,
                     int Hq, int Hkv, int N, int d, int block_m, int block_n, int causal,
                     int n_sink, int n_local, int use_minit, int repr_mode, int q_repr_mode, int reorder,

@@ -179,10 +179,10 @@ int tail_row(const Params& p, int n_cu, bool head_pairs) {
 //     one and two it is two rounds against one (N = 3072: 89 against 76 us), above three four against two, and under a causal mask
 //     the ping-pong kernel's long items find short ones to pair with
 //   many sink / local blocks: their scores are computed twice in attn_frozen.hpp
-bool prefer_frozen(const Params& p, int n_cu, bool head_pairs) {
+bool prefer_frozen(const Params& p, int n_cu, bool has_tail) {
     const long long items = (long long)p.B * p.Hq * p.Tr;
     if (p.n_sink > 4 || p.n_local > 4 || n_cu <= 0) return false;
-    return items <= n_cu || (!p.causal && p.Tc > 12 && items > 2LL * n_cu && 10 * items <= 29LL * n_cu && !tail_row(p, n_cu, head_pairs));
+    return items <= n_cu || (!p.causal && p.Tc > 12 && items > 2LL * n_cu && 10 * items <= 29LL * n_cu && !has_tail);
 }
 
 // Calls with block_m = 64 and without skipping, d = 128, that are not short ones (`p` in blocks of 128 rows): true = items of 64 rows on the generic
@@ -219,8 +219,9 @@ bool prefer_rows64(const Params& p, int n_cu, bool head_pairs, bool frozen, bool
 // dropped, non-causal N = 5100 (4.5 %), and 12 heads, N = 10200 (2.5 %).
 constexpr int VSA_GENERIC_MAX_N = 10240;
 
+// `fixed_max`: Alg. 1 as written on all rows (no kernel that takes every block's scores into the max)
 template <int MODE>
-int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
+int launch_fwd(const Params& p, int d, int block_m, hipStream_t s, bool fixed_max = false) {
     (void)hipGetLastError();
     if (!raise_lds_limits()) return VFA_ERR_HIP;
     const int g = p.Hq / p.Hkv;
@@ -234,6 +235,7 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
     Params q = p;
     if (MODE != MODE_VSA && !ablation) q.Tr = ceil_div(p.N, 128);
     bool rows64 = false;
+    int tail = 0;  // rows [0, tail) run on the ping-pong kernel, those behind them on another one
     if constexpr (MODE == MODE_VFA) {
         if (!ablation && d == 64 && p.n_sink <= 4 && p.n_local <= 4) {
             // two groups to an item while there is no more than one item per compute unit (32 heads, N = 777: 12.4 against 13.6 us;
@@ -244,14 +246,12 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s) {
             if (items <= kMaxWorkgroups256) return launch_frozen<64, 1>(q, 0, block_m, s);
         }
         if (!ablation && d == 128) {
-            const bool frozen = prefer_frozen(q, cu_count(), head_pairs);
+            if (!fixed_max) tail = tail_row(q, cu_count(), head_pairs);
+            const bool frozen = prefer_frozen(q, cu_count(), tail > 0);
             rows64 = block_m == 64 && prefer_rows64(q, cu_count(), head_pairs, frozen, false);
             if (frozen && !rows64) return launch_frozen<128, 2>(q, 0, block_m, s);
+            if (rows64) tail = 0;
         }
-    }
-    int tail = 0;  // rows [0, tail) run on the ping-pong kernel, those behind them on another one
-    if constexpr (MODE == MODE_VFA) {
-        if (!ablation && d == 128 && !rows64) tail = tail_row(q, cu_count(), head_pairs);
     }
     if constexpr (is_fa(MODE)) {
         rows64 = d == 128 && block_m == 64 && prefer_rows64(q, cu_count(), head_pairs, false, true);
@@ -331,7 +331,7 @@ int vfa_vsa_common(int mode, const void* Q, const void* K, const void* V, void* 
                    int N, int d, int block_m, int block_n, int causal, int n_sink, int n_local, int use_minit,
                    float softmax_scale, float thr_nats, unsigned char* skip_mask, void* workspace,
                    size_t workspace_bytes, void* stream, int repr_mode = 0, int reorder = 1, int freeze = 1,
-                   int rowskip = 0, float lazy_tau = -1.f, int q_repr_mode = 0) {
+                   int rowskip = 0, float lazy_tau = -1.f, int q_repr_mode = 0, bool variant = false) {
     int rc = check_common(Q, K, V, O, LSE, B, Hq, Hkv, N, d, block_m, block_n);
     if (rc != VFA_OK) return rc;
     if (n_sink < 0 || n_local < 0) return VFA_ERR_INVALID_ARG;
@@ -365,7 +365,7 @@ int vfa_vsa_common(int mode, const void* Q, const void* K, const void* V, void* 
     p.rowskip = rowskip ? 1 : 0; p.tau2 = lazy_tau >= 0.f ? lazy_tau : -1.f;
     p.c = scale * kLog2e;
     p.thr2 = thr_nats * kLog2e;
-    if (mode == MODE_VFA && reorder && freeze && !q_repr_mode && (use_minit != 1 || repr_mode == 0)) {
+    if (mode == MODE_VFA && !variant) {  // (the ablation's calls differ in the max they fix, so all of them fix one)
         const int groups = short_groups(p, d, cu_count());
         if (groups) {
             (void)hipGetLastError();
@@ -387,7 +387,7 @@ int vfa_vsa_common(int mode, const void* Q, const void* K, const void* V, void* 
         }
     }
     p.Qrepr = (const uint16_t*)qrepr;
-    return mode == MODE_VSA ? launch_fwd<MODE_VSA>(p, d, block_m, s) : launch_fwd<MODE_VFA>(p, d, block_m, s);
+    return mode == MODE_VSA ? launch_fwd<MODE_VSA>(p, d, block_m, s) : launch_fwd<MODE_VFA>(p, d, block_m, s, variant);
 }
 
 int fa_common(int mode, const void* Q, const void* K, const void* V, void* O, float* LSE, int B, int Hq, int Hkv,
@@ -509,7 +509,7 @@ int vfa_variant_fwd(const void* Q, const void* K, const void* V, void* O, float*
     return vfa_vsa_common(skipping ? MODE_VSA : MODE_VFA, Q, K, V, O, LSE, B, Hq, Hkv, N, d, block_m, block_n, causal,
                           n_sink, n_local, use_minit, softmax_scale, skip_threshold_nats, skipping ? skip_mask : nullptr,
                           workspace, workspace_bytes, stream, repr_mode, reorder, freeze, rowskip, lazy_rescale_tau,
-                          q_repr_mode);
+                          q_repr_mode, true);
 }
 
 int vfa_kblock_summary_append(const void* K, void* Krepr, int B, int Hkv, int n_cap, int n_old, int n_new, int d,

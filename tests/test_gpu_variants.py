@@ -206,3 +206,24 @@ def test_blockwise_q_repr_skip_mask_bit_exact(vfa, oracle, sname, w, thr, q_mode
     sparsity = (ref["mask"] == 1).sum() / max(1, (ref["mask"] != 2).sum())
     print(sname, "q_repr_mode", q_mode, "specials", specials, "sparsity %.3f" % sparsity, "tiles decided differently from the row-wise seed:",
           differ, stats, flush=True)
+
+
+# short sequences (where vfa_attn_fwd takes every block's scores into the max) and a call without a mask whose last rows run on a kernel of
+# their own there (a round of the ping-pong kernel on 256 units and 512 rows)
+@pytest.mark.parametrize("B,Hq,Hkv,N,d,causal", [(1, 8, 2, 100, 128, True), (1, 8, 2, 777, 128, True), (1, 8, 2, 100, 64, True), (1, 8, 2, 777, 64, False),
+                                                 (1, 32, 8, 2560, 128, False)])
+@pytest.mark.parametrize("block_m", [64, 128])
+def test_the_fixed_max_is_the_one_that_the_switches_choose(vfa, B, Hq, Hkv, N, d, causal, block_m):
+    """The method's own switches, too: with summaries (given by the caller) that put the max 170 binades above every score, all weights
+    are 0 in 32 bits, in every row."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    Q, K, V = (torch.randn((B, h, N, d), generator=gen, device="cuda").abs().bfloat16() for h in (Hq, Hkv, Hkv))
+    Q += 1
+    R = torch.zeros((B, Hkv, -(-N // 64), d), dtype=torch.bfloat16, device="cuda")
+    R[..., 0] = 150.0 * d ** 0.5  # 150 nats and more; the scores are below 32
+    assert ((Q.float().norm(dim=-1).max() * K.float().norm(dim=-1).max()) * d ** -0.5).item() < 32
+    ws = torch.zeros(vfa.workspace_bytes(B, Hkv, N, d, 64), dtype=torch.uint8, device="cuda")
+    ws[:2 * R.numel()] = R.view(torch.uint8).flatten()
+    O, L, _ = vfa.vfa_variant_fwd(Q, K, V, block_m=block_m, causal=causal, n_sink=1, n_local=1, use_minit=2, workspace=ws)
+    assert torch.isneginf(L).all() and (O == 0).all()
