@@ -641,8 +641,10 @@ int decode_common(const void* Q, const void* K, const void* V, const void* Krepr
     //   few tiles: up to five at d = 128 (8 heads, 100 keys 12.5 / 9.6, 320 12.5 / 10.4, 640 12.5 / 13.1; 32 heads, 512 12.4 / 13.1), 16 at d = 64
     //     (32 heads, 1000 keys 12.1 / 11.3, 1500 12.0 / 13.8); more heads than units, half a unit each, 16 (360 heads, d = 128, 700 keys
     //     28.6 / 27.5, 1500 49.5 / 50.5)
-    //   as many heads as nearly fill the units, or their halves: always (192 heads, d = 128, 3000 keys 57.3 / 49.4; 256 66.5 / 64.2; 400
-    //     heads, 1500 57.8 / 52.5; but 128 heads, 3000 38.3 / 42.1)
+    //   as many heads as nearly fill the units, or their halves: always (d = 128, 180 heads, 700 keys 17.7 / 14.3, 3000 53.5 / 44.2, 20000 319 /
+    //     270; 224, 8000 141 / 140, 20000 344 / 331; 256, 3000 63.1 / 60.7, 20000 387 / 384; 400, 1500 56.2 / 50.6, 20000 658 / 611; 504, 20000
+    //     747 / 743; d = 64, 180 heads, 20000 169 / 136; 480, 8000 152 / 153; but 128 heads, 3000 38.3 / 42.1, and three ranges to two
+    //     units, which end together: 384 heads, 8000 240 / 248, 20000 577 / 600)
     //   lengths that differ, which n_splits ranges even out: `all` is the longest there may be (16 x 8 heads of up to 700 keys 14.4 / 16.0;
     //     32 x 8 16.5 / 16.4, of up to 1500 20.5 / 24.5; d = 64 12.7 / 11.0 and 12.8 / 14.6)
     const long long heads = (long long)B * Hkv;
@@ -650,7 +652,7 @@ int decode_common(const void* Q, const void* K, const void* V, const void* Krepr
     bool single = false;
     const bool half = heads > n_cu;  // two workgroups to a compute unit
     if (n_splits > 1 && heads <= 2LL * n_cu) {
-        const bool filled = half ? 2 * heads >= 3LL * n_cu : 10 * heads >= 7LL * n_cu;
+        const bool filled = half ? 2 * heads > 3LL * n_cu : 10 * heads >= 7LL * n_cu;
         if (!seq_lens) single = filled || all <= (half || d == 64 ? 16 : 5);
         else single = all <= (d == 64 ? (half ? 16 : 12) : (filled && !half ? 11 : 5));
         if (single) p.n_splits = n_splits = 1;

@@ -25,7 +25,7 @@ def _exact(q, K, V, lens):
 FEW = [(1, 8, 2, 128, n) for n in (1, 64, 65, 192, 256, 257, 320, 321)] + [(1, 8, 2, 64, n) for n in (1, 65, 511, 513, 769, 1024, 1025)]
 # as many KV heads as nearly fill the units, fewer; more than units (two workgroups to each), nearly all of the halves, more
 MANY = [(24, 8, 8, 128, 700), (16, 8, 8, 128, 700), (24, 24, 8, 64, 1100), (33, 16, 8, 128, 130), (33, 16, 8, 64, 1100), (50, 8, 8, 128, 1100),
-        (64, 8, 8, 64, 1100), (65, 8, 8, 128, 130)]
+        (64, 8, 8, 64, 1100), (65, 8, 8, 128, 130), (48, 8, 8, 128, 1100), (49, 8, 8, 64, 1100)]
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,d,n", FEW + MANY)
