@@ -118,40 +118,52 @@ int launch_frozen(Params p, int row_base, int block_m, hipStream_t s) {  // rows
 }
 
 // Alg. 1 on the kernel for short sequences (attn_short.hpp): 0 = no, else its groups of keys.  `items` are blocks of 64 rows.  The other
-// kernels, with the summaries' launch in front, have twice the rate once their long items fill the compute units; the
-// lines lie where they catch up (us, theirs / two groups / four):
-//   d = 64: four groups for no more items than compute units (16 heads, N = 2048, no mask 22.9 / 19.4 / 15.7 at 8 heads; causal, few
-//     heads, up to four: 12 heads, N = 3802 47 / 43 / 37), otherwise two, up to 24 tiles (64 heads, N = 1536, no mask 37.6 / 34.9; N = 2048 45.8 / 48.4)
-//     or, causal, 32 and for fewer items 64 (32 heads, N = 2048 32.8 / 28.5; 48 heads, N = 2500 58 / 60)
-//   d = 128, four groups: as above from ten tiles on, the summaries' workgroups counted, since one fills a compute unit (8 heads, N = 1024 22.8 /
-//     15.2 / 13.4); causal, few long heads: up to two items per compute unit (12 heads, N = 2500 40.8 / 38.3 / 33.6)
-//   d = 128, two groups: up to seven tiles always (512 heads, N = 448 1.12 and 1.02 times faster, causal and not); from there the more tiles the
-//     fewer items.  Causal 128 heads, N = 777 46 / 36, N = 1024 55 / 60; 64 heads, N = 1024 35.2 / 28.9, N = 1536 52.9 / 56.0; 32 heads, N = 2048
-//     53.9 / 46.9, N = 3000 83 / 91.  Not causal 64 heads, N = 640 27.0 / 24.9, N = 1024 41.5 / 44.5; 32 heads, N = 1024 26.1 / 23.3, N = 1536 46.7 / 49.1
-//   odd groups of heads, causal, run in super-blocks of 256 rows otherwise: a longer range, but for nearly full rounds of those (32 heads
-//     over 32, N = 2500 107 / 78, N = 2048, one round, 56.5 / 59.6); not causal, a second round of a few items: the same (48 heads, N = 1300 75 / 55)
-//   many sink or local blocks: as they were
-// 1696 shapes: the mean is 1.25 to 1.38 times faster by kind; slower by more than 2 % (no mask): 32 heads, N = 2500 was (5 %; now outside).
+// kernels, with the summaries' launch in front, have up to twice the rate once their long items fill the compute units; the lines
+// lie where they catch up.  In us, theirs / this one (each line's last shapes, then the first beyond it where that was measured):
+//   four groups, from ten tiles on, for no more items than units (at d = 128 the summaries' workgroups counted, since one fills a
+//     unit): 8 heads, N = 1024 22.8 / 13.4, no mask, d = 64, N = 2048 22.9 / 15.7; causal, few long heads, whose items are uneven: up to four
+//     per unit at d = 64 (12 heads, N = 3802 47 / 37), two at d = 128 (12 heads, N = 2500 40.8 / 33.6)
+//   d = 64, two groups, no mask: up to 7 tiles always (512 heads, N = 344 36.7 / 35.1); 11 with 12 items per unit (320 heads, N = 576 49.2 /
+//     46.0; 512 heads, N = 495 54.4 / 55.9); 14 with 10 (160 heads, N = 896 50.8 / 49.2; 256 heads, N = 768 55.7 / 57.9); 16 with 7 (112 heads,
+//     N = 1024 45.3 / 43.5; 160 heads, N = 960 55.2 / 56.9); 24 with 5 (64 heads, N = 1263 40.7 / 38.6, N = 1344 42.9 / 45.5)
+//   d = 64, causal: up to 14 tiles always; 24 with 24 items per unit (256 heads, N = 1536 114.4 / 114.7; 512 heads, N = 1024 111.4 / 114.2, N =
+//     1536 213.9 / 221.9) or an odd number of them, which leaves half of the others' last block of 128 rows empty (512 heads, N = 1281 179.8 /
+//     174.3); 28 with 9 (80 heads, N = 1792 50.3 / 49.0; 192 heads, N = 1624 101.2 / 103.8); 29, odd, with 11 (96 heads, N = 1800 74.9 / 70.0; 512
+//     heads 324 / 334); 64 with 6.2 (48 heads, N = 2072 45.0 / 39.7; 64 heads, N = 2048 55.2 / 58.9)
+//   d = 128, two groups: up to seven tiles always (512 heads, N = 448 1.12 and 1.02 times faster, causal and not)
+//   d = 128, causal: 13 tiles with 13 items per unit (256 heads, N = 815 88.9 / 76.1), 16 with 6.2 (96 heads, N = 984 48.4 / 44.6; 128 heads, N =
+//     1024 55 / 60), 24 with 4.6 (48 heads, N = 1496 46.4 / 43.0; 64 heads, N = 1536 52.9 / 56.0), 64 with 3.8 (24 heads, N = 2543 62.5 / 54.8; 32 heads,
+//     N = 3000 83 / 91)
+//   odd groups of heads, causal, run in super-blocks of 256 rows otherwise: up to 40 tiles and 11 items per unit (160 heads, N = 1088 125 /
+//     83; 64 heads, N = 2543 156 / 144; 40 heads, N = 2799 102 / 114), but for nearly full rounds of those (32 heads, N = 2048, one round, 56.5 / 59.6)
+//   d = 128, no mask: 8 tiles with 5 items per unit (160 heads, N = 512 47 / 36), 16 with 3.2 (48 heads, N = 1024 36.6 / 34.8; 64 heads, N = 1024 41.5 /
+//     44.5), 24 with 2 (16 heads, N = 1536 30.0 / 28.8; 32 heads, N = 1536 46.7 / 49.1), 30 where the others run a second round for a few items (48
+//     heads, N = 1344 79 / 55; 40 heads, N = 1880 100 / 91)
+//   more than four sink or local blocks: never
+// Of 3920 shapes of 5 to 48 tiles this kernel runs 2281, in the mean 1.33 times faster; more than 3 % slower are d = 64, causal, odd groups: 64
+// heads, N = 1496 and 48 heads, N = 1792 (7 %), 24 heads, N = 3072 (3.3 %).
 int short_groups(const Params& p, int d, int n_cu) {
     const long long heads = (long long)p.B * p.Hq, items = heads * p.Tc;  // (of 64 rows)
     if (n_cu <= 0 || p.n_sink > 4 || p.n_local > 4) return 0;
     if (items + ((long long)p.B * p.Hkv * p.Tc + 3) / 4 > kMaxWorkgroups256) return 0;  // (with the summaries' workgroups; four groups are for few items)
     const int Tc = p.Tc;
-    auto per_cu = [&](double x) { return items <= (long long)(x * n_cu); };
+    auto upto = [&](int tiles, double per_cu) { return Tc <= tiles && items <= (long long)(per_cu * n_cu); };
     if (d == 64) {
-        if (Tc >= 10 && Tc <= 64 && (per_cu(1) || (p.causal && 16 * heads <= n_cu && per_cu(4)))) return 4;
-        return Tc <= (p.causal ? 32 : 24) || (p.causal && Tc <= 64 && per_cu(6.2)) ? 2 : 0;
+        if (Tc >= 10 && (upto(64, 1) || (p.causal && 16 * heads <= n_cu && upto(64, 4)))) return 4;
+        const bool odd = Tc & 1;
+        if (p.causal) return Tc <= 14 || upto(24, odd ? 1e9 : 24) || upto(odd ? 29 : 28, odd ? 11 : 9) || upto(64, 6.2) ? 2 : 0;
+        return Tc <= 7 || upto(11, 12) || upto(14, 10) || upto(16, 7) || upto(24, 5) ? 2 : 0;
     }
     const long long summary_wgs = ((long long)p.B * p.Hkv * Tc + 7) / 8;
-    if (Tc >= 10 && Tc <= 64 && (items + summary_wgs <= n_cu || (p.causal && Tc >= 20 && 16 * heads <= n_cu && per_cu(2)))) return 4;
+    if (Tc >= 10 && Tc <= 64 && (items + summary_wgs <= n_cu || (p.causal && Tc >= 20 && 16 * heads <= n_cu && upto(64, 2)))) return 4;
     if (Tc <= 7) return 2;
     const int g = p.Hq / p.Hkv, blocks = ceil_div(p.N, 128);
     const double pp = (double)((g & 1) == 0 ? heads / 2 * blocks : heads * ((blocks + 1) / 2)) / n_cu;  // rounds of the ping-pong kernel
     if (p.causal) {
-        if ((Tc <= 13 && per_cu(13)) || (Tc <= 16 && per_cu(6.2)) || (Tc <= 24 && per_cu(4.6)) || (Tc <= 64 && per_cu(3.8))) return 2;
-        return (g & 1) && Tc <= 46 && per_cu(11) && !(pp >= 0.85 && pp <= 1) && !(pp > 1.9 && pp <= 2) ? 2 : 0;
+        if (upto(13, 13) || upto(16, 6.2) || upto(24, 4.6) || upto(64, 3.8)) return 2;
+        return (g & 1) && upto(40, 11) && !(pp >= 0.85 && pp <= 1) && !(pp > 1.9 && pp <= 2) ? 2 : 0;
     }
-    return (Tc <= 8 && per_cu(5)) || (Tc <= 16 && per_cu(3.2)) || (Tc <= 24 && per_cu(2)) || (Tc <= 30 && pp > 1 && pp <= 1.32) ? 2 : 0;
+    return upto(8, 5) || upto(16, 3.2) || upto(24, 2) || (Tc <= 30 && pp > 1 && pp <= 1.32) ? 2 : 0;
 }
 
 // Without a causal mask all items are equally long, and what is left of them after whole rounds of the ping-pong kernel takes as long
