@@ -47,3 +47,21 @@ def check_o_lse(O_gpu, L_gpu, ref_O, ref_L, blocks, block_m, N, what=""):
     stats = dict(max_abs=float(err.max()), mean_abs=float(err.mean()), lse=float(lerr))
     assert stats["max_abs"] <= O_MAX_ABS and stats["mean_abs"] <= O_MEAN_ABS and stats["lse"] <= LSE_ABS, (what, stats)
     return stats
+
+
+def check_every_row(Q, K, V, O, L, causal):
+    """All rows of all heads against exact attention in 64 bits, element by element: a weight is off by up to 2^-8 of itself (bf16), so O by
+    2^-8 of the same average of |v|, and by 2^-8 of itself for its own rounding (and 1e-4 for the sums in 32 bits)."""
+    import torch
+    B, Hq, N, d = Q.shape
+    for b in range(B):
+        for h in range(Hq):
+            k, v = K[b, h * K.shape[1] // Hq].double(), V[b, h * K.shape[1] // Hq].double()
+            S = Q[b, h].double() @ k.T * d ** -0.5
+            if causal:
+                S.masked_fill_(torch.ones(N, N, dtype=torch.bool, device=S.device).triu(1), -float("inf"))
+            l = S.logsumexp(1)
+            P = (S - l[:, None]).exp()
+            o = P @ v
+            assert ((O[b, h].double() - o).abs() <= 2.0 ** -8 * (P @ v.abs() + o.abs()) + 1e-4).all(), (b, h)
+            assert (L[b, h].double() - l).abs().max() <= LSE_ABS, (b, h)

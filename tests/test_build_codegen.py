@@ -71,8 +71,8 @@ def test_inner_loops_have_no_scratch_access(other_kernels):
         for seg in tiles:
             assert not any("scratch_" in x for x in seg), m.group(1)
         seen.append(kernel.group(1))
-    assert {"attn_fwd_pp_kernel", "attn_fwd_frozen_kernel", "attn_fwd_kernel", "attn_fp8_kernel", "attn_mx4_kernel",
-            "decode_split_kernel"} <= set(seen), seen
+    assert {"attn_fwd_pp_kernel", "attn_fwd_frozen_kernel", "attn_fwd_short_kernel", "attn_fwd_kernel", "attn_fp8_kernel",
+            "attn_mx4_kernel", "decode_split_kernel"} <= set(seen), seen
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")

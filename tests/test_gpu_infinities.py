@@ -12,7 +12,8 @@ def _empty(O, L, what):
     assert (O == 0).all() and torch.isneginf(L).all(), what
 
 
-# every row's blocks are sink or local ones, where all kernels take the exact max; at 600 rows the others too, on attn_frozen.hpp
+# every row's blocks are sink or local ones, where all kernels take the exact max; at 600 rows the others too: vfa_attn_fwd runs on
+# attn_short.hpp, vfa_variant_fwd on attn_frozen.hpp
 @pytest.mark.parametrize("d,block_m", [(64, 64), (64, 128), (128, 64), (128, 128)])
 @pytest.mark.parametrize("B,Hq,Hkv,N,kw", [(1, 4, 2, 128, {}), (2, 32, 8, 100, {}), (1, 32, 2, 300, dict(n_local=4)),
                                           (1, 32, 2, 300, dict(n_local=4, use_minit=False)), (1, 4, 2, 300, dict(n_sink=5)),
@@ -40,6 +41,9 @@ def _infinite_feature(d, block_m, B, Hq, Hkv, N, kw):
     O, L = vfa.vfa_attn_fwd(Q, K, V, block_m=block_m, **kw)
     _empty(O[:, :g], L[:, :g], "vfa")
     assert torch.equal(O[:, g:], clean[0][:, g:]) and torch.equal(L[:, g:], clean[1][:, g:])
+    O, L, _ = vfa.vfa_variant_fwd(Q, K, V, block_m=block_m, **kw)
+    _empty(O[:, :g], L[:, :g], "vfa_variant")
+    assert torch.isfinite(O[:, g:].float()).all() and torch.isfinite(L[:, g:]).all()
     O, L = vfa.fa_baseline_fwd(Q, K, V, block_m=block_m, causal=kw.get("causal", True))
     _empty(O[:, :g], L[:, :g], "fa")
     q = Q[:, :, -1].contiguous()

@@ -52,9 +52,11 @@ def test_rows64(oracle, B, Hq, Hkv, N, causal):
     assert (outs[0][1] - outs[1][1]).abs().max().item() <= 2e-3
 
 
-# (what the call runs on at d = 128: the kernel of attn_frozen.hpp, the ping-pong kernel in head pairs, in block pairs, the
-# generic kernel), one row of the list for each; the same calls at d = 64
-LATER = [(1, 8, 2, 777, {}), (1, 4, 2, 1100, dict(n_sink=5)), (1, 3, 1, 1100, dict(n_sink=5)), (1, 3, 3, 1000, dict(n_sink=5, n_local=2)),
+# What vfa_attn_fwd runs on at d = 128: attn_short.hpp (n_sink <= 4 and up to 777 rows), the ping-pong kernel in head pairs, in block
+# pairs, the generic kernel (n_sink = 5), attn_frozen.hpp (4200 rows; 2113 rows at d = 64, in one group of keys, and 4200 in two).
+# vfa_variant_fwd, the same call, keeps to the kernels with a fixed max: attn_frozen.hpp for the short ones.
+LATER = [(2, 32, 8, 2113, dict(n_sink=1)), (1, 4, 2, 4200, dict(n_sink=1)),
+         (1, 8, 2, 777, {}), (1, 4, 2, 1100, dict(n_sink=5)), (1, 3, 1, 1100, dict(n_sink=5)), (1, 3, 3, 1000, dict(n_sink=5, n_local=2)),
          (3, 32, 8, 320, {}), (5, 32, 32, 200, {}), (1, 8, 2, 128, dict(n_sink=0)), (1, 8, 2, 640, dict(n_sink=0, n_local=0))]
 
 
@@ -74,6 +76,7 @@ def test_a_block_of_64_rows_does_not_see_the_next_one(d, B, Hq, Hkv, N, kw):
              "softexp": lambda k, v: vfa.fa_lazy_rescale_softexp_fwd(Q, k, v, block_m=64)}
     if kw:
         calls = {"vfa": calls["vfa"]}
+    calls["variant"] = lambda k, v: vfa.vfa_variant_fwd(Q, k, v, block_m=64, **kw)[:2]
     Tc = -(-N // 64)
     for what, call in calls.items():
         O, L = call(K, V)
