@@ -122,27 +122,9 @@ __global__ __launch_bounds__(256 * KS, (Frozen<D, KS>::TIGHT ? 3 : 2)) void attn
     // `rows` rows (0 to BN, a negative number counts as 0) at address a to LDS byte `at`
     auto request = [&](uint64_t a, int rows, const uint32_t o0, const uint32_t o1, const uint32_t o2, const uint32_t o3, uint32_t at)
                        __attribute__((always_inline)) {
-        const u32x4 rsrc = {(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a), (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)),
-                            (uint32_t)__builtin_amdgcn_readfirstlane(min(max(rows, 0), BN) * T::ROWB), 0x00020000u};
-        const uint32_t l0 = __builtin_amdgcn_readfirstlane(lds0 + at);
-        uint32_t m0_save;  // (the compiler's own value of M0 is put back at the end)
-        if (LI == 4)
-            asm volatile(
-                "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                "buffer_load_dwordx4 %2, %6, 0 offen lds\n\tbuffer_load_dwordx4 %3, %6, 0 offen offset:1024 lds\n\t"
-                "buffer_load_dwordx4 %4, %6, 0 offen offset:2048 lds\n\tbuffer_load_dwordx4 %5, %6, 0 offen offset:3072 lds\n\t"
-                "s_mov_b32 m0, %0"
-                : "=&s"(m0_save)
-                : "s"(l0), "v"(o0), "v"(o1), "v"(o2), "v"(o3), "s"(rsrc)
-                : "memory");
-        else
-            asm volatile(
-                "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                "buffer_load_dwordx4 %2, %4, 0 offen lds\n\tbuffer_load_dwordx4 %3, %4, 0 offen offset:1024 lds\n\t"
-                "s_mov_b32 m0, %0"
-                : "=&s"(m0_save)
-                : "s"(l0), "v"(o0), "v"(o1), "s"(rsrc)
-                : "memory");
+        const uint32_t bytes = min(max(rows, 0), BN) * T::ROWB;
+        if (LI == 4) request4(a, bytes, o0, o1, o2, o3, lds0 + at);
+        else request2(a, bytes, o0, o1, lds0 + at);
     };
     auto tile_addr = [&](const uint16_t* base, int j) __attribute__((always_inline)) {
         return (uint64_t)(uintptr_t)base + (uint64_t)(uint32_t)j * (BN * T::ROWB);

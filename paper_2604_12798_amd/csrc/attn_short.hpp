@@ -105,27 +105,9 @@ __global__ __launch_bounds__(128 * KQ, 2) void attn_fwd_short_kernel(const Param
         (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)(short_smem + wave * LI * 1024));
     auto request = [&](const uint16_t* base, int s, const uint32_t* o, uint32_t at) __attribute__((always_inline)) {
         const uint64_t a = (uint64_t)(uintptr_t)base + (uint64_t)(uint32_t)s * (uint32_t)F::SLOT;
-        const u32x4 rsrc = {(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a), (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)),
-                            (uint32_t)__builtin_amdgcn_readfirstlane(min(max(N - s * KT, 0), KT) * T::ROWB), 0x00020000u};
-        const uint32_t l0 = __builtin_amdgcn_readfirstlane(lds0 + at);
-        uint32_t m0_save;  // (the compiler's own value of M0 is put back at the end)
-        if constexpr (LI == 4)
-            asm volatile(
-                "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                "buffer_load_dwordx4 %2, %6, 0 offen lds\n\tbuffer_load_dwordx4 %3, %6, 0 offen offset:1024 lds\n\t"
-                "buffer_load_dwordx4 %4, %6, 0 offen offset:2048 lds\n\tbuffer_load_dwordx4 %5, %6, 0 offen offset:3072 lds\n\t"
-                "s_mov_b32 m0, %0"
-                : "=&s"(m0_save)
-                : "s"(l0), "v"(o[0]), "v"(o[1]), "v"(o[2]), "v"(o[3]), "s"(rsrc)
-                : "memory");
-        else
-            asm volatile(
-                "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                "buffer_load_dwordx4 %2, %4, 0 offen lds\n\tbuffer_load_dwordx4 %3, %4, 0 offen offset:1024 lds\n\t"
-                "s_mov_b32 m0, %0"
-                : "=&s"(m0_save)
-                : "s"(l0), "v"(o[0]), "v"(o[1]), "s"(rsrc)
-                : "memory");
+        const uint32_t bytes = min(max(N - s * KT, 0), KT) * T::ROWB;
+        if constexpr (LI == 4) request4(a, bytes, o[0], o[1], o[2], o[3], lds0 + at);
+        else request2(a, bytes, o[0], o[1], lds0 + at);
     };
     auto request_k = [&](int s) __attribute__((always_inline)) { request(Kg, s, offK, (uint32_t)(s % 3) * F::SLOT); };
     auto request_v = [&](int s) __attribute__((always_inline)) { request(Vg, s, offV, (uint32_t)(3 + (s & 1)) * F::SLOT); };

@@ -218,6 +218,49 @@ __device__ __forceinline__ void load_tile(const uint16_t* base, int first_row, i
     }
 }
 
+// A tile by buffer loads into LDS: the buffer is the tile (`bytes` of it: what lies past the end of the sequence is out of its range
+// and LDS gets zeros), the lanes' offsets are fixed for the whole kernel, and the instruction offset moves both sides, so M0 (the
+// LDS base of such a load) is set once and a request costs a few scalar instructions (lane by lane it was 30 of the 110 to 130 vector
+// instructions of an 8-bit tile).  Four adjacent pieces of 1 KiB; two; one; 64 dwords.  `lds` is the byte address of the first piece.
+__device__ __forceinline__ u32x4 tile_buffer(uint64_t base, uint32_t bytes) {
+    return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)base), (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)),
+                 (uint32_t)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u};
+}
+__device__ __forceinline__ void request4(uint64_t base, uint32_t bytes, uint32_t o0, uint32_t o1, uint32_t o2, uint32_t o3, uint32_t lds) {
+    const u32x4 rsrc = tile_buffer(base, bytes);
+    const uint32_t l0 = __builtin_amdgcn_readfirstlane(lds);
+    uint32_t m0_save;  // (the compiler's own value of M0 is put back at the end)
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %2, %6, 0 offen lds\n\tbuffer_load_dwordx4 %3, %6, 0 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %4, %6, 0 offen offset:2048 lds\n\tbuffer_load_dwordx4 %5, %6, 0 offen offset:3072 lds\n\t"
+                 "s_mov_b32 m0, %0"
+                 : "=&s"(m0_save)
+                 : "s"(l0), "v"(o0), "v"(o1), "v"(o2), "v"(o3), "s"(rsrc)
+                 : "memory");
+}
+__device__ __forceinline__ void request2(uint64_t base, uint32_t bytes, uint32_t o0, uint32_t o1, uint32_t lds) {
+    uint32_t m0_save;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %4, 0 offen lds\n\t"
+                 "buffer_load_dwordx4 %3, %4, 0 offen offset:1024 lds\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0_save)
+                 : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(o0), "v"(o1), "s"(tile_buffer(base, bytes))
+                 : "memory");
+}
+__device__ __forceinline__ void request1(uint64_t base, uint32_t bytes, uint32_t o0, uint32_t lds) {
+    uint32_t m0_save;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0_save)
+                 : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(o0), "s"(tile_buffer(base, bytes))
+                 : "memory");
+}
+__device__ __forceinline__ void request_dwords(uint64_t base, uint32_t bytes, uint32_t o0, uint32_t lds) {
+    uint32_t m0_save;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dword %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0_save)
+                 : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(o0), "s"(tile_buffer(base, bytes))
+                 : "memory");
+}
+
 // S^T tile: st[t][i] = raw score of query ql against key 32*t + 8*(i/4) + 4*hh + (i%4)
 template <int D>
 __device__ __forceinline__ void qk_tile(const uint8_t* kt, const bf16x8* qf, f32x16* st, int ql, int hh) {

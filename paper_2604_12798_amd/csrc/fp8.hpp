@@ -78,35 +78,6 @@ __device__ __forceinline__ void load_tile8(const uint8_t* base, int first_row, i
     }
 }
 
-// A tile by buffer loads into LDS: the buffer is the tile (`bytes` of it: what lies past the end of the sequence is out of its range
-// and LDS gets zeros), the lanes' offsets are fixed for the whole kernel, and the instruction offset moves both sides, so a request costs
-// a few scalar instructions (lane by lane it was 30 of the 110 to 130 vector instructions of a tile).  Two adjacent pieces of 1 KiB; one; 64 dwords.
-__device__ __forceinline__ u32x4 tile_buffer(uint64_t base, uint32_t bytes) {
-    return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)base), (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)),
-                 (uint32_t)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u};
-}
-__device__ __forceinline__ void request2(uint64_t base, uint32_t bytes, uint32_t o0, uint32_t o1, uint32_t lds) {
-    uint32_t m0_save;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %4, 0 offen lds\n\t"
-                 "buffer_load_dwordx4 %3, %4, 0 offen offset:1024 lds\n\ts_mov_b32 m0, %0"
-                 : "=&s"(m0_save)
-                 : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(o0), "v"(o1), "s"(tile_buffer(base, bytes))
-                 : "memory");
-}
-__device__ __forceinline__ void request1(uint64_t base, uint32_t bytes, uint32_t o0, uint32_t lds) {
-    uint32_t m0_save;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
-                 : "=&s"(m0_save)
-                 : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(o0), "s"(tile_buffer(base, bytes))
-                 : "memory");
-}
-__device__ __forceinline__ void request_dwords(uint64_t base, uint32_t bytes, uint32_t o0, uint32_t lds) {
-    uint32_t m0_save;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dword %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
-                 : "=&s"(m0_save)
-                 : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(o0), "s"(tile_buffer(base, bytes))
-                 : "memory");
-}
 __device__ __forceinline__ uint32_t lds_address(const uint8_t* p) {
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t*)p;
 }
