@@ -802,7 +802,7 @@ int fp8_common(int frozen, bool noexp, const void* Q8, const void* K8, const voi
         const float mant = frexpf(p.c, &ex);  // p.c = mant * 2^ex, mant in [0.5, 1)
         if (fabsf(mant - 0.5f) <= 0x1p-18f && ex - 1 >= -100 && ex - 1 <= 100) {
             fold = true;
-            p.scale_a = (127 + ex - 1) * 0x01010101;
+            p.scale_a = (int)((uint32_t)(127 + ex - 1) * 0x01010101u);
             p.c = 1.f;
         }
     }
