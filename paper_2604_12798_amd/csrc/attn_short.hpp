@@ -25,8 +25,8 @@ namespace {
 // a SIMD, 2500 cycles for 64 rows x 128 keys against 1024 of MFMA, and the 64 KiB of tiles they take (twice the bytes per row of
 // the 128-row kernels), which is why longer sequences stay with those.
 // KQ = 2: two workgroups per compute unit (80 KiB each at d = 128).  KQ = 4: one, for grids of no more items than compute units.
-// Calls in us, before and after: d = 128, 32 heads over 8, causal, N = 128 13.1 / 6.8, 512 18.1 / 10.3, 777 21.1 / 14.0, 1024 24.0 /
-// 17.6; 8 heads over 1, N = 2048 33.0 / 20.9 (KQ = 4); 160 heads, N = 320 36.5 / 19.7; d = 64, 32 heads over 8, N = 777 15.0 / 10.3.
+// Calls in us, without it and with it: d = 128, 32 heads over 8, causal, N = 200 14.4 / 7.3, 512 18.5 / 10.3, 777 22.2 / 15.2, 1024 24.4 /
+// 17.5; 8 heads over 2, N = 2048 33.2 / 20.6 (KQ = 4); 160 heads, N = 320 36.7 / 19.3; d = 64, 32 heads over 8, N = 777 15.3 / 10.2.
 constexpr float kKeepMax = 8.f;
 
 template <int D, int KQ>

@@ -169,8 +169,8 @@ int short_groups(const Params& p, int d, int n_cu) {
 // Without a causal mask all items are equally long, and what is left of them after whole rounds of the ping-pong kernel takes as long
 // as a round: the first row of that rest, which then runs on a kernel of finer items (a head's last rows: no more than one item per
 // compute unit, of 64 rows with the keys split four ways, attn_short.hpp, else, where the items are long, of 128 rows, attn_frozen.hpp), or 0.
-// In us, before / after: 16 heads, N = 5000 (one round and 904 rows) 244 / 221; 24 heads, N = 2986 143 / 120; 32 heads, N = 3000
-// (rest on attn_frozen.hpp) 161 / 152; 48 heads, N = 1751 96 / 101 with that, so only above 32 tiles.
+// In us, before / after: 16 heads, N = 5000 (one round and 904 rows) 222 / 197; 24 heads, N = 3000 141 / 119; 32 heads, N = 3000
+// (rest on attn_frozen.hpp) 149 / 144; 48 heads, N = 1751 96 / 101 with that, so only above 32 tiles.
 int tail_row(const Params& p, int n_cu, bool head_pairs) {
     if (p.causal || p.n_sink > 4 || p.n_local > 4 || n_cu <= 0 || p.Tc <= 12) return 0;
     const long long heads = (long long)p.B * p.Hq, per_band = head_pairs ? heads / 2 : heads;  // items of `band` rows
@@ -209,7 +209,7 @@ bool prefer_frozen(const Params& p, int n_cu, bool has_tail) {
 //     16 and two and a half (128 heads, N = 384 17.1 / 21.8; 96 heads, N = 777 40.9 / 45.4, N = 1024 57.5 / 47.4)
 // 645 shapes of each, against the generic kernel alone: slower by more than 2 % are Alg. 1, causal, 96 heads, N = 640 to 768 (3.5
 // to 6.3 %) and 72 heads, N = 777 (6.7 %), and the baseline, 128 heads, N = 700 (10 %); the mean is 27 and 13 % faster.  (Alg. 1's of
-// four tiles, and its causal ones, are those with many sink or local blocks: the rest are short ones by now.)
+// four tiles, and its causal ones, are those with many sink or local blocks and vfa_variant_fwd's: the rest are short ones by now.)
 bool prefer_rows64(const Params& p, int n_cu, bool head_pairs, bool frozen, bool baseline) {
     if (n_cu <= 0) return false;
     const long long heads = (long long)p.B * p.Hq, items = heads * p.Tc, slots = 2LL * n_cu;
