@@ -9,10 +9,10 @@ namespace {
 // ---------------------------------------------------------------------------------------------
 // On a short sequence the fixed max of Alg. 1 costs more than it saves: a launch of its own for the summaries (3 - 5 us), one more
 // tile product for them and for the sink and local blocks, and items long enough to pay for both.  Here every block's scores
-// enter the max exactly (all blocks are what Alg. 1 calls special ones), each wave keeping a max of its own, which it moves
-// only when a row exceeds it by more than kKeepMax, so that the rescale of O is rare; the weights are exp2(s - m - kKeepMax), at
+// enter the max exactly (all blocks are what Alg. 1 calls special ones), each wave keeping a reference of its own, m2, the max plus
+// kKeepMax, which it moves only when a row's max passes it, so that the rescale of O is rare; the weights are exp2(s - m2), at
 // most 1, and sums of large values overflow no sooner than elsewhere.  The
-// waves' sums are weighted by exp2(m - largest m) when they meet in LDS.  The summaries, which the caller may want
+// waves' sums are weighted by exp2(m2 - largest m2) when they meet in LDS.  The summaries, which the caller may want
 // from the workspace, are written by workgroups behind the items, of the same launch.
 //
 // A step is 32 KQ keys; wave (rw, kq) multiplies the 32 keys of group kq with rows 32 rw .. 32 rw + 31, so all waves are busy however few
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(128 * KQ, 2) void attn_fwd_short_kernel(const Param
             for (int r = 2 + 14 * e / H; r < 2 + 14 * (e + 1) / H; ++r) mx[r & 1] = fmaxf(mx[r & 1], st[r]);
             if (NEXT) __builtin_amdgcn_sched_barrier(0);
         }
-        const float m_new = fmaxf(m2, xhalf_max(fmaxf(mx[0], mx[1])) * p.c);
+        const float m_new = fmaxf(m2, __builtin_fmaf(xhalf_max(fmaxf(mx[0], mx[1])), p.c, kKeepMax));
         if (__builtin_amdgcn_ballot_w64(!(m_new <= m2 + kKeepMax)) != 0) {
             const float msub = m_new == -INFINITY ? 0.f : m_new;
             const float alpha = __builtin_amdgcn_exp2f(m2 - msub);
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(128 * KQ, 2) void attn_fwd_short_kernel(const Param
             for (int db = 0; db < DB; ++db) ot[db] *= alpha;
             m2 = m_new;
         }
-        const float msub = m2 == -INFINITY ? 0.f : m2 + kKeepMax;
+        const float msub = m2 == -INFINITY ? 0.f : m2;
         uint32_t pk[8];
         auto slice = [&](int q) __attribute__((always_inline)) {
             const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(st[2 * q], p.c, -msub));
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(128 * KQ, 2) void attn_fwd_short_kernel(const Param
     auto finish = [&](auto kq_c) __attribute__((always_inline)) {
         constexpr int KO = decltype(kq_c)::value;
         if (qrow < N && p.LSE && KO == 0 && hh == 0)
-            p.LSE[(size_t)(b * p.Hq + h) * N + qrow] = l > 0.f ? (m + kKeepMax + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
+            p.LSE[(size_t)(b * p.Hq + h) * N + qrow] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
         uint16_t* const Og = p.O + ((size_t)(b * p.Hq + h) * N + qrow_c) * D;
 #pragma unroll
         for (int v = 0; v < OWN; ++v) {
