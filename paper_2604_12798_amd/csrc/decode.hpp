@@ -294,12 +294,13 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void decode_split_kernel(c
 // One workgroup per query head: D / 4 threads read a partial row (16 bytes each), 1024 / D rows at a time and four such
 // rounds in flight, each group of threads with a running max of its own; the groups meet in LDS.  The order of the sums is
 // fixed.  (One thread per output element walking the ranges one by one took 8.6 us for 32 heads of 32
-// ranges and 6.3 us for 128 heads of 16, a chain of load latencies; this takes 2.8 and 4.8.)
+// ranges and 6.3 us for 128 heads of 16, a chain of load latencies; with loads behind branches and a division in front this took 3.0 and
+// 5.0, now 2.7 and 4.8.)
 template <int D, bool DEALT>
 __global__ __launch_bounds__(256) void decode_merge_kernel(const DecodeParams p) {
     constexpr int C4 = D / 4, NG = 256 / C4, U = 4;
     __shared__ float xo[NG][D], xm[NG], xl[NG];
-    const int row = blockIdx.x, b = row / p.Hq, h = row - b * p.Hq;
+    const int h = blockIdx.x, b = blockIdx.y, row = b * p.Hq + h;
     const int c4 = threadIdx.x % C4, gr = threadIdx.x / C4;
     int first = b * p.n_splits, nb = p.n_splits;
     if (DEALT) {
@@ -307,18 +308,29 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const DecodeParams p)
         first = rg.first;
         nb = rg.nb;
     }
+    const float* const pm0 = p.pm + (size_t)first * p.Hq + h;
+    const float* const pl0 = p.lpart + (size_t)first * p.Hq + h;
+    const float* const po0 = p.opart + ((size_t)first * p.Hq + h) * D + 4 * c4;
     float m = -INFINITY, l = 0.f;
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
-    for (int s0 = gr; s0 < nb; s0 += U * NG) {
+    // (every group makes a round, and a load past the last range reads the last one again: no load sits behind a branch)
+    int s0 = 0;
+    do {
         float pm[U], pl[U];
         f32x4 po[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const bool live = s0 + u * NG < nb;
-            const size_t slot = (size_t)(first + min(s0 + u * NG, nb - 1)) * p.Hq + h;
-            pm[u] = live ? p.pm[slot] : -INFINITY;
-            pl[u] = live ? p.lpart[slot] : 0.f;
-            po[u] = live ? *reinterpret_cast<const f32x4*>(p.opart + slot * D + 4 * c4) : f32x4{0.f, 0.f, 0.f, 0.f};
+            const size_t at = (size_t)min(s0 + u * NG + gr, nb - 1) * p.Hq;
+            pm[u] = pm0[at];
+            pl[u] = pl0[at];
+            po[u] = *reinterpret_cast<const f32x4*>(po0 + at * D);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool live = s0 + u * NG + gr < nb;
+            pm[u] = live ? pm[u] : -INFINITY;
+            pl[u] = live ? pl[u] : 0.f;
+            po[u] = live ? po[u] : f32x4{0.f, 0.f, 0.f, 0.f};
         }
         float mn = m;
 #pragma unroll
@@ -334,7 +346,8 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const DecodeParams p)
             o += a * po[u];
         }
         m = mn;
-    }
+        s0 += U * NG;
+    } while (s0 < nb);
     *reinterpret_cast<f32x4*>(&xo[gr][4 * c4]) = o;
     if (c4 == 0) { xm[gr] = m; xl[gr] = l; }
     __syncthreads();

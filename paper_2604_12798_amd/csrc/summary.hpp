@@ -7,9 +7,11 @@ namespace {
 // ---------------------------------------------------------------------------------------------
 // Key-block summary (Alg. 1, first loop): per dimension the element of largest magnitude of the block's keys with its
 // sign, ties to the positive value.  HBM bound: K is read once.  One WAVE per key block, four blocks per workgroup:
-// a lane owns one 16-byte chunk of every RG-th row, issues its loads eight at a time (no loop-carried dependence
-// between them), reduces in registers, and the RG lanes of a chunk combine through lane exchanges: no LDS, no
-// barrier, 128 bytes per lane in flight.
+// a lane owns one 16-byte chunk of every RG-th row, issues the loads of 64 rows together, none behind a branch, reduces in registers,
+// and the RG lanes of a chunk combine through lane exchanges: no LDS, no barrier, 256 bytes per lane in flight at d = 128.
+// A launch for a few blocks (a decode step's) is a chain of latencies: with eight predicated loads at a time and exchanges through the
+// LDS unit it took 3.6 us for 8 blocks of 2048 keys' cache and 4.6 for 128 at d = 64, now 3.0 and 3.9 (an empty kernel takes 1.5);
+// 4 x 8 heads of 32768 keys 5.0 / 4.8.
 // Works on bf16 bit patterns, two to a dword: the key (magnitude << 1) | (sign ? 0 : 1) orders elements by magnitude
 // and, at equal magnitude, puts the positive one on top, so the pick is an unsigned 16-bit maximum of keys.
 typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
@@ -19,36 +21,54 @@ __device__ inline uint32_t key_max(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
 }
 
+// max of keys with the lane 8, 16 or 32 further (which trades places with it)
+template <int M>
+__device__ __forceinline__ uint32_t key_max_across(uint32_t x) {
+    if constexpr (M == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return key_max(r[0], r[1]);
+    } else if constexpr (M == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return key_max(r[0], r[1]);
+    } else {
+        static_assert(M == 8, "rotations within rows of 16 lanes");
+        return key_max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false));  // row_ror:8
+    }
+}
+
 // N = row stride of one head's key array (its capacity), n_valid = keys present, Tc = block stride of
-// one head's summary array.
+// one head's summary array.  bh and j are the same for all lanes; `live`: write the result.
 template <int D>
 __device__ __forceinline__ void summary_of_block(const uint16_t* __restrict__ K, uint16_t* __restrict__ R, int bh, int j, int N,
-                                                 int n_valid, int Tc, int block_n, int lane) {
+                                                 int n_valid, int Tc, int block_n, int lane, bool live = true) {
     constexpr int CH = D / 8;        // 16-byte chunks per row
     constexpr int RG = 64 / CH;      // rows a wave reads at once
+    constexpr int NL = BN / RG;      // such reads in flight: 64 rows
     const int ch = lane % CH, rg = lane / CH;
     const int c0 = j * block_n, c1 = min(n_valid, c0 + block_n);
-    const uint16_t* base = K + (size_t)bh * N * D + ch * 8;
+    const uint8_t* base = reinterpret_cast<const uint8_t*>(K) + ((size_t)bh * N + c0) * (2 * D);
     const uint32_t zero_key = sabs_key(0u);  // +0: the smallest magnitude, already the positive one
     u32x4 acc = {zero_key, zero_key, zero_key, zero_key};
-    for (int r0 = c0 + rg; r0 < c1; r0 += 8 * RG) {
-        u32x4 x[8];
+    for (int r0 = c0; r0 < c1; r0 += BN, base += BN * 2 * D) {
+        u32x4 x[NL];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int r = r0 + u * RG;
-            // (non-temporal: a streaming read; 10 % faster at 64 MiB of keys, no change to the attention kernel behind it)
-            x[u] = r < c1 ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (size_t)r * D)) : u32x4{0, 0, 0, 0};
+        for (int u = 0; u < NL; ++u) {
+            // (past the end the last row is read again, which changes no maximum: no load sits behind a branch.  Non-temporal: a
+            // streaming read; 10 % faster at 64 MiB of keys, no change to the attention kernel behind it)
+            const uint32_t r = (uint32_t)min(rg + u * RG, c1 - 1 - r0);
+            x[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (r * (2 * D) + ch * 16)));
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
+        for (int u = 0; u < NL; ++u)
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[e] = key_max(acc[e], sabs_key(x[u][e]));
     }
 #pragma unroll
-    for (int m = CH; m < 64; m <<= 1)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] = key_max(acc[e], (uint32_t)__shfl_xor((int)acc[e], m));
-    if (rg == 0) {
+    for (int e = 0; e < 4; ++e) {
+        if constexpr (CH == 8) acc[e] = key_max_across<8>(acc[e]);
+        acc[e] = key_max_across<32>(key_max_across<16>(acc[e]));
+    }
+    if (rg == 0 && live) {
         const u32x4 out = {sabs_unkey(acc[0]), sabs_unkey(acc[1]), sabs_unkey(acc[2]), sabs_unkey(acc[3])};
         *reinterpret_cast<u32x4*>(R + ((size_t)bh * Tc + j) * D + ch * 8) = out;
     }
@@ -58,8 +78,10 @@ __device__ __forceinline__ void summary_of_block(const uint16_t* __restrict__ K,
 template <int D>
 __global__ __launch_bounds__(256) void kblock_summary_kernel(const uint16_t* __restrict__ K, uint16_t* __restrict__ R,
                                                              int N, int n_valid, int Tc, int block_n, int j0, int n_blocks) {
-    const int lane = threadIdx.x & 63, jb = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (jb < n_blocks) summary_of_block<D>(K, R, blockIdx.y, j0 + jb, N, n_valid, Tc, block_n, lane);
+    // (a wave without a block does the last one again and writes nothing: no branch in front of the loads, whose latency is all there is of a
+    // launch for a few blocks)
+    const int lane = threadIdx.x & 63, jb = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    summary_of_block<D>(K, R, blockIdx.y, j0 + min(jb, n_blocks - 1), N, n_valid, Tc, block_n, lane, jb < n_blocks);
 }
 
 // With per-sequence lengths (device arrays indexed by batch entry, Hkv heads each) the host does not know which blocks received
@@ -76,7 +98,7 @@ template <int D, int E>
 __global__ __launch_bounds__(E ? 256 : 1024) void kblock_summary_varlen_kernel(const uint16_t* __restrict__ K, uint16_t* __restrict__ R,
                                                                                int B, int Hkv, int N, int Tc, int block_n,
                                                                                const int* __restrict__ old_len,
-                                                                               const int* __restrict__ new_len) {
+                                                                               const int* __restrict__ new_len, int n_wg) {
     constexpr int NW = E ? 4 : 16, T = 64 * NW, C = E ? E : 1;
     __shared__ int upto[E ? 1 : T], wave_upto[16];  // blocks of one head: of the entries of the threads, of the waves up to one
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -115,7 +137,7 @@ __global__ __launch_bounds__(E ? 256 : 1024) void kblock_summary_varlen_kernel(c
         total = __builtin_amdgcn_readlane(waves_upto, NW - 1);
     }
     total *= Hkv;
-    for (int item = blockIdx.x * NW + wave; item < total; item += gridDim.x * NW) {
+    for (int item = blockIdx.x * NW + wave; item < total; item += n_wg * NW) {
         int bh = 0, j = 0, nv = 0;
         // the item's entry: b0 + l * stride, l the first lane whose sum lies behind the item
         auto found = [&](int e, int b0, int stride) __attribute__((always_inline)) {

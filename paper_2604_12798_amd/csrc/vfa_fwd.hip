@@ -598,7 +598,7 @@ int vfa_kblock_summary_append_varlen(const void* K, void* Krepr, int B, int Hkv,
         constexpr int E = decltype(e_c)::value, NW = E ? 4 : 16;
         const long long wgs = min(((long long)B * Hkv * tc_cap + NW - 1) / NW, (long long)(APPEND_WAVES / NW));
         kblock_summary_varlen_kernel<decltype(d_c)::value, E><<<(unsigned)wgs, 64 * NW, 0, s>>>(
-            (const uint16_t*)K, (uint16_t*)Krepr, B, Hkv, n_cap, tc_cap, block_n, old_lens, new_lens);
+            (const uint16_t*)K, (uint16_t*)Krepr, B, Hkv, n_cap, tc_cap, block_n, old_lens, new_lens, (int)wgs);
     };
     auto launch_d = [&](auto d_c) {
         if (B <= 64) launch(d_c, std::integral_constant<int, 1>{});
@@ -687,8 +687,8 @@ int decode_common(const void* Q, const void* K, const void* V, const void* Krepr
             if (!launched) decode_split_kernel<D, W, LENS_FIXED><<<dim3((unsigned)n_splits, (unsigned)Hkv, (unsigned)B), 64 * W, 0, s>>>(p);
         }
         if (n_splits == 1) return;
-        if (dealt) decode_merge_kernel<D, true><<<(unsigned)(B * Hq), 256, 0, s>>>(p);
-        else decode_merge_kernel<D, false><<<(unsigned)(B * Hq), 256, 0, s>>>(p);
+        if (dealt) decode_merge_kernel<D, true><<<dim3((unsigned)Hq, (unsigned)B), 256, 0, s>>>(p);
+        else decode_merge_kernel<D, false><<<dim3((unsigned)Hq, (unsigned)B), 256, 0, s>>>(p);
     };
     using std::integral_constant;
     if (single) {
