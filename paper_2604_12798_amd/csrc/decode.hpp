@@ -32,6 +32,7 @@ struct DecodeParams {
     uint16_t* O;            // [B, Hq, d]
     float* LSE;             // [B, Hq] or null
     int B, Hq, Hkv, n_cap, n_keys, n_splits;
+    int g, per;  // query heads per KV head; tiles of a range where the batch has one length
     const int* seq_lens;    // null, or [B] device array: valid keys per batch entry (clamped to [1, n_cap]) instead of n_keys
     float c;
 };
@@ -103,8 +104,10 @@ __device__ __forceinline__ Ranges varlen_find(const DecodeParams& p, int lane, i
 // contiguous; the swizzle is applied on the global side), and registers -> LDS at the positions the LDS-direct mover
 // writes.  The loads are non-temporal: the cache is streamed through once per step and is larger than L2 and the
 // memory-side cache, and plain loads, which allocate there, cost 12 % of the stream's rate (LDS-direct loads another 7 %).
-// A whole tile (FULL) is addressed as a wave-uniform tile base plus a per-lane 32-bit offset that repeats every 16 rows
-// (offs[u & 3]: four values for K at d = 128, one otherwise); a ragged last tile clamps its rows.
+// They are buffer loads whose buffer is the tile: rows past the last key are out of its range and give zeros, and a lane's offset
+// repeats every four instructions (offs[u & 3]), so a load costs no vector instruction, in a ragged tile as in a whole one
+// (against 64-bit addresses per lane, with the rows of every range's first tile clamped, and divisions for what the host knows: steps of
+// 4 x 8 heads of 32768 keys 89.5 / 86.9 us, 8 x 16 heads of 4001 keys, d = 64, 27.7 / 27.3, 16 sequences of up to 8192 keys 1.2 % faster).
 template <int D>
 __device__ __forceinline__ void tile_lane_offsets(bool is_v, int lane, uint32_t* offs) {
     using T = Tile<D>;
@@ -117,26 +120,15 @@ __device__ __forceinline__ void tile_lane_offsets(bool is_v, int lane, uint32_t*
         offs[u] = (uint32_t)((lane / T::CH) * T::ROWB + ch * 16);
     }
 }
-template <int D, bool FULL>
-__device__ __forceinline__ void tile_to_regs(const uint16_t* base, int first_row, int row_limit, bool is_v, int lane,
-                                             const uint32_t* offs, u32x4* r) {
+template <int D>
+__device__ __forceinline__ void tile_to_regs(const uint16_t* base, int tile, int n_keys, const uint32_t* offs, u32x4* r) {
     using T = Tile<D>;
-    constexpr int RPI = 1024 / T::ROWB, NI = BN / RPI;
-    if (FULL) {
-        const uint8_t* tb = reinterpret_cast<const uint8_t*>(base) + (size_t)first_row * T::ROWB;
+    constexpr int NI = BN / (1024 / T::ROWB);
+    uint8_t* const tb = const_cast<uint8_t*>(reinterpret_cast<const uint8_t*>(base) + (size_t)tile * T::BYTES);
+    const int bytes = __builtin_amdgcn_readfirstlane(min(max(n_keys - tile * BN, 0), BN) * T::ROWB);  // (scalar, whatever unit the clamp runs on)
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(tb, 0, bytes, 0x00020000);
 #pragma unroll
-        for (int u = 0; u < NI; ++u) r[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(tb + (u * 1024 + offs[u & 3])));
-    } else {
-        const int cp = lane % T::CH;
-#pragma unroll
-        for (int u = 0; u < NI; ++u) {
-            const int rr = RPI * u + lane / T::CH;
-            const int ch = cp ^ (is_v ? T::v_mix(rr) : T::k_mix(rr));
-            const int gr = min(first_row + rr, row_limit - 1);
-            r[u] = __builtin_nontemporal_load(
-                reinterpret_cast<const u32x4*>(reinterpret_cast<const uint8_t*>(base) + (size_t)gr * T::ROWB + ch * 16));
-        }
-    }
+    for (int u = 0; u < NI; ++u) r[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, offs[u & 3], u * 1024, 2));
 }
 template <int D>
 __device__ __forceinline__ void regs_to_tile(uint8_t* dst, int lane, const u32x4* r) {
@@ -169,7 +161,7 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void decode_split_kernel(c
     uint8_t* const Ks = smem + wave * 2 * T::BYTES;
     uint8_t* const Vs = Ks + T::BYTES;
     // (lengths that differ and are not dealt out: all heads of an entry start together, so that no long one starts late)
-    const int g = p.Hq / p.Hkv, hkv = LENS == LENS_FIXED ? blockIdx.y : blockIdx.z;
+    const int g = p.g, hkv = LENS == LENS_FIXED ? blockIdx.y : blockIdx.z;
     int b = LENS == LENS_FIXED ? blockIdx.z : blockIdx.y, r = blockIdx.x, nb = p.n_splits;  // batch entry, its range, the number of its ranges
     const int w = b * p.n_splits + r;  // range of the batch's list
     if (LENS == LENS_DEALT) {
@@ -179,7 +171,7 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void decode_split_kernel(c
     }
     const size_t slot = (size_t)w * p.Hq + hkv * g;
     const int n_keys = LENS == LENS_ONE ? p.n_keys : __builtin_amdgcn_readfirstlane(decode_keys(p, b));
-    const int Tc = (n_keys + BN - 1) / BN, per = (Tc + nb - 1) / nb;
+    const int Tc = (n_keys + BN - 1) / BN, per = LENS == LENS_ONE ? p.per : (Tc + nb - 1) / nb;
     const int r0 = r * per, r1 = min(Tc, r0 + per);  // its tiles
     const int share = (max(r1 - r0, 0) + W - 1) / W;
     const int t_lo = r0 + wave * share, t_hi = min(r1, t_lo + share);
@@ -203,7 +195,7 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void decode_split_kernel(c
     float m2 = -INFINITY, lsum = 0.f;
     u32x4 rk[NI], rv[NI];
     // tile t.  On entry K(t) is in LDS, rv holds V(t) and, requested after it, rk holds K(t + 1) (HASK1).
-    // HASV1 / HASK2: tiles t + 1 / t + 2 exist; FULL: the tiles requested here are whole
+    // HASV1 / HASK2: tiles t + 1 / t + 2 exist; FULL: tile t is whole
     auto body = [&](int t, auto hasv1_c, auto hask1_c, auto hask2_c, auto full_c) __attribute__((always_inline)) {
         constexpr bool HASV1 = decltype(hasv1_c)::value, HASK1 = decltype(hask1_c)::value, HASK2 = decltype(hask2_c)::value;
         constexpr bool FULL = decltype(full_c)::value;
@@ -214,31 +206,31 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void decode_split_kernel(c
         softmax_tile<true, !FULL, DB, true, true>(st, pk, ot, m2, lsum, p.c, t * BN, n_keys - 1, hh, 0.f);
         __builtin_amdgcn_sched_barrier(0);  // (requests and LDS writes go out where they are written, not where the scheduler likes them)
         regs_to_tile<D>(Vs, lane, rv);  // V(t) has landed when only K(t + 1) is still out
-        if (HASV1) tile_to_regs<D, FULL>(Vg, (t + 1) * BN, n_keys, true, lane, offv, rv);
+        if (HASV1) tile_to_regs<D>(Vg, t + 1, n_keys, offv, rv);
         __builtin_amdgcn_sched_barrier(0);
         pv_tile_pipe<D>(Vs, pk, ot, lane, hh);
         __builtin_amdgcn_sched_barrier(0);
         if (HASK1) regs_to_tile<D>(Ks, lane, rk);  // K(t + 1) has landed when only V(t + 1) is still out
-        if (HASK2) tile_to_regs<D, FULL>(Kg, (t + 2) * BN, n_keys, false, lane, offk, rk);
+        if (HASK2) tile_to_regs<D>(Kg, t + 2, n_keys, offk, rk);
         __builtin_amdgcn_sched_barrier(0);
     };
     using Y = std::true_type;
     using N_ = std::false_type;
     if (t_lo < t_hi) {
-        tile_to_regs<D, false>(Kg, t_lo * BN, n_keys, false, lane, offk, rk);
-        tile_to_regs<D, false>(Vg, t_lo * BN, n_keys, true, lane, offv, rv);
+        tile_to_regs<D>(Kg, t_lo, n_keys, offk, rk);
+        tile_to_regs<D>(Vg, t_lo, n_keys, offv, rv);
         __builtin_amdgcn_sched_barrier(0);
         regs_to_tile<D>(Ks, lane, rk);
         __builtin_amdgcn_sched_barrier(0);
         int t = t_lo;
         if (t + 2 < t_whole) {  // (the request for K(t + 1) is not behind a branch of its own: see above)
-            tile_to_regs<D, true>(Kg, (t + 1) * BN, n_keys, false, lane, offk, rk);
+            tile_to_regs<D>(Kg, t + 1, n_keys, offk, rk);
             do {  // tiles t + 1 and t + 2 are whole and inside the range
                 body(t, Y{}, Y{}, Y{}, Y{});
                 ++t;
             } while (t + 2 < t_whole);
         } else if (t + 1 < t_hi) {
-            tile_to_regs<D, false>(Kg, (t + 1) * BN, n_keys, false, lane, offk, rk);
+            tile_to_regs<D>(Kg, t + 1, n_keys, offk, rk);
         }
         if (t + 2 < t_hi) body(t++, Y{}, Y{}, Y{}, N_{});  // (at most one: t_hi <= t_whole + 1)
         if (t + 1 < t_hi) body(t++, Y{}, Y{}, N_{}, N_{});

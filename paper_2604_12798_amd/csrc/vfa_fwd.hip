@@ -671,6 +671,7 @@ int decode_common(const void* Q, const void* K, const void* V, const void* Krepr
     }
     const long long wgs = heads * n_splits;
     const int tiles = ceil_div(all, n_splits);
+    p.g = Hq / Hkv; p.per = tiles;
     // (the lines are explained at varlen_find)
     const bool dealt = seq_lens && n_splits > 1 && (B <= 64 || (B <= DEAL_MAX_B && wgs <= 8LL * n_cu && all > 2 * n_splits));
     auto launch = [&](auto d_c, auto w_c) {
