@@ -102,63 +102,59 @@ def workspace_bytes(B: int, Hkv: int, N: int, d: int, block_n: int) -> int:
     return _n().vfa_workspace_bytes(B, Hkv, N, d, block_n)
 
 
-_native = None
+_native = _bf16 = _i32 = None
 
 
 def _n():
-    """The same entry points through the CPython module `_native` (csrc/binding.cpp), which the wrappers below call."""
-    global _native
+    """The same entry points through the CPython module `_native` (csrc/binding.cpp), which the wrappers below call.  With _t
+    behind their names they take tensors for pointers; check_qkv / check_cache / bytes_of look at tensors' attributes."""
+    global _native, _bf16, _i32
     if _native is None:
         lib()  # torch and libvfa.so first, with their checks
         import importlib
+        import torch
+        _bf16, _i32 = torch.bfloat16, torch.int32
         _native = importlib.import_module(__name__ + "._native")
     return _native
 
 
-def _ptr(t):
-    return None if t is None else t.data_ptr()
+_current_device = _current_stream = None
 
 
 def _stream(stream):
-    import torch
+    global _current_device, _current_stream
     if stream is not None:
         return stream.cuda_stream
-    # (the handle behind torch.cuda.current_stream(), without making a Stream object for it)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-
-
-def _check_qkv(Q, K, V):
-    import torch
-    for t in (Q, K, V):
-        if not (t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous() and t.dim() == 4):
-            raise ValueError("Q, K, V must be contiguous 4-d bf16 tensors on the GPU")
-    B, Hq, N, d = Q.shape
-    if K.shape != V.shape or K.shape[0] != B or K.shape[2] != N or K.shape[3] != d:
-        raise ValueError("K, V must be [B, Hkv, N, d] matching Q [B, Hq, N, d]")
-    return B, Hq, K.shape[1], N, d
+    if _current_stream is None:
+        import torch
+        # (the handle behind torch.cuda.current_stream(), without making a Stream object for it)
+        _current_device, _current_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+    return _current_stream(_current_device())
 
 
 def _outputs(Q, out, lse, want_lse):
-    import torch
-    B, Hq, N, d = Q.shape
-    O = torch.empty_like(Q) if out is None else out
-    L = lse
-    if L is None and want_lse:
-        L = torch.empty((B, Hq, N), dtype=torch.float32, device=Q.device)
-    return O, L
+    if out is None or (lse is None and want_lse):
+        import torch
+        B, Hq, N, d = Q.shape
+        if out is None:
+            out = torch.empty_like(Q)
+        if lse is None and want_lse:
+            lse = torch.empty((B, Hq, N), dtype=torch.float32, device=Q.device)
+    return out, lse
 
 
 def kblock_summary(K, block_n: int = 64, out=None, stream=None, repr_mode: int = 0):
     """Key-block summaries Krepr [B, Hkv, ceil(N/block_n), d] (bf16) of K [B, Hkv, N, d].
     repr_mode 0 = sabsmax (the method); 1 / 2 / 3 = per-dimension max / mean / unsigned absmax."""
+    n = _n()
     import torch
     B, Hkv, N, d = K.shape
     Tc = -(-N // block_n)
     R = torch.empty((B, Hkv, Tc, d), dtype=torch.bfloat16, device=K.device) if out is None else out
     if repr_mode == 0:
-        rc = _n().vfa_kblock_summary(_ptr(K), _ptr(R), B, Hkv, N, d, block_n, _stream(stream))
+        rc = n.vfa_kblock_summary_t(K, R, B, Hkv, N, d, block_n, _stream(stream))
     else:
-        rc = _n().vfa_kblock_summary_mode(_ptr(K), _ptr(R), B, Hkv, N, d, block_n, int(repr_mode), _stream(stream))
+        rc = n.vfa_kblock_summary_mode_t(K, R, B, Hkv, N, d, block_n, int(repr_mode), _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_kblock_summary")
     return R
@@ -166,9 +162,10 @@ def kblock_summary(K, block_n: int = 64, out=None, stream=None, repr_mode: int =
 
 def fa_baseline_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, softmax_scale=0.0, out=None, lse=None,
                     want_lse=True, stream=None):
-    B, Hq, Hkv, N, d = _check_qkv(Q, K, V)
+    n = _n()
+    B, Hq, Hkv, N, d = n.check_qkv(Q, K, V, _bf16)
     O, L = _outputs(Q, out, lse, want_lse)
-    rc = _n().fa_baseline_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
+    rc = n.fa_baseline_fwd_t(Q, K, V, O, L, B, Hq, Hkv, N, d, block_m, block_n,
                                int(bool(causal)), float(softmax_scale), _stream(stream))
     if rc != 0:
         raise VfaError(rc, "fa_baseline_fwd")
@@ -177,9 +174,10 @@ def fa_baseline_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, softmax_sc
 
 def fa_lazy_rescale_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, softmax_scale=0.0, rescale_tau=8.0, out=None,
                         lse=None, want_lse=True, stream=None):
-    B, Hq, Hkv, N, d = _check_qkv(Q, K, V)
+    n = _n()
+    B, Hq, Hkv, N, d = n.check_qkv(Q, K, V, _bf16)
     O, L = _outputs(Q, out, lse, want_lse)
-    rc = _n().fa_lazy_rescale_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
+    rc = n.fa_lazy_rescale_fwd_t(Q, K, V, O, L, B, Hq, Hkv, N, d, block_m, block_n,
                                    int(bool(causal)), float(softmax_scale), float(rescale_tau), _stream(stream))
     if rc != 0:
         raise VfaError(rc, "fa_lazy_rescale_fwd")
@@ -188,9 +186,10 @@ def fa_lazy_rescale_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, softma
 
 def fa_lazy_rescale_softexp_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, softmax_scale=0.0, rescale_tau=8.0,
                                 out=None, lse=None, want_lse=True, stream=None):
-    B, Hq, Hkv, N, d = _check_qkv(Q, K, V)
+    n = _n()
+    B, Hq, Hkv, N, d = n.check_qkv(Q, K, V, _bf16)
     O, L = _outputs(Q, out, lse, want_lse)
-    rc = _n().fa_lazy_rescale_softexp_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m,
+    rc = n.fa_lazy_rescale_softexp_fwd_t(Q, K, V, O, L, B, Hq, Hkv, N, d, block_m,
                                            block_n, int(bool(causal)), float(softmax_scale), float(rescale_tau),
                                            _stream(stream))
     if rc != 0:
@@ -199,21 +198,22 @@ def fa_lazy_rescale_softexp_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True
 
 
 def _workspace(Q, K, block_n, workspace):
-    import torch
-    B, Hkv, N, d = K.shape
     if workspace is None:
+        import torch
+        B, Hkv, N, d = K.shape
         workspace = torch.empty(max(workspace_bytes(B, Hkv, N, d, block_n), 256), dtype=torch.uint8, device=Q.device)
-    return workspace, workspace.numel() * workspace.element_size()
+    return workspace, _n().bytes_of(workspace)
 
 
 def vfa_attn_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, n_sink=1, n_local=1, use_minit=True,
                  softmax_scale=0.0, workspace=None, out=None, lse=None, want_lse=True, stream=None):
-    B, Hq, Hkv, N, d = _check_qkv(Q, K, V)
+    n = _n()
+    B, Hq, Hkv, N, d = n.check_qkv(Q, K, V, _bf16)
     O, L = _outputs(Q, out, lse, want_lse)
     ws, ws_bytes = _workspace(Q, K, block_n, workspace)
-    rc = _n().vfa_attn_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
+    rc = n.vfa_attn_fwd_t(Q, K, V, O, L, B, Hq, Hkv, N, d, block_m, block_n,
                             int(bool(causal)), int(n_sink), int(n_local), int(use_minit), float(softmax_scale),
-                            _ptr(ws), ws_bytes, _stream(stream))
+                            ws, ws_bytes, _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_attn_fwd")
     return O, L
@@ -222,16 +222,17 @@ def vfa_attn_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, n_sink=1, n_l
 def vsa_attn_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, n_sink=1, n_local=1, use_minit=True,
                  softmax_scale=0.0, skip_threshold_nats=8.0, skip_mask=None, want_mask=True, workspace=None,
                  out=None, lse=None, want_lse=True, stream=None):
-    import torch
-    B, Hq, Hkv, N, d = _check_qkv(Q, K, V)
+    n = _n()
+    B, Hq, Hkv, N, d = n.check_qkv(Q, K, V, _bf16)
     O, L = _outputs(Q, out, lse, want_lse)
     ws, ws_bytes = _workspace(Q, K, block_n, workspace)
     M = skip_mask
     if M is None and want_mask:
+        import torch
         M = torch.empty((B, Hq, -(-N // block_m), -(-N // block_n)), dtype=torch.uint8, device=Q.device)
-    rc = _n().vsa_attn_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
+    rc = n.vsa_attn_fwd_t(Q, K, V, O, L, B, Hq, Hkv, N, d, block_m, block_n,
                             int(bool(causal)), int(n_sink), int(n_local), int(use_minit), float(softmax_scale),
-                            float(skip_threshold_nats), _ptr(M), _ptr(ws), ws_bytes, _stream(stream))
+                            float(skip_threshold_nats), M, ws, ws_bytes, _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vsa_attn_fwd")
     return O, L, M
@@ -243,7 +244,8 @@ def vfa_variant_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, n_sink=1, 
                     workspace=None, out=None, lse=None, want_lse=True, stream=None):
     """VFA / VSA with the ablation switches; returns (O, LSE, mask) with mask None when nothing is skipped."""
     import torch
-    B, Hq, Hkv, N, d = _check_qkv(Q, K, V)
+    n = _n()
+    B, Hq, Hkv, N, d = n.check_qkv(Q, K, V, _bf16)
     O, L = _outputs(Q, out, lse, want_lse)
     if workspace is None and q_repr_mode:   # query-block summaries behind the key-block summaries
         need = workspace_bytes(B, Hkv, N, d, block_n) + workspace_bytes(B, Hq, N, d, block_m)
@@ -252,11 +254,11 @@ def vfa_variant_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, n_sink=1, 
     M = skip_mask
     if M is None and skip_threshold_nats != 0.0:
         M = torch.empty((B, Hq, -(-N // block_m), -(-N // block_n)), dtype=torch.uint8, device=Q.device)
-    rc = _n().vfa_variant_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(L), B, Hq, Hkv, N, d, block_m, block_n,
+    rc = n.vfa_variant_fwd_t(Q, K, V, O, L, B, Hq, Hkv, N, d, block_m, block_n,
                                int(bool(causal)), int(n_sink), int(n_local), int(use_minit), int(repr_mode),
                                int(q_repr_mode), int(bool(reorder)), int(bool(freeze)), int(bool(rowskip)), float(lazy_rescale_tau),
                                float(softmax_scale), float(skip_threshold_nats),
-                               _ptr(M), _ptr(ws), ws_bytes, _stream(stream))
+                               M, ws, ws_bytes, _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_variant_fwd")
     return O, L, M
@@ -264,8 +266,9 @@ def vfa_variant_fwd(Q, K, V, *, block_m=128, block_n=64, causal=True, n_sink=1, 
 
 def kblock_summary_append(K, Krepr, n_old: int, n_new: int, block_n: int = 64, stream=None):
     """Refresh, in place, the summaries of the blocks of cache K [B, Hkv, n_cap, d] that hold rows [n_old, n_new)."""
+    n = _n()
     B, Hkv, n_cap, d = K.shape
-    rc = _n().vfa_kblock_summary_append(_ptr(K), _ptr(Krepr), B, Hkv, n_cap, int(n_old), int(n_new), d, block_n,
+    rc = n.vfa_kblock_summary_append_t(K, Krepr, B, Hkv, n_cap, int(n_old), int(n_new), d, block_n,
                                          _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_kblock_summary_append")
@@ -274,29 +277,38 @@ def kblock_summary_append(K, Krepr, n_old: int, n_new: int, block_n: int = 64, s
 
 def kblock_summary_append_varlen(K, Krepr, old_lens, new_lens, block_n: int = 64, stream=None):
     """As kblock_summary_append with per-sequence lengths (int32 device tensors of B entries)."""
+    n = _n()
     B, Hkv, n_cap, d = K.shape
-    rc = _n().vfa_kblock_summary_append_varlen(_ptr(K), _ptr(Krepr), B, Hkv, n_cap, _ptr(old_lens), _ptr(new_lens), d,
+    rc = n.vfa_kblock_summary_append_varlen_t(K, Krepr, B, Hkv, n_cap, old_lens, new_lens, d,
                                                 block_n, _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_kblock_summary_append_varlen")
     return Krepr
 
 
+def _decode_outputs(q, n_splits, out, lse, want_lse, workspace):
+    if out is None or workspace is None or (lse is None and want_lse):
+        import torch
+        B, Hq, d = q.shape
+        if out is None:
+            out = torch.empty_like(q)
+        if lse is None and want_lse:
+            lse = torch.empty((B, Hq), dtype=torch.float32, device=q.device)
+        if workspace is None:
+            workspace = torch.empty(max(decode_workspace_bytes(B, Hq, d, n_splits), 256), dtype=torch.uint8, device=q.device)
+    return out, lse, workspace
+
+
 def decode_varlen_fwd(q, K, V, seq_lens, *, krepr=None, block_n=64, n_sink=1, n_local=1, use_minit=True, n_splits=8,
                       softmax_scale=0.0, workspace=None, out=None, lse=None, want_lse=True, stream=None):
     """As decode_fwd with per-sequence lengths (int32 device tensor of B entries)."""
-    import torch
-    B, Hq, d = q.shape
-    Hkv, n_cap = K.shape[1], K.shape[2]
-    assert seq_lens.is_cuda and seq_lens.dtype == torch.int32 and seq_lens.numel() == B
-    O = torch.empty_like(q) if out is None else out
-    L = lse if (lse is not None or not want_lse) else torch.empty((B, Hq), dtype=torch.float32, device=q.device)
-    ws = workspace
-    if ws is None:
-        ws = torch.empty(max(decode_workspace_bytes(B, Hq, d, n_splits), 256), dtype=torch.uint8, device=q.device)
-    rc = _n().vfa_decode_varlen_fwd(_ptr(q), _ptr(K), _ptr(V), _ptr(krepr), _ptr(O), _ptr(L), B, Hq, Hkv, n_cap,
-                                     _ptr(seq_lens), d, block_n, int(n_sink), int(n_local), int(bool(use_minit)),
-                                     int(n_splits), float(softmax_scale), _ptr(ws), ws.numel() * ws.element_size(),
+    n = _n()
+    B, Hq, d, Hkv, n_cap = n.check_cache(q, K, V, None)
+    assert seq_lens.is_cuda and seq_lens.dtype == _i32 and seq_lens.numel() == B
+    O, L, ws = _decode_outputs(q, n_splits, out, lse, want_lse, workspace)
+    rc = n.vfa_decode_varlen_fwd_t(q, K, V, krepr, O, L, B, Hq, Hkv, n_cap,
+                                     seq_lens, d, block_n, int(n_sink), int(n_local), int(bool(use_minit)),
+                                     int(n_splits), float(softmax_scale), ws, n.bytes_of(ws),
                                      _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_decode_varlen_fwd")
@@ -310,20 +322,12 @@ def decode_workspace_bytes(B: int, Hq: int, d: int, n_splits: int) -> int:
 def decode_fwd(q, K, V, n_keys: int, *, krepr=None, block_n=64, n_sink=1, n_local=1, use_minit=True, n_splits=8,
                softmax_scale=0.0, workspace=None, out=None, lse=None, want_lse=True, stream=None):
     """One query token per head, q [B, Hq, d], against the first n_keys rows of the cache K, V [B, Hkv, n_cap, d]."""
-    import torch
-    B, Hq, d = q.shape
-    Hkv, n_cap = K.shape[1], K.shape[2]
-    for t in (q, K, V):
-        if not (t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous()):
-            raise ValueError("q, K, V must be contiguous bf16 tensors on the GPU")
-    O = torch.empty_like(q) if out is None else out
-    L = lse if (lse is not None or not want_lse) else torch.empty((B, Hq), dtype=torch.float32, device=q.device)
-    ws = workspace
-    if ws is None:
-        ws = torch.empty(max(decode_workspace_bytes(B, Hq, d, n_splits), 256), dtype=torch.uint8, device=q.device)
-    rc = _n().vfa_decode_fwd(_ptr(q), _ptr(K), _ptr(V), _ptr(krepr), _ptr(O), _ptr(L), B, Hq, Hkv, n_cap, int(n_keys), d,
+    n = _n()
+    B, Hq, d, Hkv, n_cap = n.check_cache(q, K, V, _bf16)
+    O, L, ws = _decode_outputs(q, n_splits, out, lse, want_lse, workspace)
+    rc = n.vfa_decode_fwd_t(q, K, V, krepr, O, L, B, Hq, Hkv, n_cap, int(n_keys), d,
                               block_n, int(n_sink), int(n_local), int(bool(use_minit)), int(n_splits), float(softmax_scale),
-                              _ptr(ws), ws.numel() * ws.element_size(), _stream(stream))
+                              ws, n.bytes_of(ws), _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_decode_fwd")
     return O, L
@@ -336,9 +340,10 @@ def decode_noalloc_fwd(q, K, V, n_keys: int, out, lse=None, *, krepr=None, block
                        n_splits=8, softmax_scale=0.0, stream=None):
     """vfa_decode_noalloc_fwd: as decode_fwd, but neither the library nor this wrapper allocates: the caller passes
     the output tensors (lse may be None) and the partial sums live in the library's fixed device array."""
+    n = _n()
     B, Hq, d = q.shape
     Hkv, n_cap = K.shape[1], K.shape[2]
-    rc = _n().vfa_decode_noalloc_fwd(_ptr(q), _ptr(K), _ptr(V), _ptr(krepr), _ptr(out), _ptr(lse), B, Hq, Hkv, n_cap,
+    rc = n.vfa_decode_noalloc_fwd_t(q, K, V, krepr, out, lse, B, Hq, Hkv, n_cap,
                                       int(n_keys), d, block_n, int(n_sink), int(n_local), int(bool(use_minit)),
                                       int(n_splits), float(softmax_scale), _stream(stream))
     if rc != 0:
@@ -348,10 +353,11 @@ def decode_noalloc_fwd(q, K, V, n_keys: int, out, lse=None, *, krepr=None, block
 
 def fp8_quantize(X, inv_scale: float, stream=None):
     """bf16 tensor -> uint8 tensor of E4M3 codes of X * inv_scale (same shape)."""
+    n = _n()
     import torch
     assert X.is_cuda and X.dtype == torch.bfloat16 and X.is_contiguous()
     Y = torch.empty(X.shape, dtype=torch.uint8, device=X.device)
-    rc = _n().vfa_fp8_quantize(_ptr(X), _ptr(Y), X.numel(), float(inv_scale), _stream(stream))
+    rc = n.vfa_fp8_quantize_t(X, Y, X.numel(), float(inv_scale), _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_fp8_quantize")
     return Y
@@ -359,10 +365,11 @@ def fp8_quantize(X, inv_scale: float, stream=None):
 
 def fp8_pack_v(V, inv_scale: float, stream=None):
     """V [B, Hkv, N, 128] bf16 -> [B, Hkv, ceil(N/64), 128, 64] uint8 (transposed, key-permuted E4M3 tiles)."""
+    n = _n()
     import torch
     B, Hkv, N, d = V.shape
     Vt = torch.empty((B, Hkv, -(-N // 64), 128, 64), dtype=torch.uint8, device=V.device)
-    rc = _n().vfa_fp8_pack_v(_ptr(V), _ptr(Vt), B, Hkv, N, d, float(inv_scale), _stream(stream))
+    rc = n.vfa_fp8_pack_v_t(V, Vt, B, Hkv, N, d, float(inv_scale), _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_fp8_pack_v")
     return Vt
@@ -372,6 +379,7 @@ def fp8_attn_fwd(Q8, K8, Vt8, *, descale_q, descale_k, descale_v, frozen=True, b
                  n_sink=1, n_local=1, use_minit=True, softmax_scale=0.0, workspace=None, out=None, lse=None,
                  want_lse=True, stream=None, noexp=False):
     """E4M3 attention; noexp=True calls vfa_fp8_attn_noexp_fwd (Alg. 1 with the weights' codes taken from the scores)."""
+    n = _n()
     import torch
     B, Hq, N, d = Q8.shape
     Hkv = K8.shape[1]
@@ -380,12 +388,12 @@ def fp8_attn_fwd(Q8, K8, Vt8, *, descale_q, descale_k, descale_v, frozen=True, b
     need = B * Hkv * (-(-N // block_n)) * 128
     ws = torch.empty(max(need, 256), dtype=torch.uint8, device=Q8.device) if workspace is None else workspace
     tail = (B, Hq, Hkv, N, d, block_m, block_n, int(bool(causal)), int(n_sink), int(n_local), int(use_minit),
-            float(softmax_scale), float(descale_q), float(descale_k), float(descale_v), _ptr(ws),
-            ws.numel() * ws.element_size(), _stream(stream))
+            float(softmax_scale), float(descale_q), float(descale_k), float(descale_v), ws,
+            n.bytes_of(ws), _stream(stream))
     if noexp:
-        rc = _n().vfa_fp8_attn_noexp_fwd(_ptr(Q8), _ptr(K8), _ptr(Vt8), _ptr(O), _ptr(L), *tail)
+        rc = n.vfa_fp8_attn_noexp_fwd_t(Q8, K8, Vt8, O, L, *tail)
     else:
-        rc = _n().vfa_fp8_attn_fwd(int(bool(frozen)), _ptr(Q8), _ptr(K8), _ptr(Vt8), _ptr(O), _ptr(L), *tail)
+        rc = n.vfa_fp8_attn_fwd_t(int(bool(frozen)), Q8, K8, Vt8, O, L, *tail)
     if rc != 0:
         raise VfaError(rc, "vfa_fp8_attn_noexp_fwd" if noexp else "vfa_fp8_attn_fwd")
     return O, L
@@ -393,12 +401,13 @@ def fp8_attn_fwd(Q8, K8, Vt8, *, descale_q, descale_k, descale_v, frozen=True, b
 
 def mxfp4_quantize(X, pre_scale: float = 1.0, stream=None):
     """bf16 tensor [..., d] (d a multiple of 32) -> (uint8 [..., d/2] E2M1 pairs, uint8 [..., d/32] E8M0 scales) of X * pre_scale."""
+    n = _n()
     import torch
     assert X.is_cuda and X.dtype == torch.bfloat16 and X.is_contiguous() and X.shape[-1] % 32 == 0
     d = X.shape[-1]
     X4 = torch.empty(X.shape[:-1] + (d // 2,), dtype=torch.uint8, device=X.device)
     XS = torch.empty(X.shape[:-1] + (d // 32,), dtype=torch.uint8, device=X.device)
-    rc = _n().vfa_mxfp4_quantize(_ptr(X), _ptr(X4), _ptr(XS), X.numel(), float(pre_scale), _stream(stream))
+    rc = n.vfa_mxfp4_quantize_t(X, X4, XS, X.numel(), float(pre_scale), _stream(stream))
     if rc != 0:
         raise VfaError(rc, "vfa_mxfp4_quantize")
     return X4, XS
@@ -413,6 +422,7 @@ def mxfp4_attn_fwd(Q4, QS, K4, KS, Vt8, *, descale_v, frozen=True, block_m=128, 
                    stream=None, noexp=False):
     """Attention with MXFP4 scores (Q4/QS, K4/KS from mxfp4_quantize) and 8-bit P.V (Vt8 from fp8_pack_v);
     noexp=True calls vfa_mxfp4_attn_noexp_fwd."""
+    n = _n()
     import torch
     B, Hq, N, dh = Q4.shape
     d, Hkv = 2 * dh, K4.shape[1]
@@ -422,9 +432,9 @@ def mxfp4_attn_fwd(Q4, QS, K4, KS, Vt8, *, descale_v, frozen=True, block_m=128, 
     if ws is None:
         ws = torch.empty(max(mxfp4_workspace_bytes(B, Hkv, N), 256), dtype=torch.uint8, device=Q4.device)
     tail = (B, Hq, Hkv, N, d, block_m, block_n, int(bool(causal)), int(n_sink), int(n_local), int(use_minit),
-            float(softmax_scale), float(descale_v), _ptr(ws), ws.numel() * ws.element_size(), _stream(stream))
-    ops = (_ptr(Q4), _ptr(QS), _ptr(K4), _ptr(KS), _ptr(Vt8), _ptr(O), _ptr(L))
-    rc = _n().vfa_mxfp4_attn_noexp_fwd(*ops, *tail) if noexp else _n().vfa_mxfp4_attn_fwd(int(bool(frozen)), *ops, *tail)
+            float(softmax_scale), float(descale_v), ws, n.bytes_of(ws), _stream(stream))
+    ops = (Q4, QS, K4, KS, Vt8, O, L)
+    rc = n.vfa_mxfp4_attn_noexp_fwd_t(*ops, *tail) if noexp else n.vfa_mxfp4_attn_fwd_t(int(bool(frozen)), *ops, *tail)
     if rc != 0:
         raise VfaError(rc, "vfa_mxfp4_attn_noexp_fwd" if noexp else "vfa_mxfp4_attn_fwd")
     return O, L, ws
