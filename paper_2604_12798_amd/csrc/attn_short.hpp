@@ -19,14 +19,16 @@ namespace {
 // rows an item has.  A wave's step: Q.K^T of the next step's keys with the row max and the first half of the weights of this
 // one's dealt out between the MFMAs, then P.V with the second half.  K slots are requested two steps ahead, V slots one, the
 // requests dealt out too (in front of the step they hold up its first MFMAs: 8 % of the time); one barrier per step.  A wave meets its keys in
-// its first steps and only the last of them needs a mask, so there are two copies of a step and no branch between
-// them (with one the compiler moved O between registers in every step: 93 us for 82 at 32 heads, N = 2048, no mask).
-// What bounds it: below 500 keys the launch and the chain of load latencies (4.3 - 5.3 us for an empty sequence); then the two waves of
-// a SIMD, 2500 cycles for 64 rows x 128 keys against 1024 of MFMA, and the 64 KiB of tiles they take (twice the bytes per row of
-// the 128-row kernels), which is why longer sequences stay with those.
+// its first steps and only the last of them needs a mask, so there are two copies of a step's code and no branch between them.
+// What bounds it: below 500 keys the launch and the chain of load latencies (4.8 us for an empty sequence); then a wave's own chain, 170
+// instructions for 16 MFMAs (512 cycles) and, alone on a SIMD, 1000 to 1100 cycles a step; two workgroups on a compute unit take 2700 for a step of
+// each, which is 2.2 times the ping-pong kernel's time per score, so longer sequences stay with that.  Measured on a single workgroup: slots
+// deeper by one step or three change nothing, all eight fragments of K in front and the weights between the MFMAs of Q.K^T only cost 8 %.
+// The first form waited in every step for the requests just made (see Q below), took a slot's place and its wrap from vector and scalar
+// arithmetic (226 instructions) and moved the scores from one step to the next.
 // KQ = 2: two workgroups per compute unit (80 KiB each at d = 128).  KQ = 4: one, for grids of no more items than compute units.
-// Calls in us, without it and with it: d = 128, 32 heads over 8, causal, N = 200 14.4 / 7.3, 512 18.5 / 10.3, 777 22.2 / 15.2, 1024 24.4 /
-// 17.5; 8 heads over 2, N = 2048 33.2 / 20.6 (KQ = 4); 160 heads, N = 320 36.7 / 19.3; d = 64, 32 heads over 8, N = 777 15.3 / 10.2.
+// Calls in us, first form / this: d = 128, 32 heads over 8, causal, N = 256 7.2 / 6.4, 512 10.0 / 8.8, 777 15.3 / 12.8, 1024 19.4 / 16.4; 8 heads, N =
+// 1536 (KQ = 4) 17.5 / 14.6; no mask, 32 heads, N = 576 14.3 / 12.2; d = 64, 32 heads over 8, causal, N = 777 10.1 / 8.4, 1536 21.3 / 17.2.
 constexpr float kKeepMax = 8.f;
 
 template <int D, int KQ>
@@ -55,135 +57,142 @@ __global__ __launch_bounds__(128 * KQ, 2) void attn_fwd_short_kernel(const Param
     const int rw = wave & 1, kq = wave >> 1;
     const int ql = lane & 31;
     const int hh = lane >> 5;
-    const int g = p.Hq / p.Hkv, G = p.B * p.Hkv;
     const int id = blockIdx.x;
     if (id >= p.n_items) {  // the summaries, for the caller: a block of keys per wave
         const int w = (id - p.n_items) * 2 * KQ + wave;
-        if (w < G * p.Tc) summary_of_block<D>(p.K, const_cast<uint16_t*>(p.Krepr), w / p.Tc, w % p.Tc, p.N, p.N, p.Tc, BN, lane);
+        if (w < p.B * p.Hkv * p.Tc) summary_of_block<D>(p.K, const_cast<uint16_t*>(p.Krepr), w / p.Tc, w % p.Tc, p.N, p.N, p.Tc, BN, lane);
         return;
     }
-    // items: late (long) query blocks first; the KV heads congruent mod 8 on one XCD, as in the other kernels
-    int b, h, i;
-    {
-        if ((G & 7) == 0) {
-            const int x = id & 7, y = id >> 3, per = p.Tr * g;
-            const int kvl = y / per, rem = y - kvl * per;
-            i = p.Tr - 1 - rem / g;
-            const int kv = kvl * 8 + x;
-            b = kv / p.Hkv;
-            h = (kv - b * p.Hkv) * g + rem % g;
-        } else {
-            const int bh = id % (p.B * p.Hq);
-            i = p.Tr - 1 - id / (p.B * p.Hq);
-            b = bh / p.Hq;
-            h = bh - b * p.Hq;
-        }
+    // items: late (long) query blocks first; the KV heads congruent mod 8 on one XCD, as in the other kernels (of the batch's query heads
+    // `head`, of its KV heads `kv`; quotients by the host's reciprocals: divisions took 0.3 us of the 5 that an empty sequence takes)
+    const int g = p.g;
+    int head, kv, i;
+    if (((p.B * p.Hkv) & 7) == 0) {
+        const int y = id >> 3, kvl = p.by_list(y), rem = y - kvl * p.Tr * g, t = p.by_g(rem);
+        kv = kvl * 8 + (id & 7);
+        head = kv * g + rem - t * g;
+        i = p.Tr - 1 - t;
+    } else {
+        const int t = p.by_list(id);
+        head = id - t * p.B * p.Hq;
+        kv = p.by_g(head);
+        i = p.Tr - 1 - t;
     }
-    b = __builtin_amdgcn_readfirstlane(b);
-    h = __builtin_amdgcn_readfirstlane(h);
-    i = __builtin_amdgcn_readfirstlane(i);
-    const int hkv = __builtin_amdgcn_readfirstlane(h / g);
     const int N = p.N;
     const int row0 = p.row_base + i * BM;
     const int n_vis = p.causal ? min(N, row0 + BM) : N;  // keys that any row sees
     const int n_steps = (n_vis + KT - 1) / KT;
 
-    const uint16_t* Qg = p.Q + ((size_t)(b * p.Hq + h) * N) * D;
-    const uint16_t* Kg = p.K + ((size_t)(b * p.Hkv + hkv) * N) * D;
-    const uint16_t* Vg = p.V + ((size_t)(b * p.Hkv + hkv) * N) * D;
-
     // ---- requests: a wave moves LI adjacent pieces (1 KiB of whole rows) of the K and of the V slot, by buffer loads whose buffer is
-    // the slot's keys: rows past the end of the sequence are out of its range and LDS gets zeros
+    // the head's keys: rows past the end of the sequence are out of its range and LDS gets zeros.  The slot's place is the loads' scalar
+    // offset, so that a request costs three scalar instructions beside them
     const int r_own = RPI * LI * wave + lane / T::CH, cp = lane % T::CH;
-    uint32_t offK[LI], offV[LI];
+    uint32_t offK[LI];
 #pragma unroll
-    for (int u = 0; u < LI; ++u) {
-        offK[u] = (uint32_t)(r_own * T::ROWB + ((cp ^ T::k_mix(r_own + RPI * u)) << 4));
-        offV[u] = (uint32_t)(r_own * T::ROWB + ((cp ^ T::v_mix(r_own + RPI * u)) << 4));
-    }
+    for (int u = 0; u < LI; ++u) offK[u] = (uint32_t)(r_own * T::ROWB + ((cp ^ T::k_mix(r_own + RPI * u)) << 4));
+    const uint32_t offV = (uint32_t)(r_own * T::ROWB + ((cp ^ T::v_mix(r_own)) << 4));  // (the same for all pieces)
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
         (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)(short_smem + wave * LI * 1024));
-    auto request = [&](const uint16_t* base, int s, const uint32_t* o, uint32_t at) __attribute__((always_inline)) {
-        const uint64_t a = (uint64_t)(uintptr_t)base + (uint64_t)(uint32_t)s * (uint32_t)F::SLOT;
-        const uint32_t bytes = min(max(N - s * KT, 0), KT) * T::ROWB;
-        if constexpr (LI == 4) request4(a, bytes, o[0], o[1], o[2], o[3], lds0 + at);
-        else request2(a, bytes, o[0], o[1], lds0 + at);
+    const uint32_t bytes = (uint32_t)N * T::ROWB;  // (launched for fewer than 2^32)
+    const u32x4 rsrcK = tile_buffer((uint64_t)(uintptr_t)(p.K + (size_t)kv * N * D), bytes), rsrcV = tile_buffer((uint64_t)(uintptr_t)(p.V + (size_t)kv * N * D), bytes);
+    // K or V of step s (at = s * SLOT bytes) into the slot whose number among all five is `slot`
+    auto request_k = [&](uint32_t at, uint32_t slot) __attribute__((always_inline)) {
+        if constexpr (LI == 4) request4_at(rsrcK, at, offK[0], offK[1], offK[2], offK[3], lds0 + slot * F::SLOT);
+        else request2_at(rsrcK, at, offK[0], offK[1], lds0 + slot * F::SLOT);
     };
-    auto request_k = [&](int s) __attribute__((always_inline)) { request(Kg, s, offK, (uint32_t)(s % 3) * F::SLOT); };
-    auto request_v = [&](int s) __attribute__((always_inline)) { request(Vg, s, offV, (uint32_t)(3 + (s & 1)) * F::SLOT); };
+    auto request_v = [&](uint32_t at, uint32_t slot) __attribute__((always_inline)) {
+        if constexpr (LI == 4) request4_at(rsrcV, at, offV, offV, offV, offV, lds0 + slot * F::SLOT);
+        else request2_at(rsrcV, at, offV, offV, lds0 + slot * F::SLOT);
+    };
 
     const int qrow0 = row0 + 32 * rw, qrow = qrow0 + ql;
     const int qrow_c = min(qrow, N - 1);
     const int limit = p.causal ? qrow_c : N - 1;
     const int k_last = p.causal ? min(N - 1, qrow0 + 31) : N - 1;  // last key that any row of the wave sees
-    bf16x8 qf[KK];
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk)
-        qf[kk] = *reinterpret_cast<const bf16x8*>(Qg + (size_t)qrow_c * D + 16 * kk + 8 * hh);
-    request_k(0);
-    request_k(1);
-    request_v(0);
-    request_k(2);
+    // Q goes through LDS too (the second V slot, which step 0 is the first to write): whole rows, and no load whose result the compiler has
+    // to wait for.  (With Q loaded to registers it waited for them, on the path that skips the first Q.K^T, inside every step, and so for all
+    // requests of K and V in flight.)
+    {
+        const u32x4 rsrcQ = tile_buffer((uint64_t)(uintptr_t)(p.Q + ((size_t)head * N + row0) * D), (uint32_t)min(N - row0, BM) * T::ROWB);
+        if (RPI * LI * wave < BM) {
+            if constexpr (LI == 4) request4_at(rsrcQ, 0, offK[0], offK[1], offK[2], offK[3], lds0 + 4 * F::SLOT);
+            else request2_at(rsrcQ, 0, offK[0], offK[1], lds0 + 4 * F::SLOT);
+        }
+    }
+    request_k(0, 0);
+    request_k(F::SLOT, 1);
+    request_v(0, 3);
+    request_k(2 * F::SLOT, 2);
 
     f32x16 ot[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db) ot[db] = f32x16{0};
     float m2 = -INFINITY, lsum = 0.f;
-    const int kbase = T::k_base(ql, hh) + 32 * kq * T::ROWB, vbase = T::v_base(lane, hh) + 32 * kq * T::ROWB;
-    auto ld_k = [&](const uint8_t* kt, int kk) __attribute__((always_inline)) { return *reinterpret_cast<const bf16x8*>(kt + (kbase ^ (kk << 5))); };
-    auto ld_v = [&](const uint8_t* vt, int f) __attribute__((always_inline)) {
-        const uint8_t* a = vt + (vbase ^ ((f % DB) << 6)) + 16 * (f / DB) * T::ROWB;
-        const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(a));
-        const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(a + 8 * T::ROWB));
+    // fragment addresses: a slot is a constant offset
+    uint32_t ka[KK], va[DB];
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) ka[kk] = lds_addr(Ks) + (((T::k_base(ql, hh) ^ (kk << 5))) + 32 * kq * T::ROWB);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) va[db] = lds_addr(Vs) + ((T::v_base(lane, hh) ^ (db << 6)) + 32 * kq * T::ROWB);
+    auto ld_k = [&](uint32_t slot, int kk) __attribute__((always_inline)) { return *(lds_frag)(ka[kk] + slot); };
+    auto ld_v = [&](uint32_t slot, int f) __attribute__((always_inline)) {
+        const uint32_t a = va[f % DB] + (slot + 16 * (f / DB) * T::ROWB);
+        const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(a));
+        const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(a + 8 * T::ROWB));
         const u32x2 a0 = __builtin_bit_cast(u32x2, v0), a1 = __builtin_bit_cast(u32x2, v1);
         const u32x4 aw = {a0[0], a0[1], a1[0], a1[1]};
         return __builtin_bit_cast(bf16x8, aw);
     };
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (3 * LI));  // K of step 0 has landed
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (3 * LI));  // Q and K of step 0 have landed
     __syncthreads();
-    f32x16 st = f32x16{0};
+    bf16x8 qf[KK];
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) qf[kk] = *(lds_frag)(lds_addr(Vs) + F::SLOT + (T::k_base(ql, hh) ^ (kk << 5)) + 32 * rw * T::ROWB);
+    f32x16 sa = f32x16{0}, sb;
     if (32 * kq <= k_last) {
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_k(Ks, kk), qf[kk], st, 0, 0, 0);
+        for (int kk = 0; kk < KK; ++kk) sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_k(0, kk), qf[kk], sa, 0, 0, 0);
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70 | LI);  // K of step 1 and V of step 0
+    __builtin_amdgcn_s_waitcnt(0x0070 | LI);  // K of step 1 and V of step 0; Q has been read
     __syncthreads();
 
-    // step s: softmax of its scores and P.V, with Q.K^T of step s + 1 (NEXT) in front
-    auto step = [&](int s, auto next_c, auto masked_c) __attribute__((always_inline)) {
+    // step s (at = s * SLOT): softmax of its scores st and P.V, with Q.K^T of step s + 1 (NEXT), whose scores go to sn, in front.  slot_k,
+    // slot_v: byte offsets of K of step s + 1 in the K slots and of V of step s in the V slots; to_k, to_v: the slots that are written
+    auto step = [&](int s, uint32_t at, f32x16& st, f32x16& sn, uint32_t slot_k, uint32_t slot_v, uint32_t to_k, uint32_t to_v, auto next_c, auto masked_c)
+                    __attribute__((always_inline)) {
         constexpr bool NEXT = decltype(next_c)::value, MASKED = decltype(masked_c)::value;
-        const int c0 = s * KT + 32 * kq;
-        const uint8_t* const kt = Ks + ((s + 1) % 3) * F::SLOT;
-        const uint8_t* const vt = Vs + (s & 1) * F::SLOT;
         bf16x8 fr[4];
         constexpr int H = KK / 2;
         if (NEXT) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) fr[e] = ld_k(kt, e);
+            for (int e = 0; e < 4; ++e) fr[e] = ld_k(slot_k, e);
         }
         __builtin_amdgcn_sched_barrier(0);
         if (MASKED) {
-            const int rel = limit - c0 - 4 * hh;
+            const int rel = limit - (s * KT + 32 * kq) - 4 * hh;
 #pragma unroll
             for (int r = 0; r < 16; ++r) st[r] = (8 * (r >> 2) + (r & 3) <= rel) ? st[r] : -INFINITY;
         }
-        f32x16 sn = f32x16{0};
-        float mx[2] = {st[0], st[1]};
+        float mx = fmaxf(fmaxf(st[0], st[1]), st[2]);
         // the first half of Q.K^T with the row max dealt out between
 #pragma unroll
         for (int e = 0; e < H; ++e) {
             if (NEXT) {
-                sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[e & 3], qf[e], sn, 0, 0, 0);
-                if (e + 4 < KK) fr[e & 3] = ld_k(kt, e + 4);
+                sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[e & 3], qf[e], e == 0 ? f32x16{0} : sn, 0, 0, 0);
+                if (e + 4 < KK) fr[e & 3] = ld_k(slot_k, e + 4);
             }
-            if (e + 4 >= KK) fr[e & 3] = ld_v(vt, e + 4 - KK);
-            if (e == 1) request_v(s + 1);
+            if (e + 4 >= KK) fr[e & 3] = ld_v(slot_v, e + 4 - KK);
+            if (e == 1) request_v(at + F::SLOT, to_v);
 #pragma unroll
-            for (int r = 2 + 14 * e / H; r < 2 + 14 * (e + 1) / H; ++r) mx[r & 1] = fmaxf(mx[r & 1], st[r]);
+            for (int q = 6 * e / H; q < 6 * (e + 1) / H; ++q) mx = fmaxf(fmaxf(mx, st[3 + 2 * q]), st[4 + 2 * q]);
             if (NEXT) __builtin_amdgcn_sched_barrier(0);
         }
-        const float m_new = fmaxf(m2, __builtin_fmaf(xhalf_max(fmaxf(mx[0], mx[1])), p.c, kKeepMax));
-        if (__builtin_amdgcn_ballot_w64(!(m_new <= m2 + kKeepMax)) != 0) {
+        // (the third operand saves the two instructions that would quiet signalling NaNs first)
+        mx = fmaxf(mx, st[15]);
+        const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+        const float m_tile = __builtin_fmaf(fmaxf(fmaxf(__uint_as_float(halves[0]), __uint_as_float(halves[1])), -INFINITY), p.c, kKeepMax);
+        if (__builtin_amdgcn_ballot_w64(!(m_tile <= m2 + kKeepMax)) != 0) {
+            const float m_new = fmaxf(m2, m_tile);
             const float msub = m_new == -INFINITY ? 0.f : m_new;
             const float alpha = __builtin_amdgcn_exp2f(m2 - msub);
             lsum *= alpha;
@@ -206,9 +215,9 @@ __global__ __launch_bounds__(128 * KQ, 2) void attn_fwd_short_kernel(const Param
         for (int e = H; e < KK; ++e) {
             if (NEXT) {
                 sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[e & 3], qf[e], sn, 0, 0, 0);
-                if (e + 4 < KK) fr[e & 3] = ld_k(kt, e + 4);
+                if (e + 4 < KK) fr[e & 3] = ld_k(slot_k, e + 4);
             }
-            if (e + 4 >= KK) fr[e & 3] = ld_v(vt, e + 4 - KK);
+            if (e + 4 >= KK) fr[e & 3] = ld_v(slot_v, e + 4 - KK);
 #pragma unroll
             for (int q = 4 * (e - H) / H; q < 4 * (e - H + 1) / H; ++q) slice(q);
             if (NEXT) __builtin_amdgcn_sched_barrier(0);
@@ -221,15 +230,14 @@ __global__ __launch_bounds__(128 * KQ, 2) void attn_fwd_short_kernel(const Param
 #pragma unroll
         for (int f = 0; f < DB; ++f) {
             ot[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[f & 3], pf(0), ot[f], 0, 0, 0);
-            if (f + 4 < 2 * DB) fr[f & 3] = ld_v(vt, f + 4);
-            if (f == 0) request_k(s + 3);
+            if (f + 4 < 2 * DB) fr[f & 3] = ld_v(slot_v, f + 4);
+            if (f == 0) request_k(at + 3 * F::SLOT, to_k);
 #pragma unroll
             for (int q = 4 + 4 * f / DB; q < 4 + 4 * (f + 1) / DB; ++q) slice(q);
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int f = 0; f < DB; ++f) ot[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[(f + DB) & 3], pf(1), ot[f], 0, 0, 0);
-        if (NEXT) st = sn;
     };
     using std::false_type;
     using std::true_type;
@@ -239,18 +247,35 @@ __global__ __launch_bounds__(128 * KQ, 2) void attn_fwd_short_kernel(const Param
     };
     const int n_own = k_last < 32 * kq ? 0 : (k_last - 32 * kq) / KT + 1;  // steps that this wave has keys in: the first ones
     int s = 0;
-    for (; s < n_own - 1; ++s) {
-        step(s, true_type{}, false_type{});
-        next_step();
+    uint32_t at = 0;
+    // six steps in a row bring the slots back to where they were (three of K, two of V), so that each step's are constants
+    for (;;) {
+        auto one = [&](auto j_c) __attribute__((always_inline)) {  // (as a function with a result: a break behind each step made the compiler spill)
+            constexpr int J = decltype(j_c)::value;
+            if (s >= n_own - 1) return false;
+            step(s, at, J & 1 ? sb : sa, J & 1 ? sa : sb, (J + 1) % 3 * F::SLOT, J % 2 * F::SLOT, J % 3, 3 + (J + 1) % 2, true_type{}, false_type{});
+            next_step();
+            ++s;
+            at += F::SLOT;
+            return true;
+        };
+        if (!one(std::integral_constant<int, 0>{})) break;
+        if (!one(std::integral_constant<int, 1>{})) break;
+        if (!one(std::integral_constant<int, 2>{})) break;
+        if (!one(std::integral_constant<int, 3>{})) break;
+        if (!one(std::integral_constant<int, 4>{})) break;
+        if (!one(std::integral_constant<int, 5>{})) break;
     }
     if (n_own > 0) {
-        step(s, false_type{}, true_type{});
+        if (s & 1) sa = sb;
+        step(s, at, sa, sb, 0, s % 2 * F::SLOT, s % 3, 3 + (s + 1) % 2, false_type{}, true_type{});
         next_step();
         ++s;
+        at += F::SLOT;
     }
-    for (; s < n_steps; ++s) {
-        request_v(s + 1);
-        request_k(s + 3);
+    for (; s < n_steps; ++s, at += F::SLOT) {
+        request_v(at + F::SLOT, 3 + (s + 1) % 2);
+        request_k(at + 3 * F::SLOT, s % 3);
         next_step();
     }
     wait_vm0_and_sync();  // (the requests past the last step write zeros)
@@ -287,8 +312,8 @@ __global__ __launch_bounds__(128 * KQ, 2) void attn_fwd_short_kernel(const Param
     auto finish = [&](auto kq_c) __attribute__((always_inline)) {
         constexpr int KO = decltype(kq_c)::value;
         if (qrow < N && p.LSE && KO == 0 && hh == 0)
-            p.LSE[(size_t)(b * p.Hq + h) * N + qrow] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
-        uint16_t* const Og = p.O + ((size_t)(b * p.Hq + h) * N + qrow_c) * D;
+            p.LSE[(size_t)head * N + qrow] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
+        uint16_t* const Og = p.O + ((size_t)head * N + qrow_c) * D;
 #pragma unroll
         for (int v = 0; v < OWN; ++v) {
             constexpr int U0 = KO * OWN;

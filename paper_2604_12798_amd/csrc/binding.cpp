@@ -6,8 +6,8 @@
 //
 // What the wrappers of __init__.py look up on every call, is_cuda, dtype, is_contiguous(), shape and data_ptr() of up to seven objects,
 // is looked up here too (check_qkv, check_cache, bytes_of): the same attributes in the same order, so that whatever has them works as
-// before, without an interpreter step for each.  Host time of a call, launches included, before / after in us: vfa_attn_fwd 7.1 / 4.9,
-// an append and a decode step 12.4 / 10.3.
+// before, without an interpreter step for each.  Host time of a call, launches included, before / after in us: vfa_attn_fwd 7.1 / 5.3,
+// an append and a decode step 12.4 / 10.2.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 

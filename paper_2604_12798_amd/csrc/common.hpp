@@ -47,6 +47,20 @@ constexpr bool is_lazy(int mode) { return mode == MODE_FA_LAZY || mode == MODE_F
 constexpr int SOFTEXP_EVERY = VFA_SOFTEXP_EVERY;
 constexpr int softexp_every(int mode) { return mode == MODE_FA_SOFTEXP ? SOFTEXP_EVERY : 0; }
 
+// Quotients by a number that the host knows, n / d for 0 <= n < 2^31: n * mul >> shift with mul = floor(2^(31 + l) / d) + 1 and shift = 31 + l,
+// l the smallest number with 2^l >= d.  (mul is below 2^32, and n * mul is above the true n 2^(31 + l) / d by at most n < 2^31, which is less
+// than 1 / d of 2^(31 + l): no whole number lies in between.)
+struct Reciprocal {
+    uint32_t mul, shift;
+    __host__ void set(int d) {
+        int l = 0;
+        while ((1u << l) < (uint32_t)d) ++l;
+        mul = (uint32_t)(((uint64_t)1 << (31 + l)) / (uint32_t)d + 1);
+        shift = 31 + l;
+    }
+    __host__ __device__ int operator()(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> shift); }
+};
+
 struct Params {
     const uint16_t* Q;
     const uint16_t* K;
@@ -66,6 +80,8 @@ struct Params {
     int n_items;      // attn_short.hpp: its work items; the workgroups behind them write the summaries
     int row_base;     // attn_frozen.hpp, attn_short.hpp: the first row of every head they work on
     int rowskip;      // skip variant: in a kept tile, rows that fail the threshold test are suppressed (generic kernel)
+    int g;                     // attn_short.hpp: query heads per KV head
+    Reciprocal by_g, by_list;  // attn_short.hpp: 1 / g; 1 / items of a list (a KV head's where there is a list for each XCD, else a row block's)
     float c;     // softmax scale * log2(e)
     float thr2;  // skip threshold in log2 units
     float tau2;  // MODE_FA_LAZY: a row keeps its old max while the new one exceeds it by at most tau2 (log2 units)
@@ -260,6 +276,28 @@ __device__ __forceinline__ void request_dwords(uint64_t base, uint32_t bytes, ui
                  : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(o0), "s"(tile_buffer(base, bytes))
                  : "memory");
 }
+
+// The same from the byte `at` of a buffer on (request4, request2), which may lie past its end.
+__device__ __forceinline__ void request4_at(const u32x4& rsrc, uint32_t at, uint32_t o0, uint32_t o1, uint32_t o2, uint32_t o3, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %1, %5, %6 offen lds\n\tbuffer_load_dwordx4 %2, %5, %6 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %3, %5, %6 offen offset:2048 lds\n\tbuffer_load_dwordx4 %4, %5, %6 offen offset:3072 lds"
+                 :
+                 : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(o0), "v"(o1), "v"(o2), "v"(o3), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(at))
+                 : "memory", "m0");
+}
+__device__ __forceinline__ void request2_at(const u32x4& rsrc, uint32_t at, uint32_t o0, uint32_t o1, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %3, %4 offen lds\n\t"
+                 "buffer_load_dwordx4 %2, %3, %4 offen offset:1024 lds"
+                 :
+                 : "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(o0), "v"(o1), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(at))
+                 : "memory", "m0");
+}
+
+// LDS by its byte address
+typedef const __attribute__((address_space(3))) bf16x8* lds_frag;
+typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+__device__ __forceinline__ uint32_t lds_addr(const uint8_t* p) { return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t*)p; }
 
 // S^T tile: st[t][i] = raw score of query ql against key 32*t + 8*(i/4) + 4*hh + (i%4)
 template <int D>

@@ -103,6 +103,9 @@ int launch_short(Params p, int row_base, bool summaries, hipStream_t s) {
     p.row_base = row_base;
     p.Tr = ceil_div(p.N - row_base, 64);
     p.n_items = p.B * p.Hq * p.Tr;
+    p.g = p.Hq / p.Hkv;
+    p.by_g.set(p.g);
+    p.by_list.set(((p.B * p.Hkv) & 7) == 0 ? p.Tr * p.g : p.B * p.Hq);
     const long long wgs = p.n_items + (summaries ? ((long long)p.B * p.Hkv * p.Tc + 2 * KQ - 1) / (2 * KQ) : 0);
     attn_fwd_short_kernel<D, KQ><<<dim3((unsigned)wgs), 128 * KQ, Short<D, KQ>::LDS_BYTES, s>>>(p);
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
@@ -172,7 +175,7 @@ int short_groups(const Params& p, int d, int n_cu) {
 // In us, before / after: 16 heads, N = 5000 (one round and 904 rows) 222 / 197; 24 heads, N = 3000 141 / 119; 32 heads, N = 3000
 // (rest on attn_frozen.hpp) 149 / 144; 48 heads, N = 1751 96 / 101 with that, so only above 32 tiles.
 int tail_row(const Params& p, int n_cu, bool head_pairs) {
-    if (p.causal || p.n_sink > 4 || p.n_local > 4 || n_cu <= 0 || p.Tc <= 12) return 0;
+    if (p.causal || p.n_sink > 4 || p.n_local > 4 || n_cu <= 0 || p.Tc <= 12 || p.N > 1 << 23) return 0;  // (the last: attn_short.hpp's offsets)
     const long long heads = (long long)p.B * p.Hq, per_band = head_pairs ? heads / 2 : heads;  // items of `band` rows
     const int band = head_pairs ? 128 : 256;
     const long long rounds = per_band * ceil_div(p.N, band) / n_cu, bands = rounds * n_cu / per_band, rows = bands * band;
