@@ -120,53 +120,48 @@ int launch_frozen(Params p, int row_base, int block_m, hipStream_t s) {  // rows
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
 }
 
-// Alg. 1 on the kernel for short sequences (attn_short.hpp): 0 = no, else its groups of keys.  `items` are blocks of 64 rows.  The other
-// kernels, with the summaries' launch in front, have up to twice the rate once their long items fill the compute units; the lines
-// lie where they catch up.  In us, theirs / this one (each line's last shapes, then the first beyond it where that was measured):
+// Alg. 1 on the kernel for short sequences (attn_short.hpp): 0 = no, else its groups of keys.  `items` are blocks of 64 rows, `rounds` those
+// of the ping-pong kernel, which has twice the rate once its items of 256 rows fill the compute units evenly.  The lines lie where the
+// others, with the summaries' launch in front, catch up.  In us, theirs / this one, about each line (2480 shapes of 7 to 96 tiles swept, with two
+// groups, four and neither; in the mean 0.4 to 0.7 % over the fastest of the three):
 //   four groups, from ten tiles on, for no more items than units (at d = 128 the summaries' workgroups counted, since one fills a
-//     unit): 8 heads, N = 1024 22.8 / 13.4, no mask, d = 64, N = 2048 22.9 / 15.7; causal, few long heads, whose items are uneven: up to four
-//     per unit at d = 64 (12 heads, N = 3802 47 / 37), two at d = 128 (12 heads, N = 2500 40.8 / 33.6)
-//   d = 64, two groups, no mask: up to 7 tiles always (512 heads, N = 344 36.7 / 35.1); 11 with 12 items per unit (320 heads, N = 576 49.2 /
-//     46.0; 512 heads, N = 495 54.4 / 55.9); 14 with 10 (160 heads, N = 896 50.8 / 49.2; 256 heads, N = 768 55.7 / 57.9); 16 with 7 (112 heads,
-//     N = 1024 45.3 / 43.5; 160 heads, N = 960 55.2 / 56.9); 24 with 5 (64 heads, N = 1263 40.7 / 38.6, N = 1344 42.9 / 45.5)
-//   d = 64, causal: up to 14 tiles always; 24 with 24 items per unit (256 heads, N = 1536 114.4 / 114.7; 512 heads, N = 1024 111.4 / 114.2, N =
-//     1536 213.9 / 221.9) or an odd number of them, which leaves half of the others' last block of 128 rows empty (512 heads, N = 1281 179.8 /
-//     174.3); 28 with 9 (80 heads, N = 1792 50.3 / 49.0; 192 heads, N = 1624 101.2 / 103.8); 29, odd, with 11 (96 heads, N = 1800 74.9 / 70.0; 512
-//     heads 324 / 334); 64 with 6.2 (48 heads, N = 2072 45.0 / 39.7; 64 heads, N = 2048 55.2 / 58.9)
-//   d = 128, two groups: up to seven tiles always (512 heads, N = 448 1.12 and 1.02 times faster, causal and not)
-//   d = 128, causal: 13 tiles with 13 items per unit (256 heads, N = 815 88.9 / 76.1), 16 with 6.2 (96 heads, N = 984 48.4 / 44.6; 128 heads, N =
-//     1024 55 / 60), 24 with 4.6 (48 heads, N = 1496 46.4 / 43.0; 64 heads, N = 1536 52.9 / 56.0), 64 with 3.8 (24 heads, N = 2543 62.5 / 54.8; 32 heads,
-//     N = 3000 83 / 91)
-//   odd groups of heads, causal, run in super-blocks of 256 rows otherwise: up to 40 tiles and 11 items per unit (160 heads, N = 1088 125 /
-//     83; 64 heads, N = 2543 156 / 144; 40 heads, N = 2799 102 / 114), but for nearly full rounds of those (32 heads, N = 2048, one round, 56.5 / 59.6)
-//   d = 128, no mask: 8 tiles with 5 items per unit (160 heads, N = 512 47 / 36), 16 with 3.2 (48 heads, N = 1024 36.6 / 34.8; 64 heads, N = 1024 41.5 /
-//     44.5), 24 with 2 (16 heads, N = 1536 30.0 / 28.8; 32 heads, N = 1536 46.7 / 49.1), 30 where the others run a second round for a few items (48
-//     heads, N = 1344 79 / 55; 40 heads, N = 1880 100 / 91)
+//     unit), against two: d = 128, 4 heads, N = 4096 35.3 / 29.9, 8 heads, N = 1024 12.3 / 11.5; causal, few long heads, whose items are uneven: up to
+//     four per unit at d = 64 (12 heads, N = 4096 35.5 / 34.3), 1.9 at d = 128 (8 heads, N = 3600 39.8 / 35.5; 16 heads, N = 1536 18.5 / 18.0)
+//   d = 64, causal: up to 34 tiles always (256 heads, N = 2176 1.03 times faster), 57 with 16 items per unit (96 heads, N = 3000 142.5 / 128.6; 8 x 32
+//     heads, N = 2500, 40 per unit 266.6 / 268.7), 96 with 8 (the mean at 88 tiles 1.13; 4 x 16 heads, N = 4096, 16 per unit 159.7 / 163.5)
+//   d = 64, no mask: up to 24 tiles always (1.10 times up to 8 items per unit, 0.99 beyond 16), 48 with 8 (1.02, beyond 0.97 to 0.99), 96 with 4 (1.08,
+//     beyond 0.95)
+//   d = 128, causal, an even number of heads per KV head: up to 47 tiles (64 heads, N = 2600 138.3 / 130.0), but for two or four nearly full
+//     rounds from 30 on, in which long and short items pair up (64 heads, N = 2048 76.8 / 80.8); 96 with 1.2 rounds (24 heads, N = 3000 71.7 /
+//     60.6; 32 heads, N = 4096, 2 rounds 125 / 137)
+//   an odd number, whose super-blocks cover both diagonals: up to 60 tiles always (48 heads, N = 2300 1.42 times), 96 unless the last round
+//     is nearly full (32 heads, N = 2700 101.4 / 77.3, N = 5000 1.35 times; N = 4096, 2 rounds 0.92)
+//   d = 128, no mask: up to 24 tiles always (128 heads, N = 640 55.4 / 37.7, 96 heads, N = 1536 141 / 119, 128 heads, N = 1536 0.95 to 0.99), 32 where
+//     the others' rounds are poorly filled (48 heads, N = 1800 104 / 90, N = 2048 114 / 105; 64 heads, N = 2048, 2 rounds 0.94), 64 with 1.3 items per unit
+//     (8 heads, N = 2560 38.9 / 36.9)
 //   more than four sink or local blocks: never
-// Of 3920 shapes of 5 to 48 tiles this kernel runs 2281, in the mean 1.33 times faster; more than 3 % slower are d = 64, causal, odd groups: 64
-// heads, N = 1496 and 48 heads, N = 1792 (7 %), 24 heads, N = 3072 (3.3 %).
 int short_groups(const Params& p, int d, int n_cu) {
     const long long heads = (long long)p.B * p.Hq, items = heads * p.Tc;  // (of 64 rows)
-    if (n_cu <= 0 || p.n_sink > 4 || p.n_local > 4) return 0;
+    if (n_cu <= 0 || p.n_sink > 4 || p.n_local > 4 || p.Tc > 96) return 0;
     if (items + ((long long)p.B * p.Hkv * p.Tc + 3) / 4 > kMaxWorkgroups256) return 0;  // (with the summaries' workgroups; four groups are for few items)
     const int Tc = p.Tc;
     auto upto = [&](int tiles, double per_cu) { return Tc <= tiles && items <= (long long)(per_cu * n_cu); };
+    const bool few_heads = p.causal && 16 * heads <= n_cu;
     if (d == 64) {
-        if (Tc >= 10 && (upto(64, 1) || (p.causal && 16 * heads <= n_cu && upto(64, 4)))) return 4;
-        const bool odd = Tc & 1;
-        if (p.causal) return Tc <= 14 || upto(24, odd ? 1e9 : 24) || upto(odd ? 29 : 28, odd ? 11 : 9) || upto(64, 6.2) ? 2 : 0;
-        return Tc <= 7 || upto(11, 12) || upto(14, 10) || upto(16, 7) || upto(24, 5) ? 2 : 0;
+        if (Tc >= 10 && (upto(96, 1) || (few_heads && upto(96, 4)))) return 4;
+        if (p.causal) return Tc <= 34 || upto(57, 16) || upto(96, 8) ? 2 : 0;
+        return Tc <= 24 || upto(48, 8) || upto(96, 4) ? 2 : 0;
     }
     const long long summary_wgs = ((long long)p.B * p.Hkv * Tc + 7) / 8;
-    if (Tc >= 10 && Tc <= 64 && (items + summary_wgs <= n_cu || (p.causal && Tc >= 20 && 16 * heads <= n_cu && upto(64, 2)))) return 4;
-    if (Tc <= 7) return 2;
+    if (Tc >= 10 && Tc <= 64 && (items + summary_wgs <= n_cu || (few_heads && Tc >= 16 && upto(64, 1.9)))) return 4;
     const int g = p.Hq / p.Hkv, blocks = ceil_div(p.N, 128);
-    const double pp = (double)((g & 1) == 0 ? heads / 2 * blocks : heads * ((blocks + 1) / 2)) / n_cu;  // rounds of the ping-pong kernel
+    const double rounds = (double)((g & 1) == 0 ? heads / 2 * blocks : heads * ((blocks + 1) / 2)) / n_cu;
     if (p.causal) {
-        if (upto(13, 13) || upto(16, 6.2) || upto(24, 4.6) || upto(64, 3.8)) return 2;
-        return (g & 1) && upto(40, 11) && !(pp >= 0.85 && pp <= 1) && !(pp > 1.9 && pp <= 2) ? 2 : 0;
+        const bool paired = Tc >= 30 && rounds > 1.75 && ceil(rounds) - rounds < 0.25 && ((int)ceil(rounds) & 1) == 0;
+        if ((g & 1) == 0) return (Tc <= 47 && !paired) || rounds <= 1.2 ? 2 : 0;
+        return Tc <= 60 || rounds < 1.2 || ceil(rounds) - rounds >= 0.15 ? 2 : 0;
     }
-    return upto(8, 5) || upto(16, 3.2) || upto(24, 2) || (Tc <= 30 && pp > 1 && pp <= 1.32) ? 2 : 0;
+    return Tc <= 24 || (Tc <= 32 && (rounds < 0.8 || (rounds > 1 && rounds <= 1.6))) || upto(64, 1.3) ? 2 : 0;
 }
 
 // Without a causal mask all items are equally long, and what is left of them after whole rounds of the ping-pong kernel takes as long

@@ -1,5 +1,5 @@
 """Alg. 1 on attn_short.hpp: every number of steps on either side of the six that its loop is unrolled by, list lengths and heads that
-are no powers of two.  Every row of every head against exact attention."""
+are no powers of two, and sizes on both sides of the lines to the other kernels.  Every row of every head against exact attention."""
 import pytest
 
 from gpu_util import check_every_row
@@ -28,3 +28,11 @@ def test_steps(d, causal, steps):
     if steps >= 5:
         _check(d, 1, 3, 1, 128 * steps - 5 * (steps % 2), causal)
 
+
+# the lines of short_groups on a chip of 256 units
+@pytest.mark.parametrize("d,Hq,Hkv,N,causal", [
+    (128, 64, 32, 3008, True), (128, 48, 48, 3840, True), (128, 4, 2, 6144, True), (64, 64, 16, 3648, True), (64, 320, 32, 2176, True), (128, 64, 16, 2048, True), (64, 16, 4, 6144, True),
+    (128, 64, 16, 1536, False), (128, 48, 16, 2048, False), (128, 4, 4, 4096, False), (64, 128, 32, 1536, False), (64, 32, 8, 3072, False), (64, 8, 8, 6144, False)])
+@pytest.mark.parametrize("behind", [0, 1])
+def test_lines(d, Hq, Hkv, N, causal, behind):
+    _check(d, 1, Hq, Hkv, N + behind, causal)
