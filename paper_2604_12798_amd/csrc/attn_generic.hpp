@@ -1,5 +1,5 @@
-// Generic bf16 attention kernel: any supported (d, block_m), all ablation switches; Alg. 2 on short sequences and where
-// attn_vsa.hpp does not cover it, the baselines at d = 64, Alg. 1 with more than four sink or local blocks on short sequences.
+// Generic bf16 attention kernel: any supported (d, block_m), all ablation switches; Alg. 2 where attn_sparse.hpp and
+// attn_vsa.hpp do not cover it, the baselines at d = 64, Alg. 1 with more than four sink or local blocks on short sequences.
 #pragma once
 #include "common.hpp"
 

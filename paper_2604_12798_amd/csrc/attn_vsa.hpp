@@ -1,4 +1,4 @@
-// VSA (Alg. 2) on the ping-pong structure for d = 128, block_m = 128: the kernel vsa_attn_fwd runs on.
+// VSA (Alg. 2) on the ping-pong structure for d = 128, block_m = 128: long sequences with more than four sink or local blocks.
 #pragma once
 #include "common.hpp"
 

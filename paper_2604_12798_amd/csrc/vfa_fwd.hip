@@ -12,6 +12,7 @@
 #include "attn_pingpong.hpp"
 #include "attn_frozen.hpp"
 #include "attn_short.hpp"
+#include "attn_sparse.hpp"
 #include "vsa_pp.hpp"
 #include "summary.hpp"
 #include "decode.hpp"
@@ -91,6 +92,7 @@ bool raise_lds_limits() {
     if (dev < 0) return false;
     if (done[dev].load(std::memory_order_acquire)) return true;
     if (!raise_short<64, 2>() || !raise_short<64, 4>() || !raise_short<128, 2>() || !raise_short<128, 4>()) return false;
+    if (!raise_lds_limit(&attn_sparse_kernel, Sparse::LDS_BYTES)) return false;
     if (!raise_frozen<64, 1>() || !raise_frozen<64, 2>() || !raise_frozen<128, 2>() || !raise_pp<MODE_VFA>() || !raise_pp<MODE_FA>() ||
         !raise_pp<MODE_FA_LAZY>() || !raise_pp<MODE_FA_SOFTEXP>() || vfa_detail_vsa_pp_raise_lds() != 0)
         return false;
@@ -218,15 +220,28 @@ bool prefer_rows64(const Params& p, int n_cu, bool head_pairs, bool frozen, bool
     return p.Tc <= 14 && (items + slots - 1) / slots <= (pairs + n_cu - 1) / n_cu;
 }
 
-// Alg. 2 at d = 128, block_m = 128: the generic kernel up to this many tokens (causal; half as many non-causal), the ping-pong
-// kernel above.  In the generic kernel a workgroup drops a tile alone (the ping-pong kernel's interval is short only where
-// both of its groups drop theirs), and the ends of a work item cost no more than its middle; the ping-pong kernel's steps
-// overlap better and don't fetch V for a dropped tile.  Generic / ping-pong us, 32/8 heads, 20 to 40 % of the tiles dropped:
-// N = 777 29 / 64, 2048 68 / 101, 4096 161 / 202, 8000 511 / 560, 10000 784 / 847, 16384 1863 / 1884, 64K (8 heads) 7147 /
-// 6290; with nothing dropped 8000 583 / 614, 10000 881 / 919, 12200 1262 / 1268, 16384 2262 / 2169; 8/1 heads 10000 268 / 290,
-// 16384 515 / 493; with 98 % dropped 10200 535 / 532; four batches of N = 8000 1901 / 2386.
-// Non-causal: N = 4096 264 / 286, 5000 395 / 454, 6100 547 / 550, nothing dropped 655 / 643.  Slower here by more than 2 %: 98 %
-// dropped, non-causal N = 5100 (4.5 %), and 12 heads, N = 10200 (2.5 %).
+// Alg. 2 at d = 128, block_m = 128 runs on attn_sparse_kernel where a block meets enough tiles for what that one does before its main
+// loop: the scores of every sink and local block but tile 0, which the loop takes again.  us on the other kernels / there:
+//   one sink and one local block (two such tiles): 32/8 heads, N = 256 15.2 / 15.4, 512 21.5 / 20.4, 2048 67 / 58, 8000 555 / 502;
+//   four and four (eight): 32/8 heads, N = 512 22.8 / 24.5, 777 30.2 / 31.0, 2048 66.8 / 65.9, 4096 174 / 163, 32768 (8 heads) 2231 / 1935;
+//   none: N = 256 14.5 / 13.3, 512 20.6 / 18.2;
+// with several items to a workgroup's place the other kernel hides its own ends, and it takes a longer loop: 128/8 heads, N = 1024, one
+// and one 64.2 / 65.4, four and four 65.7 / 74.8; 64/8 heads, N = 4096, four and four 316.6 / 315.9.
+bool prefer_sparse(const Params& p, int n_cu) {
+    const long long items = (long long)p.B * p.Hq * p.Tr;
+    if (p.n_sink > 4 || p.n_local > 4 || items > kMaxWorkgroups256 || p.N > 1 << 23) return false;  // (its LDS; a launch; 32-bit offsets)
+    const int again = (p.n_sink > 1 ? p.n_sink - 1 : 0) + (p.n_local > 0 ? p.n_local + 1 : 0);
+    return (p.causal ? p.Tc + 2 : 2 * p.Tc) >= (items > 2 * n_cu ? 10 : 4) * again;  // (twice a block's tiles, on average)
+}
+
+// Otherwise (more than four sink or local blocks, above all): the generic kernel up to this many tokens (causal; half as many
+// non-causal), the ping-pong kernel above.  In the generic kernel a workgroup drops a tile alone (the ping-pong kernel's interval
+// is short only where both of its groups drop theirs), and the ends of a work item cost no more than its middle; the ping-pong
+// kernel's steps overlap better and don't fetch V for a dropped tile.  Generic / ping-pong us, 32/8 heads, 20 to 40 % of the tiles
+// dropped: N = 8000 511 / 560, 10000 784 / 847, 16384 1863 / 1884, 64K (8 heads) 7147 / 6290; with nothing dropped 8000 583 / 614,
+// 10000 881 / 919, 12200 1262 / 1268, 16384 2262 / 2169; 8/1 heads 10000 268 / 290, 16384 515 / 493; with 98 % dropped 10200
+// 535 / 532; four batches of N = 8000 1901 / 2386.  Non-causal: N = 4096 264 / 286, 5000 395 / 454, 6100 547 / 550, nothing dropped
+// 655 / 643.
 constexpr int VSA_GENERIC_MAX_N = 10240;
 
 // `fixed_max`: Alg. 1 as written on all rows (no kernel that takes every block's scores into the max)
@@ -261,6 +276,15 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s, bool fixed_ma
             rows64 = block_m == 64 && prefer_rows64(q, cu_count(), head_pairs, frozen, false);
             if (frozen && !rows64) return launch_frozen<128, 2>(q, 0, block_m, s);
             if (rows64) tail = 0;
+        }
+    }
+    if constexpr (MODE == MODE_VSA) {
+        if (!ablation && d == 128 && block_m == 128 && prefer_sparse(p, cu_count())) {
+            q.g = g;
+            q.by_g.set(g);
+            q.by_list.set(((p.B * p.Hkv) & 7) == 0 ? p.Tr * g : p.B * p.Hq);
+            attn_sparse_kernel<<<dim3((unsigned)(p.B * p.Hq * p.Tr)), 256, Sparse::LDS_BYTES, s>>>(q);
+            return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
         }
     }
     if constexpr (is_fa(MODE)) {
