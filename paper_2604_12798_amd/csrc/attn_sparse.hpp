@@ -14,8 +14,8 @@ namespace {
 // that tile is kept; and its vote on tile k + 1, which the other waves read behind the step's barrier.  A dropped tile costs its Q.K^T and
 // its row max, and its V is not requested.
 //
-// Bound by the matrix pipe (32 MFMAs a kept tile and wave, 65 cycles a pair) where tiles are kept, by the serial end of a step (row max, vote,
-// barrier: some 1500 of 3400 cycles that issue no MFMA) where they are dropped.  So a workgroup is four waves, and the two of a compute unit
+// Bound by the matrix pipe where tiles are kept (32 MFMAs a tile and wave; 63 % busy at N = 65536, 60 % dropped), by the serial end of a step
+// where they are dropped (row max, vote, barrier, requests: with eight waves behind one barrier 1500 of a step's 3400 cycles).  So a workgroup is four waves, and the two of a compute unit
 // drift apart and fill each other's ends; eight waves behind one barrier, the keys split in two, took 378 us where this takes 338
 // (32/8 heads, N = 8000, 71 % dropped) and gained on it only below one item per compute unit.  Priority while a wave issues MFMAs: 2 %
 // (921 to 902 us, the same heads, non-causal); requests in front of P.V instead of behind it: 1 % slower.
