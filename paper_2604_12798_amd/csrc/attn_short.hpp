@@ -63,21 +63,7 @@ __global__ __launch_bounds__(128 * KQ, 2) void attn_fwd_short_kernel(const Param
         if (w < p.B * p.Hkv * p.Tc) summary_of_block<D>(p.K, const_cast<uint16_t*>(p.Krepr), w / p.Tc, w % p.Tc, p.N, p.N, p.Tc, BN, lane);
         return;
     }
-    // items: late (long) query blocks first; the KV heads congruent mod 8 on one XCD, as in the other kernels (of the batch's query heads
-    // `head`, of its KV heads `kv`; quotients by the host's reciprocals: divisions took 0.3 us of the 5 that an empty sequence takes)
-    const int g = p.g;
-    int head, kv, i;
-    if (((p.B * p.Hkv) & 7) == 0) {
-        const int y = id >> 3, kvl = p.by_list(y), rem = y - kvl * p.Tr * g, t = p.by_g(rem);
-        kv = kvl * 8 + (id & 7);
-        head = kv * g + rem - t * g;
-        i = p.Tr - 1 - t;
-    } else {
-        const int t = p.by_list(id);
-        head = id - t * p.B * p.Hq;
-        kv = p.by_g(head);
-        i = p.Tr - 1 - t;
-    }
+    const auto [head, kv, i] = item_of(p, id);
     const int N = p.N;
     const int row0 = p.row_base + i * BM;
     const int n_vis = p.causal ? min(N, row0 + BM) : N;  // keys that any row sees

@@ -44,20 +44,7 @@ __global__ __launch_bounds__(256, 2) void attn_sparse_kernel(const Params p) {
     uint8_t* const Ks = sparse_smem;
     uint8_t* const Vs = Ks + S * T::BYTES;
 
-    // items as in attn_short.hpp
-    const int id = blockIdx.x, g = p.g;
-    int head, kv, i;
-    if (((p.B * p.Hkv) & 7) == 0) {
-        const int y = id >> 3, kvl = p.by_list(y), rem = y - kvl * p.Tr * g, t = p.by_g(rem);
-        kv = kvl * 8 + (id & 7);
-        head = kv * g + rem - t * g;
-        i = p.Tr - 1 - t;
-    } else {
-        const int t = p.by_list(id);
-        head = id - t * p.B * p.Hq;
-        kv = p.by_g(head);
-        i = p.Tr - 1 - t;
-    }
+    const auto [head, kv, i] = item_of(p, blockIdx.x);
     const int N = p.N;
     const int row0 = i * BM;
     const int last_row = min(N, row0 + BM) - 1;

@@ -80,12 +80,40 @@ struct Params {
     int n_items;      // attn_short.hpp: its work items; the workgroups behind them write the summaries
     int row_base;     // attn_frozen.hpp, attn_short.hpp: the first row of every head they work on
     int rowskip;      // skip variant: in a kept tile, rows that fail the threshold test are suppressed (generic kernel)
-    int g;                     // attn_short.hpp: query heads per KV head
-    Reciprocal by_g, by_list;  // attn_short.hpp: 1 / g; 1 / items of a list (a KV head's where there is a list for each XCD, else a row block's)
+    // attn_short.hpp, attn_sparse.hpp (see item_of): query heads per KV head; items outside the lists, their query heads; 1 / g, 1 / items of a KV head, 1 / those
+    // heads
+    int g, n_rest, rest_heads;
+    Reciprocal by_g, by_list, by_rest;
     float c;     // softmax scale * log2(e)
     float thr2;  // skip threshold in log2 units
     float tau2;  // MODE_FA_LAZY: a row keeps its old max while the new one exceeds it by at most tau2 (log2 units)
 };
+
+// The order of the items (blocks of rows) of attn_short.hpp and attn_sparse.hpp.  Eights of KV heads have a list for each XCD: its KV heads one
+// after the other, late (long) blocks first, so that what an XCD works on at a time shares few KV heads in its L2.  The KV heads outside the
+// lists come first, the late blocks of all of them, then the earlier ones: with `lists` those that are left over from the eights, without it
+// all of them unless they are eights.
+__host__ inline void set_items(Params& p, bool lists) {
+    const int G = p.B * p.Hkv, n = G & 7 ? (lists ? G & 7 : G) : 0;  // KV heads outside the lists
+    p.g = p.Hq / p.Hkv;
+    p.rest_heads = n * p.g;
+    p.n_rest = p.rest_heads * p.Tr;
+    p.by_g.set(p.g);
+    p.by_list.set(p.g * p.Tr);
+    p.by_rest.set(n ? p.rest_heads : 1);
+}
+struct Item {
+    int head, kv, i;  // of the batch's query heads, of its KV heads; block of rows
+};
+__host__ __device__ __forceinline__ Item item_of(const Params& p, int id) {
+    if (id < p.n_rest) {
+        const int t = p.by_rest(id), head = p.B * p.Hq - p.rest_heads + id - t * p.rest_heads;
+        return {head, p.by_g(head), p.Tr - 1 - t};
+    }
+    id -= p.n_rest;
+    const int y = id >> 3, kvl = p.by_list(y), rem = y - kvl * p.Tr * p.g, t = p.by_g(rem), kv = kvl * 8 + (id & 7);
+    return {kv * p.g + rem - t * p.g, kv, p.Tr - 1 - t};
+}
 
 // ---------------------------------------------------------------------------------------------
 // LDS tile layout.  A tile is 64 rows of D bf16 (ROWB = 2*D bytes, CH = ROWB/16 16-byte chunks).

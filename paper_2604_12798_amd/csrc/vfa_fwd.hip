@@ -105,9 +105,11 @@ int launch_short(Params p, int row_base, bool summaries, hipStream_t s) {
     p.row_base = row_base;
     p.Tr = ceil_div(p.N - row_base, 64);
     p.n_items = p.B * p.Hq * p.Tr;
-    p.g = p.Hq / p.Hkv;
-    p.by_g.set(p.g);
-    p.by_list.set(((p.B * p.Hkv) & 7) == 0 ? p.Tr * p.g : p.B * p.Hq);
+    // KV heads that are no multiple of eight: lists for their eights, but not for causal calls whose items all start at once, since long items of a
+    // list's later KV heads would start behind the short ones of its first.  us, one order for all / lists: d = 128, causal, 144 heads over 36, N =
+    // 2204 278 / 207, 98 over 98, N = 2560 405 / 193, no mask, 141 over 47, N = 1407 313 / 160, 252 over 42, N = 640 116 / 66; d = 64, causal, 174 over 87, N = 1024
+    // 73 / 41; few items: d = 128, 40 over 20, N = 698 12.2 / 14.6, d = 64, 20 heads, N = 1329 12.5 / 15.7
+    set_items(p, !p.causal || p.n_items > (D == 128 ? 2 : 4) * cu_count());
     const long long wgs = p.n_items + (summaries ? ((long long)p.B * p.Hkv * p.Tc + 2 * KQ - 1) / (2 * KQ) : 0);
     attn_fwd_short_kernel<D, KQ><<<dim3((unsigned)wgs), 128 * KQ, Short<D, KQ>::LDS_BYTES, s>>>(p);
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
@@ -280,9 +282,7 @@ int launch_fwd(const Params& p, int d, int block_m, hipStream_t s, bool fixed_ma
     }
     if constexpr (MODE == MODE_VSA) {
         if (!ablation && d == 128 && block_m == 128 && prefer_sparse(p, cu_count())) {
-            q.g = g;
-            q.by_g.set(g);
-            q.by_list.set(((p.B * p.Hkv) & 7) == 0 ? p.Tr * g : p.B * p.Hq);
+            set_items(q, false);  // (lists for the eights of KV heads: 1.01 times slower in the mean of 500 shapes, 142 heads, N = 500 34.4 / 53.2 us)
             attn_sparse_kernel<<<dim3((unsigned)(p.B * p.Hq * p.Tr)), 256, Sparse::LDS_BYTES, s>>>(q);
             return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
         }

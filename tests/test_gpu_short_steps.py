@@ -36,3 +36,10 @@ def test_steps(d, causal, steps):
 @pytest.mark.parametrize("behind", [0, 1])
 def test_lines(d, Hq, Hkv, N, causal, behind):
     _check(d, 1, Hq, Hkv, N + behind, causal)
+
+
+# KV heads that are no eights: lists for the eights and the rest (many items, no mask), one order for all (few), the last rows of a call
+@pytest.mark.parametrize("d,B,Hq,Hkv,N,causal", [(128, 1, 45, 15, 1000, True), (128, 3, 18, 9, 600, False), (64, 2, 44, 11, 1500, True), (64, 1, 30, 15, 500, False),
+                                                 (128, 1, 40, 20, 698, True), (64, 1, 20, 20, 1329, True), (128, 1, 30, 10, 2500, False)])
+def test_kv_heads_that_are_no_eights(d, B, Hq, Hkv, N, causal):
+    _check(d, B, Hq, Hkv, N, causal)
