@@ -105,11 +105,14 @@ int launch_short(Params p, int row_base, bool summaries, hipStream_t s) {
     p.row_base = row_base;
     p.Tr = ceil_div(p.N - row_base, 64);
     p.n_items = p.B * p.Hq * p.Tr;
-    // KV heads that are no multiple of eight: lists for their eights, but not for causal calls whose items all start at once, since long items of a
-    // list's later KV heads would start behind the short ones of its first.  us, one order for all / lists: d = 128, causal, 144 heads over 36, N =
-    // 2204 278 / 207, 98 over 98, N = 2560 405 / 193, no mask, 141 over 47, N = 1407 313 / 160, 252 over 42, N = 640 116 / 66; d = 64, causal, 174 over 87, N = 1024
-    // 73 / 41; few items: d = 128, 40 over 20, N = 698 12.2 / 14.6, d = 64, 20 heads, N = 1329 12.5 / 15.7
-    set_items(p, !p.causal || p.n_items > (D == 128 ? 2 : 4) * cu_count());
+    // KV heads that are no multiple of eight.  In one order for all, an XCD meets every head that is its number mod 8 in the workgroups' order, and reads
+    // their keys in turn: lists for the eights where those are more than its L2 (4 MB) holds together.  Causal calls otherwise keep the one order, since
+    // long items of a list's later KV heads start behind the short ones of its first.  us, one order / lists: d = 128, causal, 144 heads over
+    // 36, N = 2204 278 / 207, 98 heads, N = 2560 405 / 193, no mask, 141 over 47, N = 1407 313 / 160; d = 64, causal, 174 over 87, N = 1024 73 / 41;
+    // 2 and 5 MB: d = 128, 40 over 20, N = 698 12.2 / 14.6, d = 64, 136 over 34, N = 1090 33.8 / 37.4.  1200 shapes: in the mean 0.3 % over the faster one at d = 128, 0.6 at
+    // d = 64, lines of 4 MB 0.5 and 1.1
+    const int heads = p.B * p.Hq, met = min(p.B * p.Hkv, ceil_div(heads, heads & 1 ? 1 : heads & 2 ? 2 : heads & 4 ? 4 : 8));  // (KV heads an XCD meets)
+    set_items(p, !p.causal || (double)met * p.N * 4 * D > (D == 128 ? 2.5e6 : 6e6));
     const long long wgs = p.n_items + (summaries ? ((long long)p.B * p.Hkv * p.Tc + 2 * KQ - 1) / (2 * KQ) : 0);
     attn_fwd_short_kernel<D, KQ><<<dim3((unsigned)wgs), 128 * KQ, Short<D, KQ>::LDS_BYTES, s>>>(p);
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
@@ -124,48 +127,88 @@ int launch_frozen(Params p, int row_base, int block_m, hipStream_t s) {  // rows
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
 }
 
-// Alg. 1 on the kernel for short sequences (attn_short.hpp): 0 = no, else its groups of keys.  `items` are blocks of 64 rows, `rounds` those
-// of the ping-pong kernel, which has twice the rate once its items of 256 rows fill the compute units evenly.  The lines lie where the
-// others, with the summaries' launch in front, catch up.  In us, theirs / this one, about each line (2480 shapes of 7 to 96 tiles swept, with two
-// groups, four and neither; in the mean 0.4 to 0.7 % over the fastest of the three):
+// The ping-pong kernel under a causal mask, with a list of items for each XCD (KV heads in eights): the tiles of its busiest workgroup over the
+// average.  A workgroup takes one item of each round, the rounds in alternating directions (attn_pingpong.hpp), so an XCD's only KV head, or
+// whole KV heads to a round, even out, and a long item of a later KV head on top of other long ones does not.  Four tiles for an
+// item's start and end; 1 beyond 16 rounds, where little is left of it.
+double pp_unevenness(const Params& p, bool head_pairs, int n_cu) {
+    const int g = p.Hq / p.Hkv, units = head_pairs ? g / 2 : g, rows = head_pairs ? 128 : 256, Ti = ceil_div(p.N, rows);
+    const int slots = n_cu / 8;
+    const long long len = (long long)p.B * p.Hkv / 8 * units * Ti;
+    constexpr int MAX_SLOTS = 64;
+    if (slots < 1 || slots > MAX_SLOTS || len <= slots || len > 16LL * slots) return 1.0;
+    int load[MAX_SLOTS] = {}, at = 0, step = 1, most = 0;  // (the slot of the next item; a round ends where it would leave the slots)
+    long long all = 0;
+    for (long long y = 0; y < len;) {
+        for (int i = Ti; i > 0 && y < len; --i) {
+            const int tiles = ceil_div(min(p.N, i * rows), BN) + 4;
+            for (int u = 0; u < units; ++u, ++y) {
+                most = max(most, load[at] += tiles);
+                all += tiles;
+                if (at + step < 0 || at + step >= slots) step = -step;
+                else at += step;
+            }
+        }
+    }
+    return (double)most * slots / all;
+}
+
+// Alg. 1 on the kernel for short sequences (attn_short.hpp): 0 = no, else its groups of keys.  `items` are blocks of 64 rows, `rounds` those of
+// the other kernels' items (two blocks of 128 rows at d = 128).  Its items are a quarter as long as the ping-pong kernel's, need no launch for the
+// summaries and start alone, so it wins on few tiles, on few items and where the others' rounds are poorly filled; in full rounds of long items
+// those are 1.05 to 1.15 times faster.  The lines lie where they meet.  6900 shapes of 7 to 96 tiles, 3 to 580 heads, any number to a KV head, against neither,
+// two and four groups: in the mean 0.4 % over the fastest.  Slower than without it by more than 3 %: 45, by more than 5 %: ten, the worst of them d = 128, causal, 512
+// heads, N = 1266 1.08, 21 heads, N = 4519 1.08, 24 heads, N = 4096 1.06 and d = 64, 44 heads, N = 3644 1.07.  us, theirs / this one:
 //   four groups, from ten tiles on, for no more items than units (at d = 128 the summaries' workgroups counted, since one fills a
 //     unit), against two: d = 128, 4 heads, N = 4096 35.3 / 29.9, 8 heads, N = 1024 12.3 / 11.5; causal, few long heads, whose items are uneven: up to
-//     four per unit at d = 64 (12 heads, N = 4096 35.5 / 34.3), 1.9 at d = 128 (8 heads, N = 3600 39.8 / 35.5; 16 heads, N = 1536 18.5 / 18.0)
-//   d = 64, causal: up to 34 tiles always (256 heads, N = 2176 1.03 times faster), 57 with 16 items per unit (96 heads, N = 3000 142.5 / 128.6; 8 x 32
-//     heads, N = 2500, 40 per unit 266.6 / 268.7), 96 with 8 (the mean at 88 tiles 1.13; 4 x 16 heads, N = 4096, 16 per unit 159.7 / 163.5)
-//   d = 64, no mask: up to 24 tiles always (1.10 times up to 8 items per unit, 0.99 beyond 16), 48 with 8 (1.02, beyond 0.97 to 0.99), 96 with 4 (1.08,
-//     beyond 0.95)
-//   d = 128, causal, an even number of heads per KV head: up to 47 tiles (64 heads, N = 2600 138.3 / 130.0), but for two or four nearly full
-//     rounds from 30 on, in which long and short items pair up (64 heads, N = 2048 76.8 / 80.8); 96 with 1.2 rounds (24 heads, N = 3000 71.7 /
-//     60.6; 32 heads, N = 4096, 2 rounds 125 / 137)
-//   an odd number, whose super-blocks cover both diagonals: up to 60 tiles always (48 heads, N = 2300 1.42 times), 96 unless the last round
-//     is nearly full (32 heads, N = 2700 101.4 / 77.3, N = 5000 1.35 times; N = 4096, 2 rounds 0.92)
-//   d = 128, no mask: up to 24 tiles always (128 heads, N = 640 55.4 / 37.7, 96 heads, N = 1536 141 / 119, 128 heads, N = 1536 0.95 to 0.99), 32 where
-//     the others' rounds are poorly filled (48 heads, N = 1800 104 / 90, N = 2048 114 / 105; 64 heads, N = 2048, 2 rounds 0.94), 64 with 1.3 items per unit
-//     (8 heads, N = 2560 38.9 / 36.9)
+//     four per unit at d = 64 (12 heads, N = 4096 35.5 / 34.3), 1.9 at d = 128 (8 heads, N = 3600 39.8 / 35.5; 16 heads, N = 1536 18.5 / 18.0); d = 64, no
+//     mask, long ones, up to two per unit (4 heads, N = 6144 neither 57.0, two 59.8, four 55.0)
+//   d = 64, causal: any with 8 items per unit (32 heads, N = 5541, 11 per unit 168 / 156), 57 tiles with 16 (44 heads, N = 3644 1.07 times slower, 64 heads, N =
+//     3735 163.5 / 150.6), 46 beyond (256 heads, N = 2361 259 / 239, 512 heads, N = 2560 0.96)
+//   d = 64, no mask: four items per unit, any tiles, or 48 where they fill their rounds to within a quarter; eight, 48 or 26; 32 or 20 beyond
+//     (40 heads over 10, N = 3072 0.97, 256 heads, N = 1536 0.97, 209 heads, N = 1820 239 / 215)
+//   d = 128, causal, KV heads in eights: by how uneven the ping-pong kernel's workgroups come out (pp_unevenness), the less the more tiles.  Even
+//     groups of heads: 64 over 8, N = 2048 (1.0) 76.8 / 80.8, 32 over 8, N = 3328 (1.1) 93.6 / 100.7, 32 over 16, N = 3328 (1.8) 129.8 / 100.2; 64 over 16, N = 3600 246 / 225; odd ones,
+//     whose items cover two diagonals: 128 heads, N = 2048 162 / 170, N = 3072 320 / 346, 24 heads, N = 5000 218 / 171, 48 heads, N = 5632 381 / 401
+//   d = 128, causal, other numbers of KV heads, whose list for the whole chip starts with all long items: 88 tiles with 1.5 rounds, 34 to 14 with
+//     more (36 heads over 9, N = 2254 62.7 / 57.8), odd groups 90, 52 to 38 (126 over 42, N = 2048 165 / 158, N = 3077 1.06 times faster and not taken)
+//   d = 128, no mask: rounds filled to within a quarter 18 tiles (128 heads over 32, N = 1536 147 / 154), others 72 to 14, the more rounds the fewer (12 over 4, N =
+//     2062 39.6 / 34.8; 48 heads, N = 1800 104 / 90; 74 over 37, N = 1920 169 / 151)
 //   more than four sink or local blocks: never
 int short_groups(const Params& p, int d, int n_cu) {
     const long long heads = (long long)p.B * p.Hq, items = heads * p.Tc;  // (of 64 rows)
     if (n_cu <= 0 || p.n_sink > 4 || p.n_local > 4 || p.Tc > 96) return 0;
     if (items + ((long long)p.B * p.Hkv * p.Tc + 3) / 4 > kMaxWorkgroups256) return 0;  // (with the summaries' workgroups; four groups are for few items)
-    const int Tc = p.Tc;
-    auto upto = [&](int tiles, double per_cu) { return Tc <= tiles && items <= (long long)(per_cu * n_cu); };
+    const int Tc = p.Tc, g = p.Hq / p.Hkv, kv_heads = p.B * p.Hkv, blocks = ceil_div(p.N, 128);
+    const double per_cu = (double)items / n_cu;
     const bool few_heads = p.causal && 16 * heads <= n_cu;
     if (d == 64) {
-        if (Tc >= 10 && (upto(96, 1) || (few_heads && upto(96, 4)))) return 4;
-        if (p.causal) return Tc <= 34 || upto(57, 16) || upto(96, 8) ? 2 : 0;
-        return Tc <= 24 || upto(48, 8) || upto(96, 4) ? 2 : 0;
+        if (Tc >= 10 && (per_cu <= 1 || (few_heads && per_cu <= 4) || (!p.causal && Tc >= 48 && per_cu <= 2))) return 4;
+        if (p.causal) return Tc <= (per_cu <= 8 ? 96 : per_cu <= 16 ? 57 : 46) ? 2 : 0;
+        const double rounds = (double)(heads * blocks) / (2 * n_cu);
+        const bool full = ceil(rounds) - rounds < 0.25;
+        return Tc <= (per_cu <= 4 ? (full ? 48 : 96) : per_cu <= 8 ? (full ? 26 : 48) : (full ? 20 : 32)) ? 2 : 0;
     }
-    const long long summary_wgs = ((long long)p.B * p.Hkv * Tc + 7) / 8;
-    if (Tc >= 10 && Tc <= 64 && (items + summary_wgs <= n_cu || (few_heads && Tc >= 16 && upto(64, 1.9)))) return 4;
-    const int g = p.Hq / p.Hkv, blocks = ceil_div(p.N, 128);
-    const double rounds = (double)((g & 1) == 0 ? heads / 2 * blocks : heads * ((blocks + 1) / 2)) / n_cu;
-    if (p.causal) {
-        const bool paired = Tc >= 30 && rounds > 1.75 && ceil(rounds) - rounds < 0.25 && ((int)ceil(rounds) & 1) == 0;
-        if ((g & 1) == 0) return (Tc <= 47 && !paired) || rounds <= 1.2 ? 2 : 0;
-        return Tc <= 60 || rounds < 1.2 || ceil(rounds) - rounds >= 0.15 ? 2 : 0;
+    const long long summary_wgs = ((long long)kv_heads * Tc + 7) / 8;
+    if (Tc >= 10 && Tc <= 64 && (items + summary_wgs <= n_cu || (few_heads && Tc >= 16 && per_cu <= 1.9))) return 4;
+    const bool even = (g & 1) == 0;  // (pairs of heads, else of blocks)
+    const double rounds = (double)(even ? heads / 2 * blocks : heads * ((blocks + 1) / 2)) / n_cu, idle = ceil(rounds) - rounds;
+    int upto;
+    if (!p.causal) {
+        if (idle < 0.25) upto = rounds < 6 ? 18 : 10;
+        else upto = rounds < 0.5 ? 72 : rounds < 0.75 ? 42 : rounds < 2 ? 34 : rounds < 4 ? 28 : rounds < 6 ? 20 : 14;
+    } else if (rounds <= 1.2) {
+        upto = 96;
+    } else if ((kv_heads & 7) == 0) {
+        const double uneven = log(pp_unevenness(p, even, n_cu));
+        if (even) return uneven > 0.40 - (rounds < 5 ? 11.5 : rounds < 8 ? 8 : 6) / Tc ? 2 : 0;
+        return uneven > 0.32 - (rounds < 5 || rounds >= 8 ? 10 : 7.5) / Tc ? 2 : 0;
+    } else if (even) {
+        upto = rounds <= 1.5 ? 88 : rounds < 5 ? 34 : rounds < 8 ? 30 : rounds < 12 ? 22 : 14;
+    } else {
+        upto = rounds <= 1.5 ? 90 : rounds < 4 ? 52 : rounds < 8 ? 46 : 38;
     }
-    return Tc <= 24 || (Tc <= 32 && (rounds < 0.8 || (rounds > 1 && rounds <= 1.6))) || upto(64, 1.3) ? 2 : 0;
+    return Tc <= upto ? 2 : 0;
 }
 
 // Without a causal mask all items are equally long, and what is left of them after whole rounds of the ping-pong kernel takes as long

@@ -43,3 +43,21 @@ def test_lines(d, Hq, Hkv, N, causal, behind):
                                                  (128, 1, 40, 20, 698, True), (64, 1, 20, 20, 1329, True), (128, 1, 30, 10, 2500, False)])
 def test_kv_heads_that_are_no_eights(d, B, Hq, Hkv, N, causal):
     _check(d, B, Hq, Hkv, N, causal)
+
+
+# full rounds of the other kernels stay with them, uneven ones do not (a chip of 256 units).  vfa_variant_fwd never runs on attn_short.hpp, so the
+# same bits mean the same kernel
+@pytest.mark.parametrize("d,Hq,Hkv,N,causal,short", [
+    (128, 128, 128, 2048, True, False), (128, 128, 128, 3072, True, False), (128, 48, 48, 5632, True, False), (128, 64, 16, 2048, True, False),
+    (128, 128, 32, 1536, False, False), (64, 40, 10, 3072, False, False), (128, 64, 16, 3600, True, True), (128, 24, 24, 5000, True, True),
+    (128, 32, 8, 3328, True, False), (128, 32, 16, 3328, True, True)])
+def test_rounds(d, Hq, Hkv, N, causal, short):
+    import torch
+    import paper_2604_12798_amd as vfa
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("lines of a chip of 256 units")
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    Q, K, V = (torch.randn((1, h, N, d), generator=gen, device="cuda", dtype=torch.bfloat16) for h in (Hq, Hkv, Hkv))
+    O, L = vfa.vfa_attn_fwd(Q, K, V, causal=causal)
+    O2, L2, _ = vfa.vfa_variant_fwd(Q, K, V, causal=causal)
+    assert (torch.equal(O, O2) and torch.equal(L, L2)) != short
