@@ -7,8 +7,8 @@ namespace {
 // ---------------------------------------------------------------------------------------------
 // Key-block summary (Alg. 1, first loop): per dimension the element of largest magnitude of the block's keys with its
 // sign, ties to the positive value.  HBM bound: K is read once.  One WAVE per key block, four blocks per workgroup:
-// a lane owns one 16-byte chunk of every RG-th row, issues the loads of 64 rows together, none behind a branch, reduces in registers,
-// and the RG lanes of a chunk combine through lane exchanges: no LDS, no barrier, 256 bytes per lane in flight at d = 128.
+// a lane owns one 16-byte chunk of every RG-th row, issues the loads of ROWS rows together, none behind a branch, reduces in registers,
+// and the RG lanes of a chunk combine through lane exchanges: no LDS, no barrier, 256 bytes per lane in flight at d = 128 with ROWS = 64.
 // A launch for a few blocks (a decode step's) is a chain of latencies: with eight predicated loads at a time and exchanges through the
 // LDS unit it took 3.6 us for 8 blocks of 2048 keys' cache and 4.6 for 128 at d = 64, now 3.0 and 3.9 (an empty kernel takes 1.5);
 // 4 x 8 heads of 32768 keys 5.0 / 4.8.
@@ -38,18 +38,18 @@ __device__ __forceinline__ uint32_t key_max_across(uint32_t x) {
 
 // N = row stride of one head's key array (its capacity), n_valid = keys present, Tc = block stride of
 // one head's summary array.  bh and j are the same for all lanes; `live`: write the result.
-template <int D>
+template <int D, int ROWS = BN>
 __device__ __forceinline__ void summary_of_block(const uint16_t* __restrict__ K, uint16_t* __restrict__ R, int bh, int j, int N,
                                                  int n_valid, int Tc, int block_n, int lane, bool live = true) {
     constexpr int CH = D / 8;        // 16-byte chunks per row
     constexpr int RG = 64 / CH;      // rows a wave reads at once
-    constexpr int NL = BN / RG;      // such reads in flight: 64 rows
+    constexpr int NL = ROWS / RG;    // such reads in flight
     const int ch = lane % CH, rg = lane / CH;
     const int c0 = j * block_n, c1 = min(n_valid, c0 + block_n);
     const uint8_t* base = reinterpret_cast<const uint8_t*>(K) + ((size_t)bh * N + c0) * (2 * D);
     const uint32_t zero_key = sabs_key(0u);  // +0: the smallest magnitude, already the positive one
     u32x4 acc = {zero_key, zero_key, zero_key, zero_key};
-    for (int r0 = c0; r0 < c1; r0 += BN, base += BN * 2 * D) {
+    for (int r0 = c0; r0 < c1; r0 += ROWS, base += ROWS * 2 * D) {
         u32x4 x[NL];
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
@@ -74,14 +74,29 @@ __device__ __forceinline__ void summary_of_block(const uint16_t* __restrict__ K,
     }
 }
 
+// Rows loaded together at d = 128: 64, but no more than a short block has, or than half of what its last round would read twice, and 16 where the
+// rows are more than the memory-side cache holds: a stream from memory is the faster for fewer loads at once.  us with 64 / so: 4 x 8 heads of 32768 keys,
+// blocks of 8 104 / 49, of 16 57 / 44, of 64 44.7 / 41.9, of 128 42.9 / 41.9, of 256 42.1 (16 rows 47.5); 4 x 8 of 4096, of 32 6.0 / 5.3, of 96 7.45 / 6.3, of 64 4.95 (16 rows
+// 5.5); 3 x 8 of 16384, of 64 15.9 / 15.8, 6 x 8 of 16384, of 128 31.2 (16 rows 32.3).  (d = 64 reads 64 rows with eight loads: no length gains.)
+__host__ __device__ inline bool many_rows(int block_n, long long rows) { return block_n <= 128 && rows > (block_n <= 64 ? 7 << 16 : 7 << 17); }
+template <typename F>
+__host__ inline void with_rows(int d, int block_n, long long rows, F launch) {
+    using std::integral_constant;
+    if (d == 64) launch(integral_constant<int, 64>{}, integral_constant<int, 64>{});
+    else if (block_n <= 16) launch(integral_constant<int, 128>{}, integral_constant<int, 16>{});
+    else if ((block_n - 1) % 64 < 32) launch(integral_constant<int, 128>{}, integral_constant<int, 32>{});
+    else if (many_rows(block_n, rows)) launch(integral_constant<int, 128>{}, integral_constant<int, 16>{});
+    else launch(integral_constant<int, 128>{}, integral_constant<int, 64>{});
+}
+
 // j0 = first block to (re)compute and n_blocks their number: a growing cache recomputes only the blocks that received keys.
-template <int D>
+template <int D, int ROWS>
 __global__ __launch_bounds__(256) void kblock_summary_kernel(const uint16_t* __restrict__ K, uint16_t* __restrict__ R,
                                                              int N, int n_valid, int Tc, int block_n, int j0, int n_blocks) {
     // (a wave without a block does the last one again and writes nothing: no branch in front of the loads, whose latency is all there is of a
     // launch for a few blocks)
     const int lane = threadIdx.x & 63, jb = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    summary_of_block<D>(K, R, blockIdx.y, j0 + min(jb, n_blocks - 1), N, n_valid, Tc, block_n, lane, jb < n_blocks);
+    summary_of_block<D, ROWS>(K, R, blockIdx.y, j0 + min(jb, n_blocks - 1), N, n_valid, Tc, block_n, lane, jb < n_blocks);
 }
 
 // With per-sequence lengths (device arrays indexed by batch entry, Hkv heads each) the host does not know which blocks received
@@ -94,7 +109,7 @@ __global__ __launch_bounds__(256) void kblock_summary_kernel(const uint16_t* __r
 //   a new key in each of 128 caches of 8192 rows 44 / 3.7 / 4.7; 32768 new rows in one of 128 and a key in the others 96 / 285 / 14;
 //   in every fourth 368 / 710 / 392; in all 1424 / 1521 / 1501 (waves that stay lose the order of memory, a wave for each block keeps it)
 constexpr int APPEND_WAVES = 8192;  // eight to a SIMD
-template <int D, int E>
+template <int D, int ROWS, int E>
 __global__ __launch_bounds__(E ? 256 : 1024) void kblock_summary_varlen_kernel(const uint16_t* __restrict__ K, uint16_t* __restrict__ R,
                                                                                int B, int Hkv, int N, int Tc, int block_n,
                                                                                const int* __restrict__ old_len,
@@ -137,6 +152,7 @@ __global__ __launch_bounds__(E ? 256 : 1024) void kblock_summary_varlen_kernel(c
         total = __builtin_amdgcn_readlane(waves_upto, NW - 1);
     }
     total *= Hkv;
+    const bool many = many_rows(block_n, (long long)total * block_n);
     for (int item = blockIdx.x * NW + wave; item < total; item += n_wg * NW) {
         int bh = 0, j = 0, nv = 0;
         // the item's entry: b0 + l * stride, l the first lane whose sum lies behind the item
@@ -162,7 +178,8 @@ __global__ __launch_bounds__(E ? 256 : 1024) void kblock_summary_varlen_kernel(c
             up[0] = (t ? upto[E ? 0 : t - 1] : 0) + wave_prefix(n[0]);
             found(0, t, T);
         }
-        summary_of_block<D>(K, R, bh, j, N, nv, Tc, block_n, lane);
+        if (D == 128 && ROWS == 64 && many) summary_of_block<D, 16>(K, R, bh, j, N, nv, Tc, block_n, lane);
+        else summary_of_block<D, ROWS>(K, R, bh, j, N, nv, Tc, block_n, lane);
     }
 }
 

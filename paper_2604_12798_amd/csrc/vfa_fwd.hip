@@ -395,8 +395,9 @@ int summary_launch(const void* K, void* Krepr, int B, int Hkv, int N, int d, int
     uint16_t* r = (uint16_t*)Krepr;
     (void)hipGetLastError();
     if (repr_mode == 0) {
-        if (d == 128) kblock_summary_kernel<128><<<grid4, 256, 0, s>>>(k, r, N, N, Tc, block_n, 0, Tc);
-        else kblock_summary_kernel<64><<<grid4, 256, 0, s>>>(k, r, N, N, Tc, block_n, 0, Tc);
+        with_rows(d, block_n, (long long)B * Hkv * N, [&](auto d_c, auto rows_c) {
+            kblock_summary_kernel<decltype(d_c)::value, decltype(rows_c)::value><<<grid4, 256, 0, s>>>(k, r, N, N, Tc, block_n, 0, Tc);
+        });
     } else {
         if (d == 128) kblock_summary_alt_kernel<128><<<grid, 256, 0, s>>>(k, r, N, Tc, block_n, repr_mode);
         else kblock_summary_alt_kernel<64><<<grid, 256, 0, s>>>(k, r, N, Tc, block_n, repr_mode);
@@ -602,10 +603,10 @@ int vfa_kblock_summary_append(const void* K, void* Krepr, int B, int Hkv, int n_
     const dim3 grid((unsigned)ceil_div(j1 - j0, 4), (unsigned)(B * Hkv));
     hipStream_t s = (hipStream_t)stream;
     (void)hipGetLastError();
-    if (d == 128)
-        kblock_summary_kernel<128><<<grid, 256, 0, s>>>((const uint16_t*)K, (uint16_t*)Krepr, n_cap, n_new, tc_cap, block_n, j0, j1 - j0);
-    else
-        kblock_summary_kernel<64><<<grid, 256, 0, s>>>((const uint16_t*)K, (uint16_t*)Krepr, n_cap, n_new, tc_cap, block_n, j0, j1 - j0);
+    with_rows(d, block_n, (long long)B * Hkv * (n_new - j0 * block_n), [&](auto d_c, auto rows_c) {
+        kblock_summary_kernel<decltype(d_c)::value, decltype(rows_c)::value><<<grid, 256, 0, s>>>((const uint16_t*)K, (uint16_t*)Krepr, n_cap, n_new, tc_cap, block_n,
+                                                                                                j0, j1 - j0);
+    });
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
 }
 
@@ -659,19 +660,17 @@ int vfa_kblock_summary_append_varlen(const void* K, void* Krepr, int B, int Hkv,
     const int tc_cap = ceil_div(n_cap, block_n);
     hipStream_t s = (hipStream_t)stream;
     (void)hipGetLastError();
-    auto launch = [&](auto d_c, auto e_c) {
+    auto launch = [&](auto d_c, auto rows_c, auto e_c) {
         constexpr int E = decltype(e_c)::value, NW = E ? 4 : 16;
         const long long wgs = min(((long long)B * Hkv * tc_cap + NW - 1) / NW, (long long)(APPEND_WAVES / NW));
-        kblock_summary_varlen_kernel<decltype(d_c)::value, E><<<(unsigned)wgs, 64 * NW, 0, s>>>(
+        kblock_summary_varlen_kernel<decltype(d_c)::value, decltype(rows_c)::value, E><<<(unsigned)wgs, 64 * NW, 0, s>>>(
             (const uint16_t*)K, (uint16_t*)Krepr, B, Hkv, n_cap, tc_cap, block_n, old_lens, new_lens, (int)wgs);
     };
-    auto launch_d = [&](auto d_c) {
-        if (B <= 64) launch(d_c, std::integral_constant<int, 1>{});
-        else if (B <= 256) launch(d_c, std::integral_constant<int, 4>{});
-        else launch(d_c, std::integral_constant<int, 0>{});
-    };
-    if (d == 128) launch_d(std::integral_constant<int, 128>{});
-    else launch_d(std::integral_constant<int, 64>{});
+    with_rows(d, block_n, 0, [&](auto d_c, auto rows_c) {  // (the kernel counts the rows)
+        if (B <= 64) launch(d_c, rows_c, std::integral_constant<int, 1>{});
+        else if (B <= 256) launch(d_c, rows_c, std::integral_constant<int, 4>{});
+        else launch(d_c, rows_c, std::integral_constant<int, 0>{});
+    });
     return hipGetLastError() == hipSuccess ? VFA_OK : VFA_ERR_HIP;
 }
 

@@ -1,4 +1,4 @@
-"""Key-block summaries at block lengths around the 64 rows that a wave loads together, and ragged ends: the bits of torch's own maximum."""
+"""Key-block summaries at block lengths around the 64, 32 and 16 rows that a wave loads together, and ragged ends: the bits of torch's own maximum."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -16,7 +16,8 @@ def reference(K, block_n):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("N,block_n", [(1, 64), (63, 64), (64, 64), (65, 64), (191, 64), (200, 1), (67, 7), (130, 63), (300, 65), (515, 128), (700, 200)])
+@pytest.mark.parametrize("N,block_n", [(1, 64), (63, 64), (64, 64), (65, 64), (191, 64), (200, 1), (67, 7), (130, 63), (300, 65), (515, 128), (700, 200), (130, 8), (333, 16), (90, 17), (333, 32),
+                                        (200, 33), (500, 96), (300, 97), (600, 160)])
 def test_summaries(d, N, block_n):
     import torch
     import paper_2604_12798_amd as vfa
@@ -38,3 +39,18 @@ def test_summaries(d, N, block_n):
     vfa.kblock_summary_append_varlen(cap, R2, lens(0, 0), lens(N, N // 2), block_n)
     vfa.kblock_summary_append_varlen(cap, R2, lens(N, N // 2), lens(N, N), block_n)
     assert torch.equal(R2, R)
+
+
+# more rows than the memory-side cache holds: sixteen loaded together at d = 128 (the line and behind it; both appends)
+@pytest.mark.parametrize("N", [14336, 14337, 20000])
+def test_many_blocks(N):
+    import torch
+    import paper_2604_12798_amd as vfa
+    K = torch.randn((4, 8, N, 128), generator=torch.Generator(device="cuda").manual_seed(N), device="cuda").bfloat16()
+    want = reference(K, 64).view(torch.int16)
+    assert torch.equal(vfa.kblock_summary(K, 64).view(torch.int16), want)
+    lens = lambda n: torch.full((4,), n, dtype=torch.int32, device="cuda")
+    for append in (lambda R: vfa.kblock_summary_append(K, R, 0, N, 64), lambda R: vfa.kblock_summary_append_varlen(K, R, lens(0), lens(N), 64)):
+        R = torch.zeros((4, 8, -(-N // 64), 128), dtype=torch.bfloat16, device="cuda")
+        append(R)
+        assert torch.equal(R.view(torch.int16), want)
