@@ -283,14 +283,15 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void decode_split_kernel(c
     }
 }
 
-// One workgroup per query head: D / 4 threads read a partial row (16 bytes each), 1024 / D rows at a time and four such
+// One workgroup per query head: D / 4 threads read a partial row (16 bytes each), 1024 / D rows at a time and up to four such
 // rounds in flight, each group of threads with a running max of its own; the groups meet in LDS.  The order of the sums is
 // fixed.  (One thread per output element walking the ranges one by one took 8.6 us for 32 heads of 32
 // ranges and 6.3 us for 128 heads of 16, a chain of load latencies; with loads behind branches and a division in front this took 3.0 and
-// 5.0, now 2.7 and 4.8.)
+// 5.0, now 2.7 and 4.8.  Only the rounds that the ranges fill: steps of 6400 heads of two ranges of 100 keys, four rounds of loads for
+// each / one, d = 64 16.8 / 14.4, d = 128 29.2 / 26.8.)
 template <int D, bool DEALT>
 __global__ __launch_bounds__(256) void decode_merge_kernel(const DecodeParams p) {
-    constexpr int C4 = D / 4, NG = 256 / C4, U = 4;
+    constexpr int C4 = D / 4, NG = 256 / C4;
     __shared__ float xo[NG][D], xm[NG], xl[NG];
     const int h = blockIdx.x, b = blockIdx.y, row = b * p.Hq + h;
     const int c4 = threadIdx.x % C4, gr = threadIdx.x / C4;
@@ -305,9 +306,9 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const DecodeParams p)
     const float* const po0 = p.opart + ((size_t)first * p.Hq + h) * D + 4 * c4;
     float m = -INFINITY, l = 0.f;
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
-    // (every group makes a round, and a load past the last range reads the last one again: no load sits behind a branch)
-    int s0 = 0;
-    do {
+    // U rounds from range s0 on (every group makes them, and a load past the last range reads the last one again: no load sits behind a branch)
+    auto rounds = [&](int s0, auto u_c) __attribute__((always_inline)) {
+        constexpr int U = decltype(u_c)::value;
         float pm[U], pl[U];
         f32x4 po[U];
 #pragma unroll
@@ -338,8 +339,12 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const DecodeParams p)
             o += a * po[u];
         }
         m = mn;
-        s0 += U * NG;
-    } while (s0 < nb);
+    };
+    using std::integral_constant;
+    if (nb <= NG) rounds(0, integral_constant<int, 1>{});
+    else if (nb <= 2 * NG) rounds(0, integral_constant<int, 2>{});
+    else
+        for (int s0 = 0; s0 < nb; s0 += 4 * NG) rounds(s0, integral_constant<int, 4>{});
     *reinterpret_cast<f32x4*>(&xo[gr][4 * c4]) = o;
     if (c4 == 0) { xm[gr] = m; xl[gr] = l; }
     __syncthreads();

@@ -1,6 +1,6 @@
 """Decode steps whose cache is not cut into ranges although the caller asks for several: one workgroup for each KV head, its waves
-sharing the keys.  On both sides of the lines (a chip of 256 units), against exact attention in 64 bits; bars as in the other
-parity tests."""
+sharing the keys, on both sides of the lines (a chip of 256 units); and the merge of ranges at the numbers where it changes its rounds.
+Against exact attention in 64 bits; bars as in the other parity tests."""
 import numpy as np
 import pytest
 
@@ -43,6 +43,25 @@ def test_whole_cache(B, Hq, Hkv, d, n, ragged):
         O, L = vfa.decode_varlen_fwd(q, K, V, torch.tensor(lens, dtype=torch.int32, device="cuda"), use_minit=False, n_splits=3)
     else:
         O, L = vfa.decode_fwd(q, K, V, n, use_minit=False, n_splits=3)
+    eO, eL = _exact(q, K, V, lens)
+    err = (O.double() - eO).abs()
+    assert err.max() <= O_MAX_ABS and err.mean() <= O_MEAN_ABS and (L.double() - eL).abs().max() <= LSE_ABS
+
+
+# ranges: one round of the merge (8 at d = 128, 16 at d = 64), two, four and more than four; ranges without keys among them
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_splits", [2, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 130])
+@pytest.mark.parametrize("ragged", [False, True])
+def test_ranges(d, n_splits, ragged):
+    import torch
+    import paper_2604_12798_amd as vfa
+    B, Hq, Hkv, n = 3, 6, 2, 64 * 40 + 11
+    gen = torch.Generator(device="cuda").manual_seed(n_splits)
+    q, K, V = (torch.randn(s, generator=gen, device="cuda").bfloat16() for s in ((B, Hq, d), (B, Hkv, n, d), (B, Hkv, n, d)))
+    q *= 2
+    lens = [n, 1300, 70] if ragged else [n] * B
+    kw = dict(use_minit=False, n_splits=n_splits)
+    O, L = vfa.decode_varlen_fwd(q, K, V, torch.tensor(lens, dtype=torch.int32, device="cuda"), **kw) if ragged else vfa.decode_fwd(q, K, V, n, **kw)
     eO, eL = _exact(q, K, V, lens)
     err = (O.double() - eO).abs()
     assert err.max() <= O_MAX_ABS and err.mean() <= O_MEAN_ABS and (L.double() - eL).abs().max() <= LSE_ABS
