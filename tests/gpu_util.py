@@ -65,3 +65,55 @@ def check_every_row(Q, K, V, O, L, causal):
             o = P @ v
             assert ((O[b, h].double() - o).abs() <= 2.0 ** -8 * (P @ v.abs() + o.abs()) + 1e-4).all(), (b, h)
             assert (L[b, h].double() - l).abs().max() <= LSE_ABS, (b, h)
+
+
+def vsa_kernel(w, n_cu=256):
+    """The kernel that vsa_attn_fwd runs a workload on (launch_fwd in vfa_fwd.hip)."""
+    if w.d != 128 or w.block_m != 128:
+        return "generic"
+    if w.n_sink <= 4 and w.n_local <= 4:
+        again = max(w.n_sink - 1, 0) + (w.n_local + 1 if w.n_local else 0)
+        Tc = -(-w.N // 64)
+        if (Tc + 2 if w.causal else 2 * Tc) >= (10 if w.B * w.Hq * w.Tr > 2 * n_cu else 4) * again:
+            return "sparse"
+    head_pairs = w.Hq // w.Hkv % 2 == 0
+    long = w.N > (10240 if w.causal else 5120)
+    return "ping-pong" if long and (head_pairs or (w.causal and w.n_local <= 1)) else "generic"
+
+
+def check_vsa(oracle, name, w, thr, blocks, use_minit=True):
+    """vsa_attn_fwd: every row written, masks equal to the oracle's outside the guard band, mean error of O and LSE of the blocks at the bars.
+    Each element of O: a weight is rounded to bf16 (up to 2^-8 of it, the sum in the denominator is not rounded), so O moves by at most
+    2^-8 max|V|, and O itself is rounded, 2^-8 |O| (O_MAX_ABS is short of that once |O| passes 4)."""
+    import torch
+    import paper_2604_12798_amd as vfa
+    t = wl.generate(w)
+    Q, K, V = gpu_inputs(t)
+    Qh, Kh, Vh = host_f32(t)
+    print(name, vsa_kernel(w), flush=True)
+    O = torch.full_like(Q, float("nan"))
+    L = torch.full((w.B, w.Hq, w.N), float("nan"), dtype=torch.float32, device=Q.device)
+    _, _, M = vfa.vsa_attn_fwd(Q, K, V, block_m=w.block_m, block_n=w.block_n, causal=w.causal, n_sink=w.n_sink,
+                               n_local=w.n_local, use_minit=use_minit, skip_threshold_nats=thr, out=O, lse=L)
+    torch.cuda.synchronize()
+    assert not torch.isnan(O.float()).any() and not torch.isnan(L).any(), name + ": rows left unwritten"
+    ref = oracle.blocks(Qh, Kh, Vh, w.block_m, w.block_n, w.causal, blocks, n_sink=w.n_sink, n_local=w.n_local, use_minit=use_minit,
+                        vsa=True, skip_threshold_nats=thr)
+    got = M.cpu().numpy()
+    got = np.stack([got[b, h, i] for b, h, i in blocks])
+    near = np.abs(ref["margin"]) < MASK_GUARD_NATS
+    assert near.sum() <= 4, "too many tiles sit on the threshold"
+    # a tile inside the band may fall either way, and with it what follows in its block
+    clean = ~near.any(axis=1)
+    assert np.array_equal(got[clean], ref["mask"][clean]), (name, int((got[clean] != ref["mask"][clean]).sum()))
+    at = np.asarray(blocks)[clean]
+    want_o, want_l = ref["O"][clean], ref["LSE"][clean]
+    got_o, got_l = gather_blocks(O, at, w.block_m, w.N), gather_blocks(L, at, w.block_m, w.N)
+    valid = ~np.isnan(want_l)
+    err = np.abs(got_o[valid] - want_o[valid])
+    worst = float((err / (2.0 ** -8 * (np.abs(want_o[valid]) + np.abs(Vh).max()) + 1e-5)).max())
+    stats = dict(of_bound=worst, mean_abs=float(err.mean()), lse=float(np.abs(got_l[valid] - want_l[valid]).max()))
+    assert worst <= 1 and stats["mean_abs"] <= O_MEAN_ABS and stats["lse"] <= LSE_ABS, (name, stats)
+    kept, skipped = int((ref["mask"] == 0).sum()), int((ref["mask"] == 1).sum())
+    print(name, "kept %d skipped %d" % (kept, skipped), stats, flush=True)
+    assert kept > 0 and skipped > 0, "the case should mix kept and skipped tiles"

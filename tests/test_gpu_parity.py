@@ -8,7 +8,7 @@ import pytest
 
 from paper_2604_12798_amd import workloads as wl
 
-from gpu_util import MASK_GUARD_NATS, check_o_lse, gather_blocks, gpu_inputs, host_f32, to_gpu
+from gpu_util import MASK_GUARD_NATS, check_o_lse, gather_blocks, gpu_inputs, host_f32, to_gpu, vsa_kernel
 
 pytestmark = pytest.mark.gpu
 
@@ -154,10 +154,10 @@ def test_vsa_mask_bit_exact_and_output(vfa, oracle, name, w, thr):
     assert sparsity > 0.02
 
 
-# Short sequences (the generic kernel, whose loop falls into sink / local visits, a run of unmasked ones and the rest): non-causal
-# lengths put the same visit count on every query block, so a sweep over lengths moves the ends of the three parts one by one,
-# ragged last tiles and sinks / locals shift them.  (The ping-pong kernel's step forms, which long sequences take:
-# test_gpu_vsa_routes.py.)
+# Short sequences: non-causal lengths put the same visit count on every query block, so a sweep over lengths moves the ends of a kernel's loops
+# one by one, ragged last tiles and sinks / locals shift them.  As they are on attn_sparse_kernel, whose loop takes two tiles at a time and masked ones
+# alone, but the shortest; with five sink blocks in front on the generic kernel, whose loop falls into sink / local visits, a run of unmasked ones and
+# the rest.  (The ping-pong kernel's step forms, which long sequences take: test_gpu_vsa_routes.py.)
 STEP_FORM_CASES = [
     ("pairs_tc9", W(B=1, Hq=4, Hkv=2, N=576, beta=6.0, kappa=3.0, causal=False), 5.0),
     ("pairs_tc11", W(B=1, Hq=4, Hkv=2, N=704, beta=6.0, kappa=3.0, causal=False), 5.0),
@@ -171,9 +171,13 @@ STEP_FORM_CASES = [
 ]
 
 
+@pytest.mark.parametrize("kernel", ["sparse", "generic"])
 @pytest.mark.parametrize("name,w,thr", STEP_FORM_CASES, ids=[c[0] for c in STEP_FORM_CASES])
-def test_vsa_step_forms_switch_points(vfa, oracle, name, w, thr):
+def test_vsa_step_forms_switch_points(vfa, oracle, name, w, thr, kernel):
     import torch
+    if kernel == "generic":
+        w = dataclasses.replace(w, n_sink=w.n_sink + 5)
+    assert vsa_kernel(w) == kernel
     t = wl.generate(w)
     Q, K, V = gpu_inputs(t)
     Qh, Kh, Vh = host_f32(t)

@@ -1,12 +1,13 @@
-"""Alg. 2 on both sides of the length at which its kernel changes (d = 128, block_m = 128): short sequences run one query
-block per workgroup, long ones pairs of heads or of query blocks.  Masks bit-exact outside the guard band around the
-threshold, O and LSE at the bars of the other forward tests, every row written."""
-import numpy as np
+"""Alg. 2 at d = 128, block_m = 128 on each of its kernels: up to four sink and four local blocks on attn_sparse_kernel, more of them on the
+generic kernel and, on long sequences, on the ping-pong kernel in pairs of heads or of query blocks.  Masks bit-exact outside the guard band
+around the threshold, O and LSE at the bars of the other forward tests, every row written."""
+import dataclasses
+
 import pytest
 
 from paper_2604_12798_amd import workloads as wl
 
-from gpu_util import MASK_GUARD_NATS, check_o_lse, gpu_inputs, host_f32
+from gpu_util import check_vsa, vsa_kernel
 
 pytestmark = pytest.mark.gpu
 
@@ -15,8 +16,8 @@ def W(**kw):
     return wl.small(wl.CONFIGS["cfg3"], **dict(dict(B=1, beta=6.0, kappa=3.0), **kw))
 
 
-# causal: up to 10240 tokens one block per workgroup; non-causal: up to 5120.  The visit lists of the first query blocks of
-# the long causal cases are as short as a short sequence's, those of the last ones hold more than two words of mask bits.
+# The lengths at which the kernels for more than four sink or local blocks change: causal 10240 tokens, non-causal 5120.  The visit lists of
+# the first query blocks of the long causal cases are as short as a short sequence's, those of the last ones hold more than two words of mask bits.
 CASES = [
     ("causal_10240", W(Hq=2, Hkv=1, N=10240), 4.0),
     ("causal_10241_head_pairs", W(Hq=4, Hkv=2, N=10241), 5.0),
@@ -34,10 +35,23 @@ CASES = [
 ]
 
 
+def more(w):
+    """With five sink blocks, or more, in front (five local ones where there was no sink and pairs of heads allow it)."""
+    if w.n_sink == 0 and w.Hq // w.Hkv % 2 == 0:
+        return dataclasses.replace(w, n_local=w.n_local + 4 if w.n_local else 5)
+    return dataclasses.replace(w, n_sink=w.n_sink + 5)
+
+
+# The kernel of each: as they are, and with more than four sink or local blocks
+KERNELS = {"causal_10240": ("sparse", "generic"), "noncausal_5120": ("sparse", "generic"), "causal_10500_mha_local2": ("sparse", "generic"),
+           "noncausal_5700_mha": ("sparse", "generic"), "generic_64_tiles": ("sparse", "generic"), "generic_65_tiles": ("sparse", "generic"),
+           "generic_d64_rows64": ("generic", "generic")}
+
 # The ping-pong kernel runs a step in a general or in a fast form, chosen per step from the visit list's shape (sink / local visits
 # at the head, masked or ragged tiles at the tail, five visits of look-ahead; two steps to a turn of the loop).  Non-causal lengths
 # put the same visit count on every query block, so a sweep over consecutive counts with every head of the list walks the start and
-# the end of the fast range and its parity; causal ones have every count from one up among their first query blocks.
+# the end of the fast range and its parity; causal ones have every count from one up among their first query blocks.  The same sweep as it is
+# walks attn_sparse_kernel's two-step loop.
 STEP_FORMS = [("noncausal_tc%d%s_s%dl%d" % (tc, "r" if rag else "", s, l),
                W(Hq=2, Hkv=1, N=64 * tc - rag, causal=False, n_sink=s, n_local=l), thr)
               for tc, rag, s, l, thr in ((81, 0, 1, 1, 5.0), (82, 0, 1, 1, 5.0), (83, 0, 1, 1, 9.0), (84, 0, 0, 1, 5.0), (85, 0, 2, 1, 5.0),
@@ -48,43 +62,26 @@ STEP_FORMS += [("causal_%s_%d_s%dl%d" % ("blocks" if Hq == Hkv else "heads", N, 
                                              (2, 1, 10304, 1, 1, 4.0), (2, 1, 10345, 2, 2, 4.0), (2, 1, 10432, 0, 1, 6.0), (2, 1, 10305, 2, 0, 4.0))]
 
 
+@pytest.mark.parametrize("kernel", ["sparse", "ping-pong"])
 @pytest.mark.parametrize("name,w,thr", STEP_FORMS, ids=[c[0] for c in STEP_FORMS])
-def test_vsa_step_forms(oracle, name, w, thr):
-    assert w.N > (10240 if w.causal else 5120) and w.block_m == 128, "a sequence that the generic kernel takes"
+def test_vsa_step_forms(oracle, name, w, thr, kernel):
+    if kernel == "ping-pong":
+        w = more(w)
+        if w.Hq == w.Hkv and w.n_local > 1:
+            w = dataclasses.replace(w, n_local=1)  # (pairs of blocks take one local block at most)
+    assert vsa_kernel(w) == kernel
     rows = [0, 1, w.Tr // 2, w.Tr - 2, w.Tr - 1] if not w.causal else [*range(0, 16), w.Tr - 2, w.Tr - 1]
-    _check(oracle, name, w, thr, rows)
+    check_vsa(oracle, name, w, thr, _blocks(w, rows))
 
 
+@pytest.mark.parametrize("many", [False, True])
 @pytest.mark.parametrize("name,w,thr", CASES, ids=[c[0] for c in CASES])
-def test_vsa_routes(oracle, name, w, thr):
+def test_vsa_routes(oracle, name, w, thr, many):
+    w = more(w) if many else w
+    assert vsa_kernel(w) == KERNELS.get(name, ("sparse", "ping-pong"))[many]
     last = w.Tr - 1
-    _check(oracle, name, w, thr, sorted(set([*range(0, 12), last // 2, last - 2, last - 1, last])))
+    check_vsa(oracle, name, w, thr, _blocks(w, sorted(set([*range(0, 12), last // 2, last - 2, last - 1, last]))))
 
 
-def _check(oracle, name, w, thr, rows):
-    import torch
-    import paper_2604_12798_amd as vfa
-    t = wl.generate(w)
-    Q, K, V = gpu_inputs(t)
-    Qh, Kh, Vh = host_f32(t)
-    blocks = [(0, h, i) for h in range(min(w.Hq, 2)) for i in rows if 0 <= i < w.Tr]
-    print(name, flush=True)
-    O = torch.full_like(Q, float("nan"))
-    L = torch.full((w.B, w.Hq, w.N), float("nan"), dtype=torch.float32, device=Q.device)
-    _, _, M = vfa.vsa_attn_fwd(Q, K, V, block_m=w.block_m, block_n=w.block_n, causal=w.causal, n_sink=w.n_sink,
-                               n_local=w.n_local, skip_threshold_nats=thr, out=O, lse=L)
-    torch.cuda.synchronize()
-    assert not torch.isnan(O.float()).any() and not torch.isnan(L).any(), name + ": rows left unwritten"
-    ref = oracle.blocks(Qh, Kh, Vh, w.block_m, w.block_n, w.causal, blocks, n_sink=w.n_sink, n_local=w.n_local,
-                        vsa=True, skip_threshold_nats=thr)
-    got = M.cpu().numpy()
-    got = np.stack([got[b, h, i] for b, h, i in blocks])
-    near = np.abs(ref["margin"]) < MASK_GUARD_NATS
-    assert near.sum() <= 4, "too many tiles sit on the threshold"
-    # a tile inside the band may fall either way, and with it what follows in its block
-    clean = ~near.any(axis=1)
-    assert np.array_equal(got[clean], ref["mask"][clean]), (name, int((got[clean] != ref["mask"][clean]).sum()))
-    stats = check_o_lse(O, L, ref["O"][clean], ref["LSE"][clean], np.asarray(blocks)[clean], w.block_m, w.N, name)
-    kept, skipped = int((ref["mask"] == 0).sum()), int((ref["mask"] == 1).sum())
-    print(name, "kept %d skipped %d" % (kept, skipped), stats, flush=True)
-    assert kept > 0 and skipped > 0, "the case should mix kept and skipped tiles"
+def _blocks(w, rows):
+    return [(0, h, i) for h in range(min(w.Hq, 2)) for i in rows if 0 <= i < w.Tr]
