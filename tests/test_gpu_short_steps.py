@@ -29,10 +29,12 @@ def test_steps(d, causal, steps):
         _check(d, 1, 3, 1, 128 * steps - 5 * (steps % 2), causal)
 
 
-# the lines of short_groups on a chip of 256 units
+# the lines of short_groups on a chip of 256 units, the last length on this kernel and the next one
 @pytest.mark.parametrize("d,Hq,Hkv,N,causal", [
-    (128, 64, 32, 3008, True), (128, 48, 48, 3840, True), (128, 4, 2, 6144, True), (64, 64, 16, 3648, True), (64, 320, 32, 2176, True), (128, 64, 16, 2048, True), (64, 16, 4, 6144, True),
-    (128, 64, 16, 1536, False), (128, 48, 16, 2048, False), (128, 4, 4, 4096, False), (64, 128, 32, 1536, False), (64, 32, 8, 3072, False), (64, 8, 8, 6144, False)])
+    (128, 4, 2, 6144, True), (128, 14, 7, 5632, True), (128, 60, 15, 2176, True), (128, 45, 45, 3328, True), (128, 3, 3, 4096, False),
+    (128, 16, 4, 2688, False), (128, 40, 10, 2176, False), (128, 80, 20, 1792, False), (128, 48, 12, 1152, False),
+    (64, 16, 4, 6144, True), (64, 64, 16, 3648, True), (64, 96, 16, 2944, True), (64, 8, 8, 6144, False), (64, 20, 5, 3072, False), (64, 72, 18, 1664, False),
+    (64, 36, 9, 3072, False), (64, 152, 38, 1280, False), (64, 84, 21, 2048, False), (64, 8, 2, 3008, False)])
 @pytest.mark.parametrize("behind", [0, 1])
 def test_lines(d, Hq, Hkv, N, causal, behind):
     _check(d, 1, Hq, Hkv, N + behind, causal)
