@@ -305,7 +305,10 @@ __device__ __forceinline__ void request_dwords(uint64_t base, uint32_t bytes, ui
                  : "memory");
 }
 
-// The same from the byte `at` of a buffer on (request4, request2), which may lie past its end.
+// The same from the byte `at` of a buffer on (request4, request2), which may lie past its end.  The range check takes the scalar offset in: a lane's
+// offset is held against what the buffer has left behind `at`, and what lies past its end comes as zeros, also where nothing is left.  Measured on buffers
+// that cover a part of an allocation, 0 to 64 KiB, with `at` before, on and up to 512 KiB past their end, every byte; the tests with NaN behind the last key
+// rest on it.  M0 is not put back: the compiler is told, and has no use for it in the kernels that call these (a test of the generated code).
 __device__ __forceinline__ void request4_at(const u32x4& rsrc, uint32_t at, uint32_t o0, uint32_t o1, uint32_t o2, uint32_t o3, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
                  "buffer_load_dwordx4 %1, %5, %6 offen lds\n\tbuffer_load_dwordx4 %2, %5, %6 offen offset:1024 lds\n\t"

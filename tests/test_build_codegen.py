@@ -85,3 +85,17 @@ def test_decode_needs_no_function_attribute(other_kernels):
     for name, size in lds.items():
         d, waves = (int(x) for x in re.search(r"ILi(\d+)ELi(\d)E", name).groups())
         assert size == waves * 2 * 64 * 2 * d, (name, size)  # a tile of K and one of V for each wave
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_only_requests_use_m0(other_kernels):
+    """request4_at and request2_at leave M0 as they set it, so the compiler must have no use of its own for it in the kernels that call them."""
+    seen = set()
+    for m in re.finditer(r"^(_Z\S*):[^\n]*\n(.*?)\.Lfunc_end", other_kernels, re.S | re.M):
+        kernel = re.search(r"attn_fwd_short_kernel|attn_sparse_kernel", m.group(1))
+        if not kernel:
+            continue
+        assert re.search(r"#ASMSTART\n\s*s_mov_b32 m0, ", m.group(2)), m.group(1)
+        assert not re.search(r"\bm0\b", re.sub(r"#ASMSTART.*?#ASMEND", "", m.group(2), flags=re.S)), m.group(1)
+        seen.add(kernel.group(0))
+    assert len(seen) == 2, seen

@@ -65,3 +65,18 @@ def test_ranges(d, n_splits, ragged):
     eO, eL = _exact(q, K, V, lens)
     err = (O.double() - eO).abs()
     assert err.max() <= O_MAX_ABS and err.mean() <= O_MEAN_ABS and (L.double() - eL).abs().max() <= LSE_ABS
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [1, 2, 17, 63, 64, 65, 127, 700, 4033])
+@pytest.mark.parametrize("n_splits", [1, 4])
+def test_nothing_behind_the_keys_is_read(d, n, n_splits):
+    """A tile of NaN behind the last key, whatever part of its tile that one leaves empty."""
+    import torch
+    import paper_2604_12798_amd as vfa
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    q, K, V = (torch.randn(s, generator=gen, device="cuda").bfloat16() for s in ((2, 8, d), (2, 2, n + 64, d), (2, 2, n + 64, d)))
+    K[:, :, n:], V[:, :, n:] = float("nan"), float("nan")
+    O, L = vfa.decode_fwd(q, K, V, n, use_minit=False, n_splits=n_splits)
+    eO, eL = _exact(q, K, V, [n, n])
+    assert (O.double() - eO).abs().max() <= O_MAX_ABS and (L.double() - eL).abs().max() <= LSE_ABS

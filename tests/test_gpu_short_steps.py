@@ -63,3 +63,19 @@ def test_rounds(d, Hq, Hkv, N, causal, short):
     O, L = vfa.vfa_attn_fwd(Q, K, V, causal=causal)
     O2, L2, _ = vfa.vfa_variant_fwd(Q, K, V, causal=causal)
     assert (torch.equal(O, O2) and torch.equal(L, L2)) != short
+
+
+# a slot's rows behind the last key are the next head's, or nothing: K and V come by requests whose range ends with the head's keys
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N", [1, 33, 65, 100, 191, 700, 1025])
+@pytest.mark.parametrize("Hkv,causal", [(2, True), (2, False), (40, True)])
+def test_the_next_head_is_not_read(d, N, Hkv, causal):
+    import torch
+    import paper_2604_12798_amd as vfa
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    Q, K, V = (torch.randn((1, Hkv, N, d), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    O, L = vfa.vfa_attn_fwd(Q, K, V, causal=causal)
+    K[:, 1::2], V[:, 1::2] = float("nan"), float("nan")
+    O2, L2 = vfa.vfa_attn_fwd(Q, K, V, causal=causal)
+    assert torch.equal(O2[:, ::2], O[:, ::2]) and torch.equal(L2[:, ::2], L[:, ::2])
+    assert torch.isfinite(O[:, ::2].float()).all()
