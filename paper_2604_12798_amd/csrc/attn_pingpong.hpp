@@ -1,5 +1,5 @@
 // Ping-pong bf16 attention kernel for d = 128, block_m = 128: the kernel the headline workloads run on
-// (Alg. 1 and the online-softmax baselines; Alg. 2 has a kernel of its own in attn_vsa.hpp).
+// (Alg. 1 and the online-softmax baselines; Alg. 2 has kernels of its own, in attn_sparse.hpp and, on this structure, in attn_vsa.hpp).
 #pragma once
 #include "common.hpp"
 

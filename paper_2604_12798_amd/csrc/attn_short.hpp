@@ -20,10 +20,11 @@ namespace {
 // one's dealt out between the MFMAs, then P.V with the second half.  K slots are requested two steps ahead, V slots one, the
 // requests dealt out too (in front of the step they hold up its first MFMAs: 8 % of the time); one barrier per step.  A wave meets its keys in
 // its first steps and only the last of them needs a mask, so there are two copies of a step's code and no branch between them.
-// What bounds it: below 500 keys the launch and the chain of load latencies (4.8 us for an empty sequence); then a wave's own chain, 170
-// instructions for 16 MFMAs (512 cycles) and, alone on a SIMD, 1000 to 1100 cycles a step; two workgroups on a compute unit take 2700 for a step of
-// each, which is 2.2 times the ping-pong kernel's time per score, so longer sequences stay with that.  Measured on a single workgroup: slots
-// deeper by one step or three change nothing, all eight fragments of K in front and the weights between the MFMAs of Q.K^T only cost 8 %.
+// What bounds it: below 500 keys the launch and the chain of load latencies (4.6 us for an empty sequence); then a wave's own chain, 170
+// instructions for 16 MFMAs: 0.5 us a step where a workgroup has a compute unit to itself, 1.06 to 1.13 for a step of each of two (64 keys and
+// rows, d = 128, no mask).  Per score that is 1.05 to 1.17 times the ping-pong kernel's time in full rounds of long items, so those stay with that one.
+// Measured on a single workgroup: slots deeper by one step or three change nothing, all eight fragments of K in front and the weights between the MFMAs
+// of Q.K^T only cost 8 %.
 // The first form waited in every step for the requests just made (see Q below), took a slot's place and its wrap from vector and scalar
 // arithmetic (226 instructions) and moved the scores from one step to the next.
 // KQ = 2: two workgroups per compute unit (80 KiB each at d = 128).  KQ = 4: one, for grids of no more items than compute units.

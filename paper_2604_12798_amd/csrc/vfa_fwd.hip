@@ -272,6 +272,8 @@ bool prefer_rows64(const Params& p, int n_cu, bool head_pairs, bool frozen, bool
 //   none: N = 256 14.5 / 13.3, 512 20.6 / 18.2;
 // with several items to a workgroup's place the other kernel hides its own ends, and it takes a longer loop: 128/8 heads, N = 1024, one
 // and one 64.2 / 65.4, four and four 65.7 / 74.8; 64/8 heads, N = 4096, four and four 316.6 / 315.9.
+// 1500 shapes of 2 to 300 tiles, up to 4 and 4 blocks, 0 to 90 % dropped: masks are the same on all; 0.91 to 0.97 of the other kernels' time in the mean; slower by more than 3 % are three
+// (118 heads over 59, N = 1536 111.5 / 116.3, 99 over 33, N = 1536 94.6 / 98.1, 110 over 55, N = 2056 191 / 198).
 bool prefer_sparse(const Params& p, int n_cu) {
     const long long items = (long long)p.B * p.Hq * p.Tr;
     if (p.n_sink > 4 || p.n_local > 4 || items > kMaxWorkgroups256 || p.N > 1 << 23) return false;  // (its LDS; a launch; 32-bit offsets)
