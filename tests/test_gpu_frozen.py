@@ -92,6 +92,8 @@ def test_what_lds_held_before_does_not_matter(oracle, d):
         _check(oracle, _w(B=b, Hq=32, Hkv=8, N=n, d=d, n_sink=1, n_local=0), sample=6, before=poison)
     for b, hq, n in ((2, 32, 4200), (1, 4, 6272)):  # calls of vfa_attn_fwd on this kernel (the first at d = 64: one group of keys)
         _check(oracle, _w(B=b, Hq=hq, Hkv=hq // 2, N=n, d=d), sample=4, before=poison, same=n == 6272 or d == 64)
+    for b, hq, n in ((2, 32, 2113), (1, 4, 4200)):  # of vfa_variant_fwd only
+        _check(oracle, _w(B=b, Hq=hq, Hkv=hq // 2, N=n, d=d), sample=4, before=poison)
 
 
 # calls that are too long for the kernel of short sequences (attn_short.hpp): d = 64 with one group of keys (three workgroups to a unit)
@@ -105,10 +107,21 @@ def test_longer_calls(oracle, B, Hq, N, d, causal, kw, block_m, use_minit):
     _check(oracle, _w(B=B, Hq=Hq, Hkv=4, N=N, d=d, causal=causal, block_m=block_m, **kw), use_minit=use_minit, sample=4, same=True)
 
 
+# lengths at which vfa_attn_fwd is still on attn_short.hpp and vfa_variant_fwd on this kernel
+@pytest.mark.parametrize("B,Hq,N,d,causal,kw", [(2, 32, 2113, 64, True, {}), (2, 32, 2113, 64, True, dict(n_sink=4, n_local=4)), (2, 32, 1600, 64, False, {}),
+                                                (2, 32, 1601, 64, False, dict(n_sink=0, n_local=3)), (1, 8, 4200, 64, True, {}), (1, 8, 4200, 64, False, {}),
+                                                (1, 8, 2500, 128, False, {}), (1, 8, 2501, 128, False, dict(n_sink=3, n_local=0)),
+                                                (1, 4, 4200, 64, True, {}), (1, 4, 4200, 128, True, {})])
+@pytest.mark.parametrize("block_m,use_minit", [(128, True), (64, True), (128, False)])
+def test_long_calls_of_the_short_kernel(oracle, B, Hq, N, d, causal, kw, block_m, use_minit):
+    _check(oracle, _w(B=B, Hq=Hq, Hkv=4, N=N, d=d, causal=causal, block_m=block_m, **kw), use_minit=use_minit, sample=4)
+
+
 # d = 64, many heads: on both sides of the lines to attn_short.hpp (of a chip of 256 units), and short calls, every row
 @pytest.mark.parametrize("B,Hq,N,causal", [(16, 32, 448, False), (16, 32, 449, False), (8, 32, 704, False), (8, 32, 705, False), (4, 36, 1280, False), (4, 36, 1281, False),
                                            (4, 21, 2048, False), (4, 21, 2049, False), (16, 32, 896, True), (16, 32, 897, True), (6, 16, 2944, True), (6, 16, 2945, True),
-                                           (4, 16, 3648, True), (4, 16, 3649, True)])
+                                           (4, 16, 3648, True), (4, 16, 3649, True), (5, 32, 960, False), (7, 16, 1025, False), (2, 32, 1345, False),
+                                           (16, 32, 960, True), (6, 32, 1600, True), (6, 16, 1792, True), (6, 16, 1856, True)])
 def test_many_heads(B, Hq, N, causal):
     import torch
     import paper_2604_12798_amd as vfa

@@ -13,12 +13,15 @@ from gpu_util import check_o_lse, check_vsa, gpu_inputs, host_f32, vsa_kernel
 
 pytestmark = pytest.mark.gpu
 
-# (name, base config, overrides), over 96 tiles, where vfa_attn_fwd is not on attn_short.hpp: items = B * Hq/2 * Tr (head pairs) or B * Hq * ceil(Tr/2) (block pairs)
+# (name, base config, overrides), but for two over 96 tiles, where vfa_attn_fwd is not on attn_short.hpp: items = B * Hq/2 * Tr (head pairs) or B * Hq * ceil(Tr/2) (block pairs)
 CASES = [
     ("chip_list_head_pairs", "cfg3", dict(B=3, Hq=4, Hkv=2, N=6272)),    # B*Hkv = 6: 294 items in one list
     ("xcd_lists_block_pairs", "cfg2", dict(B=1, Hq=8, Hkv=8, N=8448)),   # 8 lists of 33 items: partial round
     ("xcd_lists_head_pairs", "cfg3", dict(B=1, Hq=16, Hkv=8, N=6272)),   # 8 lists of 49 items: partial round
     ("chip_list_ragged", "cfg3", dict(B=1, Hq=6, Hkv=3, N=11300)),       # 267 items, ragged last block
+    # (vfa_attn_fwd is on attn_short.hpp, vfa_variant_fwd and the baselines are not)
+    ("chip_list_baselines", "cfg3", dict(B=3, Hq=4, Hkv=2, N=5632)),     # 264 items
+    ("xcd_lists_baselines", "cfg3", dict(B=1, Hq=16, Hkv=8, N=4480)),    # 8 lists of 35 items
 ]
 
 
@@ -54,7 +57,9 @@ def test_persistent_workgroups(oracle, name, base, over):
     print(name, "fa", check_o_lse(O_fa, L_fa, Oe, Le, blocks, w.block_m, w.N, "fa_baseline_fwd vs exact"), flush=True)
     O_v, L_v = run(vfa.vfa_attn_fwd, **vkw)
     print(name, "vfa", check_o_lse(O_v, L_v, ref["O"], ref["LSE"], blocks, w.block_m, w.N, "vfa_attn_fwd vs oracle"), flush=True)
-    assert torch.equal(O_v, vfa.vfa_variant_fwd(Q, K, V, **vkw)[0]), "vfa_attn_fwd is on another kernel"  # (vfa_variant_fwd is never on attn_short.hpp)
+    O_x, L_x = run(lambda *a, **k: vfa.vfa_variant_fwd(*a, **k)[:2], **vkw)  # (never on attn_short.hpp)
+    print(name, "variant", check_o_lse(O_x, L_x, ref["O"], ref["LSE"], blocks, w.block_m, w.N, "vfa_variant_fwd vs oracle"), flush=True)
+    assert torch.equal(O_v, O_x) == (w.Tc > 96), "vfa_attn_fwd is on another kernel"
     O_l, L_l = run(vfa.fa_lazy_rescale_fwd, rescale_tau=8.0, **kw)
     # every row, against each other (bf16 outputs of the same attention: a few ulps of bf16 apart at most)
     for what, (Oa, La) in {"vfa": (O_v, L_v), "fa_lazy": (O_l, L_l)}.items():
@@ -80,6 +85,11 @@ VSA_CASES = [
     ("chip_list_no_mask", "cfg3", dict(B=1, Hq=20, Hkv=10, N=5185, n_sink=1, n_local=5, causal=False), 5.0, True),
     ("xcd_lists_no_estimate", "cfg3", dict(B=1, Hq=16, Hkv=8, N=10304, n_sink=5), 5.0, False),
     ("chip_list_no_estimate", "cfg2", dict(B=1, Hq=7, Hkv=7, N=10500, n_sink=5), 4.0, False),
+    # the same sizes with one sink and one local block: attn_sparse_kernel
+    ("sparse_xcd_lists_16_heads", "cfg3", dict(B=1, Hq=16, Hkv=8, N=10304), 5.0, True),
+    ("sparse_one_list_12_heads", "cfg3", dict(B=2, Hq=6, Hkv=3, N=10250), 5.0, True),
+    ("sparse_xcd_lists_8_heads", "cfg2", dict(B=1, Hq=8, Hkv=8, N=10304), 4.0, True),
+    ("sparse_one_list_7_heads", "cfg2", dict(B=1, Hq=7, Hkv=7, N=10500), 4.0, True),
 ]
 
 
@@ -90,7 +100,7 @@ def test_persistent_workgroups_vsa(oracle, name, base, over, thr, minit):
     w = wl.small(wl.CONFIGS[base], **dict(dict(beta=6.0, kappa=3.0), **over))
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
     items = w.B * (w.Hq // 2) * w.Tr if (w.Hq // w.Hkv) % 2 == 0 else w.B * w.Hq * ((w.Tr + 1) // 2)
-    assert vsa_kernel(w) == "ping-pong" and items > n_cu, "not the persistent form of Alg. 2's ping-pong kernel"
+    assert vsa_kernel(w) == ("sparse" if name.startswith("sparse") else "ping-pong") and items > n_cu, "not the persistent form of Alg. 2's ping-pong kernel"
     print(f"{name}: {items} items on {n_cu} CUs", flush=True)
     # blocks of the first round and of the later ones: long, short and the last
     blocks = [(w.B - 1, h, i) for h in sorted({0, w.Hq // 2, w.Hq - 1}) for i in sorted({0, 1, w.Tr // 3, w.Tr - 2, w.Tr - 1})]

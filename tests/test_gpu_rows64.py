@@ -57,8 +57,8 @@ def test_rows64(oracle, B, Hq, Hkv, N, causal):
 
 # What vfa_attn_fwd runs on at d = 128: attn_short.hpp (n_sink <= 4 and up to 777 rows), the ping-pong kernel in head pairs and in block pairs (n_sink =
 # 5), attn_frozen.hpp (6272 rows); at d = 64 attn_short.hpp, the generic kernel (n_sink = 5), attn_frozen.hpp in one group of keys (4200 rows) and in two (6272).
-# vfa_variant_fwd, the same call, keeps to the kernels with a fixed max: attn_frozen.hpp for the short ones.
-LATER = [(2, 32, 8, 4200, dict(n_sink=1)), (1, 4, 2, 6272, dict(n_sink=1)),
+# vfa_variant_fwd, the same call, keeps to the kernels with a fixed max: attn_frozen.hpp for the short ones (2113 and 4200 rows: long calls of attn_short.hpp).
+LATER = [(2, 32, 8, 4200, dict(n_sink=1)), (1, 4, 2, 6272, dict(n_sink=1)), (2, 32, 8, 2113, dict(n_sink=1)), (1, 4, 2, 4200, dict(n_sink=1)),
          (1, 8, 2, 777, {}), (1, 4, 2, 1100, dict(n_sink=5)), (1, 3, 1, 1100, dict(n_sink=5)), (1, 3, 3, 1000, dict(n_sink=5, n_local=2)),
          (3, 32, 8, 320, {}), (5, 32, 32, 200, {}), (1, 8, 2, 128, dict(n_sink=0)), (1, 8, 2, 640, dict(n_sink=0, n_local=0))]
 

@@ -34,7 +34,10 @@ def test_steps(d, causal, steps):
     (128, 4, 2, 6144, True), (128, 14, 7, 5632, True), (128, 60, 15, 2176, True), (128, 45, 45, 3328, True), (128, 3, 3, 4096, False),
     (128, 16, 4, 2688, False), (128, 40, 10, 2176, False), (128, 80, 20, 1792, False), (128, 48, 12, 1152, False),
     (64, 16, 4, 6144, True), (64, 64, 16, 3648, True), (64, 96, 16, 2944, True), (64, 8, 8, 6144, False), (64, 20, 5, 3072, False), (64, 72, 18, 1664, False),
-    (64, 36, 9, 3072, False), (64, 152, 38, 1280, False), (64, 84, 21, 2048, False), (64, 8, 2, 3008, False)])
+    (64, 36, 9, 3072, False), (64, 152, 38, 1280, False), (64, 84, 21, 2048, False), (64, 8, 2, 3008, False),
+    # (other lengths about which calls change kernels, or did by number of tiles alone)
+    (128, 64, 32, 3008, True), (128, 48, 48, 3840, True), (64, 320, 32, 2176, True), (128, 64, 16, 2048, True), (128, 64, 16, 1536, False),
+    (128, 48, 16, 2048, False), (128, 4, 4, 4096, False), (64, 128, 32, 1536, False), (64, 32, 8, 3072, False)])
 @pytest.mark.parametrize("behind", [0, 1])
 def test_lines(d, Hq, Hkv, N, causal, behind):
     _check(d, 1, Hq, Hkv, N + behind, causal)
