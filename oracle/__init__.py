@@ -1,4 +1,4 @@
-"""ctypes loader for the float64 CPU checker in vfa_oracle.c.
+"""ctypes loader for the float64 CPU oracle in vfa_oracle.c.
 
 TEST INFRASTRUCTURE ONLY.  Tests, the smoke check and the benchmark's cpu_baseline
 leg may import this; the GPU library and its Python binding never do.  Nothing here

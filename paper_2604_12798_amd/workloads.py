@@ -1,6 +1,6 @@
 """Seeded synthetic inputs for the VFA / VSA attention forward path.
 
-This module is the only thing the GPU path's callers and the CPU checker have in
+This module is the only thing the GPU path's callers and the CPU oracle have in
 common: it produces Q, K, V as bf16 bit patterns (numpy uint16) from a seed, so that
 both sides read the same numbers.  It holds none of the method's arithmetic (no
 softmax, no block summaries, no visit order); it only shapes the *scores* Q K^T so
