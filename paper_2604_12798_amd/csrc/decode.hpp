@@ -330,13 +330,12 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const DecodeParams p)
         for (int u = 0; u < U; ++u) mn = fmaxf(mn, pm[u]);
         const float msub = mn == -INFINITY ? 0.f : mn;
         const float a0 = __builtin_amdgcn_exp2f(m - msub);
-        l *= a0;
-        o *= a0;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < U; ++u) {  // (which product of the first two is rounded is spelled out: the same bits however many rounds there are)
             const float a = __builtin_amdgcn_exp2f(pm[u] - msub);
-            l += a * pl[u];
-            o += a * po[u];
+            l = u == 0 ? __builtin_fmaf(l, a0, a * pl[u]) : __builtin_fmaf(a, pl[u], l);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = u == 0 ? __builtin_fmaf(o[e], a0, a * po[u][e]) : __builtin_fmaf(a, po[u][e], o[e]);
         }
         m = mn;
     };

@@ -80,3 +80,18 @@ def test_nothing_behind_the_keys_is_read(d, n, n_splits):
     O, L = vfa.decode_fwd(q, K, V, n, use_minit=False, n_splits=n_splits)
     eO, eL = _exact(q, K, V, [n, n])
     assert (O.double() - eO).abs().max() <= O_MAX_ABS and (L.double() - eL).abs().max() <= LSE_ABS
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("tiles", [2, 5, 12, 20, 40])
+def test_ranges_without_keys_change_nothing(d, tiles):
+    """More ranges than tiles: one tile to a range, whatever their number, so the same partial sums and, in one, two or four rounds of the merge, the same bits."""
+    import torch
+    import paper_2604_12798_amd as vfa
+    gen = torch.Generator(device="cuda").manual_seed(tiles)
+    q, K, V = (torch.randn(s, generator=gen, device="cuda").bfloat16() for s in ((8, 32, d), (8, 4, 64 * tiles, d), (8, 4, 64 * tiles, d)))
+    want = vfa.decode_fwd(q, K, V, 64 * tiles - 3, use_minit=False, n_splits=tiles)
+    for n_splits in (8, 9, 16, 17, 32, 33, 64, 65, 130):
+        if n_splits > tiles:
+            got = vfa.decode_fwd(q, K, V, 64 * tiles - 3, use_minit=False, n_splits=n_splits)
+            assert all(torch.equal(x, y) for x, y in zip(got, want)), n_splits
